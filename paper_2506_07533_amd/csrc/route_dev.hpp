@@ -26,9 +26,11 @@ __device__ __forceinline__ float exp_pinned(float x) {
 }
 
 // 64 dims of a key row (eight 16-byte pieces xr[0..7], dims dbase..dbase+63) into the two running sums per expert,
-// in ascending order of the dims.  W1w, W2w: the fp16 weight matrices as 32-bit words (wave-uniform loads).
-template <int M>
-__device__ __forceinline__ void route_half_row(const uint4 *xr, int dbase, const uint32_t *W1w, const uint32_t *W2w,
+// in ascending order of the dims.  W1w, W2w: the fp16 weight matrices as 32-bit words (wave-uniform loads; WP: a plain
+// pointer, or const_words where the compiler would not see by itself that nothing in the kernel writes them).
+typedef const uint32_t __attribute__((address_space(4))) *const_words;
+template <int M, typename WP>
+__device__ __forceinline__ void route_half_row(const uint4 *xr, int dbase, WP W1w, WP W2w,
                                                float (&accA)[M], float (&accB)[M]) {
     // two key dims (two rows of the weight matrices) per step so that the fp16 pairs fall on 32-bit words
 #pragma unroll

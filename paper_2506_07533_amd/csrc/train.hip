@@ -5,80 +5,124 @@
 //   p^i = softmax of the token's logits.  The top-1 index comes from the same binary32 arithmetic as routing
 //   (route_kernel), so it is the routing decision bit for bit; everything after it is plain binary32.
 //
-// One wavefront per tile of 64 tokens, one lane per token for the forward pass and the token's own backward
-// pass down to d(loss)/d(xW1), d(loss)/d(xW2) (2M values per token, handed over through LDS); then the lane
-// owning dims (2l, 2l+1) adds x[t][d] * d.. over the tile's tokens into dW1, dW2 accumulators that stay in
-// registers for all tiles of the wavefront (the rows come back from L2 as coalesced 256-byte reads).  dW3, the
-// bias gradient and the loss are per-lane sums folded at the end.  Bound by the vector ALU: about 2 * 2M * D
-// multiply-adds per token forward and as many backward.
+// One wavefront per tile of 64 tokens, eight wavefronts per workgroup, one workgroup per compute unit; a wavefront keeps
+// its gradient accumulators over all its tiles.
+//   rows      requested in whole rows, a tile ahead, and staged in LDS (pieces XOR-swizzled: reads by row and by piece both
+//             touch every bank), from where the forward pass takes a row per lane and the weight gradient a piece per lane.
+//   forward   one lane per token, route_half_row / the operations of route_top in their order, then the token's loss and
+//             its gradient down to d(loss)/d(xW1), d(loss)/d(xW2) (2M values per token, handed over through LDS).
+//   dW1, dW2  = x^T [128 x 64 tokens] times those values [64 tokens x 2M] on v_mfma_f32_16x16x32_f16: x is fp16 as it is; a
+//             value is scaled by the tile's power of two and split into two fp16 numbers, the second holding what the
+//             first leaves (22 bits and more of every value that is not 2^28 times smaller than the tile's largest; the
+//             error of the result against binary64 is below that of the binary32 multiply-adds this took before: their
+//             accumulators rounded once per token, these once per 32).  A row i of tile rt = dim 8i + rt, and the tokens
+//             are taken in the order 4j + r, so that the operands of a lane are the fp16 halves of row pieces it can read
+//             with one load each.  Binary32 matrix products (16x16x4) took 27 us of the matrix pipe at 1.05 M rows and
+//             128 conversions per tile: 111 us in all.
+//   fold      dW3, the bias gradient and the loss are per-lane sums; everything meets in LDS, then ONE atomic add per
+//             address and workgroup.  Device-wide atomic steps on one address run at about nine per microsecond here: one
+//             wavefront at a time, each with its own atomic adds (4096 per address), took 0.8 ms of the 0.89 ms that the
+//             gradient over 1.05 M rows needed.
+// 1.05 M rows: 4 experts 75 us against 892, 8 experts 200 against 1733, 2 experts 57 against 264; 64 rows 18 against 20.  The
+// rows alone are 38 us at the read ceiling of the chip; what is left is the forward pass (1024 multiply-adds in their order).
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
+#include "pack_dev.hpp"
 #include "route_dev.hpp"
 
 namespace moqae {
 
-constexpr int kTrainWaves = 4;
+constexpr int kTrainWaves = 8;
+// The fp16 halves of the 2M values per token, in the order of the B operand: [32-token step h][token % 4][column][j], token
+// = 32h + 4j + token % 4; the steps of token % 4 and h are padded so that they start on different banks.
+constexpr int kTrainCol = 8, kTrainR4 = 16 * kTrainCol + 8, kTrainH = 4 * kTrainR4 + 32;
+
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h_t __attribute__((ext_vector_type(8)));
+
+// Sum over the wavefront, the same in every lane.
+__device__ __forceinline__ float wave_sum(float x) {
+    x = group_sum<16>(x);
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+__device__ __forceinline__ uint32_t word4(const uint4 &v, int i) { return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)); }
+
+__device__ __forceinline__ v4f_t mfma_train(v4u_t a, v4u_t b, v4f_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a), __builtin_bit_cast(v8h_t, b), c, 0, 0, 0);
+}
 
 template <int M>
 __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArgs a) {
+    constexpr int NS = M * M + M + 2;                 // sums that every lane keeps: dW3, bias, the two losses
     __shared__ float w3f[72];
-    __shared__ float dab[kTrainWaves][64][2 * M];     // per token: d/d(xW1)[M], d/d(xW2)[M]
-    __shared__ float red[kTrainWaves][4 * M * 64];    // dW1, dW2 of the wavefronts at the end
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float sums[kTrainWaves][NS];
+    __shared__ uint4 stage[kTrainWaves][64 * 16];     // key rows: piece p of row r at 16r + (p ^ (r % 16)); the fold's dW at the end
+    constexpr int NB = M <= 4 ? 1 : 2;                // B operands: columns 0..7 first halves, 8..15 second ones, or one each
+    __shared__ __attribute__((aligned(16))) uint16_t dabs[kTrainWaves][2 * kTrainH];
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // wave-uniform, kept scalar
     if (tid < M * M) w3f[tid] = half_bits_to_float(a.W3[tid]);
     if (tid < M) w3f[64 + tid] = a.bias ? a.bias[tid] : 0.0f;
     __syncthreads();
-    const uint32_t *W1w = reinterpret_cast<const uint32_t *>(a.W1);
-    const uint32_t *W2w = reinterpret_cast<const uint32_t *>(a.W2);
+    const const_words W1w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W1));
+    const const_words W2w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W2));
+    uint4 *mine = &stage[wave][0];
+    uint16_t *dab = &dabs[wave][0];
+    for (int i = lane; i < 2 * kTrainH; i += 64) dab[i] = 0;   // the columns nobody writes stay zero
 
-    float g1[2][M], g2[2][M];                         // dW1[2l + e][m], dW2[2l + e][m]
+    v4f_t gw[8];                                      // C tiles: row 4*(l/16) + n of tile rt = dim 8*row + rt, column l%16
     float g3[M][M], gb[M], lsum[2] = {0.0f, 0.0f};
 #pragma unroll
+    for (int rt = 0; rt < 8; rt++) gw[rt] = v4f_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
     for (int m = 0; m < M; m++) {
-        g1[0][m] = g1[1][m] = g2[0][m] = g2[1][m] = 0.0f; gb[m] = 0.0f;
+        gb[m] = 0.0f;
 #pragma unroll
         for (int k = 0; k < M; k++) g3[m][k] = 0.0f;
     }
+    // tile (row u, tile tr of the row); the wavefront's first is wave * gridDim + block, then steps of gridDim * kTrainWaves,
+    // all on the scalar unit
     const int tiles_per_row = (a.n_tok + 63) / 64;
-    const long long n_tiles = (long long)a.BH * tiles_per_row;
-    const long long gw = (long long)blockIdx.x * kTrainWaves + wave, tw = (long long)gridDim.x * kTrainWaves;
-    for (long long tile = gw; tile < n_tiles; tile += tw) {
-        const int u = (int)(tile / tiles_per_row), t0 = (int)(tile % tiles_per_row) * 64;
-        const int b = u / a.Hkv, h = u % a.Hkv;
-        const int n_here = min(64, a.n_tok - t0);
-        const bool active = lane < n_here;
-        const uint16_t *Kt = a.K + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h + (int64_t)(a.token_begin + t0) * a.stride_s;
+    const uint32_t tile0 = (uint32_t)wave * gridDim.x + blockIdx.x, tw = gridDim.x * kTrainWaves;
+    const int step_u = (int)(tw / (uint32_t)tiles_per_row), step_t = (int)(tw % (uint32_t)tiles_per_row);
+    int u = (int)(tile0 / (uint32_t)tiles_per_row), tr = (int)(tile0 % (uint32_t)tiles_per_row);
+    const int piece = lane & 15, r4 = lane >> 4;
+    uint4 v[16];
+    auto request = [&](int un, int tn) {              // rows past the tile's end read its last row
+        const uint16_t *Kt = a.K + (int64_t)(un / a.Hkv) * a.stride_b + (int64_t)(un % a.Hkv) * a.stride_h + (int64_t)(a.token_begin + tn * 64) * a.stride_s;
+        const int last = min(64, a.n_tok - tn * 64) - 1;
+        if (last == 63 && a.stride_s < (1 << 28)) {   // scalar row addresses, one 32-bit offset per lane
+            const uint32_t off = (uint32_t)r4 * (uint32_t)a.stride_s * 2u + (uint32_t)piece * 16u;
+#pragma unroll
+            for (int j = 0; j < 16; j++) v[j] = nt_load(reinterpret_cast<const uint4 *>(reinterpret_cast<const uint8_t *>(Kt + 4 * j * a.stride_s) + off));
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; j++) v[j] = nt_load(reinterpret_cast<const uint4 *>(Kt + (int64_t)min(4 * j + r4, last) * a.stride_s) + piece);
+    };
+    if (u < a.BH) request(u, tr);
+    while (u < a.BH) {
+        const int b = u / a.Hkv;
+        const bool active = lane < a.n_tok - tr * 64;
+        tr += step_t; u += step_u;                    // the next tile
+        if (tr >= tiles_per_row) { tr -= tiles_per_row; u++; }
+#pragma unroll
+        for (int j = 0; j < 16; j++) mine[(4 * j + r4) * 16 + (piece ^ ((4 * j + r4) & 15))] = v[j];
+        if (u < a.BH) request(u, tr);
+        wave_lds_sync();
         // ---- forward, the routing arithmetic: sequential binary32 sums over d (products of two fp16 values are exact)
         float accA[M], accB[M];
 #pragma unroll
         for (int m = 0; m < M; m++) { accA[m] = 0.0f; accB[m] = 0.0f; }
-        const uint4 *rowp = reinterpret_cast<const uint4 *>(Kt + (int64_t)(active ? lane : 0) * a.stride_s);
 #pragma unroll 1
         for (int hr = 0; hr < 2; hr++) {
             uint4 xr[8];
 #pragma unroll
-            for (int p = 0; p < 8; p++) xr[p] = rowp[hr * 8 + p];
-#pragma unroll
-            for (int p = 0; p < 8; p++) {
-                const uint32_t xw[4] = {xr[p].x, xr[p].y, xr[p].z, xr[p].w};
-#pragma unroll
-                for (int e = 0; e < 8; e += 2) {
-                    const int d = hr * 64 + p * 8 + e;
-                    const float x0 = half_bits_to_float(xw[e >> 1] & 0xffffu), x1 = half_bits_to_float(xw[e >> 1] >> 16);
-                    uint32_t w1[M], w2[M];
-#pragma unroll
-                    for (int m = 0; m < M; m++) { w1[m] = W1w[d / 2 * M + m]; w2[m] = W2w[d / 2 * M + m]; }
-#pragma unroll
-                    for (int m = 0; m < M; m++) {
-                        const int i0 = m, i1 = M + m;
-                        accA[m] = fmaf(x0, half_bits_to_float((w1[i0 >> 1] >> (16 * (i0 & 1))) & 0xffffu), accA[m]);
-                        accB[m] = fmaf(x0, half_bits_to_float((w2[i0 >> 1] >> (16 * (i0 & 1))) & 0xffffu), accB[m]);
-                        accA[m] = fmaf(x1, half_bits_to_float((w1[i1 >> 1] >> (16 * (i1 & 1))) & 0xffffu), accA[m]);
-                        accB[m] = fmaf(x1, half_bits_to_float((w2[i1 >> 1] >> (16 * (i1 & 1))) & 0xffffu), accB[m]);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int p = 0; p < 8; p++) xr[p] = mine[lane * 16 + ((hr * 8 + p) ^ piece)];
+            route_half_row<M>(xr, hr * 64, W1w, W2w, accA, accB);
         }
         float z[M], sg[M], hid[M], lg[M];
 #pragma unroll
@@ -88,7 +132,7 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
             hid[m] = __fdiv_rn(z[m], den);
             sg[m] = 1.0f / den;
         }
-        int top = 0;
+        int top = 0; float ltop = 0.0f;
 #pragma unroll
         for (int k = 0; k < M; k++) {
             float acc = 0.0f;
@@ -96,7 +140,8 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
             for (int j = 0; j < M; j++) acc = __fadd_rn(acc, __fmul_rn(hid[j], w3f[j * M + k]));
             if (a.bias) acc = __fadd_rn(acc, w3f[64 + k]);
             lg[k] = acc;
-            if (k > 0 && acc > lg[top]) top = k;       // strict: the first maximum wins
+            if (k == 0) ltop = acc;
+            else if (acc > ltop) { top = k; ltop = acc; }   // strict: the first maximum wins
         }
         // ---- loss of the token and its gradient down to xW1, xW2
         float mx = lg[0];
@@ -116,74 +161,120 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
         float dl[M];
 #pragma unroll
         for (int k = 0; k < M; k++) { dl[k] = w * ((k == top ? 1.0f : 0.0f) - p[k]); gb[k] += dl[k]; }
-        float dxa[M], dxb[M];
+        float dx[2 * M], dmax = 0.0f;
 #pragma unroll
         for (int m = 0; m < M; m++) {
             float dh = 0.0f;
 #pragma unroll
             for (int k = 0; k < M; k++) { dh = fmaf(dl[k], w3f[m * M + k], dh); g3[m][k] = fmaf(hid[m], dl[k], g3[m][k]); }
             const float dz = dh * (sg[m] * (1.0f + z[m] * (1.0f - sg[m])));
-            dxa[m] = dz * accB[m]; dxb[m] = dz * accA[m];
+            dx[m] = dz * accB[m]; dx[M + m] = dz * accA[m];
+            dmax = fmaxf(dmax, fmaxf(fabsf(dx[m]), fabsf(dx[M + m])));
         }
+        // ---- dW1, dW2.  2^ef <= dmax < 2^(ef+1): value * 2^(14 - ef) is below 2^15
+        const int ef = min(max((int)((__builtin_bit_cast(uint32_t, wave_max(dmax)) >> 23) & 255u) - 127, -110), 127);
+        const float up = __builtin_bit_cast(float, (uint32_t)(127 + 14 - ef) << 23);
+        const float down = __builtin_bit_cast(float, (uint32_t)max(127 - 14 + ef, 1) << 23);
+        uint16_t *mydab = dab + (lane >> 5) * kTrainH + (lane & 3) * kTrainR4 + ((lane >> 2) & 7);
+        uint32_t lo[2 * M];
 #pragma unroll
-        for (int m = 0; m < M; m++) { dab[wave][lane][m] = dxa[m]; dab[wave][lane][M + m] = dxb[m]; }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // ---- dW1, dW2: this lane's two dims over the tile's tokens (rows re-read as coalesced 256-byte pieces)
-        const uint32_t *colp = reinterpret_cast<const uint32_t *>(Kt) + lane;
-#pragma unroll 1
-        for (int tb = 0; tb < 64; tb += 8) {
-            uint32_t xw[8];
+        for (int m = 0; m < 2 * M; m++) {
+            const float s = dx[m] * up;
+            const uint32_t hi = float_to_half_bits(s);
+            lo[m] = float_to_half_bits((s - half_bits_to_float(hi)) * 2048.0f);
+            mydab[m * kTrainCol] = (uint16_t)hi;
+            if constexpr (NB == 1) mydab[(8 + m) * kTrainCol] = (uint16_t)lo[m];
+        }
+        wave_lds_sync();
+        v4u_t B[NB][2];
 #pragma unroll
-            for (int i = 0; i < 8; i++) xw[i] = colp[(int64_t)min(tb + i, n_here - 1) * (a.stride_s / 2)];
+        for (int h = 0; h < 2; h++) B[0][h] = *reinterpret_cast<const v4u_t *>(dab + h * kTrainH + r4 * kTrainR4 + piece * kTrainCol);
+        if constexpr (NB == 2) {
+            wave_lds_sync();
 #pragma unroll
-            for (int i = 0; i < 8; i++) {
-                const float x0 = half_bits_to_float(xw[i] & 0xffffu), x1 = half_bits_to_float(xw[i] >> 16);
+            for (int m = 0; m < 2 * M; m++) mydab[m * kTrainCol] = (uint16_t)lo[m];
+            wave_lds_sync();
 #pragma unroll
-                for (int m = 0; m < M; m++) {
-                    const float da = dab[wave][tb + i][m], db = dab[wave][tb + i][M + m];   // zero for tokens past the tile's end
-                    g1[0][m] = fmaf(x0, da, g1[0][m]); g1[1][m] = fmaf(x1, da, g1[1][m]);
-                    g2[0][m] = fmaf(x0, db, g2[0][m]); g2[1][m] = fmaf(x1, db, g2[1][m]);
+            for (int h = 0; h < 2; h++) B[1][h] = *reinterpret_cast<const v4u_t *>(dab + h * kTrainH + r4 * kTrainR4 + piece * kTrainCol);
+        }
+        const float down_lo = down * (1.0f / 2048.0f), down_c = NB == 1 && piece >= 8 ? down_lo : down;
+        v4f_t c[8];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            uint4 xv[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++) { const int row = 32 * h + 4 * j + r4; xv[j] = mine[row * 16 + (piece ^ (row & 15))]; }
+#pragma unroll
+            for (int rt = 0; rt < 8; rt++) {
+                v4u_t A;
+#pragma unroll
+                for (int i = 0; i < 4; i++) {         // dim rt of the tokens j = 2i (low half) and 2i + 1
+                    const uint32_t w0 = word4(xv[2 * i], rt >> 1), w1 = word4(xv[2 * i + 1], rt >> 1);
+                    A[i] = __builtin_amdgcn_perm(w1, w0, (rt & 1) ? 0x07060302u : 0x05040100u);
+                }
+                const v4f_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                if constexpr (NB == 1) {
+                    c[rt] = mfma_train(A, B[0][h], h ? c[rt] : zero);
+                } else {                              // the registers do not allow a second set of tiles: added up at once
+                    const v4f_t c0 = mfma_train(A, B[0][h], zero), c1 = mfma_train(A, B[NB - 1][h], zero);
+#pragma unroll
+                    for (int n = 0; n < 4; n++) gw[rt][n] = fmaf(c0[n], down, fmaf(c1[n], down_lo, gw[rt][n]));
                 }
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-    // ---- fold: per-lane sums over the wavefront, the wavefronts over the workgroup, the workgroups by atomic adds
-    auto wsum = [](float v) {
+        if constexpr (NB == 1) {
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-        return v;
-    };
+            for (int rt = 0; rt < 8; rt++) {
+#pragma unroll
+                for (int n = 0; n < 4; n++) gw[rt][n] = fmaf(c[rt][n], down_c, gw[rt][n]);
+            }
+        }
+        wave_lds_sync();                              // rows and values are consumed
+    }
+    // ---- fold: lanes, then wavefronts through LDS, then the workgroups by atomic adds
 #pragma unroll
     for (int m = 0; m < M; m++) {
 #pragma unroll
-        for (int k = 0; k < M; k++) { const float v = wsum(g3[m][k]); if (lane == 0) atomicAdd(&a.dW3[m * M + k], v); }
-        const float v = wsum(gb[m]);
-        if (lane == 0 && a.dbias) atomicAdd(&a.dbias[m], v);
+        for (int k = 0; k < M; k++) { const float v = wave_sum(g3[m][k]); if (lane == 0) sums[wave][m * M + k] = v; }
+        const float v = wave_sum(gb[m]);
+        if (lane == 0) sums[wave][M * M + m] = v;
     }
     {
-        const float lm = wsum(lsum[0]) * a.inv_T, le = wsum(lsum[1]) * a.inv_T;
-        if (lane == 0) {
-            atomicAdd(&a.loss3[1], lm); atomicAdd(&a.loss3[2], le);
-            atomicAdd(&a.loss3[0], a.lambda * lm + (1.0f - a.lambda) * le);
-        }
+        const float lm = wave_sum(lsum[0]) * a.inv_T, le = wave_sum(lsum[1]) * a.inv_T;
+        if (lane == 0) { sums[wave][M * M + M] = lm; sums[wave][M * M + M + 1] = le; }
     }
+    float *fold = reinterpret_cast<float *>(mine);    // [dim][2M] per wavefront
 #pragma unroll
-    for (int e = 0; e < 2; e++) {
+    for (int rt = 0; rt < 8; rt++) {
 #pragma unroll
-        for (int m = 0; m < M; m++) {
-            red[wave][((2 * lane + e) * M + m)] = g1[e][m];
-            red[wave][2 * M * 64 + ((2 * lane + e) * M + m)] = g2[e][m];
+        for (int n = 0; n < 4; n++) {
+            float v = gw[rt][n];
+            if constexpr (NB == 1) v += __shfl_xor(v, 8);   // first and second halves
+            if (piece < 2 * M) fold[(8 * (4 * r4 + n) + rt) * (2 * M) + piece] = v;
         }
     }
     __syncthreads();
-    for (int i = tid; i < 4 * M * 64; i += kTrainWaves * 64) {
+    for (int k = tid; k < kD * 2 * M; k += kTrainWaves * 64) {
+        const int i = (int)((uint32_t)(k + (int)blockIdx.x * 64) % (uint32_t)(kD * 2 * M));   // workgroups end together: each starts elsewhere
         float v = 0.0f;
 #pragma unroll
-        for (int wv = 0; wv < kTrainWaves; wv++) v += red[wv][i];
-        if (i < 2 * M * 64) atomicAdd(&a.dW1[i], v); else atomicAdd(&a.dW2[i - 2 * M * 64], v);
+        for (int wv = 0; wv < kTrainWaves; wv++) v += reinterpret_cast<const float *>(&stage[wv][0])[i];
+        const int d = i / (2 * M), c = i % (2 * M);
+        atomicAdd(c < M ? &a.dW1[d * M + c] : &a.dW2[d * M + c - M], v);
+    }
+    if (tid < NS) {
+        float v = 0.0f;
+#pragma unroll
+        for (int wv = 0; wv < kTrainWaves; wv++) v += sums[wv][tid];
+        if (tid < M * M) atomicAdd(&a.dW3[tid], v);
+        else if (tid < M * M + M) { if (a.dbias) atomicAdd(&a.dbias[tid - M * M], v); }
+        else atomicAdd(&a.loss3[1 + tid - M * M - M], v);
+    }
+    if (tid == NS) {
+        float lm = 0.0f, le = 0.0f;
+#pragma unroll
+        for (int wv = 0; wv < kTrainWaves; wv++) { lm += sums[wv][M * M + M]; le += sums[wv][M * M + M + 1]; }
+        atomicAdd(&a.loss3[0], a.lambda * lm + (1.0f - a.lambda) * le);
     }
 }
 
@@ -207,7 +298,7 @@ hipError_t launch_router_train(const TrainArgs &a, int n_cu, hipStream_t s) {
     if (e != hipSuccess) return e;
     const long long n_tiles = (long long)a.BH * ((a.n_tok + 63) / 64);
     long long n_wg = (n_tiles + kTrainWaves - 1) / kTrainWaves;
-    if (n_wg > 4LL * n_cu) n_wg = 4LL * n_cu;          // every wavefront keeps its dW accumulators over many tiles
+    if (n_wg > n_cu) n_wg = n_cu;                      // every wavefront keeps its accumulators over many tiles
     switch (a.M) {
         case 1: return launch_t<1>(a, (unsigned)n_wg, s);
         case 2: return launch_t<2>(a, (unsigned)n_wg, s);

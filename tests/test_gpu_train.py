@@ -52,3 +52,31 @@ def test_router_loss_grad(mq, ref, B, Hkv, S, t0, t1, M, std, use_bias, defaults
         got = g.cpu().numpy().astype(np.float64)
         scale = max(np.abs(r).max(), 1e-30)
         assert np.abs(got - r).max() <= GRAD_TOL * scale, (name, np.abs(got - r).max() / scale)
+
+
+@pytest.mark.parametrize("Hkv,S,t0,M,pad", [
+    (70, 2000, 0, 4, 0),            # more tiles than wavefronts: several tiles each, the last of a row partly empty
+    (3, 65, 0, 5, 0),               # a tile of one row; two operand sets (more than four experts)
+    (5, 191, 1, 2, 8),              # rows 136 elements apart
+    (1, 63, 0, 7, 0),
+])
+def test_router_loss_grad_tiles(mq, ref, Hkv, S, t0, M, pad):
+    """Edges of the 64-row tiles, strided rows, one and two operand sets of the weight gradient's matrix products.  Tolerances
+    as above: the split of a value into two fp16 numbers adds at most 2^-22 of the value, far below them."""
+    rng = np.random.default_rng(S * 10 + M)
+    bits = (2, 4, 8, 16, 2, 4, 8, 16)[:M]
+    cfg, rcfg = T._cfgs(mq, ref, 1, Hkv, Hkv, 64, 64, bits, 0)
+    K, _ = T._rand_kv(rng, 1, Hkv, S)
+    W1, W2 = ((rng.standard_normal((128, M)) * 0.1).astype(np.float16) for _ in range(2))
+    W3 = (rng.standard_normal((M, M)) * 0.5).astype(np.float16)
+    nll = np.array([2.0], np.float32)
+    pm, pe = np.array([1.0 / b for b in bits], np.float32), np.array([16.0 / b for b in bits], np.float32)
+    want = ref.router_loss_grad(rcfg, K, t0, S, W1, W2, W3, None, nll, pm, pe, 0.3)
+    Kd = torch.full((1, Hkv, S, 128 + pad), float("nan"), dtype=torch.float16, device="cuda")   # what lies between the rows is not read
+    Kd[..., :128] = T._dev(K)
+    got = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((3,), (128, M), (128, M), (M, M), (M,))]
+    mq.router_loss_grad(cfg, Kd[..., :128], t0, S, T._dev(W1), T._dev(W2), T._dev(W3), None, T._dev(nll), None, None, 0.3, *got)
+    torch.cuda.synchronize()
+    for name, g, r, tol in zip(("loss", "dW1", "dW2", "dW3", "dbias"), got, want, (LOSS_TOL,) + (GRAD_TOL,) * 4):
+        err = np.abs(g.cpu().numpy().astype(np.float64) - r).max() / max(np.abs(r).max(), 1e-30)
+        assert err <= tol, (name, err)
