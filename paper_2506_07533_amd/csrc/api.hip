@@ -205,10 +205,10 @@ int moqae_route_chunks(const moqae_cfg *cfg,
     a.W1 = static_cast<const uint16_t *>(W1); a.W2 = static_cast<const uint16_t *>(W2);
     a.W3 = static_cast<const uint16_t *>(W3); a.bias = logit_bias;
     a.expert = expert; a.expert_stride = expert_stride; a.votes = votes;
-    a.chunk_begin = chunk_begin; a.N = cfg->chunk; a.Hkv = cfg->n_kv_heads;
+    a.chunk_begin = chunk_begin; a.n_chunks = chunk_end - chunk_begin;
+    a.N = cfg->chunk; a.BH = cfg->batch * cfg->n_kv_heads; a.Hkv = cfg->n_kv_heads;
     a.freeze_chunks = cfg->freeze_chunks; a.e16 = e16 < 0 ? 0 : e16;
-    hipError_t e = launch_route(a, cfg->n_experts, chunk_end - chunk_begin, cfg->batch * cfg->n_kv_heads,
-                                static_cast<hipStream_t>(stream));
+    hipError_t e = launch_route(a, cfg->n_experts, cu_count(), static_cast<hipStream_t>(stream));
     return e == hipSuccess ? MOQAE_OK : MOQAE_E_HIP;
 }
 

@@ -10,9 +10,9 @@ struct RouteArgs {
     const uint16_t *K; int64_t stride_b, stride_h, stride_s;
     const uint16_t *W1, *W2, *W3; const float *bias;
     uint8_t *expert; int64_t expert_stride; int32_t *votes;
-    int chunk_begin, N, Hkv, freeze_chunks, e16;
+    int chunk_begin, n_chunks, N, BH, Hkv, freeze_chunks, e16;
 };
-hipError_t launch_route(const RouteArgs &a, int M, int n_chunks, int BH, hipStream_t s);
+hipError_t launch_route(const RouteArgs &a, int M, int n_cu, hipStream_t s);
 
 struct PackArgs {
     const uint16_t *K, *V; int64_t stride_b, stride_h, stride_s;

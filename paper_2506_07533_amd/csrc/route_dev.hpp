@@ -1,4 +1,4 @@
-// Device code of the router shared by route_kernel and the fused route + pack kernel (Eq. (1)-(2), Sec. 3.2).
+// Device code of the router shared by the routing, the fused route + pack and the training kernels (Eq. (1)-(2), Sec. 3.2).
 #pragma once
 #include "moqae_dev.hpp"
 
@@ -27,7 +27,8 @@ __device__ __forceinline__ float exp_pinned(float x) {
 
 // 64 dims of a key row (eight 16-byte pieces xr[0..7], dims dbase..dbase+63) into the two running sums per expert,
 // in ascending order of the dims.  W1w, W2w: the fp16 weight matrices as 32-bit words (wave-uniform loads; WP: a plain
-// pointer, or const_words where the compiler would not see by itself that nothing in the kernel writes them).
+// pointer, or const_words where the compiler would not see by itself that nothing in the kernel writes them; dbase should
+// then vary in a loop around the call, or the weights of the whole row are loaded ahead of it).
 typedef const uint32_t __attribute__((address_space(4))) *const_words;
 template <int M, typename WP>
 __device__ __forceinline__ void route_half_row(const uint4 *xr, int dbase, WP W1w, WP W2w,

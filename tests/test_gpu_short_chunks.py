@@ -1,0 +1,52 @@
+"""Chunks shorter than a window of 64 tokens share wavefronts in the routing kernel and take a wavefront per side in the
+packing kernel: windows that end inside a row, frozen chunks inside a window, calls that begin inside one, odd numbers of
+chunk sides; bit-exact against the CPU oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import test_gpu_parity as T                                              # noqa: E402  (helpers only)
+
+mq = T.mq
+
+
+@pytest.mark.parametrize("B,Hkv,N,C,M,freeze,c0,pad", [
+    (1, 3, 32, 7, 4, 1, 0, 0),          # a window of one chunk at the end of every row
+    (2, 2, 32, 9, 8, 3, 1, 8),          # the call begins in the middle of a window; rows 136 elements apart
+    (1, 2, 16, 5, 3, 2, 0, 0),
+    (1, 5, 8, 19, 2, 10, 3, 0),         # a window frozen as a whole, one in part
+    (3, 1, 8, 1, 1, 0, 0, 0),
+    (2, 40, 32, 210, 4, 1, 0, 0),       # more windows than wavefronts of the grid: several each
+])
+def test_route_windows_of_short_chunks(mq, ref, B, Hkv, N, C, M, freeze, c0, pad):
+    rng = np.random.default_rng(N * 1000 + C)
+    bits = (16, 2, 4, 8, 2, 4, 8, 16)[:M]
+    cfg, rcfg = T._cfgs(mq, ref, B, Hkv, Hkv, N, 32, bits, freeze)
+    K, _ = T._rand_kv(rng, B, Hkv, C * N)
+    W = [(rng.standard_normal(s) * 0.3).astype(np.float16) for s in ((128, M), (128, M), (M, M))]
+    e_ref, v_ref = ref.route_chunks(rcfg, K, 0, C, *W)
+    Kd = torch.full((B, Hkv, C * N, 128 + pad), float("nan"), dtype=torch.float16, device="cuda")
+    Kd[..., :128] = T._dev(K)
+    expert = torch.full((B * Hkv, C), 255, dtype=torch.uint8, device="cuda")
+    votes = torch.full((B * Hkv, C, M), -1, dtype=torch.int32, device="cuda")
+    mq.route_chunks(cfg, Kd[..., :128], c0, C, *[T._dev(w) for w in W], None, expert, votes)
+    torch.cuda.synchronize()
+    e, v = expert.cpu().numpy(), votes.cpu().numpy()
+    assert np.array_equal(e[:, c0:], e_ref[:, c0:]) and np.array_equal(v[:, c0:], v_ref[:, c0:])
+    assert (e[:, :c0] == 255).all() and (v[:, :c0] == -1).all()         # entries before the call's chunks are not touched
+
+
+@pytest.mark.parametrize("B,Hkv,N,G,C,kpc", [
+    (1, 2, 8, 64, 5, 0), (2, 1, 16, 32, 3, 0), (1, 3, 32, 32, 7, 1), (1, 3, 32, 64, 1, 0), (2, 2, 64, 64, 5, 1), (1, 1, 8, 32, 1, 0),
+])
+def test_pack_wavefront_per_side(mq, ref, B, Hkv, N, G, C, kpc):
+    rng = np.random.default_rng(N * 100 + G + C)
+    cfg, rcfg = T._cfgs(mq, ref, B, Hkv, Hkv, N, G, (2, 4, 8, 16), 0, kpc)
+    K, V = T._rand_kv(rng, B, Hkv, C * N)
+    expert = rng.integers(0, 4, (B * Hkv, C)).astype(np.uint8)
+    (arena, used, off, status), (arena_ref, used_ref, off_ref, st_ref) = T._pack_both(mq, ref, cfg, rcfg, K, V, 0, C, expert)
+    assert int(status.item()) == st_ref == 0 and int(used.item()) == int(used_ref[0])
+    assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    assert np.array_equal(arena.cpu().numpy(), arena_ref)
