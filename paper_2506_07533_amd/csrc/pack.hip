@@ -229,6 +229,29 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(PackArgs a) {
     pack_side<G, KPC>(src, a.stride_s, N, bits, isV, blk, vcodes, tid, kPackThreads);
 }
 
+// Short chunks: one wavefront per (K or V, chunk, row), four of them in a workgroup.  A 32-token chunk has 64 or 128 (token
+// row, group) items per side, a fraction of pack_kernel's 256 threads.  2.1 M rows, groups of 64 (32) tokens, against
+// pack_kernel: 8 tokens 467 (384) us against 846 (767), 16 tokens 259 (249) against 455 (410), 32 tokens 251 (259) against
+// 280 (266).  At 64 tokens pack_kernel is the better one (245 against 253), except for keys per channel in groups of 64:
+// there K is ONE token group, a wavefront's work whatever the workgroup (255 against 302).
+static bool pack_by_wavefront(const PackArgs &a) { return a.N < 64 || (a.N == 64 && a.kpc && a.G == 64); }
+template <int G, bool KPC>
+__global__ __launch_bounds__(kPackThreads) void pack_wave_kernel(PackArgs a) {
+    extern __shared__ uint8_t vcodes[];               // [4][N][kVRow] code bytes (V only)
+    if (*a.status != 0) return;
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int side = (int)blockIdx.x * (kPackThreads / 64) + wave;       // K and V of a chunk side by side
+    if (side >= 2 * a.n_chunks) return;
+    const int isV = side & 1, c = a.chunk_begin + (side >> 1), u = (int)blockIdx.y, N = a.N;
+    const int bits = a.bits_of[a.expert[(int64_t)u * a.expert_stride + c]];
+    uint8_t *blk = a.arena + a.chunk_off[(int64_t)u * a.off_stride + c];
+    const int b = u / a.Hkv, h = u % a.Hkv;
+    const uint16_t *src = (isV ? a.V : a.K) + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h
+                        + (int64_t)c * N * a.stride_s;
+    pack_side<G, KPC, true>(src, a.stride_s, N, bits, isV, blk, vcodes + wave * N * kVRow, lane, 64);
+}
+
 // The new end of the arena = the end of the last block in (b, h, c) order.  A kernel of its own, after
 // the plan: the workgroups of the plan read the counter at different times, so none of them may move
 // it, and the few registers this takes would cost the pack kernel occupancy.
@@ -265,7 +288,17 @@ hipError_t launch_pack(const PackArgs &a, hipStream_t s) {
     if (e != hipSuccess) return e;
     dim3 grid(2u, (unsigned)a.n_chunks, (unsigned)a.BH);
     const size_t lds = (size_t)a.N * kVRow;
-    if (a.kpc) {
+    if (pack_by_wavefront(a)) {
+        constexpr int kSides = kPackThreads / 64;
+        const dim3 wgrid((unsigned)((2 * a.n_chunks + kSides - 1) / kSides), (unsigned)a.BH);
+        if (a.kpc) {
+            if (a.G == 32) hipLaunchKernelGGL((pack_wave_kernel<32, true>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
+            else           hipLaunchKernelGGL((pack_wave_kernel<64, true>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
+        } else {
+            if (a.G == 32) hipLaunchKernelGGL((pack_wave_kernel<32, false>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
+            else           hipLaunchKernelGGL((pack_wave_kernel<64, false>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
+        }
+    } else if (a.kpc) {
         if (a.G == 32) hipLaunchKernelGGL((pack_kernel<32, true>), grid, dim3(kPackThreads), lds, s, a);
         else           hipLaunchKernelGGL((pack_kernel<64, true>), grid, dim3(kPackThreads), lds, s, a);
     } else {
