@@ -36,7 +36,7 @@ HBM_PEAK_GBPS = 8000.0        # MI355X HBM3E, vendor figure
 # times base-128 digits of a 21-bit fixed-point copy of q / of the softmax weights on v_mfma_i32_16x16x64_i8, exact
 # integer sums; grouped queries: fp16 code fields times fp16 weights on v_mfma_f32_16x16x32_f16; softmax and all
 # accumulation in binary32 (no narrower than the FP16 de-quantisation of the paper's "Limitations" section).
-DTYPE = {1: "i8-mfma fixed-point 21b / f32 accumulate", 0: "f16-mfma / f32 accumulate"}
+DTYPE = {1: "i8-mfma fixed-point 24b / f32 accumulate", 0: "f16-mfma / f32 accumulate"}
 
 
 def measured_traffic(workload):

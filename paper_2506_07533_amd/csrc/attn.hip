@@ -587,7 +587,7 @@ __device__ __forceinline__ void mc_value_dots(const VRegs<G> &v, int lane, int w
 // v_mfma_i32_16x16x64_i8 computes C[i][x] += sum_k A[i][k] B[k][x] on signed bytes; lane l = 16*xq + x
 // holds A[x][16xq..16xq+15], B[16xq..16xq+15][x] and C[4xq..4xq+3][x].  The codes are the B operand:
 // masking a code word byte-wise leaves one code per byte (2 bits: four planes, the code shifted left
-// by 0, 2, 4, 5 bits; 4 bits: the low and the high nibbles; 8 bits: the bytes themselves, minus 128
+// by 0, 2, 0, 2 bits; 4 bits: the low and the high nibbles; 8 bits: the bytes themselves, minus 128
 // through a sign flip).  The other factor -- q for the scores, softmax weight * V scale for the values --
 // is turned into a fixed-point integer, multiplied by the power of two that undoes its plane's shift,
 // and split into four base-128 digits that sit in four rows of A; the four digit sums come back in the
@@ -602,21 +602,25 @@ __device__ __forceinline__ void mc_value_dots(const VRegs<G> &v, int lane, int w
 __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
     return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
 }
+constexpr int kFix = 23;                                 // fixed-point numbers are below 2^(kFix + 1): four digits hold 28 bits, planes take 2
 // sum_n 128^n C[n] as fp32 (the two halves are exact integers below 2^31)
 __device__ __forceinline__ float iq_combine(v4i c) {
     const int hi = c[3] * 128 + c[2], lo = c[1] * 128 + c[0];
     return fmaf((float)hi, 16384.0f, (float)lo);
 }
-// The byte planes of a code word.  2 bits: byte y of plane p holds code 8*(y%2) + 2p + y/2 of the word,
-// shifted left by {0, 2, 4, 5}[p]; 4 bits: code 4*(y%2) + 2p + y/2; 8 bits: code 2*(y%2) + y/2, minus 128.
+// The byte planes of a code word.  2 bits: byte y of plane p holds code 8*(y%2) + 2p + y/2 of the word, shifted left by
+// {0, 2, 0, 2}[p] (five operations, as the shifts {0, 2, 4, 5} would take that leave three planes where they lie; but the
+// factor that every product carries is 2^2 and not 2^6, so that q and the weights have room for 24 bits and not 21:
+// the error of an attention output against binary64 went from 9.9e-6 to 1.3e-6 at 128k tokens); 4 bits: code 4*(y%2) + 2p + y/2; 8 bits: code 2*(y%2) + y/2, minus 128.
 template <int BITS> struct IQ {
     static constexpr int NP = 8 / BITS;                  // planes of a word
-    static constexpr int LGM = BITS == 2 ? 6 : 0;        // log2 of the factor every product carries
+    static constexpr int LGM = BITS == 2 ? 2 : 0;        // log2 of the factor every product carries
     static constexpr int BI = BITS == 2 ? 0 : (BITS == 4 ? 1 : 2);
     __device__ static __forceinline__ void planes(uint32_t w, int *m) {
         if constexpr (BITS == 2) {
+            const uint32_t h = w >> 4;
             m[0] = (int)(w & 0x03030303u); m[1] = (int)(w & 0x0c0c0c0cu);
-            m[2] = (int)(w & 0x30303030u); m[3] = (int)((w >> 1) & 0x60606060u);
+            m[2] = (int)(h & 0x03030303u); m[3] = (int)(h & 0x0c0c0c0cu);
         } else if constexpr (BITS == 4) {
             m[0] = (int)(w & 0x0f0f0f0fu); m[1] = (int)((w >> 4) & 0x0f0f0f0fu);
         } else {
@@ -885,9 +889,9 @@ __device__ __forceinline__ float iq_weights(const VRegs<G> &v, int lane, int wav
         wmax = fmaxf(wmax, wv[jj]);
     }
     wmax = wave_max(wmax);
-    // 2^ef <= wmax < 2^(ef+1) (ef >= -100): weight * 2^(20 - ef) < 2^21
+    // 2^ef <= wmax < 2^(ef+1) (ef >= -100): weight * 2^(23 - ef) < 2^24
     const int ef = max((int)((__builtin_bit_cast(uint32_t, wmax) >> 23) & 255u) - 127, -100);
-    const float up = __builtin_bit_cast(float, (uint32_t)(127 + 20 - ef) << 23);
+    const float up = __builtin_bit_cast(float, (uint32_t)(127 + kFix - ef) << 23);
     uint8_t *img = reinterpret_cast<uint8_t *>(&L.wa[wave][0][0]);
 #pragma unroll
     for (int jj = 0; jj < MV; jj++) {
@@ -898,7 +902,7 @@ __device__ __forceinline__ float iq_weights(const VRegs<G> &v, int lane, int wav
         dst[32] = (uint8_t)((W >> 14) & 127u); dst[48] = (uint8_t)((W >> 21) & 127u);
     }
     wave_sync();
-    return __builtin_bit_cast(float, (uint32_t)(127 + ef - 20 - IQ<BITS>::LGM) << 23);
+    return __builtin_bit_cast(float, (uint32_t)(127 + ef - kFix - IQ<BITS>::LGM) << 23);
 }
 
 // Weighted value sum of a quantised unit on the integer matrix cores.
@@ -939,7 +943,7 @@ __device__ __forceinline__ void iq_values(const VRegs<G> &v, int lane, int wave,
 }
 
 // Tables of the integer path for the queries of one row (REP == 1), built by the whole workgroup
-// once L.qraw is in place:  iq[d] = q_d as a fixed-point integer below 2^21 in magnitude, qa = the
+// once L.qraw is in place:  iq[d] = q_d as a fixed-point integer below 2^24 in magnitude, qa = the
 // eight A operands of the score products (2 bits: word 0..3 of a slot; 4 bits: word pair 0, 1;
 // 8 bits: register parity 0, 1), iqpart = sum of iq over a lane's dims inside one group (times the
 // common factor of the bit-width), iqscale = softmax scale (log2 domain) / fixed-point factors.
@@ -950,9 +954,9 @@ __device__ __forceinline__ void iq_build_q(AttnLds<G, 1, NWV> &L, int tid, int l
     float qm = fmaxf(fabsf(half_bits_to_float(pr & 0xffffu)), fabsf(half_bits_to_float(pr >> 16)));
     qm = wave_max(qm);
     const int ef = qm > 0.0f ? (int)((__builtin_bit_cast(uint32_t, qm) >> 23) & 255u) - 127 : 0;   // 2^ef <= max |q| < 2^(ef+1)
-    const float up = __builtin_bit_cast(float, (uint32_t)(127 + 20 - ef) << 23);
+    const float up = __builtin_bit_cast(float, (uint32_t)(127 + kFix - ef) << 23);
     const uint16_t *qraw = reinterpret_cast<const uint16_t *>(L.qraw);
-    if (tid < 3) L.iqscale[tid] = scale_log2 * __builtin_bit_cast(float, (uint32_t)(127 + ef - 20 - (tid == 0 ? 6 : 0)) << 23);
+    if (tid < 3) L.iqscale[tid] = scale_log2 * __builtin_bit_cast(float, (uint32_t)(127 + ef - kFix - (tid == 0 ? IQ<2>::LGM : 0)) << 23);
     int s16 = 0;                                          // sums of iq over blocks of 16 dims (wavefronts 0 and 1)
     if (tid < kD) {
         s16 = L.iq[tid] = (int)rintf(half_bits_to_float(qraw[tid]) * up);
@@ -969,7 +973,7 @@ __device__ __forceinline__ void iq_build_q(AttnLds<G, 1, NWV> &L, int tid, int l
 #pragma unroll
         for (int y = 0; y < 4; y++) {
             int d, sh = 0;                                // dim of byte 4m + y, power of two that undoes the plane's shift
-            if (t < 4)      { d = (xq & 1) * 64 + t * 16 + 8 * (y & 1) + 2 * m + (y >> 1); sh = m == 3 ? 1 : 6 - 2 * m; }
+            if (t < 4)      { d = (xq & 1) * 64 + t * 16 + 8 * (y & 1) + 2 * m + (y >> 1); sh = (m & 1) ? 0 : 2; }
             else if (t < 6) { d = xq * 32 + (2 * (t - 4) + (m >> 1)) * 8 + 4 * (y & 1) + 2 * (m & 1) + (y >> 1); }
             else            { d = (4 * (t - 6) + xq) * 16 + m * 4 + 2 * (y & 1) + (y >> 1); }
             const int Q = L.iq[d];
@@ -989,7 +993,7 @@ __device__ __forceinline__ void iq_build_q(AttnLds<G, 1, NWV> &L, int tid, int l
             const int nb = E / gs / 16, b0 = (part * E + gi * (E / gs)) / 16;
             for (int k = 0; k < nb; k++) sq += L.iqs16[b0 + k];
         }
-        L.iqpart[bi][part][gi] = (float)sq * (bi == 0 ? 64.0f : 1.0f);
+        L.iqpart[bi][part][gi] = (float)sq * (bi == 0 ? (float)(1 << IQ<2>::LGM) : 1.0f);
     }
 }
 
@@ -1005,7 +1009,7 @@ __device__ __forceinline__ void iq_build_wpos(AttnLds<G, 1, NWV> &L, int tid) {
         if (tv < (128 >> bi)) {
             int blk = 0, xq, b, sh = 0;
             if (bi == 0)      { blk = tv >> 6; const int tb = tv & 63, e = tb & 15, p = (e & 7) >> 1;
-                                xq = tb >> 4; b = 4 * p + (e >> 3) + 2 * (e & 1); sh = p == 3 ? 1 : 6 - 2 * p; }
+                                xq = tb >> 4; b = 4 * p + (e >> 3) + 2 * (e & 1); sh = (p & 1) ? 0 : 2; }
             else if (bi == 1) { const int tb = tv & 31, e = tb & 7, p = (e & 3) >> 1;
                                 xq = tb >> 3; b = 8 * (tv >> 5) + 4 * p + (e >> 2) + 2 * (e & 1); }
             else              { const int e = tv & 3;
