@@ -78,12 +78,12 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     v4u qmc[REP > 1 ? 3 : 1][4][REP > 1 ? 64 : 1];       // grouped queries: score operands A per (bit-width, pass, lane)
     float comb[NWV][REP][kD + 2];                        // per-wavefront (o, m, l) at the end of a row segment
     uint32_t qraw[REP * 64];                             // the row's queries as loaded (fp16 pairs)
-    unsigned long long desc[kDescCap];                   // chunk descriptors of the current pass: offset | expert
+    unsigned long long desc[kDescCap + 2];               // chunk descriptors of the current pass: offset | log2 bits (Gather: see there)
     // ticket queue of the workgroup: local tickets [0, limit) are granted; batch i maps local
     // tickets from bl[i] on to the row's tickets from bg[i] on
     uint16_t ustart[kDescCap];                           // first unit of every chunk of the segment
     uint16_t inv[kUnitCap];                              // unit -> chunk of the segment
-    uint32_t wscan[NWV];
+    uint32_t wscan[NWV], wscan2[NWV];
     uint32_t U[kMaxWeightedRowsLds + 1], r0;            // prefix sums of the rows' units
     uint32_t next, limit, done, fetching, g_seen, nb;
     uint32_t bl[kMaxBatches], bg[kMaxBatches];
@@ -149,7 +149,38 @@ struct Unit {
     int tail_rows;                                       // residual units: valid residual rows from the unit's first row on (else huge)
     const uint8_t *kb, *vb;                              // bases: the chunk block (both), or the residual K and V rows of the row
     uint32_t kc, km, vc, vm;                             // byte offsets of the unit's K codes / K meta (from kb), V codes / V meta (from vb)
+    // units of short chunks (see Gather): kb = the arena, the blocks' offsets in it desc[first .. last] (K side), + voff entries for the V side
+    bool half;                                           // 8 tokens at 2 bits: every second run of 8 tokens of the unit does not exist
+    int first, last, voff;
 };
+
+// Units of short chunks (8, 16, 32 tokens; one query head per KV head).  A unit of one such chunk would hold a few hundred
+// bytes to 2 KiB of codes instead of 8 KiB and cost nearly as much as a full one, so a unit takes as many chunks of the same
+// bit-width as fill it: the row's block offsets are ordered by bit-width at the set-up (the order of the tokens does not
+// matter to a softmax; the residual rows of K and V are two more entries, as distances from the arena) and every lane's 16
+// bytes are addressed through the entry of the lane's chunk, so that the registers hold what a unit of one long chunk would.  A chunk counts
+// as NV tokens: N, but 16 for 8 tokens at 2 bits, whose V slice is half empty (the second half of the K tokens is masked).
+// The chunk and the place inside it are a part that depends on the lane, computed once, plus a scalar part per register;
+// entries past the unit's last chunk read the last one again.
+// 8 sequences x 32 heads x 8k tokens, 60/30/5/5 % at 2/4/8/16 bits, 32-token chunks: 76 us a call against 122, 16 tokens 78
+// against 212, 8 tokens 104 against 387; a cache of 2-bit chunks alone 46 against 110, of 8-bit chunks, whose units were full
+// before, 103 against 99.  Grouped queries keep a unit per chunk: their kernel is bound by instruction issue and at its
+// register limit (tried: 0.26 to 1.17 of the speed), as do 64-token chunks, where only 2-bit units gain (the mix 0.95).
+struct Gather {
+    int lgb, lgnv, N;
+    bool raw;
+    __device__ __forceinline__ Gather(const Unit &u, int N_) : lgb(u.lgb), N(N_), raw(u.lgb == 4), arena(u.kb) {
+        lgnv = max(31 - __builtin_clz((unsigned)N_), u.lgb == 1 ? 4 : 3);
+    }
+    const uint8_t *arena;
+    template <typename LDS> __device__ __forceinline__ const uint8_t *block(const LDS &L, int entry) const { return arena + L.desc[entry]; }
+    __device__ __forceinline__ uint32_t code_bytes() const { return (uint32_t)N << (4 + lgb); }
+    __device__ __forceinline__ uint32_t vcode_bytes() const { return (uint32_t)max(N, lgb == 1 ? 16 : 8) << (4 + lgb); }
+};
+// log2 of the units a chunk of 2^lgnv tokens takes (positive), or of the chunks a unit takes (negative)
+__device__ __forceinline__ int gather_shift(int N, int lgb) {
+    return max(31 - __builtin_clz((unsigned)N), lgb == 4 ? 4 : (lgb == 1 ? 4 : 3)) - (8 - lgb);
+}
 
 template <int G> struct KRegs {
     static constexpr int GSMAX = 2;                      // a 2-bit slot of 64 codes spans two groups of 32; per-channel keys: two dims
@@ -176,14 +207,46 @@ __device__ __forceinline__ uint32_t ld4(const uint8_t *sbase, uint32_t voff) {
 
 // The V side: the 16-byte slots 64*j + l of the unit's V KiBs and its (token, group) meta
 // words 64*jj + l, same conventions.
-// SMALL (chunks of 8, 16 or 32 tokens, one unit per quantised chunk): the chunk is one token block of QD = 1, 2 or
+// GATH: units of several short chunks, see Gather.
+// SMALL (chunks of 8, 16 or 32 tokens, one unit per quantised chunk; grouped queries): the chunk is one token block of QD = 1, 2 or
 // 4 slices, its V codes are 2 (8 bits: 4) tiles of 16*QD slots.  With QD < 4 lanes 0..16*QD-1 take tile i into c[i]
 // as the lanes of the first slices of a full block would; the lanes of the absent slices and the registers of the
 // absent tiles / second block hold zeros.  The meta words of a short chunk are fewer than 64: the lanes past
 // them read the last one (their tokens have weight 0).
-template <int G, bool SMALL>
-__device__ __forceinline__ void load_v(const Unit &u, int lane, VRegs<G> &v, int N) {
+template <int G, bool SMALL, bool GATH, typename LDS>
+__device__ __forceinline__ void load_v(const Unit &u, int lane, VRegs<G> &v, int N, const LDS &L) {
     constexpr int NG = kD / G;
+    if constexpr (GATH) {
+        // register i: tile cg of token block bu of a full unit, lane slice qd = lane / 16; the slice's tokens lie in one chunk
+        const Gather g(u, N);
+        const int qd = lane >> 4, first = u.first + u.voff, last = u.last + u.voff;
+        const int lgqd = min(2, g.lgnv - (u.lgb == 1 ? 4 : 3));           // log2 of the slices of a chunk's token block
+        const uint32_t vbase = g.raw ? u.vc : g.code_bytes() + (uint32_t)N * (NG * 4);
+        {
+            const int lchunk = first + (g.raw ? 0 : qd >> lgqd);
+            const uint32_t loff = vbase + (g.raw ? (uint32_t)lane * 16u : (uint32_t)((qd & ((1 << lgqd) - 1)) * 16 + (lane & 15)) * 16u);
+            const uint8_t *b0 = g.block(L, min(lchunk, last)) + loff;
+            const uint8_t *b1 = g.block(L, min(lchunk + (u.lgb < 3 ? 1 << (2 - lgqd) : 0), last)) + loff;   // 8 bits: one block of four tiles
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint32_t tile = u.lgb == 3 ? (uint32_t)i : (uint32_t)(i & 1);
+                const uint32_t o = g.raw ? (uint32_t)min(i, u.nsub - 1) * 1024u : tile << (8 + lgqd);
+                v.c[i] = ld16(i < 2 ? b0 : b1, o);
+            }
+        }
+        {
+            const int s2 = g.lgnv + (NG == 2 ? 1 : 2);                    // log2 of the meta words of a chunk (as NV tokens)
+            const int words = N * NG;
+            const int lchunk = first + (g.raw ? 0 : lane >> s2);
+            const uint32_t loff = vbase + (g.raw ? 0u : g.vcode_bytes() + (uint32_t)(lane & (words - 1)) * 4u);
+#pragma unroll
+            for (int jj = 0; jj < VRegs<G>::MV; jj++) {
+                const int k = g.raw ? 0 : (64 * jj) >> s2;
+                v.m[jj] = ld4(g.block(L, min(lchunk + k, last)) + loff, g.raw ? 0u : (uint32_t)((64 * jj) & (words - 1)) * 4u);
+            }
+        }
+        return;
+    }
     const int nw = u.nvalid * NG;                                         // SMALL: meta words of the unit (u.nsub counts whole KiB of codes)
     const uint32_t vv = u.vc + (uint32_t)lane * 16u, vmo = u.vm + (uint32_t)(SMALL ? min(lane, nw - 1) : lane) * 4u;
     const int nvm = u.lgb == 4 ? 1 : (SMALL ? max(nw >> 6, 1) : (u.nsub * NG) >> u.lgb);   // rows of 64 meta words, >= 1
@@ -641,10 +704,47 @@ __device__ __forceinline__ uint32_t word_of(const uint4 &c, int i) {
 // raw fp16 units keep the slot order and have no meta.
 // KPC (keys quantised per channel): the meta words are [token group][dim]; lane l takes the words of dims 2l, 2l+1 of
 // the (up to four) token groups the unit's tokens lie in.
-template <int G, bool KPC, bool SMALL>
-__device__ __forceinline__ void load_k_iq(const Unit &u, int lane, KRegs<G> &k) {
+template <int G, bool KPC, bool SMALL, typename LDS>
+__device__ __forceinline__ void load_k_iq(const Unit &u, int lane, KRegs<G> &k, int N, const LDS &L) {
     constexpr int NG = kD / G;
     const uint32_t xq = (uint32_t)lane >> 4, c = (uint32_t)lane & 15u;
+    if constexpr (SMALL) {
+        const Gather g(u, N);
+        {
+            const int s2 = g.lgnv + u.lgb;                                // log2 of the 16-byte slots of a chunk: at least 5
+            const int lchunk = u.first + (g.raw ? 0 : lane >> s2);
+            const uint32_t loff = g.raw ? u.kc + (uint32_t)lane * 16u : (uint32_t)(lane & ((1 << s2) - 1)) * 16u;
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const uint32_t o = g.raw ? (uint32_t)min(j, u.nsub - 1) * 1024u : (uint32_t)((64 * j) & ((1 << s2) - 1)) * 16u;
+                k.c[j] = ld16(g.block(L, min(lchunk + (g.raw ? 0 : (64 * j) >> s2), u.last)) + loff, o);
+            }
+        }
+        const uint32_t mbase = g.raw ? u.kc : g.code_bytes();
+        if constexpr (KPC) {                              // 32-token chunks in groups of 32: a token group per chunk (or, at 16 bits, none)
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const uint2 mm = ld8(g.block(L, min(u.first + (g.raw ? 0 : j), u.last)) + mbase, g.raw ? 0u : (uint32_t)lane * 8u);
+                k.m[j][0] = mm.x; k.m[j][1] = mm.y;
+            }
+            return;
+        }
+        // token of register j: a part of the lane's, below 32, and 32j, 16j or 16 (j / 2)
+        const uint32_t lt = u.lgb == 1 ? 16u * (xq >> 1) + c : c;
+        const uint32_t grp = u.lgb == 1 ? (xq & 1u) * (NG / 2) : (u.lgb == 2 ? (NG == 2 ? (xq >> 1) : xq) : (NG == 2 ? 0u : (xq >> 1)));
+        const uint32_t nv1 = (1u << g.lgnv) - 1u;
+        const int lchunk = u.first + (g.raw ? 0 : (int)(lt >> g.lgnv));
+        const uint32_t loff = mbase + (g.raw ? 0u : ((lt & nv1) * NG + grp) * 4u);
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint32_t tj = u.lgb == 1 ? 32u * j : (u.lgb == 2 ? 16u * j : 16u * (j >> 1));
+            const uint32_t o = g.raw ? 0u : ((tj & nv1) * NG + (u.lgb == 3 ? (uint32_t)(j & 1) * (NG / 2) : 0u)) * 4u;
+            const uint8_t *mb = g.block(L, min(lchunk + (g.raw ? 0 : (int)(tj >> g.lgnv)), u.last)) + loff;
+            k.m[j][0] = ld4(mb, o);
+            if constexpr (NG == 4) k.m[j][1] = ld4(mb, o + (u.lgb == 1 ? 4u : 0u));
+        }
+        return;
+    }
     const uint32_t vk = u.kc + (uint32_t)lane * 16u;
 #pragma unroll
     for (int j = 0; j < 4; j++) k.c[j] = ld16(u.kb, vk + (uint32_t)min(j, u.nsub - 1) * 1024u);   // short unit: the last KiB is read again (ignored)
@@ -667,7 +767,7 @@ __device__ __forceinline__ void load_k_iq(const Unit &u, int lane, KRegs<G> &k) 
     const uint32_t w2 = c * NG + (NG == 2 ? (xq >> 1) : xq);
     const uint32_t w3 = c * NG + (NG == 2 ? 0u : (xq >> 1));
     const uint32_t vm = u.lgb == 4 ? u.kc + c * 4u : u.km + (u.lgb == 1 ? w1 : (u.lgb == 2 ? w2 : w3)) * 4u;
-    const int jmax = (SMALL || u.lgb == 1) ? u.nsub - 1 : 3;   // a short unit's block ends early
+    const int jmax = u.lgb == 1 ? u.nsub - 1 : 3;              // a short unit's block ends early
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         const uint32_t jc = (uint32_t)min(j, jmax);
@@ -703,8 +803,7 @@ __device__ __forceinline__ void iq_regroup(const KRegs<G> &k, int lane, int wave
 }
 
 // Scores of a quantised unit -> L.sc (log2 domain), running maximum updated.
-// SMALL: the unit may hold fewer tokens than a KiB of codes does (chunks of 8 and 16 tokens); the scores of the
-// tokens past u.nvalid are masked one by one.
+// SMALL: the unit may end inside a KiB of codes; the scores of the tokens past u.nvalid are masked one by one.
 template <int BITS, int G, int NWV, bool SMALL>
 __device__ __forceinline__ void iq_scores(const Unit &u, const KRegs<G> &k, int lane, int wave,
                                           AttnLds<G, 1, NWV> &L, WaveState<1> &st) {
@@ -742,7 +841,7 @@ __device__ __forceinline__ void iq_scores(const Unit &u, const KRegs<G> &k, int 
                 ps = fmaf(half_bits_to_float(k.m[j][gi] >> 16), qp[gi], ps);
             }
             ps += __shfl_xor(ps, 16);
-            const bool ok = SMALL ? 32 * j + 16 * (xq >> 1) + c < u.nvalid : j < u.nsub;   // KiB past a short unit: ignored
+            const bool ok = SMALL ? 32 * j + 16 * (xq >> 1) + c < u.nvalid && !(u.half && (c & 8)) : j < u.nsub;   // KiB past a short unit: ignored
             s4[j] = ok ? ps * sc : -INFINITY;
             lmax = fmaxf(lmax, s4[j]);
         }
@@ -1056,18 +1155,23 @@ __device__ __forceinline__ int bits_of_expert(const AttnArgs &a, int e) {
 __device__ __forceinline__ int lgb_of_bits(int bits) { return bits == 2 ? 1 : (bits == 4 ? 2 : (bits == 8 ? 3 : 4)); }
 __device__ __forceinline__ uint32_t units_of_chunk(int N, int lgb) { return (uint32_t)((N + (256 >> lgb) - 1) >> (8 - lgb)); }
 
+// Chunks of up to this many tokens share units (one query head per KV head; keys per channel below 64 tokens).
+constexpr int kGatherMax = 32;
+__host__ __device__ inline bool gathers(int N, int rep, int kpc) { return rep == 1 && N <= (kpc ? 32 : kGatherMax); }
+
 // Chunks per row segment: at most kDescCap, and at most kUnitCap units if all of them were FP16.
 __host__ __device__ inline int attn_segment_chunks(int N) { return min(kDescCap, kUnitCap / max(N / 16, 1)); }
 
 // RAGGED: the sequences of the batch have their own numbers of chunks and residual rows (a.seq_chunks,
 // a.seq_tail, device arrays indexed by sequence); a.n_chunks is then the bound that sizes the segments.
-// SMALL: chunks of 8, 16 or 32 tokens (a.N < 64), see load_v.  KPC: keys quantised per channel (REP == 1 only), see pc_scores.
+// SMALL: chunks of 8, 16 or 32 tokens, see Gather (one query head per KV head) and load_v (grouped queries).  KPC: keys quantised per channel (REP == 1 only), see pc_scores.
 template <int G, int REP, int NWV, bool RAGGED, bool SMALL, bool KPC>
 __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
     static_assert(!KPC || REP == 1, "per-channel keys: one query head per KV head");
     __shared__ AttnLds<G, REP, NWV> L;
     constexpr int NG = kD / G;
     constexpr int NT = NWV * 64;
+    constexpr bool GATH = SMALL && REP == 1;             // units of several short chunks
     using KR = std::conditional_t<REP == 1, KRegs<G>, KRegsMC<G, REP>>;
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // wave-uniform, kept scalar
@@ -1194,10 +1298,20 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             if (seg > 0) __syncthreads();                // previous segment's tables consumed
             // chunks [cs + tid*KPT, +KPT) per thread: descriptor, units per chunk, exclusive scan
             uint32_t ucnt[2] = {0u, 0u}, mine = 0u;
+            unsigned long long dsc2[2] = {0ull, 0ull};    // GATH: the thread's descriptors, and its chunks per bit-width:
+            uint32_t ca = 0u, cb = 0u;                    // 2 | 4 bits, 8 | 16 bits in half-words
+            int cls[4] = {0, 0, 0, 0}, cpos[4], upos[5];  // GATH: chunks per bit-width, first place in desc, first unit
 #pragma unroll
             for (int k = 0; k < 2; k++) {
                 const int c = cs + tid * KPT + k;
-                if (k < KPT && c < ce) {
+                if constexpr (GATH) {
+                    if (k < KPT && c < ce) {
+                        const int lgb = lgb_of_bits(bits_of(seg == 0 ? e_first[k] : erow[c]));
+                        dsc2[k] = (seg == 0 ? o_first[k] : orow[c]) | (unsigned long long)lgb;   // block offsets are multiples of 256
+                        const uint32_t one = 1u << (16 * ((lgb - 1) & 1));
+                        if (lgb <= 2) ca += one; else cb += one;
+                    }
+                } else if (k < KPT && c < ce) {
                     const int bits = bits_of(seg == 0 ? e_first[k] : erow[c]);
                     const int lgb = bits == 2 ? 1 : (bits == 4 ? 2 : (bits == 8 ? 3 : 4));
                     L.desc[c - cs] = (seg == 0 ? o_first[k] : orow[c]) | (unsigned long long)lgb;   // block offsets are multiples of 256
@@ -1205,13 +1319,46 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     mine += ucnt[k];
                 }
             }
-            const uint32_t incl = wave_incl_scan(mine);
-            if (lane == 63) L.wscan[wave] = incl;
+            const uint32_t incl = wave_incl_scan(GATH ? ca : mine), incl_b = GATH ? wave_incl_scan(cb) : 0u;
+            if (lane == 63) { L.wscan[wave] = incl; if constexpr (GATH) L.wscan2[wave] = incl_b; }
             if (tid == 0) { L.next = (uint32_t)NWV; L.limit = 0; L.done = 0; L.fetching = 0; L.g_seen = 0; L.nb = 0; }   // the first draws are fixed: wavefront v holds local ticket v
             __syncthreads();
             uint32_t pos = incl - mine, n_chunk_units = 0;
+            if constexpr (GATH) {
+                uint32_t pa = incl - ca, pb = incl_b - cb, ta = 0u, tb = 0u;
 #pragma unroll
-            for (int wv = 0; wv < NWV; wv++) { if (wv < wave) pos += L.wscan[wv]; n_chunk_units += L.wscan[wv]; }
+                for (int wv = 0; wv < NWV; wv++) {
+                    if (wv < wave) { pa += L.wscan[wv]; pb += L.wscan2[wv]; }
+                    ta += L.wscan[wv]; tb += L.wscan2[wv];
+                }
+                ta = (uint32_t)__builtin_amdgcn_readfirstlane((int)ta); tb = (uint32_t)__builtin_amdgcn_readfirstlane((int)tb);
+                cls[0] = (int)(ta & 0xffffu); cls[1] = (int)(ta >> 16); cls[2] = (int)(tb & 0xffffu); cls[3] = (int)(tb >> 16);
+                int at = 0, un = 0;
+#pragma unroll
+                for (int b = 0; b < 4; b++) {
+                    const int sh = gather_shift(N, b + 1);
+                    cpos[b] = at; upos[b] = un;
+                    at += cls[b]; un += sh >= 0 ? cls[b] << sh : (cls[b] + (1 << -sh) - 1) >> -sh;
+                }
+                upos[4] = un; n_chunk_units = (uint32_t)un;
+                if (tid < 2) L.desc[kDescCap + tid] = reinterpret_cast<uintptr_t>(tid ? a.V_tail : a.K_tail) + (size_t)u * N * 256 - reinterpret_cast<uintptr_t>(a.arena);   // the residual rows
+                // the block addresses ordered by bit-width
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    const int lgb = (int)(dsc2[k] & 7u);
+                    if (lgb) {
+                        const uint32_t run = lgb <= 2 ? pa : pb;
+                        const int place = (int)((run >> (16 * ((lgb - 1) & 1))) & 0xffffu)
+                                        + (lgb == 1 ? cpos[0] : (lgb == 2 ? cpos[1] : (lgb == 3 ? cpos[2] : cpos[3])));
+                        L.desc[place] = dsc2[k] & ~7ull;
+                        const uint32_t one = 1u << (16 * ((lgb - 1) & 1));
+                        if (lgb <= 2) pa += one; else pb += one;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int wv = 0; wv < NWV; wv++) { if (wv < wave) pos += L.wscan[wv]; n_chunk_units += L.wscan[wv]; }
+            }
             const uint32_t T = n_chunk_units + (uint32_t)(seg == n_seg - 1 ? (n_tail + 15) / 16 : 0);
             unsigned int *counter = a.counters + ((size_t)u * n_seg + seg) * kCounterStride;
             // no cap for a workgroup whose whole interval lies in this row, or that covers the whole row
@@ -1225,7 +1372,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                 if (g_first + (uint32_t)NWV >= T || granted >= quota) L.done = 1u;
             }
 #pragma unroll
-            for (int k = 0; k < 2; k++) {
+            for (int k = 0; k < (GATH ? 0 : 2); k++) {
                 const int c = cs + tid * KPT + k;
                 if (k < KPT && c < ce) {
                     L.ustart[c - cs] = (uint16_t)pos;
@@ -1297,7 +1444,28 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                        t >= (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bl[bcur + 1])) bcur++;
                 const uint32_t tk = (uint32_t)__builtin_amdgcn_readfirstlane((int)(L.bg[bcur] + (t - L.bl[bcur])));
                 issue_draw();
-                if (tk < n_chunk_units) {
+                if (GATH && tk < n_chunk_units) {
+                    const int lgb = (int)tk < upos[1] ? 1 : ((int)tk < upos[2] ? 2 : ((int)tk < upos[3] ? 3 : 4));
+                    const int b0 = lgb == 1 ? upos[0] : (lgb == 2 ? upos[1] : (lgb == 3 ? upos[2] : upos[3]));
+                    const int c0 = lgb == 1 ? cpos[0] : (lgb == 2 ? cpos[1] : (lgb == 3 ? cpos[2] : cpos[3]));
+                    const int nc = lgb == 1 ? cls[0] : (lgb == 2 ? cls[1] : (lgb == 3 ? cls[2] : cls[3]));
+                    const int idx = (int)tk - b0, sh = gather_shift(N, lgb);
+                    un.lgb = lgb; un.tail_rows = 1 << 20; un.kb = a.arena; un.vb = a.arena;
+                    int t0 = 0;
+                    if (sh >= 0) {                       // a chunk is one unit, or at 16 bits one or two
+                        un.first = un.last = c0 + (idx >> sh);
+                        t0 = (idx & ((1 << sh) - 1)) << (8 - lgb);
+                        un.nvalid = min(N - t0, 256 >> lgb);
+                    } else {
+                        const int n = min(1 << -sh, nc - (idx << -sh));
+                        un.first = c0 + (idx << -sh); un.last = un.first + n - 1;
+                        un.nvalid = n << (8 - lgb + sh);                 // NV tokens each
+                    }
+                    un.voff = 0; un.half = lgb == 1 && N == 8;
+                    un.nsub = max((un.nvalid + (1 << (6 - lgb)) - 1) >> (6 - lgb), 1);
+                    un.kc = (uint32_t)t0 << 8; un.vc = un.kc + ((uint32_t)N << 8);   // raw fp16 rows
+                    un.km = un.vm = 0u;
+                } else if (tk < n_chunk_units) {
                     const int cl = __builtin_amdgcn_readfirstlane((int)L.inv[tk]);
                     const unsigned long long dsc = L.desc[cl];
                     const uint32_t dlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)dsc);
@@ -1326,6 +1494,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     un.vb = reinterpret_cast<const uint8_t *>(a.V_tail) + (size_t)u * N * 256;
                     un.kc = un.vc = (uint32_t)row0 * 256u;
                     un.km = un.kc; un.vm = un.vc;
+                    if constexpr (GATH) { un.kb = un.vb = a.arena; un.first = un.last = kDescCap; un.voff = 1; un.half = false; }
                 }
                 return true;
             };
@@ -1337,9 +1506,9 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             VRegs<G> va, vb;
             bool have = next_unit(cur);
             auto load_keys = [&](const Unit &un) {
-                if constexpr (REP == 1) load_k_iq<G, KPC, SMALL>(un, lane, kr); else load_k_mc<G, REP, SMALL>(un, lane, kr);
+                if constexpr (REP == 1) load_k_iq<G, KPC, SMALL>(un, lane, kr, N, L); else load_k_mc<G, REP, SMALL>(un, lane, kr);
             };
-            if (have) { load_keys(cur); load_v<G, SMALL>(cur, lane, va, N); }
+            if (have) { load_keys(cur); load_v<G, SMALL, GATH>(cur, lane, va, N, L); }
             if (seg == 0) {                              // the q tables, behind the first units' loads
                 if constexpr (kLateTables) build_q_tables();
                 if constexpr (REP > 1) {
@@ -1360,7 +1529,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
 #pragma unroll
                     for (int mi = 0; mi < 4; mi++) ak[mi] = L.qmc[bi][mi][lane];
                 }
-                load_v<G, SMALL>(pf, lane, vn, N);              // a whole unit ahead
+                load_v<G, SMALL, GATH>(pf, lane, vn, N, L);              // a whole unit ahead
                 if constexpr (REP == 1 && KPC) {
                     if (lgb == 1)      pc_scores<2, G, NWV>(cur, kr, lane, wave, a.scale_log2, L, st);
                     else if (lgb == 2) pc_scores<4, G, NWV>(cur, kr, lane, wave, a.scale_log2, L, st);
@@ -1476,7 +1645,11 @@ __global__ __launch_bounds__(256) void attn_prep_kernel(AttnArgs a, int n_seg) {
     }
     for (int c = tid; c < C; c += 256) {                 // a unit costs its 8 KiB of codes plus its meta words, in steps of 512 bytes
         const int lgb = lgb_of_bits(bits_of_expert(a, erow[c]));
-        units += units_of_chunk(a.N, lgb) * (uint32_t)(16 + (lgb < 4 ? (4 * NG) >> lgb : 0));
+        const uint32_t cost = (uint32_t)(16 + (lgb < 4 ? (4 * NG) >> lgb : 0));
+        if (gathers(a.N, a.rep, a.kpc)) {                // a chunk's part of a unit, rounded
+            const int sh = gather_shift(a.N, lgb);
+            units += sh >= 0 ? cost << sh : max((cost + (1u << (-sh - 1))) >> -sh, 1u);
+        } else units += units_of_chunk(a.N, lgb) * cost;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) units += __shfl_xor(units, o);
@@ -1552,7 +1725,7 @@ template <int REP> constexpr int waves_per_wg() { return 8; }
 template <int G, int REP, bool KPC>
 static void launch_split(const AttnArgs &a, dim3 grid, dim3 block, hipStream_t s) {
     constexpr int NWV = waves_per_wg<REP>();
-    if (a.N < 64) {
+    if (a.N < 64 || gathers(a.N, REP, KPC)) {
         if (a.seq_chunks) hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, true, KPC>), grid, block, 0, s, a);
         else              hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, true, KPC>), grid, block, 0, s, a);
     } else {

@@ -1,6 +1,6 @@
-"""Chunks shorter than a window of 64 tokens share wavefronts in the routing kernel and take a wavefront per side in the
-packing kernel: windows that end inside a row, frozen chunks inside a window, calls that begin inside one, odd numbers of
-chunk sides; bit-exact against the CPU oracle."""
+"""Chunks shorter than a window of 64 tokens share wavefronts in the routing kernel, take a wavefront per side in the packing
+kernel and share units in the decode kernel: windows that end inside a row, frozen chunks inside a window, calls that begin
+inside one, odd numbers of chunk sides (bit-exact against the CPU oracle); units with fewer chunks than they hold."""
 import numpy as np
 import pytest
 
@@ -50,3 +50,24 @@ def test_pack_wavefront_per_side(mq, ref, B, Hkv, N, G, C, kpc):
     assert int(status.item()) == st_ref == 0 and int(used.item()) == int(used_ref[0])
     assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
     assert np.array_equal(arena.cpu().numpy(), arena_ref)
+
+
+@pytest.mark.parametrize("B,Hkv,N,G,C,tail,mix", [
+    (1, 2, 32, 64, 9, 31, (1, 0, 0, 0)),        # 2 bits: four chunks a unit, the last unit holds one
+    (2, 1, 32, 32, 7, 5, (0, 1, 0, 0)),         # 4 bits: two a unit
+    (1, 3, 16, 64, 13, 0, (0.4, 0.3, 0.2, 0.1)),
+    (1, 1, 16, 32, 11, 15, (0, 0, 1, 0)),       # 8 bits: two a unit
+    (1, 2, 8, 64, 17, 7, (1, 0, 0, 0)),         # half slices: eight chunks a unit, every second run of 8 tokens masked
+    (1, 2, 8, 32, 21, 3, (0, 0.5, 0.5, 0)),     # eight and four a unit
+    (1, 1, 8, 64, 1, 0, (1, 0, 0, 0)),
+    (1, 2, 32, 64, 5, 17, (0, 0, 0, 1)),        # raw rows: two units a chunk
+    (1, 1, 8, 32, 1100, 1, (0.6, 0.3, 0.05, 0.05)),   # more chunks than a row segment holds
+    (1, 2, 32, 32, 1030, 0, (0.3, 0.3, 0.2, 0.2)),
+    (2, 2, 32, 64, 0, 9, (1, 0, 0, 0)),         # residual only
+])
+def test_units_of_several_chunks(mq, ref, B, Hkv, N, G, C, tail, mix):
+    """24-bit fixed point (2^-24 of the largest query entry / of a unit's largest weight) and binary32 sums over at most
+    33 k tokens: below 2e-5 of a row's largest output; a chunk that is misplaced or counted twice shows as 1e-3 and more."""
+    rng = np.random.default_rng(N * 10000 + C)
+    expert = rng.choice(4, size=(B * Hkv, max(C, 1)), p=mix).astype(np.uint8)
+    assert T._attn_case(mq, ref, B, Hkv, Hkv, N, G, C, tail, (2, 4, 8, 16), C + N, expert=expert) <= 2e-5
