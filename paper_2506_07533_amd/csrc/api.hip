@@ -71,15 +71,31 @@ int cu_count() {
 }
 
 // Persistent workgroups of the decode kernel: one per compute unit (its eight wavefronts of up to 256
-// registers and its LDS tables fill one), but never more than there are tickets of 128 tokens to hand to
-// their wavefronts.  The only device query is the number of compute units of the current device.
-int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail) {
-    const int rep = c->n_q_heads / c->n_kv_heads;
-    const int per_cu = 1;
+// registers and its LDS tables fill one), but never more than there is work for.  The only device query is
+// the number of compute units of the current device.
+//   Long caches: a ticket of 128 tokens for every wavefront.
+//   Short ones: two wavefronts (grouped queries, whose set-up and partials cost more: one) per unit of work, a unit being 64
+//   tokens of a chunk or 16 rows of the residual, the first chunk counted at 16 bits (it usually is), at most 32 workgroups
+//   a row: such a call is all latency, and a compute unit with fewer units finishes them sooner (32 heads: a residual of 100 rows alone 57 -> 18 us, 2k tokens 27 -> 21; one head:
+//   8k tokens 19 -> 16; more than 32 workgroups on a row meet at its ticket counter and in the merge: 30k tokens on two
+//   rows 22 -> 24 us).  Their partial slots stay below 7 MiB, so that every call moqae_decode_attn_static took it still takes;
+//   the bound depends on the configuration alone: a workspace for more chunks always serves fewer.
+int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false) {
+    const int rep = c->n_q_heads / c->n_kv_heads, waves = attn_waves_per_wg(rep);
     const int64_t rows = (int64_t)c->batch * c->n_kv_heads;
     const int64_t tickets = rows * ((int64_t)n_chunks * (c->chunk >= 256 ? c->chunk / 128 : 1) + (n_tail + 127) / 128);
-    int64_t n = (int64_t)cu_count() * per_cu;
-    const int64_t cap = (tickets + attn_waves_per_wg(rep) - 1) / attn_waves_per_wg(rep);
+    int64_t cap = (tickets + waves - 1) / waves;
+    if (rows <= 512) {
+        const int64_t units = (int64_t)n_chunks * (c->chunk >= 64 ? c->chunk / 64 : 1) + (n_chunks > 0 ? c->chunk / 16 : 0) + (n_tail + 15) / 16;
+        const int64_t slots = (7 << 20) / ((int64_t)c->batch * c->n_q_heads * (kD + 2) * (int64_t)sizeof(float));   // per row
+        int64_t most = ragged ? slots : (slots > 3 ? (slots - 3) * (rows + 7) / 8 : 0);   // attn_max_partials(most, rows) <= slots
+        if (!ragged && most < slots) most = slots;
+        int64_t n = rows * units * (rep == 1 ? 2 : 1) / waves;
+        if (n > 32 * rows) n = 32 * rows;
+        if (n > most) n = most;
+        if (cap < n) cap = n;
+    }
+    int64_t n = cu_count();
     if (n > cap) n = cap;
     if (n < 1) n = 1;
     return (int)n;
@@ -99,7 +115,7 @@ uint64_t workspace_bytes(const moqae_cfg *c, int n_chunks) {
 }
 // Ragged batches: one long sequence among short ones can meet every workgroup's interval.
 uint64_t workspace_bytes_ragged(const moqae_cfg *c, int max_chunks) {
-    const int n_wg = choose_wgs(c, max_chunks, c->chunk - 1);
+    const int n_wg = choose_wgs(c, max_chunks, c->chunk - 1, true);
     const uint64_t rows = (uint64_t)c->batch * c->n_q_heads;
     return counters_bytes(c, max_chunks) + rows * (uint64_t)n_wg * (kD + 2) * sizeof(float);
 }
@@ -492,7 +508,7 @@ int moqae_decode_attn_ragged(const moqae_cfg *cfg,
     a.part = reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + counters_bytes(cfg, max_chunks)); a.out = out;
     a.scale_log2 = softmax_scale * 1.4426950408889634f;
     a.n_chunks = max_chunks; a.n_tail = cfg->chunk - 1;
-    a.n_wg = choose_wgs(cfg, max_chunks, cfg->chunk - 1);
+    a.n_wg = choose_wgs(cfg, max_chunks, cfg->chunk - 1, true);
     a.max_partials = a.n_wg;
     a.N = cfg->chunk; a.G = cfg->group; a.Hkv = cfg->n_kv_heads; a.rep = cfg->n_q_heads / cfg->n_kv_heads;
     a.BH = cfg->batch * cfg->n_kv_heads;

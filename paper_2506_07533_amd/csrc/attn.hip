@@ -1237,6 +1237,13 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
         //      queries, the chunk descriptors of the first segment and the first batch of tickets.  The
         //      tables derived from q are built later, while the first units' codes are on their way.
         const int KPT = (seg_chunks + NT - 1) / NT;      // chunks per thread of a segment (<= 2)
+        // size of the first batch: a wavefront's worth each, but an even share of the row's tickets (estimated from its cost,
+        // 16 a unit and more, without the set-up's) where the row has fewer: short rows then spread over all their compute units
+        uint32_t b_first = (uint32_t)NWV;
+        if (REP == 1 && ru < 16ull * NWV * P + kRowSetupCost) {   // (grouped queries: the registers this takes are spilled in the unit loop)
+            const uint32_t est = ru > kRowSetupCost ? (uint32_t)(ru - kRowSetupCost) >> 4 : 1u;
+            b_first = min((uint32_t)NWV, max(1u, (est + P - 1u) / P));
+        }
         uint32_t q_first = 0u, g_first = 0u;
         uint8_t e_first[2] = {0, 0};
         uint64_t o_first[2] = {0ull, 0ull};
@@ -1253,7 +1260,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                 const int c = tid * KPT + k;
                 if (k < KPT && c < min(C, seg_chunks)) { e_first[k] = erow[c]; o_first[k] = orow[c]; }
             }
-            if (tid == 0) g_first = atomicAdd(a.counters + (size_t)u * n_seg * kCounterStride, (unsigned int)NWV);
+            if (tid == 0) g_first = atomicAdd(a.counters + (size_t)u * n_seg * kCounterStride, b_first);
             __syncthreads();                             // LDS of the previous row is free
             if (tid < REP * 64) L.qraw[tid] = q_first;
         }
@@ -1366,10 +1373,10 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             if (P == 1u) {                               // nobody shares the row: every ticket is this workgroup's, no counter in memory needed
                 if (tid == 0) { L.bl[0] = 0u; L.bg[0] = 0u; L.nb = 1u; L.limit = T; L.g_seen = T; L.done = 1u; }
             } else if (seg == 0 && tid == 0) {           // the batch asked for during the row set-up
-                const uint32_t granted = g_first < T ? min((uint32_t)NWV, T - g_first) : 0u;
-                L.g_seen = g_first + (uint32_t)NWV;
+                const uint32_t granted = g_first < T ? min(b_first, T - g_first) : 0u;
+                L.g_seen = g_first + b_first;
                 if (granted) { L.bl[0] = 0u; L.bg[0] = g_first; L.nb = 1u; L.limit = granted; }
-                if (g_first + (uint32_t)NWV >= T || granted >= quota) L.done = 1u;
+                if (g_first + b_first >= T || granted >= quota) L.done = 1u;
             }
 #pragma unroll
             for (int k = 0; k < (GATH ? 0 : 2); k++) {
