@@ -71,3 +71,21 @@ def test_units_of_several_chunks(mq, ref, B, Hkv, N, G, C, tail, mix):
     rng = np.random.default_rng(N * 10000 + C)
     expert = rng.choice(4, size=(B * Hkv, max(C, 1)), p=mix).astype(np.uint8)
     assert T._attn_case(mq, ref, B, Hkv, Hkv, N, G, C, tail, (2, 4, 8, 16), C + N, expert=expert) <= 2e-5
+
+
+@pytest.mark.parametrize("Hkv,N,C,M,freeze", [
+    (2, 128, 3, 4, 1), (1, 96, 5, 3, 0), (3, 224, 2, 8, 0), (2, 256, 1, 2, 0),   # a wavefront per 64 tokens of a chunk
+    (65, 96, 8, 4, 1), (40, 160, 13, 5, 0),                                     # 520 chunks: a wavefront per chunk
+])
+def test_route_few_and_many_long_chunks(mq, ref, Hkv, N, C, M, freeze):
+    rng = np.random.default_rng(N + C)
+    cfg, rcfg = T._cfgs(mq, ref, 1, Hkv, Hkv, N, 32, (16, 2, 4, 8, 2, 4, 8, 16)[:M], freeze)
+    K, _ = T._rand_kv(rng, 1, Hkv, C * N)
+    W = [(rng.standard_normal(s) * 0.3).astype(np.float16) for s in ((128, M), (128, M), (M, M))]
+    bias = (rng.standard_normal(M) * 0.05).astype(np.float32)
+    e_ref, v_ref = ref.route_chunks(rcfg, K, 0, C, *W, bias)
+    expert = torch.full((Hkv, C), 255, dtype=torch.uint8, device="cuda")
+    votes = torch.full((Hkv, C, M), -1, dtype=torch.int32, device="cuda")
+    mq.route_chunks(cfg, T._dev(K), 0, C, *[T._dev(w) for w in W], T._dev(bias), expert, votes)
+    torch.cuda.synchronize()
+    assert np.array_equal(expert.cpu().numpy(), e_ref) and np.array_equal(votes.cpu().numpy(), v_ref)
