@@ -89,3 +89,15 @@ def test_route_few_and_many_long_chunks(mq, ref, Hkv, N, C, M, freeze):
     mq.route_chunks(cfg, T._dev(K), 0, C, *[T._dev(w) for w in W], T._dev(bias), expert, votes)
     torch.cuda.synchronize()
     assert np.array_equal(expert.cpu().numpy(), e_ref) and np.array_equal(votes.cpu().numpy(), v_ref)
+
+
+@pytest.mark.parametrize("BH,C", [(64, 16), (41, 25), (1, 1025), (64, 32)])    # 1024, 1025 and 2048 chunks: one workgroup plans, or one per row
+def test_pack_plan_of_small_tables(mq, ref, BH, C):
+    rng = np.random.default_rng(BH + C)
+    cfg, rcfg = T._cfgs(mq, ref, 1, BH, BH, 8, 64, (2, 4, 8, 16), 0)
+    K, V = T._rand_kv(rng, 1, BH, C * 8)
+    expert = rng.integers(0, 4, (BH, C)).astype(np.uint8)
+    (arena, used, off, status), (arena_ref, used_ref, off_ref, st_ref) = T._pack_both(mq, ref, cfg, rcfg, K, V, 0, C, expert, start=300)
+    assert int(status.item()) == st_ref == 0 and int(used.item()) == int(used_ref[0])
+    assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    assert np.array_equal(arena.cpu().numpy(), arena_ref)
