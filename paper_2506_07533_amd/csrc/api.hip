@@ -78,24 +78,27 @@ int cu_count() {
 //   tokens of a chunk or 16 rows of the residual, the first chunk counted at 16 bits (it usually is), at most 32 workgroups
 //   a row: such a call is all latency, and a compute unit with fewer units finishes them sooner (32 heads: a residual of 100 rows alone 57 -> 18 us, 2k tokens 27 -> 21; one head:
 //   8k tokens 19 -> 16; more than 32 workgroups on a row meet at its ticket counter and in the merge: 30k tokens on two
-//   rows 22 -> 24 us).  Their partial slots stay below 7 MiB, so that every call moqae_decode_attn_static took it still takes;
-//   the bound depends on the configuration alone: a workspace for more chunks always serves fewer.
+//   rows 22 -> 24 us).  Not for more rows than compute units, where the workgroups' intervals cut more rows the more there
+//   are (480 rows of 400 tokens 34 -> 41 us), nor for ragged batches (160 rows of up to 192 tokens 32 -> 33).  The partial
+//   slots stay below 7 MiB, so that every call moqae_decode_attn_static took it still takes; the bound depends on the
+//   configuration alone: a workspace for more chunks always serves fewer.
 int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false) {
+    const int cus = cu_count();
     const int rep = c->n_q_heads / c->n_kv_heads, waves = attn_waves_per_wg(rep);
     const int64_t rows = (int64_t)c->batch * c->n_kv_heads;
     const int64_t tickets = rows * ((int64_t)n_chunks * (c->chunk >= 256 ? c->chunk / 128 : 1) + (n_tail + 127) / 128);
     int64_t cap = (tickets + waves - 1) / waves;
-    if (rows <= 512) {
+    if (rows <= cus && !ragged) {
         const int64_t units = (int64_t)n_chunks * (c->chunk >= 64 ? c->chunk / 64 : 1) + (n_chunks > 0 ? c->chunk / 16 : 0) + (n_tail + 15) / 16;
         const int64_t slots = (7 << 20) / ((int64_t)c->batch * c->n_q_heads * (kD + 2) * (int64_t)sizeof(float));   // per row
-        int64_t most = ragged ? slots : (slots > 3 ? (slots - 3) * (rows + 7) / 8 : 0);   // attn_max_partials(most, rows) <= slots
-        if (!ragged && most < slots) most = slots;
+        int64_t most = slots > 3 ? (slots - 3) * (rows + 7) / 8 : 0;      // attn_max_partials(most, rows) <= slots
+        if (most < slots) most = slots;
         int64_t n = rows * units * (rep == 1 ? 2 : 1) / waves;
         if (n > 32 * rows) n = 32 * rows;
         if (n > most) n = most;
         if (cap < n) cap = n;
     }
-    int64_t n = cu_count();
+    int64_t n = cus;
     if (n > cap) n = cap;
     if (n < 1) n = 1;
     return (int)n;
@@ -117,7 +120,9 @@ uint64_t workspace_bytes(const moqae_cfg *c, int n_chunks) {
 uint64_t workspace_bytes_ragged(const moqae_cfg *c, int max_chunks) {
     const int n_wg = choose_wgs(c, max_chunks, c->chunk - 1, true);
     const uint64_t rows = (uint64_t)c->batch * c->n_q_heads;
-    return counters_bytes(c, max_chunks) + rows * (uint64_t)n_wg * (kD + 2) * sizeof(float);
+    const uint64_t own = counters_bytes(c, max_chunks) + rows * (uint64_t)n_wg * (kD + 2) * sizeof(float);
+    const uint64_t uniform = workspace_bytes(c, max_chunks);              // serves the uniform calls on the same cache too
+    return own > uniform ? own : uniform;
 }
 
 // Device address of `scratch` on every GPU, looked up once per device with that device current.

@@ -23,6 +23,7 @@ def test_workspace_grows_with_chunks_and_keeps_the_static_limit():
         assert sizes == sorted(sizes), (B, H, rep, N, C)
         ragged = [mq.decode_workspace_bytes_ragged(cfg, c) for c in (C, C + 1, C + 70, C + 4000)]
         assert ragged == sorted(ragged), (B, H, rep, N, C)
+        assert all(r >= s for r, s in zip(ragged, sizes)), (B, H, rep, N, C)   # a ragged workspace serves uniform calls
         if torch.cuda.is_available():
             cus = torch.cuda.get_device_properties(0).multi_processor_count
         # one wavefront per ticket of 128 tokens: the size of a workspace by the rule for long caches alone
