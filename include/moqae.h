@@ -261,8 +261,8 @@ uint64_t moqae_decode_workspace_bytes_multi(const moqae_cfg *cfg, int32_t n_chun
  * the values Eq. (3) and Eq. (4) print, 1/B_j and 16/B_j (the text under Eq. (4) describes its penalty as the
  * inverse of Eq. (3)'s, which B_j/16 would be: pass it explicitly if that is wanted).
  * Out (device fp32, overwritten): loss[3] = L, L_model, L_mem; dW1, dW2 [D, M]; dW3 [M, M]; dbias [M] or NULL.
- * Evaluated in binary32 (dW1, dW2: products with values split into two fp16 numbers, binary32 sums); sums over rows are
- * added in no fixed order (results agree to rounding, not bit for bit).
+ * Evaluated in binary32 (dW1, dW2: products with values split into two fp16 numbers on a power of two of every column and
+ * 64 rows, 22 bits and more down to 2^-28 of the largest of the column there; binary32 sums); sums over rows are added in no fixed order (results agree to rounding, not bit for bit).
  */
 int moqae_router_loss_grad(const moqae_cfg *cfg,
                            const void *K, int64_t stride_b, int64_t stride_h, int64_t stride_s,

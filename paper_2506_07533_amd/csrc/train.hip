@@ -12,10 +12,13 @@
 //   forward   one lane per token, route_half_row / the operations of route_top in their order, then the token's loss and
 //             its gradient down to d(loss)/d(xW1), d(loss)/d(xW2) (2M values per token, handed over through LDS).
 //   dW1, dW2  = x^T [128 x 64 tokens] times those values [64 tokens x 2M] on v_mfma_f32_16x16x32_f16: x is fp16 as it is; a
-//             value is scaled by the tile's power of two and split into two fp16 numbers, the second holding what the
-//             first leaves (22 bits and more of every value that is not 2^28 times smaller than the tile's largest; the
-//             error of the result against binary64 is below that of the binary32 multiply-adds this took before: their
-//             accumulators rounded once per token, these once per 32).  A row i of tile rt = dim 8i + rt, and the tokens
+//             value is scaled by a power of two of its own column (expert and matrix) and tile and split into two fp16 numbers,
+//             the second holding what the first leaves: 22 bits and more of every value that is not 2^28 times smaller than
+//             its column's largest in the tile.  One scale for all columns would lose the experts whose gradients are small
+//             beside another's (a saturated router has such): relative error of a column 2^-34 (2^-44) of the largest 4e-6
+//             (2.5e-3), with its own scale 1e-7 as with the binary32 multiply-adds this took before (+2 % of time at 4
+//             experts, +5 % at 7).  Elsewhere the error against binary64 is that of those multiply-adds or below: their
+//             accumulators rounded once per token, these once per 32.  A row i of tile rt = dim 8i + rt, and the tokens
 //             are taken in the order 4j + r, so that the operands of a lane are the fp16 halves of row pieces it can read
 //             with one load each.  Binary32 matrix products (16x16x4) took 27 us of the matrix pipe at 1.05 M rows and
 //             128 conversions per tile: 111 us in all.
@@ -23,8 +26,10 @@
 //             address and workgroup.  Device-wide atomic steps on one address run at about nine per microsecond here: one
 //             wavefront at a time, each with its own atomic adds (4096 per address), took 0.8 ms of the 0.89 ms that the
 //             gradient over 1.05 M rows needed.
-// 1.05 M rows: 4 experts 75 us against 892, 8 experts 200 against 1733, 2 experts 57 against 264; 64 rows 18 against 20.  The
-// rows alone are 38 us at the read ceiling of the chip; what is left is the forward pass (1024 multiply-adds in their order).
+// 1.05 M rows: 4 experts 80 us against 888 (router_train_8k of perf/: 77 against 892), 8 experts 184 against 1742, 2 experts 58
+// against 264; 64 rows 18 against 20.  The rows alone are 38 us at the read ceiling of the chip; what is left is the forward
+// pass (1024 multiply-adds in their order).  With 7 and 8 experts the 256 registers that eight wavefronts leave are not
+// enough: 116 and 164 bytes of scratch a lane, and more than twice the time of 4 experts.
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
 #include "pack_dev.hpp"
@@ -52,6 +57,34 @@ __device__ __forceinline__ uint32_t word4(const uint4 &v, int i) { return i == 0
 
 __device__ __forceinline__ v4f_t mfma_train(v4u_t a, v4u_t b, v4f_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a), __builtin_bit_cast(v8h_t, b), c, 0, 0, 0);
+}
+
+// Largest of every one of P columns (a power of two; v[i]: the lane's entry of column i, compared as an unsigned number) over
+// the wavefront: lane l returns that of column l / (64 / P).  Every step halves the columns a lane carries, then the lanes of
+// a column meet: 26 instructions for 8 columns, where a reduction of each would take 48.
+template <int P>
+__device__ __forceinline__ uint32_t column_max(uint32_t (&v)[P], int lane) {
+#pragma unroll
+    for (int i = 0; i < P / 2; i++) {                 // lanes 32.. take the upper half of the columns
+        const auto r = __builtin_amdgcn_permlane32_swap(v[i], v[i + P / 2], false, false);
+        v[i] = max(r[0], r[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < (P >= 4 ? P / 4 : 1); i++) {  // odd rows of 16 lanes the upper half of those
+        const auto r = __builtin_amdgcn_permlane16_swap(v[i], v[P >= 4 ? i + P / 4 : i], false, false);
+        v[i] = max(r[0], r[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < (P >= 8 ? P / 8 : 1); i++) {
+        const uint32_t other = v[P >= 8 ? i + P / 8 : i];
+        v[i] = max((lane & 8) ? other : v[i], dpp_u<0x128>((lane & 8) ? v[i] : other));   // row_ror:8
+    }
+    {
+        const uint32_t other = v[P >= 16 ? 1 : 0];
+        v[0] = max((lane & 4) ? other : v[0], dpp_u<DPP_HALF_MIRROR>((lane & 4) ? v[0] : other));
+    }
+    v[0] = max(v[0], dpp_u<DPP_XOR2>(v[0]));
+    return max(v[0], dpp_u<DPP_XOR1>(v[0]));
 }
 
 template <int M>
@@ -161,7 +194,7 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
         float dl[M];
 #pragma unroll
         for (int k = 0; k < M; k++) { dl[k] = w * ((k == top ? 1.0f : 0.0f) - p[k]); gb[k] += dl[k]; }
-        float dx[2 * M], dmax = 0.0f;
+        float dx[2 * M];
 #pragma unroll
         for (int m = 0; m < M; m++) {
             float dh = 0.0f;
@@ -169,17 +202,27 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
             for (int k = 0; k < M; k++) { dh = fmaf(dl[k], w3f[m * M + k], dh); g3[m][k] = fmaf(hid[m], dl[k], g3[m][k]); }
             const float dz = dh * (sg[m] * (1.0f + z[m] * (1.0f - sg[m])));
             dx[m] = dz * accB[m]; dx[M + m] = dz * accA[m];
-            dmax = fmaxf(dmax, fmaxf(fabsf(dx[m]), fabsf(dx[M + m])));
         }
-        // ---- dW1, dW2.  2^ef <= dmax < 2^(ef+1): value * 2^(14 - ef) is below 2^15
-        const int ef = min(max((int)((__builtin_bit_cast(uint32_t, wave_max(dmax)) >> 23) & 255u) - 127, -110), 127);
-        const float up = __builtin_bit_cast(float, (uint32_t)(127 + 14 - ef) << 23);
-        const float down = __builtin_bit_cast(float, (uint32_t)max(127 - 14 + ef, 1) << 23);
+        // ---- dW1, dW2.  A scale for every column: 2^ef <= its largest < 2^(ef+1): value * 2^(14 - ef) is below 2^15
+        constexpr int P = M <= 1 ? 2 : (M <= 2 ? 4 : 8);                        // columns of a reduction, padded
+        constexpr int R = M <= 4 ? 1 : 2, CR = 2 * M / R;                       // all at once, or W1's and W2's (fewer registers: 8 experts 204 us at once, 184 so)
+        uint32_t upbits[R];
+        float down = 0.0f;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            uint32_t mag[P] = {};
+#pragma unroll
+            for (int i = 0; i < CR; i++) mag[i] = __builtin_bit_cast(uint32_t, fabsf(dx[r * CR + i]));
+            const int ef = min(max((int)(column_max(mag, lane) >> 23) - 127, -110), 127);   // of column r * CR + lane / (64 / P)
+            upbits[r] = (uint32_t)(127 + 14 - ef) << 23;
+            const float dn = __shfl(__builtin_bit_cast(float, (uint32_t)max(127 - 14 + ef, 1) << 23), ((NB == 1 ? piece & 7 : piece) - r * CR) * (64 / P));
+            if (r == 0 || piece >= CR) down = dn;
+        }
         uint16_t *mydab = dab + (lane >> 5) * kTrainH + (lane & 3) * kTrainR4 + ((lane >> 2) & 7);
         uint32_t lo[2 * M];
 #pragma unroll
         for (int m = 0; m < 2 * M; m++) {
-            const float s = dx[m] * up;
+            const float s = dx[m] * __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_readlane((int)upbits[m / CR], (m % CR) * (64 / P)));
             const uint32_t hi = float_to_half_bits(s);
             lo[m] = float_to_half_bits((s - half_bits_to_float(hi)) * 2048.0f);
             mydab[m * kTrainCol] = (uint16_t)hi;
