@@ -989,14 +989,15 @@ __device__ __forceinline__ float iq_weights(const VRegs<G> &v, int lane, int wav
         wmax = fmaxf(wmax, wv[jj]);
     }
     wmax = wave_max(wmax);
-    // 2^ef <= wmax < 2^(ef+1) (ef >= -100): weight * 2^(23 - ef) < 2^24
+    // 2^ef <= wmax < 2^(ef+1) (ef >= -100): weight * 2^(23 - ef) < 2^24.  Rounded to the nearest integer: adding 0.5 and cutting
+    // off would round twice, and from 2^23 on, where every binary32 number is an integer, make odd weights one larger
     const int ef = max((int)((__builtin_bit_cast(uint32_t, wmax) >> 23) & 255u) - 127, -100);
     const float up = __builtin_bit_cast(float, (uint32_t)(127 + kFix - ef) << 23);
     uint8_t *img = reinterpret_cast<uint8_t *>(&L.wa[wave][0][0]);
 #pragma unroll
     for (int jj = 0; jj < MV; jj++) {
         const uint32_t pos = L.wpos[IQ<BITS>::BI][jj][lane];         // byte offset of digit 0 | plane shift << 16
-        const uint32_t W = (uint32_t)(wv[jj] * up + 0.5f) << (pos >> 16);
+        const uint32_t W = (uint32_t)rintf(wv[jj] * up) << (pos >> 16);
         uint8_t *dst = img + (pos & 0xffffu);
         dst[0] = (uint8_t)(W & 127u); dst[16] = (uint8_t)((W >> 7) & 127u);
         dst[32] = (uint8_t)((W >> 14) & 127u); dst[48] = (uint8_t)((W >> 21) & 127u);

@@ -1,0 +1,37 @@
+"""The fixed-point numbers of the decode kernel for one query head per KV head: 24 bits, rounded to the nearest."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import test_gpu_parity as T                                              # noqa: E402  (helpers only)
+
+mq = T.mq
+
+
+@pytest.mark.parametrize("e,G", [(0, 64), (1, 32), (2, 64)])
+def test_weights_are_not_rounded_to_one_side(mq, ref, e, G):
+    """Softmax weights within a factor of two of each other (the upper half of the fixed-point range) on values code * 1 + 0:
+    the output is a mean of the codes, and its signed relative error, averaged over 512 rows x 128 dims, shows a one-sided
+    rounding.  One unit of the fixed-point weights is 2^-24 to 2^-23 of them: half a unit too much, as odd weights would be
+    with +0.5 in binary32, is 4e-8.  The binary32 sums err by some 3e-8 a row, either way: 1e-9 in the mean of 512."""
+    rng = np.random.default_rng(77 + e)
+    B, H, N, C = 8, 64, 64, 6
+    bits = (2, 4, 8)[e]
+    cfg, rcfg = T._cfgs(mq, ref, B, H, H, N, G, (2, 4, 8, 16), 0)
+    K = (rng.standard_normal((B, H, C * N, 128)) * 0.05).astype(np.float16)
+    V = rng.integers(192 if bits == 8 else 0, 2 ** bits, (B, H, C * N, 128)).astype(np.float16)   # 8 bits: the kernel's codes are minus 128
+    V[..., ::G] = 0; V[..., 1::G] = 2 ** bits - 1                        # every group: zero 0, scale 1
+    q = (rng.standard_normal((B, H, 128)) * 0.5).astype(np.float16)
+    expert = np.full((B * H, C), e, np.uint8)
+    (arena, used, off, status), (arena_ref, used_ref, off_ref, st_ref) = T._pack_both(mq, ref, cfg, rcfg, K, V, 0, C, expert)
+    want = ref.decode_attn(rcfg, q, arena_ref, off_ref, expert, C, None, None, 0, 1 / math.sqrt(128))
+    out = torch.full((B, H, 128), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(mq.decode_workspace_bytes(cfg, C), dtype=torch.uint8, device="cuda")
+    mq.decode_attn(cfg, T._dev(q), arena, off, T._dev(expert), C, None, None, 0, 1 / math.sqrt(128), out, ws)
+    torch.cuda.synchronize()
+    rel = (out.cpu().numpy().astype(np.float64) / want - 1.0)[..., 2:G]
+    assert abs(rel.mean()) <= 1e-8 and np.abs(rel).max() <= 1e-6, (rel.mean(), np.abs(rel).max())
