@@ -78,7 +78,7 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     v4u qmc[REP > 1 ? 3 : 1][4][REP > 1 ? 64 : 1];       // grouped queries: score operands A per (bit-width, pass, lane)
     float comb[NWV][REP][kD + 2];                        // per-wavefront (o, m, l) at the end of a row segment
     uint32_t qraw[REP * 64];                             // the row's queries as loaded (fp16 pairs)
-    unsigned long long desc[kDescCap + 2];               // chunk descriptors of the current pass: offset | log2 bits (Gather: see there)
+    unsigned long long desc[kDescCap];                   // chunk descriptors of the current pass: offset | log2 bits (Gather: offsets, ordered by bit-width)
     // ticket queue of the workgroup: local tickets [0, limit) are granted; batch i maps local
     // tickets from bl[i] on to the row's tickets from bg[i] on
     uint16_t ustart[kDescCap];                           // first unit of every chunk of the segment
@@ -149,27 +149,41 @@ struct Unit {
     int tail_rows;                                       // residual units: valid residual rows from the unit's first row on (else huge)
     const uint8_t *kb, *vb;                              // bases: the chunk block (both), or the residual K and V rows of the row
     uint32_t kc, km, vc, vm;                             // byte offsets of the unit's K codes / K meta (from kb), V codes / V meta (from vb)
-    // units of short chunks (see Gather): kb = the arena, the blocks' offsets in it desc[first .. last] (K side), + voff entries for the V side
-    bool half;                                           // 8 tokens at 2 bits: every second run of 8 tokens of the unit does not exist
-    int first, last, voff;
+    // units of several short chunks (see Gather): kb = the arena, the blocks' offsets in it desc[first .. last]
+    bool gath, half;                                     // half: 8 tokens at 2 bits, every second run of 8 tokens of the unit does not exist
+    int first, last;
 };
+
+// a ? x : y field by field: a choice between the two objects would keep them in memory, whose loads the waits would count.
+__device__ __forceinline__ Unit either(bool a, Unit x, Unit y) {
+    Unit r;
+    r.lgb = a ? x.lgb : y.lgb; r.nsub = a ? x.nsub : y.nsub; r.nvalid = a ? x.nvalid : y.nvalid; r.tail_rows = a ? x.tail_rows : y.tail_rows;
+    r.kb = a ? x.kb : y.kb; r.vb = a ? x.vb : y.vb;
+    r.kc = a ? x.kc : y.kc; r.km = a ? x.km : y.km; r.vc = a ? x.vc : y.vc; r.vm = a ? x.vm : y.vm;
+    r.gath = a ? x.gath : y.gath; r.half = a ? x.half : y.half; r.first = a ? x.first : y.first; r.last = a ? x.last : y.last;
+    return r;
+}
 
 // Units of short chunks (8, 16, 32 tokens; one query head per KV head).  A unit of one such chunk would hold a few hundred
 // bytes to 2 KiB of codes instead of 8 KiB and cost nearly as much as a full one, so a unit takes as many chunks of the same
 // bit-width as fill it: the row's block offsets are ordered by bit-width at the set-up (the order of the tokens does not
-// matter to a softmax; the residual rows of K and V are two more entries, as distances from the arena) and every lane's 16
+// matter to a softmax) and every lane's 16
 // bytes are addressed through the entry of the lane's chunk, so that the registers hold what a unit of one long chunk would.  A chunk counts
 // as NV tokens: N, but 16 for 8 tokens at 2 bits, whose V slice is half empty (the second half of the K tokens is masked).
 // The chunk and the place inside it are a part that depends on the lane, computed once, plus a scalar part per register;
 // entries past the unit's last chunk read the last one again.
-// 8 sequences x 32 heads x 8k tokens, 60/30/5/5 % at 2/4/8/16 bits, 32-token chunks: 76 us a call against 122, 16 tokens 78
-// against 212, 8 tokens 104 against 387; a cache of 2-bit chunks alone 46 against 110, of 8-bit chunks, whose units were full
-// before, 103 against 99.  Grouped queries keep a unit per chunk: their kernel is bound by instruction issue and at its
-// register limit (tried: 0.26 to 1.17 of the speed), as do 64-token chunks, where only 2-bit units gain (the mix 0.95).
+// Units that are one chunk or a part of one anyway (8 bits at 32 tokens, raw rows) and the residual keep a scalar base: the
+// look-ups gain them nothing.  Both branches of a loader issue the same number of loads in the same order, so that the
+// waits on them can be counted exactly.
+// 8 sequences x 32 heads x 8k tokens, 60/30/5/5 % at 2/4/8/16 bits, 32-token chunks: 71 us a call against 122 with a unit per
+// chunk, 16 tokens 70 against 207, 8 tokens 90 against 385.  One bit-width alone (4 sequences x 32 heads x 4k tokens, groups of
+// 64): 32 tokens 22.5 / 28.1 / 38.4 / 53.1 us at 2 / 4 / 8 / 16 bits against 43.7 / 41.0 / 39.3 / 54.1 (with look-ups for all
+// units, and the unit's fields in memory, 23.9 / 30.9 / 40.7 / 55.5), 8 tokens at 16 bits 82 against 84 (90).
+// Grouped queries keep a unit per chunk: their kernel is bound by instruction issue and at its register limit (tried: 0.26 to
+// 1.17 of the speed), as do 64-token chunks, where only 2-bit units gain (the mix 0.95).
 struct Gather {
-    int lgb, lgnv, N;
-    bool raw;
-    __device__ __forceinline__ Gather(const Unit &u, int N_) : lgb(u.lgb), N(N_), raw(u.lgb == 4), arena(u.kb) {
+    int lgb, lgnv, N;                                    // lgb 1, 2, 3: raw rows are not gathered
+    __device__ __forceinline__ Gather(const Unit &u, int N_) : lgb(u.lgb), N(N_), arena(u.kb) {
         lgnv = max(31 - __builtin_clz((unsigned)N_), u.lgb == 1 ? 4 : 3);
     }
     const uint8_t *arena;
@@ -177,6 +191,8 @@ struct Gather {
     __device__ __forceinline__ uint32_t code_bytes() const { return (uint32_t)N << (4 + lgb); }
     __device__ __forceinline__ uint32_t vcode_bytes() const { return (uint32_t)max(N, lgb == 1 ? 16 : 8) << (4 + lgb); }
 };
+// The entry of bit-width lgb; by value, for the reason given at either()
+__device__ __forceinline__ int of_width(int lgb, int a, int b, int c, int d) { return lgb == 1 ? a : (lgb == 2 ? b : (lgb == 3 ? c : d)); }
 // log2 of the units a chunk of 2^lgnv tokens takes (positive), or of the chunks a unit takes (negative)
 __device__ __forceinline__ int gather_shift(int N, int lgb) {
     return max(31 - __builtin_clz((unsigned)N), lgb == 4 ? 4 : (lgb == 1 ? 4 : 3)) - (8 - lgb);
@@ -216,51 +232,49 @@ __device__ __forceinline__ uint32_t ld4(const uint8_t *sbase, uint32_t voff) {
 template <int G, bool SMALL, bool GATH, typename LDS>
 __device__ __forceinline__ void load_v(const Unit &u, int lane, VRegs<G> &v, int N, const LDS &L) {
     constexpr int NG = kD / G;
-    if constexpr (GATH) {
+    if (GATH && u.gath) {
         // register i: tile cg of token block bu of a full unit, lane slice qd = lane / 16; the slice's tokens lie in one chunk
         const Gather g(u, N);
-        const int qd = lane >> 4, first = u.first + u.voff, last = u.last + u.voff;
+        const int qd = lane >> 4;
         const int lgqd = min(2, g.lgnv - (u.lgb == 1 ? 4 : 3));           // log2 of the slices of a chunk's token block
-        const uint32_t vbase = g.raw ? u.vc : g.code_bytes() + (uint32_t)N * (NG * 4);
+        const uint32_t vbase = g.code_bytes() + (uint32_t)N * (NG * 4);
         {
-            const int lchunk = first + (g.raw ? 0 : qd >> lgqd);
-            const uint32_t loff = vbase + (g.raw ? (uint32_t)lane * 16u : (uint32_t)((qd & ((1 << lgqd) - 1)) * 16 + (lane & 15)) * 16u);
-            const uint8_t *b0 = g.block(L, min(lchunk, last)) + loff;
-            const uint8_t *b1 = g.block(L, min(lchunk + (u.lgb < 3 ? 1 << (2 - lgqd) : 0), last)) + loff;   // 8 bits: one block of four tiles
+            const int lchunk = u.first + (qd >> lgqd);
+            const uint32_t loff = vbase + (uint32_t)((qd & ((1 << lgqd) - 1)) * 16 + (lane & 15)) * 16u;
+            const uint8_t *b0 = g.block(L, min(lchunk, u.last)) + loff;
+            const uint8_t *b1 = g.block(L, min(lchunk + (u.lgb < 3 ? 1 << (2 - lgqd) : 0), u.last)) + loff;   // 8 bits: one block of four tiles
 #pragma unroll
             for (int i = 0; i < 4; i++) {
                 const uint32_t tile = u.lgb == 3 ? (uint32_t)i : (uint32_t)(i & 1);
-                const uint32_t o = g.raw ? (uint32_t)min(i, u.nsub - 1) * 1024u : tile << (8 + lgqd);
-                v.c[i] = ld16(i < 2 ? b0 : b1, o);
+                v.c[i] = ld16(i < 2 ? b0 : b1, tile << (8 + lgqd));
             }
         }
         {
             const int s2 = g.lgnv + (NG == 2 ? 1 : 2);                    // log2 of the meta words of a chunk (as NV tokens)
             const int words = N * NG;
-            const int lchunk = first + (g.raw ? 0 : lane >> s2);
-            const uint32_t loff = vbase + (g.raw ? 0u : g.vcode_bytes() + (uint32_t)(lane & (words - 1)) * 4u);
+            const int lchunk = u.first + (lane >> s2);
+            const uint32_t loff = vbase + g.vcode_bytes() + (uint32_t)(lane & (words - 1)) * 4u;
 #pragma unroll
-            for (int jj = 0; jj < VRegs<G>::MV; jj++) {
-                const int k = g.raw ? 0 : (64 * jj) >> s2;
-                v.m[jj] = ld4(g.block(L, min(lchunk + k, last)) + loff, g.raw ? 0u : (uint32_t)((64 * jj) & (words - 1)) * 4u);
-            }
+            for (int jj = 0; jj < VRegs<G>::MV; jj++)
+                v.m[jj] = ld4(g.block(L, min(lchunk + ((64 * jj) >> s2), u.last)) + loff, (uint32_t)((64 * jj) & (words - 1)) * 4u);
         }
         return;
     }
+    constexpr bool PART = SMALL && !GATH;                 // a gathering kernel's other units are whole
     const int nw = u.nvalid * NG;                                         // SMALL: meta words of the unit (u.nsub counts whole KiB of codes)
-    const uint32_t vv = u.vc + (uint32_t)lane * 16u, vmo = u.vm + (uint32_t)(SMALL ? min(lane, nw - 1) : lane) * 4u;
-    const int nvm = u.lgb == 4 ? 1 : (SMALL ? max(nw >> 6, 1) : (u.nsub * NG) >> u.lgb);   // rows of 64 meta words, >= 1
+    const uint32_t vv = u.vc + (uint32_t)lane * 16u, vmo = u.vm + (uint32_t)(PART ? min(lane, nw - 1) : lane) * 4u;
+    const int nvm = u.lgb == 4 ? 1 : (PART ? max(nw >> 6, 1) : (u.nsub * NG) >> u.lgb);   // rows of 64 meta words, >= 1
     // slots per tile (64 for whole 1-KiB tiles) and tiles of the chunk's one block; one code path for both shapes, so
     // that the waits on the loads around these can be counted exactly
-    const int ts = SMALL && u.lgb < 4 ? min(64, (max(N, u.lgb == 1 ? 16 : 8) << 4) >> (u.lgb == 1 ? 4 : 3)) : 64;
-    const bool part = SMALL && ts < 64;
+    const int ts = PART && u.lgb < 4 ? min(64, (max(N, u.lgb == 1 ? 16 : 8) << 4) >> (u.lgb == 1 ? 4 : 3)) : 64;
+    const bool part = PART && ts < 64;
     const int ntile = u.lgb == 3 ? 4 : 2;
     const uint32_t vh = u.vc + (uint32_t)(lane & (ts - 1)) * 16u;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         const uint4 t = ld16(u.vb, vh + (part ? (uint32_t)(min(i, ntile - 1) * ts) * 16u : (uint32_t)min(i, u.nsub - 1) * 1024u));
         const bool ok = !part || (lane < ts && i < ntile);
-        v.c[i] = SMALL ? uint4{ok ? t.x : 0u, ok ? t.y : 0u, ok ? t.z : 0u, ok ? t.w : 0u} : t;
+        v.c[i] = PART ? uint4{ok ? t.x : 0u, ok ? t.y : 0u, ok ? t.z : 0u, ok ? t.w : 0u} : t;
     }
 #pragma unroll
     for (int jj = 0; jj < VRegs<G>::MV; jj++) v.m[jj] = ld4(u.vb, vmo + (uint32_t)min(jj, nvm - 1) * 256u);
@@ -708,23 +722,20 @@ template <int G, bool KPC, bool SMALL, typename LDS>
 __device__ __forceinline__ void load_k_iq(const Unit &u, int lane, KRegs<G> &k, int N, const LDS &L) {
     constexpr int NG = kD / G;
     const uint32_t xq = (uint32_t)lane >> 4, c = (uint32_t)lane & 15u;
-    if constexpr (SMALL) {
+    if (SMALL && u.gath) {
         const Gather g(u, N);
         {
             const int s2 = g.lgnv + u.lgb;                                // log2 of the 16-byte slots of a chunk: at least 5
-            const int lchunk = u.first + (g.raw ? 0 : lane >> s2);
-            const uint32_t loff = g.raw ? u.kc + (uint32_t)lane * 16u : (uint32_t)(lane & ((1 << s2) - 1)) * 16u;
+            const int lchunk = u.first + (lane >> s2);
+            const uint32_t loff = (uint32_t)(lane & ((1 << s2) - 1)) * 16u;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const uint32_t o = g.raw ? (uint32_t)min(j, u.nsub - 1) * 1024u : (uint32_t)((64 * j) & ((1 << s2) - 1)) * 16u;
-                k.c[j] = ld16(g.block(L, min(lchunk + (g.raw ? 0 : (64 * j) >> s2), u.last)) + loff, o);
-            }
+            for (int j = 0; j < 4; j++)
+                k.c[j] = ld16(g.block(L, min(lchunk + ((64 * j) >> s2), u.last)) + loff, (uint32_t)((64 * j) & ((1 << s2) - 1)) * 16u);
         }
-        const uint32_t mbase = g.raw ? u.kc : g.code_bytes();
-        if constexpr (KPC) {                              // 32-token chunks in groups of 32: a token group per chunk (or, at 16 bits, none)
+        if constexpr (KPC) {                              // 32-token chunks in groups of 32: a token group per chunk
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const uint2 mm = ld8(g.block(L, min(u.first + (g.raw ? 0 : j), u.last)) + mbase, g.raw ? 0u : (uint32_t)lane * 8u);
+                const uint2 mm = ld8(g.block(L, min(u.first + j, u.last)) + g.code_bytes(), (uint32_t)lane * 8u);
                 k.m[j][0] = mm.x; k.m[j][1] = mm.y;
             }
             return;
@@ -733,13 +744,13 @@ __device__ __forceinline__ void load_k_iq(const Unit &u, int lane, KRegs<G> &k, 
         const uint32_t lt = u.lgb == 1 ? 16u * (xq >> 1) + c : c;
         const uint32_t grp = u.lgb == 1 ? (xq & 1u) * (NG / 2) : (u.lgb == 2 ? (NG == 2 ? (xq >> 1) : xq) : (NG == 2 ? 0u : (xq >> 1)));
         const uint32_t nv1 = (1u << g.lgnv) - 1u;
-        const int lchunk = u.first + (g.raw ? 0 : (int)(lt >> g.lgnv));
-        const uint32_t loff = mbase + (g.raw ? 0u : ((lt & nv1) * NG + grp) * 4u);
+        const int lchunk = u.first + (int)(lt >> g.lgnv);
+        const uint32_t loff = g.code_bytes() + ((lt & nv1) * NG + grp) * 4u;
 #pragma unroll
         for (int j = 0; j < 4; j++) {
             const uint32_t tj = u.lgb == 1 ? 32u * j : (u.lgb == 2 ? 16u * j : 16u * (j >> 1));
-            const uint32_t o = g.raw ? 0u : ((tj & nv1) * NG + (u.lgb == 3 ? (uint32_t)(j & 1) * (NG / 2) : 0u)) * 4u;
-            const uint8_t *mb = g.block(L, min(lchunk + (g.raw ? 0 : (int)(tj >> g.lgnv)), u.last)) + loff;
+            const uint32_t o = ((tj & nv1) * NG + (u.lgb == 3 ? (uint32_t)(j & 1) * (NG / 2) : 0u)) * 4u;
+            const uint8_t *mb = g.block(L, min(lchunk + (int)(tj >> g.lgnv), u.last)) + loff;
             k.m[j][0] = ld4(mb, o);
             if constexpr (NG == 4) k.m[j][1] = ld4(mb, o + (u.lgb == 1 ? 4u : 0u));
         }
@@ -1350,7 +1361,6 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     at += cls[b]; un += sh >= 0 ? cls[b] << sh : (cls[b] + (1 << -sh) - 1) >> -sh;
                 }
                 upos[4] = un; n_chunk_units = (uint32_t)un;
-                if (tid < 2) L.desc[kDescCap + tid] = reinterpret_cast<uintptr_t>(tid ? a.V_tail : a.K_tail) + (size_t)u * N * 256 - reinterpret_cast<uintptr_t>(a.arena);   // the residual rows
                 // the block addresses ordered by bit-width
 #pragma unroll
                 for (int k = 0; k < 2; k++) {
@@ -1358,7 +1368,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     if (lgb) {
                         const uint32_t run = lgb <= 2 ? pa : pb;
                         const int place = (int)((run >> (16 * ((lgb - 1) & 1))) & 0xffffu)
-                                        + (lgb == 1 ? cpos[0] : (lgb == 2 ? cpos[1] : (lgb == 3 ? cpos[2] : cpos[3])));
+                                        + of_width(lgb, cpos[0], cpos[1], cpos[2], cpos[3]);
                         L.desc[place] = dsc2[k] & ~7ull;
                         const uint32_t one = 1u << (16 * ((lgb - 1) & 1));
                         if (lgb <= 2) pa += one; else pb += one;
@@ -1453,27 +1463,32 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                        t >= (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bl[bcur + 1])) bcur++;
                 const uint32_t tk = (uint32_t)__builtin_amdgcn_readfirstlane((int)(L.bg[bcur] + (t - L.bl[bcur])));
                 issue_draw();
+                Unit n;                                  // assigned as a whole: stores of single fields through the reference, merged across
+                                                         // the branches, would keep the unit in memory
                 if (GATH && tk < n_chunk_units) {
                     const int lgb = (int)tk < upos[1] ? 1 : ((int)tk < upos[2] ? 2 : ((int)tk < upos[3] ? 3 : 4));
-                    const int b0 = lgb == 1 ? upos[0] : (lgb == 2 ? upos[1] : (lgb == 3 ? upos[2] : upos[3]));
-                    const int c0 = lgb == 1 ? cpos[0] : (lgb == 2 ? cpos[1] : (lgb == 3 ? cpos[2] : cpos[3]));
-                    const int nc = lgb == 1 ? cls[0] : (lgb == 2 ? cls[1] : (lgb == 3 ? cls[2] : cls[3]));
-                    const int idx = (int)tk - b0, sh = gather_shift(N, lgb);
-                    un.lgb = lgb; un.tail_rows = 1 << 20; un.kb = a.arena; un.vb = a.arena;
-                    int t0 = 0;
+                    const int idx = (int)tk - of_width(lgb, upos[0], upos[1], upos[2], upos[3]);
+                    const int c0 = of_width(lgb, cpos[0], cpos[1], cpos[2], cpos[3]), nc = of_width(lgb, cls[0], cls[1], cls[2], cls[3]);
+                    const int sh = gather_shift(N, lgb);
+                    n.lgb = lgb; n.tail_rows = 1 << 20;
+                    n.gath = sh < 0; n.half = lgb == 1 && N == 8; n.first = n.last = 0;
                     if (sh >= 0) {                       // a chunk is one unit, or at 16 bits one or two
-                        un.first = un.last = c0 + (idx >> sh);
-                        t0 = (idx & ((1 << sh) - 1)) << (8 - lgb);
-                        un.nvalid = min(N - t0, 256 >> lgb);
+                        const unsigned long long dsc = L.desc[c0 + (idx >> sh)];
+                        n.kb = n.vb = a.arena + (((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(dsc >> 32)) << 32)
+                                                   | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)dsc));
+                        const int t0 = (idx & ((1 << sh) - 1)) << (8 - lgb);
+                        n.nvalid = min(N - t0, 256 >> lgb);
+                        const uint32_t cb = (uint32_t)N << (4 + lgb), mb = lgb == 4 ? 0u : (uint32_t)N * NG * 4;
+                        n.kc = (uint32_t)t0 << (4 + lgb); n.vc = n.kc + cb + mb;
+                        n.km = lgb == 4 ? n.kc : cb; n.vm = lgb == 4 ? n.vc : n.vc + cb;
                     } else {
-                        const int n = min(1 << -sh, nc - (idx << -sh));
-                        un.first = c0 + (idx << -sh); un.last = un.first + n - 1;
-                        un.nvalid = n << (8 - lgb + sh);                 // NV tokens each
+                        const int nch = min(1 << -sh, nc - (idx << -sh));
+                        n.kb = n.vb = a.arena;
+                        n.kc = n.km = n.vc = n.vm = 0u;
+                        n.first = c0 + (idx << -sh); n.last = n.first + nch - 1;
+                        n.nvalid = nch << (8 - lgb + sh);                 // NV tokens each
                     }
-                    un.voff = 0; un.half = lgb == 1 && N == 8;
-                    un.nsub = max((un.nvalid + (1 << (6 - lgb)) - 1) >> (6 - lgb), 1);
-                    un.kc = (uint32_t)t0 << 8; un.vc = un.kc + ((uint32_t)N << 8);   // raw fp16 rows
-                    un.km = un.vm = 0u;
+                    n.nsub = max((n.nvalid + (1 << (6 - lgb)) - 1) >> (6 - lgb), 1);
                 } else if (tk < n_chunk_units) {
                     const int cl = __builtin_amdgcn_readfirstlane((int)L.inv[tk]);
                     const unsigned long long dsc = L.desc[cl];
@@ -1483,28 +1498,29 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     const int lgb = (int)(dlo & 7u);
                     const uint8_t *blk = a.arena + (((unsigned long long)dhi << 32) | (dlo & ~0xffu));
                     const int t0 = sidx << (8 - lgb);
-                    un.lgb = lgb;
-                    un.nsub = max(min(4, (N - t0) >> (6 - lgb)), 1); un.nvalid = min(N - t0, 256 >> lgb); un.tail_rows = 1 << 20;
-                    un.kb = blk; un.vb = blk;
+                    n.lgb = lgb;
+                    n.nsub = max(min(4, (N - t0) >> (6 - lgb)), 1); n.nvalid = min(N - t0, 256 >> lgb); n.tail_rows = 1 << 20;
+                    n.kb = blk; n.vb = blk;
                     if (lgb == 4) {
-                        un.kc = (uint32_t)t0 << 8; un.vc = un.kc + ((uint32_t)N << 8);
-                        un.km = un.kc; un.vm = un.kc;    // no meta: see load_k
+                        n.kc = (uint32_t)t0 << 8; n.vc = n.kc + ((uint32_t)N << 8);
+                        n.km = n.kc; n.vm = n.kc;    // no meta: see load_k
                     } else {
                         const uint32_t cb = (uint32_t)N << (4 + lgb), mb = (uint32_t)N * NG * 4;
-                        un.kc = (uint32_t)t0 << (4 + lgb);
-                        un.km = KPC ? cb + (uint32_t)(t0 / G) * (kD * 4u) : cb + (uint32_t)t0 * NG * 4;
-                        un.vc = un.kc + cb + mb;
-                        un.vm = cb + mb + (SMALL ? (uint32_t)max(N, lgb == 1 ? 16 : 8) << (4 + lgb) : cb) + (uint32_t)t0 * NG * 4;   // 8 tokens at 2 bits: V codes of a whole slice
+                        n.kc = (uint32_t)t0 << (4 + lgb);
+                        n.km = KPC ? cb + (uint32_t)(t0 / G) * (kD * 4u) : cb + (uint32_t)t0 * NG * 4;
+                        n.vc = n.kc + cb + mb;
+                        n.vm = cb + mb + (SMALL ? (uint32_t)max(N, lgb == 1 ? 16 : 8) << (4 + lgb) : cb) + (uint32_t)t0 * NG * 4;   // 8 tokens at 2 bits: V codes of a whole slice
                     }
                 } else {                                 // 16 rows of the FP16 residual
                     const int row0 = (int)(tk - n_chunk_units) * 16;
-                    un.lgb = 4; un.nsub = SMALL ? min(4, N >> 2) : 4; un.nvalid = min(16, n_tail - row0); un.tail_rows = n_tail - row0;   // the buffers hold N rows
-                    un.kb = reinterpret_cast<const uint8_t *>(a.K_tail) + (size_t)u * N * 256;
-                    un.vb = reinterpret_cast<const uint8_t *>(a.V_tail) + (size_t)u * N * 256;
-                    un.kc = un.vc = (uint32_t)row0 * 256u;
-                    un.km = un.kc; un.vm = un.vc;
-                    if constexpr (GATH) { un.kb = un.vb = a.arena; un.first = un.last = kDescCap; un.voff = 1; un.half = false; }
+                    n.lgb = 4; n.nsub = SMALL ? min(4, N >> 2) : 4; n.nvalid = min(16, n_tail - row0); n.tail_rows = n_tail - row0;   // the buffers hold N rows
+                    n.kb = reinterpret_cast<const uint8_t *>(a.K_tail) + (size_t)u * N * 256;
+                    n.vb = reinterpret_cast<const uint8_t *>(a.V_tail) + (size_t)u * N * 256;
+                    n.kc = n.vc = (uint32_t)row0 * 256u;
+                    n.km = n.kc; n.vm = n.vc;
+                    n.gath = n.half = false; n.first = n.last = 0;
                 }
+                un = n;
                 return true;
             };
 
@@ -1529,7 +1545,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             const float scale24 = a.scale_log2 * kTwo24;
             auto step = [&](const VRegs<G> &vc, VRegs<G> &vn) {
                 const bool have_next = next_unit(nxt);
-                const Unit &pf = have_next ? nxt : cur;  // nothing left: re-read the current unit (ignored)
+                const Unit pf = either(have_next, nxt, cur);   // nothing left: re-read the current unit (ignored)
                 const int lgb = cur.lgb;
                 float p4[REP][4];                         // fp16 units: weights handed from scores to values
                 v4u ak[4];                                // grouped queries: the score operands of this bit-width

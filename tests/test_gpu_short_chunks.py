@@ -73,6 +73,38 @@ def test_units_of_several_chunks(mq, ref, B, Hkv, N, G, C, tail, mix):
     assert T._attn_case(mq, ref, B, Hkv, Hkv, N, G, C, tail, (2, 4, 8, 16), C + N, expert=expert) <= 2e-5
 
 
+@pytest.mark.parametrize("B,Hkv,N,G,C,mix,kpc", [
+    (2, 2, 32, 64, 37, (0.3, 0.3, 0.2, 0.2), 0),      # units of one chunk (8 bits, raw) beside units of several
+    (1, 3, 16, 32, 50, (0.4, 0.2, 0.2, 0.2), 0),
+    (1, 2, 8, 64, 1100, (0.4, 0.3, 0.2, 0.1), 0),     # two segments
+    (2, 1, 32, 32, 45, (0.3, 0.3, 0.2, 0.2), 1),      # keys per channel
+    (1, 2, 32, 32, 1030, (0.25, 0.25, 0.25, 0.25), 1),
+    (1, 1, 32, 32, 9, (0, 0, 1, 0), 1),
+    (1, 2, 8, 32, 70, (0, 0, 0, 1), 0),
+])
+def test_units_of_several_chunks_on_a_plan(mq, ref, B, Hkv, N, G, C, mix, kpc):
+    """Row costs of a plan (made without the residual's length), then calls with a growing residual; tolerance as above."""
+    rng = np.random.default_rng(N * 10 + C)
+    cfg, rcfg = T._cfgs(mq, ref, B, Hkv, Hkv, N, G, (2, 4, 8, 16), 0, kpc)
+    K, V = T._rand_kv(rng, B, Hkv, C * N + N)
+    expert = rng.choice(4, size=(B * Hkv, C), p=mix).astype(np.uint8)
+    (arena, used, off, status), (arena_ref, used_ref, off_ref, st_ref) = T._pack_both(mq, ref, cfg, rcfg, K, V, 0, C, expert)
+    ws = torch.empty(mq.decode_workspace_bytes(cfg, C), dtype=torch.uint8, device="cuda").fill_(0xFF)
+    out = torch.zeros((B, Hkv, 128), dtype=torch.float32, device="cuda")
+    ed, scale = T._dev(expert), 128 ** -0.5
+    mq.decode_plan(cfg, ed, C, ws)
+    for rows in (0, 1, N // 2 + 1, N - 1):
+        q = rng.standard_normal((B, Hkv, 128), dtype=np.float32).astype(np.float16)
+        Kt = np.full((B, Hkv, N, 128), np.nan, np.float16); Vt = np.full_like(Kt, np.inf)   # rows past n_tail hold junk
+        Kt[:, :, :rows] = K[:, :, C * N:C * N + rows]; Vt[:, :, :rows] = V[:, :, C * N:C * N + rows]
+        want = ref.decode_attn(rcfg, q, arena_ref, off_ref, expert, C, Kt, Vt, rows, scale)
+        out.fill_(float("nan"))
+        mq.decode_attn(cfg, T._dev(q), arena, off, ed, C, T._dev(Kt), T._dev(Vt), rows, scale, out, ws, planned=True)
+        torch.cuda.synchronize()
+        err = (np.abs(out.cpu().numpy() - want).max(-1) / np.abs(want).max(-1)).max()
+        assert err <= 2e-5, (rows, err)
+
+
 @pytest.mark.parametrize("Hkv,N,C,M,freeze", [
     (2, 128, 3, 4, 1), (1, 96, 5, 3, 0), (3, 224, 2, 8, 0), (2, 256, 1, 2, 0),   # a wavefront per 64 tokens of a chunk
     (65, 96, 8, 4, 1), (40, 160, 13, 5, 0),                                     # 520 chunks: a wavefront per chunk
