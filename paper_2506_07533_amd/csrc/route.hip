@@ -13,11 +13,14 @@
 // wavefronts that go by half rows (64 dims): the next half rows are requested, in whole 128-byte lines, before the current
 // ones are multiplied, and reach their lanes through LDS.  32-token chunks, 2.1 M rows: 104 us against 156 (5.2 TB/s; the
 // multiply-adds in their order alone take about 70).  For one window per chunk and more it is not the better one: 231 us
-// against 224 for 128-token chunks, 5.2 M rows.
+// against 224 for 128-token chunks, 5.2 M rows.  The windows begin after a row's frozen chunks, whose keys are not read:
+// 256 rows of 64 chunks of 32 tokens, 1 frozen 28.3 us a call against 28.8 with windows over all of them, 3 frozen 26.9
+// against 28.9, 60 or all frozen 11.6 (a call's launch) against 28.9.
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
 #include "pack_dev.hpp"
 #include "route_dev.hpp"
+#include <algorithm>
 
 namespace moqae {
 
@@ -109,39 +112,41 @@ __global__ __launch_bounds__(kShortWaves * 64) void route_short_kernel(RouteArgs
     if (a.bias && tid < M) w3f[64 + tid] = a.bias[tid];
     __syncthreads();
 
+    // routing freezing: the first chunks of every row are never routed
+    const int n_frozen = min(max(a.freeze_chunks - a.chunk_begin, 0), a.n_chunks);
+    const uint32_t win0 = (uint32_t)wave * gridDim.x + blockIdx.x, stride = gridDim.x * kShortWaves;
+    const int c_begin = a.chunk_begin + n_frozen, n_chunks = a.n_chunks - n_frozen;
     const int N = a.N, cpw = 64 / N;                 // chunks of a window
-    const int per_row = (a.n_chunks + cpw - 1) / cpw;
+    const int per_row = max((n_chunks + cpw - 1) / cpw, 1);
     const const_words W1w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W1));
     const const_words W2w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W2));
 
-    // window t of row u; steps of all wavefronts of the grid, on the scalar unit
-    const uint32_t win0 = (uint32_t)wave * gridDim.x + blockIdx.x, stride = gridDim.x * kShortWaves;
+    // window t of row u, from win0 on in steps of all wavefronts of the grid, on the scalar unit
     const int step_u = (int)(stride / (uint32_t)per_row), step_t = (int)(stride % (uint32_t)per_row);
-    int u = (int)(win0 / (uint32_t)per_row), t = (int)(win0 % (uint32_t)per_row), h = 0;
+    int u = n_chunks > 0 ? (int)(win0 / (uint32_t)per_row) : a.BH, t = (int)(win0 % (uint32_t)per_row), h = 0;
     auto advance = [&]() {
         t += step_t; u += step_u;
         if (t >= per_row) { t -= per_row; u++; }
     };
-    auto tokens_of = [&](int st) { return min(cpw, a.n_chunks - st * cpw) * N; };
+    auto tokens_of = [&](int st) { return min(cpw, n_chunks - st * cpw) * N; };
     auto store = [&](int su, int st, const int (&cnt)[M]) {   // lane j: chunk j of the window
-        const int c = a.chunk_begin + st * cpw + lane;
-        if (lane >= cpw || c >= a.chunk_begin + a.n_chunks) return;
-        const bool frozen = c < a.freeze_chunks;     // routing freezing: never routed, FP16 expert
+        const int c = c_begin + st * cpw + lane;
+        if (lane >= cpw || c >= c_begin + n_chunks) return;
         int best = 0, cbest = cnt[0];
 #pragma unroll
         for (int k = 1; k < M; k++) if (cnt[k] > cbest) { best = k; cbest = cnt[k]; }
         const int64_t eidx = (int64_t)su * a.expert_stride + c;
-        a.expert[eidx] = (uint8_t)(frozen ? a.e16 : best);
+        a.expert[eidx] = (uint8_t)best;
         if (a.votes) {
 #pragma unroll
-            for (int k = 0; k < M; k++) a.votes[eidx * M + k] = frozen ? 0 : cnt[k];
+            for (int k = 0; k < M; k++) a.votes[eidx * M + k] = cnt[k];
         }
     };
     uint4 v[8];                                      // half rows as loaded: register j, piece lane%8 of row 8j + lane/8
     const int r8 = lane >> 3, p8 = lane & 7;
     auto request = [&]() {                           // rows past the window's tokens read its last row
         const uint16_t *Kc = a.K + (int64_t)(u / a.Hkv) * a.stride_b + (int64_t)(u % a.Hkv) * a.stride_h
-                           + (int64_t)(a.chunk_begin + t * cpw) * N * a.stride_s + h * 64;
+                           + (int64_t)(c_begin + t * cpw) * N * a.stride_s + h * 64;
         const int last = tokens_of(t) - 1;
 #pragma unroll
         for (int j = 0; j < 8; j++) v[j] = nt_load(reinterpret_cast<const uint4 *>(Kc + (int64_t)min(8 * j + r8, last) * a.stride_s) + p8);
@@ -177,6 +182,17 @@ __global__ __launch_bounds__(kShortWaves * 64) void route_short_kernel(RouteArgs
         }
         store(cu, ct, cnt);
     }
+    // frozen chunks take the FP16 expert
+    for (uint32_t ru = win0; n_frozen > 0 && ru < (uint32_t)a.BH; ru += stride) {
+        const int64_t e0 = (int64_t)ru * a.expert_stride + a.chunk_begin;
+        for (int c = lane; c < n_frozen; c += 64) {
+            a.expert[e0 + c] = (uint8_t)a.e16;
+            if (a.votes) {
+#pragma unroll
+                for (int k = 0; k < M; k++) a.votes[(e0 + c) * M + k] = 0;
+            }
+        }
+    }
 }
 
 template <int M>
@@ -186,11 +202,12 @@ static hipError_t launch_m(const RouteArgs &a, int n_cu, hipStream_t s) {
     } else if (a.N >= 64) {
         hipLaunchKernelGGL(route_kernel<M>, dim3((unsigned)a.n_chunks, (unsigned)a.BH), dim3(kRouteThreads), 0, s, a);
     } else {
-        const int cpw = 64 / a.N;
-        const long long windows = (long long)a.BH * ((a.n_chunks + cpw - 1) / cpw);
+        const int cpw = 64 / a.N, n_frozen = std::min(std::max(a.freeze_chunks - a.chunk_begin, 0), a.n_chunks);
+        const long long windows = (long long)a.BH * ((a.n_chunks - n_frozen + cpw - 1) / cpw);
         // a window per workgroup as long as there are compute units, then all four wavefronts of a workgroup
         long long n_wg = (windows + kShortWaves - 1) / kShortWaves;
         if (n_wg < n_cu) n_wg = windows < n_cu ? windows : n_cu;
+        if (n_wg < 1) n_wg = std::min(a.BH, n_cu);   // frozen chunks only: a row per wavefront
         if (n_wg > (long long)kShortWgPerCu * n_cu) n_wg = (long long)kShortWgPerCu * n_cu;
         hipLaunchKernelGGL(route_short_kernel<M>, dim3((unsigned)n_wg), dim3(kShortWaves * 64), 0, s, a);
     }

@@ -19,6 +19,10 @@ mq = T.mq
     (1, 5, 8, 19, 2, 10, 3, 0),         # a window frozen as a whole, one in part
     (3, 1, 8, 1, 1, 0, 0, 0),
     (2, 40, 32, 210, 4, 1, 0, 0),       # more windows than wavefronts of the grid: several each
+    (2, 3, 32, 9, 4, 9, 0, 0),          # every chunk of the call frozen: no windows
+    (1, 40, 8, 150, 4, 149, 2, 0),      # one chunk left; more frozen chunks than lanes
+    (3, 30, 16, 70, 8, 65, 1, 8),
+    (1, 1, 32, 1, 4, 5, 0, 0),
 ])
 def test_route_windows_of_short_chunks(mq, ref, B, Hkv, N, C, M, freeze, c0, pad):
     rng = np.random.default_rng(N * 1000 + C)
