@@ -74,11 +74,18 @@ int cu_count() {
 // registers and its LDS tables fill one), but never more than there is work for.  The only device query is
 // the number of compute units of the current device.
 //   Long caches: a ticket of 128 tokens for every wavefront.
-//   Short ones: two wavefronts (grouped queries, whose set-up and partials cost more: one) per unit of work, a unit being 64
-//   tokens of a chunk or 16 rows of the residual, the first chunk counted at 16 bits (it usually is), at most 32 workgroups
-//   a row: such a call is all latency, and a compute unit with fewer units finishes them sooner (32 heads: a residual of 100 rows alone 57 -> 18 us, 2k tokens 27 -> 21; one head:
-//   8k tokens 19 -> 16; more than 32 workgroups on a row meet at its ticket counter and in the merge: 30k tokens on two
-//   rows 22 -> 24 us).  Not for more rows than compute units, where the workgroups' intervals cut more rows the more there
+//   Short ones: two wavefronts (grouped queries, whose set-up and partials cost more: one) per 64 tokens of a chunk, per
+//   shorter chunk or per 16 rows of the residual, the first chunk counted at 16 bits (it usually is), at most 32 workgroups a
+//   row: such a call is all latency, and a compute unit with fewer units finishes them sooner (32 heads: a residual of 100 rows
+//   alone 57 -> 18 us, 2k tokens 27 -> 21; one head: 8k tokens 19 -> 16; more than 32 workgroups on a row meet at its ticket
+//   counter and in the merge: 30k tokens on two rows 22 -> 24 us).  Short chunks share units, so that this is more workgroups
+//   than they have units for, but counted by 64 tokens they were not faster (geometric mean over 100 calls of up to 8k tokens
+//   in 8 to 32-token chunks 1.17 of the speed of one wavefront per 128 tokens, by chunks 1.19).
+//   A multiple of the rows: rows of equal cost are then not cut, a workgroup that meets two of them sets up both one after the
+//   other (500 tokens x 32 heads of one bit-width: 20 us without, 15 with; mixed bit-widths 20.2 and 20.0).  Rounded up, or
+//   down where that leaves at most a sixteenth of the compute units idle and every row has three workgroups (with fewer, mixed
+//   rows need the rest: 300 tokens x 240 rows 24 us on 256 workgroups, 29 on 240).
+//   Not for more rows than compute units, where the workgroups' intervals cut more rows the more there
 //   are (480 rows of 400 tokens 34 -> 41 us), nor for ragged batches (160 rows of up to 192 tokens 32 -> 33).  The partial
 //   slots stay below 7 MiB, so that every call moqae_decode_attn_static took it still takes; the bound depends on the
 //   configuration alone: a workspace for more chunks always serves fewer.
@@ -94,7 +101,11 @@ int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false
         int64_t most = slots > 3 ? (slots - 3) * (rows + 7) / 8 : 0;      // attn_max_partials(most, rows) <= slots
         if (most < slots) most = slots;
         int64_t n = rows * units * (rep == 1 ? 2 : 1) / waves;
+        if (n < cap) n = cap;
+        n = (n + rows - 1) / rows * rows;
         if (n > 32 * rows) n = 32 * rows;
+        const int64_t even = cus / rows * rows;
+        if (n > even) n = 3 * rows <= cus && 16 * even >= 15 * (int64_t)cus ? even : cus;
         if (n > most) n = most;
         if (cap < n) cap = n;
     }

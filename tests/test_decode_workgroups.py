@@ -44,6 +44,9 @@ def test_workspace_grows_with_chunks_and_keeps_the_static_limit():
     (1, 8, 2, 128, 64, 3, 127),      # grouped queries
     (1, 40, 40, 128, 64, 0, 90),     # residual only
     (70, 8, 8, 64, 64, 1, 30),       # more rows than workgroups
+    (1, 40, 40, 64, 64, 30, 7),      # 240 workgroups, six a row
+    (3, 40, 40, 64, 64, 6, 40),      # 256 workgroups on 120 rows: rows are cut
+    (1, 5, 5, 8, 64, 40, 3), (1, 32, 32, 32, 64, 15, 20),   # short chunks, a multiple of the rows
 ])
 def test_short_calls(ref, B, Hq, Hkv, N, G, C, T):
     """24-bit fixed point and binary32 sums: 2e-5 of a row's largest output; grouped queries hold their weights in fp16 (2e-3)."""
