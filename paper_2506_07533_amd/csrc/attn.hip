@@ -1251,9 +1251,10 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
         //      tables derived from q are built later, while the first units' codes are on their way.
         const int KPT = (seg_chunks + NT - 1) / NT;      // chunks per thread of a segment (<= 2)
         // size of the first batch: a wavefront's worth each, but an even share of the row's tickets (estimated from its cost,
-        // 16 a unit and more, without the set-up's) where the row has fewer: short rows then spread over all their compute units
+        // 16 a unit and more, without the set-up's) where the row has fewer: short rows then spread over all their compute units (not where the rows are too many to be weighted,
+        // and ru is no cost)
         uint32_t b_first = (uint32_t)NWV;
-        if (REP == 1 && !RAGGED && ru < 16ull * NWV * P + kRowSetupCost) {   // (grouped queries: the registers this takes are spilled in the unit loop; ragged batches of short rows: 32.0 -> 33.7 us)
+        if (REP == 1 && !RAGGED && weighted && ru < 16ull * NWV * P + kRowSetupCost) {   // (grouped queries: the registers this takes are spilled in the unit loop; ragged batches of short rows: 32.0 -> 33.7 us)
             const uint32_t est = ru > kRowSetupCost ? (uint32_t)(ru - kRowSetupCost) >> 4 : 1u;
             b_first = min((uint32_t)NWV, max(1u, (est + P - 1u) / P));
         }

@@ -44,6 +44,9 @@ def test_workspace_grows_with_chunks_and_keeps_the_static_limit():
     (1, 8, 2, 128, 64, 3, 127),      # grouped queries
     (1, 40, 40, 128, 64, 0, 90),     # residual only
     (70, 8, 8, 64, 64, 1, 30),       # more rows than workgroups
+    (41, 25, 25, 64, 64, 9, 30),     # more than 1024 rows, whose costs are not weighed, most of them cut
+    (130, 8, 8, 32, 64, 5, 3),
+    (205, 10, 5, 128, 64, 2, 17),    # the same with grouped queries
     (1, 40, 40, 64, 64, 30, 7),      # 240 workgroups, six a row
     (3, 40, 40, 64, 64, 6, 40),      # 256 workgroups on 120 rows: rows are cut
     (1, 5, 5, 8, 64, 40, 3), (1, 32, 32, 32, 64, 15, 20),   # short chunks, a multiple of the rows
