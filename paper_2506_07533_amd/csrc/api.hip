@@ -128,11 +128,13 @@ uint64_t workspace_bytes(const moqae_cfg *c, int n_chunks) {
     return counters_bytes(c, n_chunks) + rows * (uint64_t)attn_max_partials(n_wg, BH) * (kD + 2) * sizeof(float);
 }
 // Ragged batches: one long sequence among short ones can meet every workgroup's interval.
-uint64_t workspace_bytes_ragged(const moqae_cfg *c, int max_chunks) {
+uint64_t ragged_need(const moqae_cfg *c, int max_chunks) {                // what a ragged call itself needs
     const int n_wg = choose_wgs(c, max_chunks, c->chunk - 1, true);
     const uint64_t rows = (uint64_t)c->batch * c->n_q_heads;
-    const uint64_t own = counters_bytes(c, max_chunks) + rows * (uint64_t)n_wg * (kD + 2) * sizeof(float);
-    const uint64_t uniform = workspace_bytes(c, max_chunks);              // serves the uniform calls on the same cache too
+    return counters_bytes(c, max_chunks) + rows * (uint64_t)n_wg * (kD + 2) * sizeof(float);
+}
+uint64_t workspace_bytes_ragged(const moqae_cfg *c, int max_chunks) {     // serves the uniform calls on the same cache too
+    const uint64_t own = ragged_need(c, max_chunks), uniform = workspace_bytes(c, max_chunks);
     return own > uniform ? own : uniform;
 }
 
@@ -512,7 +514,7 @@ int moqae_decode_attn_ragged(const moqae_cfg *cfg,
     if (!aligned(n_chunks_seq, 4) || !aligned(n_tail_seq, 4)) return MOQAE_E_INVAL;
     if (max_chunks > 0 && (!aligned(arena, 256) || !aligned(chunk_off, 8))) return MOQAE_E_INVAL;
     if (!aligned(K_tail, 16) || !aligned(V_tail, 16)) return MOQAE_E_INVAL;
-    if (workspace_bytes < workspace_bytes_ragged(cfg, max_chunks)) return MOQAE_E_WORKSPACE;
+    if (workspace_bytes < ragged_need(cfg, max_chunks)) return MOQAE_E_WORKSPACE;
 
     AttnArgs a;
     a.q = static_cast<const uint16_t *>(q); a.arena = static_cast<const uint8_t *>(arena);

@@ -58,3 +58,39 @@ def test_short_calls(ref, B, Hq, Hkv, N, G, C, T):
         pytest.skip("no GPU")
     from paper_2506_07533_amd import binding as mq
     assert P._attn_case(mq, ref, B, Hq, Hkv, N, G, C, T, (2, 4, 8, 16), 7 * C + T) <= (2e-5 if Hq == Hkv else P.ATTN_TOL)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,N,C", [(8, 64, 8), (4, 32, 3), (1, 128, 30)])
+def test_ragged_call_needs_its_own_workspace_only(ref, H, N, C):
+    """Short caches: a uniform call takes more workgroups, and its workspace is the larger one.  A ragged call runs on what its
+    own rule gives (a ticket of 128 tokens per wavefront, a partial per workgroup and row) and is refused below it."""
+    import test_gpu_parity as P
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2506_07533_amd import binding as mq
+    rng = np.random.default_rng(N)
+    cfg, rcfg = P._cfgs(mq, ref, 2, H, H, N, 64, (2, 4, 8, 16), 0)
+    cus, rows = torch.cuda.get_device_properties(0).multi_processor_count, 2 * H
+    n_wg = max(1, min(cus, (rows * (C + (N - 1 + 127) // 128) + 7) // 8))
+    own = (rows * 256 + 8 * rows + 255) // 256 * 256 + rows * n_wg * 130 * 4
+    assert own < mq.decode_workspace_bytes_ragged(cfg, C)
+    K, V = P._rand_kv(rng, 2, H, C * N)
+    expert = rng.integers(0, 4, (rows, C)).astype(np.uint8)
+    (arena, used, off, status), (arena_ref, used_ref, off_ref, _) = P._pack_both(mq, ref, cfg, rcfg, K, V, 0, C, expert)
+    q = rng.standard_normal((2, H, 128), dtype=np.float32).astype(np.float16)
+    Kt = torch.zeros((2, H, N, 128), dtype=torch.float16, device="cuda")
+    counts, tails = (torch.tensor(x, dtype=torch.int32, device="cuda") for x in ([C, 1], [0, 0]))
+    out = torch.full((2, H, 128), float("nan"), dtype=torch.float32, device="cuda")
+    room = torch.full((own + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    call = lambda ws: mq.decode_attn_ragged(cfg, P._dev(q), arena, off, P._dev(expert), counts, C, Kt, Kt, tails, 128 ** -0.5, out, ws)
+    with pytest.raises(mq.MoqaeError) as e:
+        call(room[:own - 256])
+    assert e.value.code == mq.E_WORKSPACE
+    call(room[:own])
+    torch.cuda.synchronize()
+    assert bool((room[own:] == 0xA5).all())                              # nothing beyond it is written
+    whole = ref.decode_attn(rcfg, q, arena_ref, off_ref, expert, C, None, None, 0, 128 ** -0.5)
+    first = ref.decode_attn(rcfg, q, arena_ref, off_ref, expert, 1, None, None, 0, 128 ** -0.5)
+    want = np.stack([whole[0], first[1]])
+    assert (np.abs(out.cpu().numpy() - want).max(-1) / np.abs(want).max(-1)).max() <= 2e-5
