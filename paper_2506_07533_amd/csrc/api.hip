@@ -489,7 +489,7 @@ int moqae_decode_plan(const moqae_cfg *cfg, const uint8_t *expert, int64_t desc_
     AttnArgs a = {};
     a.expert = expert; a.desc_stride = desc_stride;
     a.counters = static_cast<unsigned int *>(workspace);
-    a.n_chunks = n_chunks; a.n_tail = cfg->chunk / 2;
+    a.n_chunks = n_chunks; a.n_tail = cfg->chunk / 2; a.kpc = cfg->k_per_channel;
     a.N = cfg->chunk; a.G = cfg->group; a.Hkv = cfg->n_kv_heads; a.rep = cfg->n_q_heads / cfg->n_kv_heads;
     a.BH = cfg->batch * cfg->n_kv_heads;
     for (int j = 0; j < 8; j++) a.bits_of[j] = j < cfg->n_experts ? cfg->expert_bits[j] : 16;

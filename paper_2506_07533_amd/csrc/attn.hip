@@ -81,8 +81,8 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     unsigned long long desc[kDescCap];                   // chunk descriptors of the current pass: offset | log2 bits (Gather: offsets, ordered by bit-width)
     // ticket queue of the workgroup: local tickets [0, limit) are granted; batch i maps local
     // tickets from bl[i] on to the row's tickets from bg[i] on
-    uint16_t ustart[kDescCap];                           // first unit of every chunk of the segment
-    uint16_t inv[kUnitCap];                              // unit -> chunk of the segment
+    uint16_t ustart[kDescCap];                           // first unit of every chunk of the segment (not with Gather, whose units
+    uint16_t inv[kUnitCap];                              // follow from the counts), and unit -> chunk of the segment
     uint32_t wscan[NWV], wscan2[NWV];
     uint32_t U[kMaxWeightedRowsLds + 1], r0;            // prefix sums of the rows' units
     uint32_t next, limit, done, fetching, g_seen, nb;
@@ -1168,9 +1168,8 @@ __device__ __forceinline__ int bits_of_expert(const AttnArgs &a, int e) {
 __device__ __forceinline__ int lgb_of_bits(int bits) { return bits == 2 ? 1 : (bits == 4 ? 2 : (bits == 8 ? 3 : 4)); }
 __device__ __forceinline__ uint32_t units_of_chunk(int N, int lgb) { return (uint32_t)((N + (256 >> lgb) - 1) >> (8 - lgb)); }
 
-// Chunks of up to this many tokens share units (one query head per KV head; keys per channel below 64 tokens).
-constexpr int kGatherMax = 32;
-__host__ __device__ inline bool gathers(int N, int rep, int kpc) { return rep == 1 && N <= (kpc ? 32 : kGatherMax); }
+// Chunks shorter than 64 tokens share units (one query head per KV head).
+__host__ __device__ inline bool gathers(int N, int rep) { return rep == 1 && N < 64; }
 
 // Chunks per row segment: at most kDescCap, and at most kUnitCap units if all of them were FP16.
 __host__ __device__ inline int attn_segment_chunks(int N) { return min(kDescCap, kUnitCap / max(N / 16, 1)); }
@@ -1490,7 +1489,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                         n.nvalid = nch << (8 - lgb + sh);                 // NV tokens each
                     }
                     n.nsub = max((n.nvalid + (1 << (6 - lgb)) - 1) >> (6 - lgb), 1);
-                } else if (tk < n_chunk_units) {
+                } else if (!GATH && tk < n_chunk_units) {
                     const int cl = __builtin_amdgcn_readfirstlane((int)L.inv[tk]);
                     const unsigned long long dsc = L.desc[cl];
                     const uint32_t dlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)dsc);
@@ -1672,7 +1671,7 @@ __global__ __launch_bounds__(256) void attn_prep_kernel(AttnArgs a, int n_seg) {
     for (int c = tid; c < C; c += 256) {                 // a unit costs its 8 KiB of codes plus its meta words, in steps of 512 bytes
         const int lgb = lgb_of_bits(bits_of_expert(a, erow[c]));
         const uint32_t cost = (uint32_t)(16 + (lgb < 4 ? (4 * NG) >> lgb : 0));
-        if (gathers(a.N, a.rep, a.kpc)) {                // a chunk's part of a unit, rounded
+        if (gathers(a.N, a.rep)) {                       // a chunk's part of a unit, rounded
             const int sh = gather_shift(a.N, lgb);
             units += sh >= 0 ? cost << sh : max((cost + (1u << (-sh - 1))) >> -sh, 1u);
         } else units += units_of_chunk(a.N, lgb) * cost;
@@ -1751,9 +1750,11 @@ template <int REP> constexpr int waves_per_wg() { return 8; }
 template <int G, int REP, bool KPC>
 static void launch_split(const AttnArgs &a, dim3 grid, dim3 block, hipStream_t s) {
     constexpr int NWV = waves_per_wg<REP>();
-    if (a.N < 64 || gathers(a.N, REP, KPC)) {
-        if (a.seq_chunks) hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, true, KPC>), grid, block, 0, s, a);
-        else              hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, true, KPC>), grid, block, 0, s, a);
+    if (a.N < 64) {
+        if constexpr (!(KPC && G == 64)) {               // groups of 64 tokens do not fit a shorter chunk (checked by the caller)
+            if (a.seq_chunks) hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, true, KPC>), grid, block, 0, s, a);
+            else              hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, true, KPC>), grid, block, 0, s, a);
+        }
     } else {
         if (a.seq_chunks) hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, false, KPC>), grid, block, 0, s, a);
         else              hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, false, KPC>), grid, block, 0, s, a);
