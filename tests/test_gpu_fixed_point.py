@@ -35,3 +35,21 @@ def test_weights_are_not_rounded_to_one_side(mq, ref, e, G):
     torch.cuda.synchronize()
     rel = (out.cpu().numpy().astype(np.float64) / want - 1.0)[..., 2:G]
     assert abs(rel.mean()) <= 1e-8 and np.abs(rel).max() <= 1e-6, (rel.mean(), np.abs(rel).max())
+
+
+@pytest.mark.parametrize("H,N,G,C,tail,mix", [
+    (2, 128, 64, 300, 77, (0.6, 0.3, 0.05, 0.05)),
+    (1, 256, 32, 160, 3, (0.6, 0.3, 0.05, 0.05)),
+    (3, 64, 64, 500, 0, (1, 0, 0, 0)),
+    (2, 128, 32, 280, 0, (0, 1, 0, 0)),
+    (2, 128, 64, 260, 50, (0, 0, 1, 0)),
+    (2, 32, 64, 1000, 9, (0.6, 0.3, 0.05, 0.05)),     # units of several chunks
+])
+def test_long_rows(mq, ref, H, N, G, C, tail, mix):
+    """Rows of 32k to 41k tokens.  A score errs by 2^-25 of the largest query entry times the keys' absolute sum (some 1e-6 of a
+    score's spread), a weight by 2^-25 to 2^-24, exp2 by 2^-24, the binary32 sums of 300 units by a few 2^-24, all either way:
+    6e-7 to 1.3e-6 of a row's largest output.  Fixed-point numbers of 21 bits give 1.8e-6 to 6.7e-6 on these rows."""
+    rng = np.random.default_rng(C)
+    expert = rng.choice(4, size=(H, C), p=mix).astype(np.uint8)
+    err = T._attn_case(mq, ref, 1, H, H, N, G, C, tail, (2, 4, 8, 16), N + C, expert=expert)
+    assert err <= 2.5e-6, err
