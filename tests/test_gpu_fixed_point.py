@@ -33,7 +33,7 @@ def test_weights_are_not_rounded_to_one_side(mq, ref, e, G):
     ws = torch.empty(mq.decode_workspace_bytes(cfg, C), dtype=torch.uint8, device="cuda")
     mq.decode_attn(cfg, T._dev(q), arena, off, T._dev(expert), C, None, None, 0, 1 / math.sqrt(128), out, ws)
     torch.cuda.synchronize()
-    rel = (out.cpu().numpy().astype(np.float64) / want - 1.0)[..., 2:G]
+    rel = out.cpu().numpy().astype(np.float64)[..., 2:G] / want[..., 2:G] - 1.0
     assert abs(rel.mean()) <= 1e-8 and np.abs(rel).max() <= 1e-6, (rel.mean(), np.abs(rel).max())
 
 
