@@ -76,7 +76,7 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     uint16_t zrow[WLS];                                  // zeros: the weight row of the unused tile rows
     float qsumg[REP][NG];                                // sum of q over a group, times 2^-24
     v4u qmc[REP > 1 ? 3 : 1][4][REP > 1 ? 64 : 1];       // grouped queries: score operands A per (bit-width, pass, lane)
-    float comb[NWV][REP][kD + 2];                        // per-wavefront (o, m, l) at the end of a row segment
+    alignas(8) float comb[NWV][REP][kD + 2];                        // per-wavefront (o, m, l) at the end of a row segment
     uint32_t qraw[REP * 64];                             // the row's queries as loaded (fp16 pairs)
     unsigned long long desc[kDescCap];                   // chunk descriptors of the current pass: offset | log2 bits (Gather: offsets, ordered by bit-width)
     // ticket queue of the workgroup: local tickets [0, limit) are granted; batch i maps local
@@ -1279,14 +1279,14 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
         }
         constexpr bool kLateTables = REP == 1;           // grouped queries: the builders would not fit beside the loads in flight
         auto build_q_tables = [&]() {                    // by the whole workgroup; L.qraw is in place
-            const uint16_t *qraw = reinterpret_cast<const uint16_t *>(L.qraw);
             if (tid < REP * 64) L.qtab[tid / 64][tid % 64] = L.qraw[tid];   // raw fp16 rows: lane part = l%16 holds dims 8*part..+7
             if constexpr (REP == 1) iq_build_q<G, NWV>(L, tid, lane, a.scale_log2);
             if constexpr (REP > 1) {
-                for (int i = tid; i < REP * NG; i += NT) {
-                    float sq = 0.0f;
-                    for (int d = 0; d < G; d++) sq += half_bits_to_float(qraw[(i / NG) * kD + (i % NG) * G + d]);
-                    L.qsumg[i / NG][i % NG] = sq * kTwoM24;
+                if (tid < REP * 64) {                     // a wavefront per head, its groups lie in whole rows of 16 lanes
+                    const uint32_t qw = L.qraw[tid];
+                    float sq = group_sum<16>(half_bits_to_float(qw & 0xffffu) + half_bits_to_float(qw >> 16));
+                    if constexpr (G == 64) sq += __shfl_xor(sq, 16);
+                    if ((tid & (G / 2 - 1)) == 0) L.qsumg[wave][lane / (G / 2)] = sq * kTwoM24;
                 }
                 for (int i = tid; i < AttnLds<G, REP, NWV>::WLS; i += NT) L.zrow[i] = 0;
                 if (wave < 4) mc_build_q<G, REP>(L.qraw, lane, wave, L);
@@ -1600,40 +1600,40 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             }
         }
 
-        // ---- (c) fold the wavefronts' states: o[d] = acc[d] * 2^24 + sum_t p_t zero_{t,g(d)}
+        // ---- (c) fold the wavefronts' states: o[d] = acc[d] * 2^24 + sum_t p_t zero_{t,g(d)}.  The sums over lanes are DPP
+        //      steps, and the matrix-core sums of a dim (held by one lane) are laid down in LDS first and picked up by the
+        //      dim's lane in one read: adding them where they lie, one dependent read-modify-write per tile behind twelve
+        //      dependent permutes per head, took 2.2 us of a call (one head per KV head) and 4 to 5 us (four).
+        if constexpr (REP == 1) {
 #pragma unroll
-        for (int r = 0; r < REP; r++) {
-            float lt = st.lsum[r], zt = st.z[r];
+            for (int ct = 0; ct < 8; ct++)                // column tile ct: the lane quarter of its group holds the sums
+                if ((lane >> 4) == (16 * ct) / G) L.comb[wave][0][16 * ct + (lane & 15)] = st.accq[0][ct];
+        } else {
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) lt += __shfl_xor(lt, o);
+            for (int n = 0; n < 4; n++) {                 // tile row 4 * (l / 16) + n = head * NG + group
+                const int slot = 4 * (lane >> 4) + n;
+                if (slot < REP * NG) {
+                    float *dst = &L.comb[wave][slot / NG][lane & 15];
 #pragma unroll
-            for (int o = 32; o >= NG; o >>= 1) zt += __shfl_xor(zt, o);   // lanes with equal lane % NG
-            const float zg = __shfl(zt, (2 * lane) / G);
-            float *dst = &L.comb[wave][r][0];
-            dst[2 * lane] = fmaf(st.acc[r][0], kTwo24, zg);
-            dst[2 * lane + 1] = fmaf(st.acc[r][1], kTwo24, zg);
-            if (lane == 0) { dst[kD] = st.m[r]; dst[kD + 1] = lt; }
-            if constexpr (REP == 1) {
-                wave_sync();
-#pragma unroll
-                for (int ct = 0; ct < 8; ct++)            // column tile ct: the lane quarter of its group holds the sums
-                    if ((lane >> 4) == (16 * ct) / G) dst[16 * ct + (lane & 15)] += st.accq[r][ct];
-            }
-        }
-        if constexpr (REP > 1) {                          // matrix-core tiles: row = head * NG + group, column = dim
-            wave_sync();
-            const int x = lane & 15, qd = lane >> 4;
-#pragma unroll
-            for (int ct = 0; ct < 8; ct++) {
-#pragma unroll
-                for (int n = 0; n < 4; n++) {
-                    const int slot = 4 * qd + n;
-                    if (slot < REP * NG && slot % NG == (16 * ct) / G) {
-                        float *dst = &L.comb[wave][slot / NG][16 * ct + x];
-                        *dst = fmaf(st.accA[ct][n], kTwo24, *dst);
-                    }
+                    for (int ct = 0; ct < 8; ct++)
+                        if (slot % NG == (16 * ct) / G) dst[16 * ct] = st.accA[ct][n] * kTwo24;
                 }
             }
+        }
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < REP; r++) {
+            float *dst = &L.comb[wave][r][0];
+            const float lt = wave_sum(st.lsum[r]);
+            float zg[NG];                                 // sums over the lanes with equal lane % NG
+            strided_wave_sum<NG>(st.z[r], zg);
+            float z = zg[0];
+#pragma unroll
+            for (int g = 1; g < NG; g++) z = (2 * lane) / G == g ? zg[g] : z;
+            float2 o = *reinterpret_cast<const float2 *>(&dst[2 * lane]);
+            o.x += fmaf(st.acc[r][0], kTwo24, z); o.y += fmaf(st.acc[r][1], kTwo24, z);
+            *reinterpret_cast<float2 *>(&dst[2 * lane]) = o;
+            if (lane == 0) { dst[kD] = st.m[r]; dst[kD + 1] = lt; }
         }
         __syncthreads();
         const int slot = w - wg_first;

@@ -96,6 +96,34 @@ __device__ __forceinline__ float wave_max(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
 
+// Sum over the whole wavefront, returned wave-uniform (the steps of wave_max).
+__device__ __forceinline__ float wave_sum(float x) {
+    MOQAE_DPP_FIRST("v_add_f32", "quad_perm:[1,0,3,2]" MOQAE_DPP_FULL);
+    MOQAE_DPP_STEP("v_add_f32", "quad_perm:[2,3,0,1]" MOQAE_DPP_FULL);
+    MOQAE_DPP_STEP("v_add_f32", "row_half_mirror" MOQAE_DPP_FULL);
+    MOQAE_DPP_STEP("v_add_f32", "row_mirror" MOQAE_DPP_FULL);
+    MOQAE_DPP_STEP("v_add_f32", "row_bcast:15 row_mask:0xa bank_mask:0xf");
+    MOQAE_DPP_STEP("v_add_f32", "row_bcast:31 row_mask:0xc bank_mask:0xf");
+    MOQAE_DPP_END();
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
+}
+// out[g] = sum over the lanes with lane % NG == g (NG = 2 or 4), wave-uniform: rotations inside a row of 16, then the rows.
+template <int NG>
+__device__ __forceinline__ void strided_wave_sum(float x, float (&out)[NG]) {
+    MOQAE_DPP_FIRST("v_add_f32", "row_ror:8" MOQAE_DPP_FULL);
+    MOQAE_DPP_STEP("v_add_f32", "row_ror:4" MOQAE_DPP_FULL);
+    if constexpr (NG == 2) MOQAE_DPP_STEP("v_add_f32", "row_ror:2" MOQAE_DPP_FULL);
+    MOQAE_DPP_END();
+#pragma unroll
+    for (int g = 0; g < NG; g++) {
+        float s = 0.0f;
+#pragma unroll
+        for (int row = 0; row < 4; row++)
+            s += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16 * row + g));
+        out[g] = s;
+    }
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Tokens the V code area of a chunk has room for: N, but at least one slice of the V layout (max(32/b, 8) tokens):

@@ -46,13 +46,6 @@ typedef float v4f_t __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h_t __attribute__((ext_vector_type(8)));
 
-// Sum over the wavefront, the same in every lane.
-__device__ __forceinline__ float wave_sum(float x) {
-    x = group_sum<16>(x);
-    x += __shfl_xor(x, 16);
-    return x + __shfl_xor(x, 32);
-}
-
 __device__ __forceinline__ uint32_t word4(const uint4 &v, int i) { return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)); }
 
 __device__ __forceinline__ v4f_t mfma_train(v4u_t a, v4u_t b, v4f_t c) {
