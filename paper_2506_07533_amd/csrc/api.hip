@@ -115,6 +115,44 @@ int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false
     return (int)n;
 }
 
+// Short calls give every row the same number of workgroups (what choose_wgs asks for, down to a multiple of the rows): no
+// intervals, so that no workgroup waits for the rows' costs or sets up the end of one row and the start of the next (each about
+// 8 us; with more than that many rows the intervals cut most of them).  part = tokens of a row per wavefront.
+//   part <= 128: every workgroup takes an even share of its row's tickets: no costs, no counters, no kernel that prepares them,
+//   and with one workgroup per row, which then writes the output itself, no merge.  Rows whose mixes of bit-widths differ end at
+//   different times, but the worst of them (all at 16 bits) has eight units per wavefront.  Up to three rounds of workgroups of
+//   one row each (600 tokens: 640 rows 49.5 -> 42.4 us, 1600 rows 89 -> 94).
+//   part <= 640, tables of at most 16 KiB: the same, if no row costs much more than the mean.  Every workgroup adds up all costs
+//   while its row's descriptors are on their way (1 us); else intervals, whose parts of a row are static too.
+//   part <= 1400: by the costs in the workspace; a row's workgroups share its tickets through its counter.  Above that the
+//   ends of uneven rows cost what the second set-ups do (128k tokens x 32 rows 122.5 and 122.8 us).
+// "Much more": a second set-up is worth about 10 us, in which a wavefront does 220 tokens (50 where sixteen (query head, group)
+// pairs fill the tile); where a counter evens out what a row's workgroups do, that is shared by the row's P workgroups, down to
+// a quarter (16 rows of 84k tokens under four queries, groups of 32, P = 16: 188 us on intervals, 197 on fixed rows 6 % apart).
+// 8 heads x 2k tokens 23.0 -> 16.6 us a step (on the GPU), 16 x 500 19.8 -> 13.6, 120 x 200 21.6 -> 13.5, 40 x 389 under four queries each
+// 32.1 -> 23.5, 32 x 32k under four queries 58 -> 50, 256 x 8k in 32-token chunks 69 -> 58.
+constexpr int kSplitEven = 128, kSplitWeighed = 640, kSplitPlanned = 1400, kSplitSetup = 220, kSplitRounds = 3;
+bool rows_split(const moqae_cfg *c, AttnArgs &a) {
+    const int64_t rows = a.BH, tokens = ((int64_t)a.n_chunks + 1) * c->chunk, cus = cu_count();
+    a.row_wgs = a.weigh = a.weigh_ws = 0;
+    int64_t n = choose_wgs(c, a.n_chunks, c->chunk - 1);
+    const bool room = n >= rows;                          // the workspace has partials for n workgroups
+    if (n % rows) n = n > rows ? n / rows * rows : rows;
+    const int64_t P = n / rows, part = tokens / (P * attn_waves_per_wg(1));
+    if (part <= kSplitEven) {
+        if (n > kSplitRounds * cus) return false;
+    } else {
+        if (part > kSplitPlanned || n > cus || !room) return false;
+        const int64_t setup = a.rep * (kD / a.G) >= 16 ? kSplitSetup / 4 : kSplitSetup;
+        if (part > kSplitWeighed || !attn_weigh(a, (int)(100 + 100 * setup / part))) {
+            if (64 * n < 63 * cus) return false;
+            a.weigh = (int)(100 + 25 * setup * (P + 3) / (P * part)); a.weigh_ws = 1;
+        }
+    }
+    a.n_wg = (int)n; a.row_wgs = (int)P;
+    return true;
+}
+
 // Workspace: the ticket counters of the rows, then one partial (o[D], m, l) per query head and per
 // workgroup that can touch its row.  Sized for the largest residual (n_tail = chunk - 1) so that it
 // does not depend on n_tail.
@@ -306,11 +344,11 @@ static int decode_uniform(const moqae_cfg *cfg,
     a.part = reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + counters_bytes(cfg, n_chunks)); a.out = out;
     a.scale_log2 = softmax_scale * 1.4426950408889634f;
     a.n_chunks = n_chunks; a.n_tail = n_tail;
-    a.n_wg = choose_wgs(cfg, n_chunks, n_tail);
-    a.max_partials = attn_max_partials(a.n_wg, cfg->batch * cfg->n_kv_heads);
     a.N = cfg->chunk; a.G = cfg->group; a.Hkv = cfg->n_kv_heads; a.rep = cfg->n_q_heads / cfg->n_kv_heads;
     a.BH = cfg->batch * cfg->n_kv_heads;
     for (int j = 0; j < 8; j++) a.bits_of[j] = j < cfg->n_experts ? cfg->expert_bits[j] : 16;
+    if (!rows_split(cfg, a)) a.n_wg = choose_wgs(cfg, n_chunks, n_tail);
+    a.max_partials = a.row_wgs > 0 && !a.weigh ? a.row_wgs : attn_max_partials(a.n_wg, a.BH);
     hipError_t e = launch_attn(a, static_cast<hipStream_t>(stream), g_time_begin, g_time_end);
     return e == hipSuccess ? MOQAE_OK : MOQAE_E_HIP;
 }
@@ -493,6 +531,7 @@ int moqae_decode_plan(const moqae_cfg *cfg, const uint8_t *expert, int64_t desc_
     a.N = cfg->chunk; a.G = cfg->group; a.Hkv = cfg->n_kv_heads; a.rep = cfg->n_q_heads / cfg->n_kv_heads;
     a.BH = cfg->batch * cfg->n_kv_heads;
     for (int j = 0; j < 8; j++) a.bits_of[j] = j < cfg->n_experts ? cfg->expert_bits[j] : 16;
+    rows_split(cfg, a);
     return launch_attn_plan(a, static_cast<hipStream_t>(stream)) == hipSuccess ? MOQAE_OK : MOQAE_E_HIP;
 }
 
@@ -527,6 +566,7 @@ int moqae_decode_attn_ragged(const moqae_cfg *cfg,
     a.scale_log2 = softmax_scale * 1.4426950408889634f;
     a.n_chunks = max_chunks; a.n_tail = cfg->chunk - 1;
     a.n_wg = choose_wgs(cfg, max_chunks, cfg->chunk - 1, true);
+    a.row_wgs = a.weigh = a.weigh_ws = 0;                 // rows of different lengths
     a.max_partials = a.n_wg;
     a.N = cfg->chunk; a.G = cfg->group; a.Hkv = cfg->n_kv_heads; a.rep = cfg->n_q_heads / cfg->n_kv_heads;
     a.BH = cfg->batch * cfg->n_kv_heads;

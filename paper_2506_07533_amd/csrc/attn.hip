@@ -3,7 +3,7 @@
 // paper: the quantised keys are de-quantised before they meet the query; softmax needs high
 // precision).
 //
-// attn_prep_kernel    zeroes the ticket counters and counts the units of every (sequence, KV head) row.
+// attn_prep_kernel    zeroes the ticket counters and counts the units of every (sequence, KV head) row (not for short calls).
 // attn_split_kernel   one persistent workgroup per CU (8 wavefronts).  A workgroup owns an interval
 //                     of the rows, balanced by units; inside a row its wavefronts draw tickets
 //                     (one "unit" each) from counters shared by the workgroups of the row.  A unit is
@@ -22,7 +22,7 @@
 //                       the weights, all heads of the group in one product;
 //                     - raw fp16 rows (16-bit chunks, FP16 residual): v_dot2_f32_f16 / mixed FMAs.
 //                     Every workgroup writes one partial (m, l, o[D]) per row it touched.
-// attn_merge_kernel   log-sum-exp merge of the partials of one query head, normalisation.
+// attn_merge_kernel   log-sum-exp merge of the partials of one query head, normalisation (not where a row has one workgroup).
 #include <type_traits>
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
@@ -84,7 +84,7 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     uint16_t ustart[kDescCap];                           // first unit of every chunk of the segment (not with Gather, whose units
     uint16_t inv[kUnitCap];                              // follow from the counts), and unit -> chunk of the segment
     uint32_t wscan[NWV], wscan2[NWV];
-    uint32_t U[kMaxWeightedRowsLds + 1], r0;            // prefix sums of the rows' units
+    uint32_t U[kMaxWeightedRowsLds + 1], r0, uneven;            // prefix sums of the rows' units
     uint32_t next, limit, done, fetching, g_seen, nb;
     uint32_t bl[kMaxBatches], bg[kMaxBatches];
 };
@@ -194,8 +194,9 @@ struct Gather {
 // The entry of bit-width lgb; by value, for the reason given at either()
 __device__ __forceinline__ int of_width(int lgb, int a, int b, int c, int d) { return lgb == 1 ? a : (lgb == 2 ? b : (lgb == 3 ? c : d)); }
 // log2 of the units a chunk of 2^lgnv tokens takes (positive), or of the chunks a unit takes (negative)
-__device__ __forceinline__ int gather_shift(int N, int lgb) {
-    return max(31 - __builtin_clz((unsigned)N), lgb == 4 ? 4 : (lgb == 1 ? 4 : 3)) - (8 - lgb);
+__host__ __device__ __forceinline__ int gather_shift(int N, int lgb) {
+    const int lgn = 31 - __builtin_clz((unsigned)N), least = lgb == 4 || lgb == 1 ? 4 : 3;
+    return (lgn > least ? lgn : least) - (8 - lgb);
 }
 
 template <int G> struct KRegs {
@@ -1141,18 +1142,28 @@ __device__ __forceinline__ void iq_build_wpos(AttnLds<G, 1, NWV> &L, int tid) {
 // decisions), and workgroup w of NW owns the interval [w*Utot/NW, (w+1)*Utot/NW): part of a row, or
 // several rows, always the same amount of work whatever the rows' mixes of bit-widths.  With more than
 // kMaxWeightedRows rows every row counts the same (U[u] = u * NW) and many rows average out.
+// Short calls (a.row_wgs > 0) give every row the same number of workgroups instead, whose row is known without the costs: its
+// queries and descriptors are requested first thing.  Where rows may differ (a.weigh) the costs are looked at while those are on
+// their way, and intervals are taken after all if one row costs much more than the mean.
 // Inside a row segment the workgroup's wavefronts draw tickets (one unit each) from counters shared by
 // the workgroups of the row: a wavefront or workgroup that runs faster just takes more tickets, and
 // all of them finish the row together.  The workgroup then folds its wavefronts' softmax states into
 // ONE partial per row; partial slot of workgroup w in row u = w - (first workgroup that touches u).
 constexpr int kMaxWeightedRows = 1024;
-// Workgroups whose intervals meet row [ub, ue) (ue > ub): lo_w = floor(w*Utot/NW) < ue and lo_{w+1} > ub.
-__device__ inline int wg_first_of_row(unsigned long long ub, unsigned long long Utot, int NW) {
-    return (int)(((ub + 1) * (unsigned long long)NW + Utot - 1) / Utot) - 1;
-}
-__device__ inline int wg_last_of_row(unsigned long long ue, unsigned long long Utot, int NW) {
-    return (int)((ue * (unsigned long long)NW + Utot - 1) / Utot) - 1;
-}
+constexpr uint32_t kRowDone = 0xffffffffu;               // in the place of a row's workgroups: the output is written, nothing to merge
+// Workgroup w's interval begins at floor(w * Utot / NW) (all 32-bit: w * (Utot % NW) < NW^2).
+struct Axis {
+    uint32_t Utot, NW, q, r;
+    __device__ __forceinline__ Axis(uint32_t U, uint32_t nw) : Utot(U), NW(nw), q(U / nw), r(U % nw) {}
+    __device__ __forceinline__ uint32_t begin(uint32_t w) const { return w * q + w * r / NW; }
+    // largest w with begin(w) <= x, 0 <= x < Utot: an estimate, then exact
+    __device__ __forceinline__ int owner(uint32_t x) const {
+        int w = min((int)((float)x * ((float)NW / (float)Utot)), (int)NW - 1);
+        while (begin((uint32_t)w) > x) w--;
+        while (begin((uint32_t)w + 1u) <= x) w++;
+        return w;
+    }
+};
 // Partial slots per row.  A row's units are at most 8 times another's (16 against 2 bits), so a row
 // holds at most 8/(BH+7) of all units and meets at most NW times that, plus two, intervals.
 int attn_max_partials(int NW, int BH) {
@@ -1165,14 +1176,81 @@ __device__ __forceinline__ int bits_of_expert(const AttnArgs &a, int e) {
     for (int k = 0; k < 8; k++) b = (e == k) ? a.bits_of[k] : b;
     return b;
 }
-__device__ __forceinline__ int lgb_of_bits(int bits) { return bits == 2 ? 1 : (bits == 4 ? 2 : (bits == 8 ? 3 : 4)); }
-__device__ __forceinline__ uint32_t units_of_chunk(int N, int lgb) { return (uint32_t)((N + (256 >> lgb) - 1) >> (8 - lgb)); }
+__host__ __device__ __forceinline__ int lgb_of_bits(int bits) { return bits == 2 ? 1 : (bits == 4 ? 2 : (bits == 8 ? 3 : 4)); }
+__host__ __device__ __forceinline__ uint32_t units_of_chunk(int N, int lgb) { return (uint32_t)((N + (256 >> lgb) - 1) >> (8 - lgb)); }
 
 // Chunks shorter than 64 tokens share units (one query head per KV head).
 __host__ __device__ inline bool gathers(int N, int rep) { return rep == 1 && N < 64; }
 
+// Cost of a chunk: a unit costs its 8 KiB of codes plus its meta words, in steps of 512 bytes.
+__host__ __device__ inline uint32_t chunk_cost(int N, int rep, int NG, int lgb) {
+    const uint32_t cost = (uint32_t)(16 + (lgb < 4 ? (4 * NG) >> lgb : 0));
+    if (!gathers(N, rep)) return units_of_chunk(N, lgb) * cost;
+    const int sh = gather_shift(N, lgb);                 // a chunk's part of a unit, rounded
+    if (sh >= 0) return cost << sh;
+    const uint32_t part = (cost + (1u << (-sh - 1))) >> -sh;
+    return part > 1u ? part : 1u;
+}
+
 // Chunks per row segment: at most kDescCap, and at most kUnitCap units if all of them were FP16.
 __host__ __device__ inline int attn_segment_chunks(int N) { return min(kDescCap, kUnitCap / max(N / 16, 1)); }
+
+// The costs of all rows, added up by every workgroup from the whole table of decisions (at most kWeighPieces 16-byte pieces per
+// thread, in the second-level cache after the first workgroup), instead of by a kernel before this one.  A byte permute turns
+// four decisions into their costs (a.cost_lut), a dot product adds them up.
+constexpr int kWeighPieces = 2;
+struct Weigh {
+    int ppr, n;                                          // pieces per row and in all
+    uint32_t magic;                                      // p / ppr = p * magic >> 20 for p < 1024
+    __device__ __forceinline__ Weigh(const AttnArgs &a) : ppr((a.n_chunks + 15) / 16), n(a.BH * ppr), magic(a.weigh_magic) {}
+    __device__ __forceinline__ int row(int p) const { return (int)((uint32_t)p * magic >> 20); }
+};
+template <int NT>
+__device__ __forceinline__ void load_decisions(const AttnArgs &a, int tid, uint4 (&piece)[kWeighPieces]) {
+    static_assert(kWeighPieces * NT <= 1024, "see Weigh::magic");
+    const Weigh g(a);
+#pragma unroll
+    for (int k = 0; k < kWeighPieces; k++) {
+        const int p = tid + k * NT, row = g.row(p);
+        piece[k] = uint4{0u, 0u, 0u, 0u};
+        if (p >= g.n) continue;
+        const int c = (p - row * g.ppr) * 16;
+        const uint8_t *src = a.expert + (int64_t)row * a.desc_stride + c;
+        if (((reinterpret_cast<uintptr_t>(a.expert) | (uintptr_t)a.desc_stride) & 15u) == 0) piece[k] = *reinterpret_cast<const uint4 *>(src);
+        else {                                           // rows that cannot be read in whole pieces
+            uint32_t wv[4] = {0u, 0u, 0u, 0u};
+            for (int i = 0; i < 16; i++) if (c + i < a.n_chunks) wv[i >> 2] |= (uint32_t)src[i] << (8 * (i & 3));
+            piece[k] = uint4{wv[0], wv[1], wv[2], wv[3]};
+        }
+    }
+}
+// Fills cost[0 .. BH) (LDS, holding a.cost_base); true if the largest is at most a.weigh percent of the mean.
+template <int NT>
+__device__ __forceinline__ bool weigh_rows(const AttnArgs &a, int tid, int lane, const uint4 (&piece)[kWeighPieces], uint32_t *cost) {
+    const Weigh g(a);
+#pragma unroll
+    for (int k = 0; k < kWeighPieces; k++) {
+        const int p = tid + k * NT;
+        if (p < g.n) {
+            const int row = g.row(p), left = a.n_chunks - (p - row * g.ppr) * 16;   // chunks of the piece
+            const uint32_t wv[4] = {piece[k].x, piece[k].y, piece[k].z, piece[k].w};
+            uint32_t sum = 0u;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int nb = min(max(left - 4 * i, 0), 4);
+                const uint32_t keep = nb == 4 ? ~0u : (1u << (8 * nb)) - 1u;
+                const uint32_t sel = (wv[i] & 0x07070707u & keep) | (0x0c0c0c0cu & ~keep);      // selector 12: zero
+                sum = __builtin_amdgcn_udot4(__builtin_amdgcn_perm(a.cost_lut[1], a.cost_lut[0], sel), 0x01010101u, sum, false);
+            }
+            atomicAdd(&cost[row], sum);
+        }
+    }
+    __syncthreads();
+    uint32_t total = 0u, most = 0u;                      // at most four rows per lane; every wavefront for itself
+#pragma unroll
+    for (int k = 0; k < 4; k++) { const uint32_t c = lane + 64 * k < a.BH ? cost[lane + 64 * k] : 0u; total += c; most = max(most, c); }
+    return wave_max((float)most) * (float)a.BH * 100.0f <= wave_sum((float)total) * (float)a.weigh;
+}
 
 // RAGGED: the sequences of the batch have their own numbers of chunks and residual rows (a.seq_chunks,
 // a.seq_tail, device arrays indexed by sequence); a.n_chunks is then the bound that sizes the segments.
@@ -1194,40 +1272,83 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
 
     const int seg_chunks = attn_segment_chunks(N);
     const int n_seg = max(1, (a.n_chunks + seg_chunks - 1) / seg_chunks);
-    // ---- the workgroup's interval of the unit axis
-    const bool weighted = a.BH <= kMaxWeightedRows;
+    // ---- the workgroup's interval of the unit axis, or its part of a row (a.row_wgs workgroups per row, see AttnArgs)
+    const int RW = a.row_wgs;
+    bool fixed = RW > 0;
+    uint32_t q_first = 0u;                               // a row's queries and the chunk descriptors of its first segment, as loaded
+    uint8_t e_first[2] = {0, 0};
+    uint64_t o_first[2] = {0ull, 0ull};
+    const int KPT = (seg_chunks + NT - 1) / NT;          // chunks per thread of a segment (<= 2)
+    auto request_row = [&](int u, int C) {
+        static_assert(REP * 64 <= NT, "one query word per thread");
+        // head r of the row = query r / rep_in, query head (u % Hkv) * rep_in + r % rep_in of q [B, nq, Hkv * rep_in, D]
+        if (tid < REP * 64) {
+            const int r = tid >> 6, bq = u / a.Hkv;
+            const int64_t qrow = ((int64_t)bq * a.nq + r / a.rep_in) * (a.Hkv * a.rep_in) + (u % a.Hkv) * a.rep_in + r % a.rep_in;
+            q_first = reinterpret_cast<const uint32_t *>(a.q)[qrow * 64 + (tid & 63)];
+        }
+        const uint8_t *erow = a.expert + (int64_t)u * a.desc_stride;
+        const uint64_t *orow = a.chunk_off + (int64_t)u * a.desc_stride;
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int c = tid * KPT + k;
+            if (k < KPT && c < min(C, seg_chunks)) { e_first[k] = erow[c]; o_first[k] = orow[c]; }
+        }
+    };
+    const bool weigh = !RAGGED && a.weigh != 0 && !a.weigh_ws;          // the costs are added up here, see weigh_rows
+    const bool by_counter = RW == 0 || a.weigh_ws;       // the workgroups of a row draw its tickets from a counter
+    uint4 piece[kWeighPieces];
+    if (weigh) {
+        load_decisions<NT>(a, tid, piece);
+        for (int i = tid; i < a.BH; i += NT) L.U[i + 1] = a.cost_base;
+    }
+    if (fixed) request_row(w / RW, a.n_chunks);
+    bool weighted = by_counter && a.BH <= kMaxWeightedRows;
+    uint32_t v0 = 0u, v1 = 0u;                           // costs of rows 2 * tid, 2 * tid + 1
+    const int i0 = 2 * tid;
+    if (weighted) {
+        const uint32_t *row_units = a.counters + (size_t)a.BH * n_seg * kCounterStride;
+        v0 = i0 < a.BH ? row_units[i0] : 0u; v1 = i0 + 1 < a.BH ? row_units[i0 + 1] : 0u;
+    }
+    if constexpr (REP == 1) iq_build_wpos<G, NWV>(L, tid);              // behind the loads
+    if (weigh) {
+        __syncthreads();
+        if (!weigh_rows<NT>(a, tid, lane, piece, &L.U[1])) {            // too uneven: intervals of equal cost
+            fixed = false; weighted = true;
+            v0 = i0 < a.BH ? L.U[i0 + 1] : 0u; v1 = i0 + 1 < a.BH ? L.U[i0 + 2] : 0u;
+            __syncthreads();
+        }
+    }
     if (weighted) {                                      // U = inclusive scan of the rows' unit counts, two rows per thread
         static_assert(kMaxWeightedRows <= 2 * NT, "two rows per thread");
-        const uint32_t *row_units = a.counters + (size_t)a.BH * n_seg * kCounterStride;
-        const int i0 = 2 * tid;
-        const uint32_t v0 = i0 < a.BH ? row_units[i0] : 0u, v1 = i0 + 1 < a.BH ? row_units[i0 + 1] : 0u;
-        if constexpr (REP == 1) iq_build_wpos<G, NWV>(L, tid);          // behind the load
         const uint32_t incl = wave_incl_scan(v0 + v1);
         if (lane == 63) L.wscan[wave] = incl;
+        if (tid == 0) L.uneven = 0u;
         __syncthreads();
-        uint32_t excl = incl - (v0 + v1);
+        uint32_t excl = incl - (v0 + v1), total = 0u;
 #pragma unroll
-        for (int wv = 0; wv < NWV; wv++) if (wv < wave) excl += L.wscan[wv];
+        for (int wv = 0; wv < NWV; wv++) { if (wv < wave) excl += L.wscan[wv]; total += L.wscan[wv]; }
+        if (fixed && (float)max(v0, v1) * (float)a.BH * 100.0f > (float)total * (float)a.weigh) L.uneven = 1u;
         if (tid == 0) { L.U[0] = 0u; L.r0 = 0u; }
         if (i0 < a.BH) L.U[i0 + 1] = excl + v0;
         if (i0 + 1 < a.BH) L.U[i0 + 2] = excl + v0 + v1;
         __syncthreads();
-    } else {
-        if constexpr (REP == 1) iq_build_wpos<G, NWV>(L, tid);          // made visible by the barriers of the row set-up
+        if (fixed) fixed = L.uneven == 0u;
     }
-    auto Uof = [&](int u) -> unsigned long long { return weighted ? (unsigned long long)L.U[u] : (unsigned long long)u * NW; };
-    const unsigned long long Utot = Uof(a.BH);
-    const unsigned long long lo = (unsigned long long)w * Utot / NW, hi = (unsigned long long)(w + 1) * Utot / NW;
-    int r0 = (int)(lo / (unsigned long long)NW);         // the row that holds unit lo
-    if (weighted) {
+    auto Uof = [&](int u) -> uint32_t { return weighted ? L.U[u] : (uint32_t)u * (uint32_t)NW; };
+    const Axis axis(Uof(a.BH), (uint32_t)NW);
+    const uint32_t lo = axis.begin((uint32_t)w), hi = axis.begin((uint32_t)w + 1u);
+    int r0 = fixed ? w / RW : (int)(lo / (uint32_t)NW);     // the row that holds unit lo
+    if (weighted && !fixed) {
         for (int i = tid; i < a.BH; i += NT)
-            if ((unsigned long long)L.U[i] <= lo && lo < (unsigned long long)L.U[i + 1]) L.r0 = (uint32_t)i;
+            if (L.U[i] <= lo && lo < L.U[i + 1]) L.r0 = (uint32_t)i;
         __syncthreads();
         r0 = (int)L.r0;
     }
     uint32_t *row_wgs = a.counters + (size_t)a.BH * n_seg * kCounterStride + a.BH;   // for the merge: workgroups per row
-    for (int u = r0; u < a.BH && lo < hi && Uof(u) < hi; u++) {
-        const unsigned long long ub = Uof(u), ue = Uof(u + 1), ru = ue - ub;
+    const int u_end = fixed ? r0 + 1 : a.BH;
+    for (int u = r0; u < u_end && (fixed || (lo < hi && Uof(u) < hi)); u++) {
+        const uint32_t ub = Uof(u), ue = Uof(u + 1), ru = ue - ub;   // (fixed and not weighted: not used)
         if (ru == 0) continue;
         const uint8_t *erow = a.expert + (int64_t)u * a.desc_stride;
         const uint64_t *orow = a.chunk_off + (int64_t)u * a.desc_stride;
@@ -1239,43 +1360,31 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
         // workgroups that share this row's tickets, and the share of the row inside this workgroup's
         // interval: a workgroup whose interval covers only part of the row takes at most that part of
         // the tickets (it owes the rest of its time to the neighbouring row)
-        const int wg_first = wg_first_of_row(ub, Utot, NW);
-        const uint32_t P = (uint32_t)(wg_last_of_row(ue, Utot, NW) - wg_first + 1);
-        const unsigned long long ov = min(hi, ue) - max(lo, ub);
+        const int wg_first = fixed ? u * RW : axis.owner(ub);
+        const uint32_t P = fixed ? (uint32_t)RW : (uint32_t)(axis.owner(ue - 1u) - wg_first + 1);
+        const uint32_t ov = min(hi, ue) - max(lo, ub);
         const bool whole = (lo >= ub && hi <= ue) || (ub >= lo && ue <= hi);   // the interval inside the row, or the row inside it
-        if (w == wg_first && tid == 0) row_wgs[u] = P;
+        if ((!RW || a.weigh) && w == wg_first && tid == 0) row_wgs[u] = fixed && RW == 1 ? kRowDone : P;
 
         // ---- (a) row set-up.  One round trip to memory for everything the first units need: the raw
         //      queries, the chunk descriptors of the first segment and the first batch of tickets.  The
         //      tables derived from q are built later, while the first units' codes are on their way.
-        const int KPT = (seg_chunks + NT - 1) / NT;      // chunks per thread of a segment (<= 2)
         // size of the first batch: a wavefront's worth each, but an even share of the row's tickets (estimated from its cost,
         // 16 a unit and more, without the set-up's) where the row has fewer: short rows then spread over all their compute units (not where the rows are too many to be weighted,
         // and ru is no cost)
         uint32_t b_first = (uint32_t)NWV;
-        if (REP == 1 && !RAGGED && weighted && ru < 16ull * NWV * P + kRowSetupCost) {   // (grouped queries: the registers this takes are spilled in the unit loop; ragged batches of short rows: 32.0 -> 33.7 us)
-            const uint32_t est = ru > kRowSetupCost ? (uint32_t)(ru - kRowSetupCost) >> 4 : 1u;
+        if (REP == 1 && !RAGGED && weighted && by_counter && ru < 16u * NWV * P + kRowSetupCost) {   // (grouped queries: the registers this takes are spilled in the unit loop; ragged batches of short rows: 32.0 -> 33.7 us)
+            const uint32_t est = ru > kRowSetupCost ? (ru - kRowSetupCost) >> 4 : 1u;
             b_first = min((uint32_t)NWV, max(1u, (est + P - 1u) / P));
         }
-        uint32_t q_first = 0u, g_first = 0u;
-        uint8_t e_first[2] = {0, 0};
-        uint64_t o_first[2] = {0ull, 0ull};
+        uint32_t g_first = 0u;
         {
-            static_assert(REP * 64 <= NT, "one query word per thread");
-            // head r of the row = query r / rep_in, query head (u % Hkv) * rep_in + r % rep_in of q [B, nq, Hkv * rep_in, D]
-            if (tid < REP * 64) {
-                const int r = tid >> 6, bq = u / a.Hkv;
-                const int64_t qrow = ((int64_t)bq * a.nq + r / a.rep_in) * (a.Hkv * a.rep_in) + (u % a.Hkv) * a.rep_in + r % a.rep_in;
-                q_first = reinterpret_cast<const uint32_t *>(a.q)[qrow * 64 + (tid & 63)];
-            }
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const int c = tid * KPT + k;
-                if (k < KPT && c < min(C, seg_chunks)) { e_first[k] = erow[c]; o_first[k] = orow[c]; }
-            }
-            if (tid == 0) g_first = atomicAdd(a.counters + (size_t)u * n_seg * kCounterStride, b_first);
+            if (!fixed) request_row(u, C);
+            const uint32_t q_row = q_first;
+            if (by_counter && tid == 0) g_first = atomicAdd(a.counters + (size_t)u * n_seg * kCounterStride, b_first);
             __syncthreads();                             // LDS of the previous row is free
-            if (tid < REP * 64) L.qraw[tid] = q_first;
+            if (tid < REP * 64) L.qraw[tid] = q_row;
+            q_first = 0u;                                // not carried through the unit loop
         }
         constexpr bool kLateTables = REP == 1;           // grouped queries: the builders would not fit beside the loads in flight
         auto build_q_tables = [&]() {                    // by the whole workgroup; L.qraw is in place
@@ -1381,9 +1490,19 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             const uint32_t T = n_chunk_units + (uint32_t)(seg == n_seg - 1 ? (n_tail + 15) / 16 : 0);
             unsigned int *counter = a.counters + ((size_t)u * n_seg + seg) * kCounterStride;
             // no cap for a workgroup whose whole interval lies in this row, or that covers the whole row
-            const uint32_t quota = whole ? 0xffffffffu : (uint32_t)(((unsigned long long)T * ov + ru - 1) / ru);
-            if (P == 1u) {                               // nobody shares the row: every ticket is this workgroup's, no counter in memory needed
-                if (tid == 0) { L.bl[0] = 0u; L.bg[0] = 0u; L.nb = 1u; L.limit = T; L.g_seen = T; L.done = 1u; }
+            const uint32_t quota = whole || fixed || !by_counter ? 0xffffffffu : (uint32_t)((float)T * ((float)ov / (float)ru)) + 2u;   // never below T * ov / ru
+            if (P == 1u || !by_counter) {                       // nobody shares the row, or everybody's part of it is fixed: no counter in memory needed
+                if (tid == 0) {
+                    uint32_t g0 = 0u, g1 = T;
+                    if (P > 1u && fixed) {
+                        const uint32_t part = (uint32_t)(w - wg_first);
+                        g0 = T * part / P; g1 = T * (part + 1u) / P;
+                    } else if (P > 1u) {                 // the interval's part of the row; neighbours round the same number
+                        if (lo > ub) g0 = (uint32_t)((float)T * ((float)(lo - ub) / (float)ru));
+                        if (hi < ue) g1 = (uint32_t)((float)T * ((float)(hi - ub) / (float)ru));
+                    }
+                    L.bl[0] = 0u; L.bg[0] = g0; L.nb = 1u; L.limit = g1 - g0; L.g_seen = T; L.done = 1u;
+                }
             } else if (seg == 0 && tid == 0) {           // the batch asked for during the row set-up
                 const uint32_t granted = g_first < T ? min(b_first, T - g_first) : 0u;
                 L.g_seen = g_first + b_first;
@@ -1400,6 +1519,8 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                 }
             }
             __syncthreads();
+
+            if (seg == 0) { e_first[0] = e_first[1] = 0; o_first[0] = o_first[1] = 0ull; }   // not carried through the unit loop
 
             // One wavefront at a time asks the row's counter for the next batch.
             auto fetch = [&]() {
@@ -1649,6 +1770,11 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                 num = fmaf(L.comb[wv][r][d], f, num);
                 den = fmaf(L.comb[wv][r][kD + 1], f, den);
             }
+            if (RW == 1 && fixed) {                       // the row's only workgroup: no merge
+                const int64_t orow = ((int64_t)(u / a.Hkv) * a.nq + r / a.rep_in) * (a.Hkv * a.rep_in) + (u % a.Hkv) * a.rep_in + r % a.rep_in;
+                a.out[orow * kD + d] = den > 0.0f ? num / den : 0.0f;
+                continue;
+            }
             float *dst = a.part + (((int64_t)u * REP + r) * a.max_partials + slot) * (kD + 2);
             dst[d] = num;
             if (d == 0) { dst[kD] = M; dst[kD + 1] = den; }
@@ -1670,13 +1796,9 @@ __global__ __launch_bounds__(256) void attn_prep_kernel(AttnArgs a, int n_seg) {
         C = min(max(a.seq_chunks[u / a.Hkv], 0), a.n_chunks);
         n_tail = min(max(a.seq_tail[u / a.Hkv], 0), a.N - 1);
     }
-    for (int c = tid; c < C; c += 256) {                 // a unit costs its 8 KiB of codes plus its meta words, in steps of 512 bytes
+    for (int c = tid; c < C; c += 256) {
         const int lgb = lgb_of_bits(bits_of_expert(a, erow[c]));
-        const uint32_t cost = (uint32_t)(16 + (lgb < 4 ? (4 * NG) >> lgb : 0));
-        if (gathers(a.N, a.rep)) {                       // a chunk's part of a unit, rounded
-            const int sh = gather_shift(a.N, lgb);
-            units += sh >= 0 ? cost << sh : max((cost + (1u << (-sh - 1))) >> -sh, 1u);
-        } else units += units_of_chunk(a.N, lgb) * cost;
+        units += chunk_cost(a.N, a.rep, NG, lgb);
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) units += __shfl_xor(units, o);
@@ -1705,7 +1827,7 @@ size_t attn_counter_bytes(int BH, int n_chunks, int N) {
 constexpr int kMergeGroups = 8;
 __global__ __launch_bounds__(kD *kMergeGroups) void attn_merge_kernel(const float *__restrict__ part,
                                                                        float *__restrict__ out, int rep,
-                                                                       const uint32_t *__restrict__ row_wgs, int max_partials,
+                                                                       const uint32_t *__restrict__ row_wgs, int fixed_wgs, int max_partials,
                                                                        unsigned int *zero_counters, int n_seg, int Hkv, int nq, int rep_in) {
     __shared__ float numl[kMergeGroups][kD];
     __shared__ float denl[kMergeGroups], ml[kMergeGroups];
@@ -1714,7 +1836,9 @@ __global__ __launch_bounds__(kD *kMergeGroups) void attn_merge_kernel(const floa
     // calls that run on a plan (moqae_decode_plan) leave the ticket counters as they found them: zero
     if (zero_counters && row % rep == 0)
         for (int i = tid; i < n_seg; i += kD * kMergeGroups) zero_counters[((size_t)u * n_seg + i) * kCounterStride] = 0u;
-    const int P = (int)row_wgs[u];
+    const uint32_t wgs = fixed_wgs ? (uint32_t)fixed_wgs : row_wgs[u];
+    if (wgs == kRowDone) return;
+    const int P = (int)wgs;
     const float *p0 = part + (int64_t)row * max_partials * (kD + 2);
     // this group's partials, merged on the way (online rescaling)
     float m = -INFINITY, num = 0.0f, den = 0.0f;
@@ -1768,7 +1892,8 @@ static hipError_t launch_gr(const AttnArgs &a, hipStream_t s, hipEvent_t ev_begi
     constexpr int NWV = waves_per_wg<REP>();
     const int n_seg = attn_row_segments(a.n_chunks, a.N);
     if (a.kpc && REP != 1) return hipErrorInvalidValue;  // per-channel keys: one query head per KV head (checked by the caller)
-    if (!a.planned) {
+    const bool by_counter = a.row_wgs == 0 || a.weigh_ws;   // else no costs, no counters are needed
+    if (!a.planned && by_counter) {
         hipLaunchKernelGGL(attn_prep_kernel, dim3((unsigned)a.BH), dim3(256), 0, s, a, n_seg);
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
@@ -1784,10 +1909,11 @@ static hipError_t launch_gr(const AttnArgs &a, hipStream_t s, hipEvent_t ev_begi
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (ev_end && hipEventRecord(ev_end, s) != hipSuccess) return hipErrorInvalidValue;
+    if (a.row_wgs == 1 && !a.weigh) return hipSuccess;   // written by the rows' workgroups
     hipLaunchKernelGGL(attn_merge_kernel, dim3((unsigned)(a.BH * a.rep)), dim3(kD * kMergeGroups), 0, s,
                        (const float *)a.part, a.out, a.rep,
-                       (const uint32_t *)(a.counters + (size_t)a.BH * n_seg * kCounterStride + a.BH), a.max_partials,
-                       a.planned ? a.counters : (unsigned int *)nullptr, n_seg, a.Hkv, a.nq, a.rep_in);
+                       (const uint32_t *)(a.counters + (size_t)a.BH * n_seg * kCounterStride + a.BH), a.weigh ? 0 : a.row_wgs, a.max_partials,
+                       a.planned && by_counter ? a.counters : (unsigned int *)nullptr, n_seg, a.Hkv, a.nq, a.rep_in);
     return hipGetLastError();
 }
 
@@ -1798,8 +1924,23 @@ int attn_waves_per_wg(int rep) { (void)rep; return 8; }
 // The first kernel of a decode call alone: ticket counters zeroed, the rows' costs (with a nominal residual of half
 // a chunk, so that a row with any token has a cost) and zero workgroup counts left in the workspace.
 hipError_t launch_attn_plan(const AttnArgs &a, hipStream_t s) {
+    if (a.row_wgs > 0 && !a.weigh_ws) return hipSuccess; // calls on this cache use none of it
     hipLaunchKernelGGL(attn_prep_kernel, dim3((unsigned)a.BH), dim3(256), 0, s, a, attn_row_segments(a.n_chunks, a.N));
     return hipGetLastError();
+}
+
+bool attn_weigh(AttnArgs &a, int percent) {
+    const int ppr = (a.n_chunks + 15) / 16;
+    if ((int64_t)a.BH * ppr > kWeighPieces * waves_per_wg<1>() * 64 || a.BH > 4 * 64) return false;
+    const int NG = kD / a.G;
+    const uint32_t step = (chunk_cost(a.N, a.rep, NG, 4) + 254u) / 255u;       // costs that fit a byte
+    a.weigh = percent; a.weigh_ws = 0;
+    a.weigh_magic = ppr > 0 ? ((1u << 20) + (uint32_t)ppr - 1u) / (uint32_t)ppr : 0u;
+    a.cost_base = (kRowSetupCost + 16u * (uint32_t)((a.n_tail + 15) / 16)) / step;
+    a.cost_lut[0] = a.cost_lut[1] = 0u;
+    for (int e = 0; e < 8; e++)
+        a.cost_lut[e >> 2] |= ((chunk_cost(a.N, a.rep, NG, lgb_of_bits(a.bits_of[e])) + step - 1u) / step) << (8 * (e & 3));
+    return true;
 }
 
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end) {

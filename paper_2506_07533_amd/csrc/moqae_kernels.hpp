@@ -68,6 +68,10 @@ struct AttnArgs {
     int n_chunks, n_tail, n_wg, max_partials, N, G, Hkv, rep, BH;
     int kpc;                    // keys quantised per channel
     int nq, rep_in;             // queries per sequence (1: decode of one token) and query heads per KV head of one query; rep = nq * rep_in
+    int row_wgs;                // > 0: every row has this many workgroups (n_wg = row_wgs * BH), which share its tickets evenly; 0: see attn_split_kernel
+    int weigh;                  // row_wgs > 0: if some row costs more than this many percent of the mean, intervals of equal cost instead; 0: never
+    int weigh_ws;               // weigh: by the costs in the workspace (attn_prep_kernel), and the workgroups of a row share its tickets by its counter
+    uint32_t weigh_magic, cost_base, cost_lut[2];   // weigh: see attn_weigh (cost of a row's set-up and residual, of a chunk per expert: bytes)
     int planned;                // the workspace holds a plan: no prep kernel, the merge kernel zeroes the counters again
     int bits_of[8];
 };
@@ -75,6 +79,7 @@ hipError_t launch_attn_plan(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn(const AttnArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 int attn_waves_per_wg(int rep);
 int attn_max_partials(int n_wg, int BH);        // partial slots per row
+bool attn_weigh(AttnArgs &a, int percent);      // sets the weigh fields if the split kernel can add up the rows' costs by itself
 size_t attn_counter_bytes(int BH, int n_chunks, int N); // bytes of the ticket counters at the start of the workspace
 
 

@@ -94,3 +94,48 @@ def test_ragged_call_needs_its_own_workspace_only(ref, H, N, C):
     first = ref.decode_attn(rcfg, q, arena_ref, off_ref, expert, 1, None, None, 0, 128 ** -0.5)
     want = np.stack([whole[0], first[1]])
     assert (np.abs(out.cpu().numpy() - want).max(-1) / np.abs(want).max(-1)).max() <= 2e-5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,N,G,C,heavy", [
+    (1, 8, 8, 64, 32, 33, False),        # an even share of the tickets for each of a row's workgroups
+    (1, 8, 2, 128, 64, 1, False),        # more workgroups than tickets
+    (240, 1, 1, 64, 64, 3, False),       # one workgroup per row, which writes the output
+    (60, 16, 4, 32, 64, 5, False),       # the same for grouped queries
+    (350, 2, 2, 64, 64, 2, False),       # more rows than compute units
+    (4, 16, 16, 64, 64, 80, False),      # costs added up by the workgroups, table rows of whole 16-byte pieces
+    (4, 16, 16, 64, 64, 70, False),      # table rows that begin anywhere
+    (4, 16, 16, 64, 64, 70, True),       # one row costs several times the others: intervals
+    (2, 64, 32, 64, 64, 65, True),
+    (8, 32, 32, 32, 64, 70, False),      # costs in the workspace, tickets by counters
+    (8, 32, 32, 32, 64, 70, True),
+    (2, 8, 2, 8, 64, 1100, False),       # two segments of a row
+])
+def test_fixed_workgroups_per_row(ref, B, Hq, Hkv, N, G, C, heavy):
+    """Calls on a plan, whose residual grows, and without one, on both sides of every line of the rule; tolerances as in test_short_calls."""
+    import test_gpu_parity as P
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2506_07533_amd import binding as mq
+    rng = np.random.default_rng(B * C + N)
+    cfg, rcfg = P._cfgs(mq, ref, B, Hq, Hkv, N, G, (2, 4, 8, 16), 1)
+    K, V = P._rand_kv(rng, B, Hkv, C * N + N)
+    BH = B * Hkv
+    expert = np.tile(rng.integers(0, 4, (1, C)).astype(np.uint8), (BH, 1))   # rows of equal cost
+    if heavy:
+        expert[:] = 0
+        expert[BH // 3] = 3
+    (arena, used, off, status), (arena_ref, used_ref, off_ref, _) = P._pack_both(mq, ref, cfg, rcfg, K, V, 0, C, expert)
+    ed, scale = P._dev(expert), 128 ** -0.5
+    ws = torch.full((mq.decode_workspace_bytes(cfg, C),), 0xFF, dtype=torch.uint8, device="cuda")
+    mq.decode_plan(cfg, ed, C, ws)
+    for rows, planned in ((1, True), (N - 1, True), (0, True), (N // 2, False)):
+        q = rng.standard_normal((B, Hq, 128), dtype=np.float32).astype(np.float16)
+        Kt = np.full((B, Hkv, N, 128), np.nan, np.float16); Vt = Kt.copy()
+        Kt[:, :, :rows] = K[:, :, C * N:C * N + rows]; Vt[:, :, :rows] = V[:, :, C * N:C * N + rows]
+        want = ref.decode_attn(rcfg, q, arena_ref, off_ref, expert, C, Kt, Vt, rows, scale)
+        out = torch.full((B, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+        mq.decode_attn(cfg, P._dev(q), arena, off, ed, C, P._dev(Kt), P._dev(Vt), rows, scale, out, ws, planned=planned)
+        torch.cuda.synchronize()
+        err = (np.abs(out.cpu().numpy() - want).max(-1) / np.abs(want).max(-1)).max()
+        assert err <= (2e-5 if Hq == Hkv else P.ATTN_TOL), (rows, planned, err)
