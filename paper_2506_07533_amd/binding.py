@@ -148,27 +148,45 @@ def abi_version() -> int:
 
 
 def chunk_block_bytes(cfg: Cfg, bits: int) -> int:
-    return int(lib().moqae_chunk_block_bytes(C.byref(cfg.c()), bits))
+    return int(lib().moqae_chunk_block_bytes(_cref(cfg), bits))
 
 
 def arena_upper_bound(cfg: Cfg, n_chunks_total: int) -> int:
-    return int(lib().moqae_arena_upper_bound(C.byref(cfg.c()), n_chunks_total))
+    return int(lib().moqae_arena_upper_bound(_cref(cfg), n_chunks_total))
 
 
 def decode_workspace_bytes(cfg: Cfg, n_chunks: int) -> int:
-    return int(lib().moqae_decode_workspace_bytes(C.byref(cfg.c()), n_chunks))
+    return int(lib().moqae_decode_workspace_bytes(_cref(cfg), n_chunks))
 
 
 def decode_workspace_bytes_ragged(cfg: Cfg, max_chunks: int) -> int:
-    return int(lib().moqae_decode_workspace_bytes_ragged(C.byref(cfg.c()), max_chunks))
+    return int(lib().moqae_decode_workspace_bytes_ragged(_cref(cfg), max_chunks))
 
 
+# A short call is a few microseconds of GPU time, so the marshalling is kept to what it takes: pointers as plain ints, the
+# stream's handle without a Stream object (0.3 us instead of 3), one structure per configuration (a decode step of two calls
+# took 23 us on the host and its kernels 16.6).
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+_cfgs: dict = {}                                          # by value: a Cfg may be changed between calls
+
+
+def _cref(cfg: Cfg):
+    """Reference to the C structure of the configuration's present values."""
+    key = (cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.chunk, cfg.group, tuple(cfg.expert_bits), cfg.freeze_chunks,
+           cfg.k_per_channel)
+    ref = _cfgs.get(key)
+    if ref is None:
+        if len(_cfgs) >= 256:
+            _cfgs.clear()
+        ref = _cfgs[key] = C.byref(cfg.c())
+    return ref
 
 
 def _check(rc: int, what: str):
@@ -197,8 +215,8 @@ def route_chunks(cfg: Cfg, K: torch.Tensor, chunk_begin: int, chunk_end: int,
         assert w.is_cuda and w.dtype == torch.float16 and w.is_contiguous()
     if bias is not None:
         assert bias.is_cuda and bias.dtype == torch.float32 and bias.is_contiguous()
-    kptr = C.c_void_p(K.data_ptr() - token0 * ss * 2)
-    _check(lib().moqae_route_chunks(C.byref(cfg.c()), kptr, sb, sh, ss, chunk_begin, chunk_end,
+    kptr = K.data_ptr() - token0 * ss * 2
+    _check(lib().moqae_route_chunks(_cref(cfg), kptr, sb, sh, ss, chunk_begin, chunk_end,
                                     _ptr(W1), _ptr(W2), _ptr(W3), _ptr(bias), _ptr(expert), expert.shape[1],
                                     _ptr(votes), _stream()), "moqae_route_chunks")
 
@@ -215,7 +233,7 @@ def quantize_pack(cfg: Cfg, K: torch.Tensor, V: torch.Tensor, chunk_begin: int, 
     assert arena.dtype == torch.uint8 and arena.is_contiguous() and arena_used.dtype == torch.int64
     assert status.dtype == torch.int32
     shift = token0 * ss * 2
-    _check(lib().moqae_quantize_pack(C.byref(cfg.c()), C.c_void_p(K.data_ptr() - shift), C.c_void_p(V.data_ptr() - shift),
+    _check(lib().moqae_quantize_pack(_cref(cfg), K.data_ptr() - shift, V.data_ptr() - shift,
                                      sb, sh, ss, chunk_begin, chunk_end, _ptr(expert), expert.shape[1],
                                      _ptr(arena), arena.numel(), _ptr(arena_used), _ptr(chunk_off), chunk_off.shape[1],
                                      _ptr(status), _stream()), "moqae_quantize_pack")
@@ -239,38 +257,38 @@ def router_loss_grad(cfg: Cfg, K: torch.Tensor, token_begin: int, token_end: int
     if dbias is not None:
         assert dbias.is_cuda and dbias.dtype == torch.float32 and tuple(dbias.shape) == (M,)
     arr = lambda p: None if p is None else (C.c_float * M)(*[float(v) for v in p])
-    _check(lib().moqae_router_loss_grad(C.byref(cfg.c()), _ptr(K), sb, sh, ss, token_begin, token_end, _ptr(W1), _ptr(W2), _ptr(W3),
+    _check(lib().moqae_router_loss_grad(_cref(cfg), _ptr(K), sb, sh, ss, token_begin, token_end, _ptr(W1), _ptr(W2), _ptr(W3),
                                         _ptr(bias), _ptr(nll), arr(penalty_model), arr(penalty_mem), float(lam),
                                         _ptr(loss), _ptr(dW1), _ptr(dW2), _ptr(dW3), _ptr(dbias), _stream()),
            "moqae_router_loss_grad")
 
 
 def pool_page_bytes(cfg: Cfg, expert: int) -> int:
-    return int(lib().moqae_pool_page_bytes(C.byref(cfg.c()), expert))
+    return int(lib().moqae_pool_page_bytes(_cref(cfg), expert))
 
 
 def pool_base(cfg: Cfg, n_pages: Sequence[int], expert: int) -> int:
-    return int(lib().moqae_pool_base(C.byref(cfg.c()), C.byref(_pc(n_pages)), expert))
+    return int(lib().moqae_pool_base(_cref(cfg), C.byref(_pc(n_pages)), expert))
 
 
 def pool_arena_bytes(cfg: Cfg, n_pages: Sequence[int]) -> int:
-    return int(lib().moqae_pool_arena_bytes(C.byref(cfg.c()), C.byref(_pc(n_pages))))
+    return int(lib().moqae_pool_arena_bytes(_cref(cfg), C.byref(_pc(n_pages))))
 
 
 def pool_state_bytes(cfg: Cfg, n_pages: Sequence[int]) -> int:
-    return int(lib().moqae_pool_state_bytes(C.byref(cfg.c()), C.byref(_pc(n_pages))))
+    return int(lib().moqae_pool_state_bytes(_cref(cfg), C.byref(_pc(n_pages))))
 
 
 def pool_init(cfg: Cfg, n_pages: Sequence[int], state: torch.Tensor) -> None:
     """state: int32 / uint8 device tensor of pool_state_bytes() bytes."""
     assert state.is_cuda and state.is_contiguous() and state.numel() * state.element_size() >= pool_state_bytes(cfg, n_pages)
-    _check(lib().moqae_pool_init(C.byref(cfg.c()), C.byref(_pc(n_pages)), _ptr(state), _stream()), "moqae_pool_init")
+    _check(lib().moqae_pool_init(_cref(cfg), C.byref(_pc(n_pages)), _ptr(state), _stream()), "moqae_pool_init")
 
 
 def pool_free_pages(cfg: Cfg, n_pages: Sequence[int], state: torch.Tensor) -> list:
     """Free pages of every pool (synchronises: a test / monitoring aid)."""
     counts = torch.zeros(8, dtype=torch.int32, device=state.device)
-    _check(lib().moqae_pool_free_pages(C.byref(cfg.c()), C.byref(_pc(n_pages)), _ptr(state), _ptr(counts), _stream()),
+    _check(lib().moqae_pool_free_pages(_cref(cfg), C.byref(_pc(n_pages)), _ptr(state), _ptr(counts), _stream()),
            "moqae_pool_free_pages")
     return [int(v) for v in counts.cpu().tolist()][:len(cfg.expert_bits)]
 
@@ -297,8 +315,8 @@ def route_pack_paged(cfg: Cfg, n_pages: Sequence[int], K: torch.Tensor, V: torch
     if votes is not None:
         assert votes.dtype == torch.int32 and votes.is_contiguous() and votes.shape[:2] == expert.shape
     shift = token0 * ss * 2
-    _check(lib().moqae_route_pack_paged(C.byref(cfg.c()), C.byref(_pc(n_pages)), C.c_void_p(K.data_ptr() - shift),
-                                        C.c_void_p(V.data_ptr() - shift), sb, sh, ss, chunk_begin, chunk_end,
+    _check(lib().moqae_route_pack_paged(_cref(cfg), C.byref(_pc(n_pages)), K.data_ptr() - shift,
+                                        V.data_ptr() - shift, sb, sh, ss, chunk_begin, chunk_end,
                                         _ptr(W[0]), _ptr(W[1]), _ptr(W[2]), _ptr(W[3]), _ptr(expert), expert.shape[1], _ptr(votes),
                                         _ptr(arena), _ptr(state), _ptr(chunk_off), chunk_off.shape[1], _ptr(status), _stream()),
            "moqae_route_pack_paged")
@@ -307,7 +325,7 @@ def route_pack_paged(cfg: Cfg, n_pages: Sequence[int], K: torch.Tensor, V: torch
 def pool_release(cfg: Cfg, n_pages: Sequence[int], expert: torch.Tensor, chunk_off: torch.Tensor, row_begin: int, row_end: int,
                  chunk_begin: int, chunk_end: int, state: torch.Tensor) -> None:
     assert expert.dtype == torch.uint8 and expert.is_contiguous() and chunk_off.dtype == torch.int64 and chunk_off.is_contiguous()
-    _check(lib().moqae_pool_release(C.byref(cfg.c()), C.byref(_pc(n_pages)), _ptr(expert), expert.shape[1], _ptr(chunk_off),
+    _check(lib().moqae_pool_release(_cref(cfg), C.byref(_pc(n_pages)), _ptr(expert), expert.shape[1], _ptr(chunk_off),
                                     chunk_off.shape[1], row_begin, row_end, chunk_begin, chunk_end, _ptr(state), _stream()),
            "moqae_pool_release")
 
@@ -318,7 +336,7 @@ def decode_plan(cfg: Cfg, expert: Optional[torch.Tensor], n_chunks: int, workspa
     if n_chunks > 0:
         assert expert.dtype == torch.uint8 and expert.is_contiguous() and expert.is_cuda
         stride = expert.shape[1]
-    _check(lib().moqae_decode_plan(C.byref(cfg.c()), _ptr(expert), stride, n_chunks, _ptr(workspace),
+    _check(lib().moqae_decode_plan(_cref(cfg), _ptr(expert), stride, n_chunks, _ptr(workspace),
                                    workspace.numel() * workspace.element_size(), _stream()), "moqae_decode_plan")
 
 
@@ -341,14 +359,14 @@ def decode_attn(cfg: Cfg, q: torch.Tensor, arena: Optional[torch.Tensor], chunk_
             assert t.is_cuda and t.dtype == torch.float16 and t.is_contiguous()
             assert t.shape == (cfg.batch, cfg.n_kv_heads, cfg.chunk, cfg.head_dim)
     fn = lib().moqae_decode_attn_planned if planned else lib().moqae_decode_attn
-    _check(fn(C.byref(cfg.c()), _ptr(q), _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
+    _check(fn(_cref(cfg), _ptr(q), _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
               n_chunks, _ptr(K_tail), _ptr(V_tail), n_tail, float(softmax_scale), _ptr(out),
               _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()),
            "moqae_decode_attn_planned" if planned else "moqae_decode_attn")
 
 
 def decode_workspace_bytes_multi(cfg: Cfg, n_chunks: int, n_queries: int) -> int:
-    return int(lib().moqae_decode_workspace_bytes_multi(C.byref(cfg.c()), n_chunks, n_queries))
+    return int(lib().moqae_decode_workspace_bytes_multi(_cref(cfg), n_chunks, n_queries))
 
 
 def decode_attn_multi(cfg: Cfg, q: torch.Tensor, arena: Optional[torch.Tensor], chunk_off: Optional[torch.Tensor],
@@ -367,7 +385,7 @@ def decode_attn_multi(cfg: Cfg, q: torch.Tensor, arena: Optional[torch.Tensor], 
     for t in (K_tail, V_tail):
         assert t.is_cuda and t.dtype == torch.float16 and t.is_contiguous()
         assert t.shape == (cfg.batch, cfg.n_kv_heads, cfg.chunk, cfg.head_dim)
-    _check(lib().moqae_decode_attn_multi(C.byref(cfg.c()), _ptr(q), Q, _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
+    _check(lib().moqae_decode_attn_multi(_cref(cfg), _ptr(q), Q, _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
                                          n_chunks, _ptr(K_tail), _ptr(V_tail), n_tail, float(softmax_scale), _ptr(out),
                                          _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()),
            "moqae_decode_attn_multi")
@@ -394,7 +412,7 @@ def decode_attn_static(cfg: Cfg, q: torch.Tensor, arena: Optional[torch.Tensor],
         for t in (K_tail, V_tail):
             assert t.is_cuda and t.dtype == torch.float16 and t.is_contiguous()
             assert t.shape == (cfg.batch, cfg.n_kv_heads, cfg.chunk, cfg.head_dim)
-    _check(lib().moqae_decode_attn_static(C.byref(cfg.c()), _ptr(q), _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
+    _check(lib().moqae_decode_attn_static(_cref(cfg), _ptr(q), _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
                                           n_chunks, _ptr(K_tail), _ptr(V_tail), n_tail, float(softmax_scale), _ptr(out),
                                           _stream()), "moqae_decode_attn_static")
 
@@ -418,7 +436,7 @@ def decode_attn_ragged(cfg: Cfg, q: torch.Tensor, arena: Optional[torch.Tensor],
     for t in (K_tail, V_tail):
         assert t.is_cuda and t.dtype == torch.float16 and t.is_contiguous()
         assert t.shape == (cfg.batch, cfg.n_kv_heads, cfg.chunk, cfg.head_dim)
-    _check(lib().moqae_decode_attn_ragged(C.byref(cfg.c()), _ptr(q), _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
+    _check(lib().moqae_decode_attn_ragged(_cref(cfg), _ptr(q), _ptr(arena), _ptr(chunk_off), _ptr(expert), stride,
                                           _ptr(n_chunks_seq), max_chunks, _ptr(K_tail), _ptr(V_tail), _ptr(n_tail_seq),
                                           float(softmax_scale), _ptr(out), _ptr(workspace),
                                           workspace.numel() * workspace.element_size(), _stream()),
@@ -434,5 +452,5 @@ def append_tail(cfg: Cfg, k_new: torch.Tensor, v_new: torch.Tensor, K_tail: torc
     for t in (K_tail, V_tail):
         assert t.is_cuda and t.dtype == torch.float16 and t.is_contiguous()
         assert t.shape == (cfg.batch, cfg.n_kv_heads, cfg.chunk, cfg.head_dim)
-    _check(lib().moqae_append_tail(C.byref(cfg.c()), _ptr(k_new), _ptr(v_new), _ptr(K_tail), _ptr(V_tail), n_tail,
+    _check(lib().moqae_append_tail(_cref(cfg), _ptr(k_new), _ptr(v_new), _ptr(K_tail), _ptr(V_tail), n_tail,
                                    _stream()), "moqae_append_tail")
