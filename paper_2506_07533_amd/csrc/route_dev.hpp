@@ -156,4 +156,169 @@ __device__ __forceinline__ void route_tokens(const uint16_t *Kc, int n_tok, int6
     }
 }
 
+// ---- decisions on the matrix cores -----------------------------------------------------------
+// The decision is defined by binary32 sums in the order of the dims: 1024 dependent-order multiply-adds per token at four
+// experts, which bound the kernels that route.  The same sums on v_mfma_f32_16x16x32_f16 (products exact, binary32 sums in an
+// order of their own) differ from them by rounding only, so that nearly every token's arg-max can be told from them with
+// certainty.  Every addition errs by at most its rounding times the absolute sum so far: in order, dim d is in 128 - d additions of
+// relative error 2^-24; in the matrix core, in at most 32 per step of 32 dims, from its own step on (over 800 000 sums of eight kinds,
+// cancelling ones and wide ranges among them, its error was never above a tenth of that).  So the two
+// differ by at most sum_d ((128 - d) + 32 (4 - d / 32)) 2^-24 |x_d w_d|, which comes from a second product, |x| times the weights
+// scaled so (rounded up), and is carried through SiLU and W3.  A token whose two best logits are closer than that (ties, else about one in a
+// thousand) sends its wavefront through the sums in order.  The result is the same, bit for bit, always.
+typedef float v4f_r __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u_r __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h_r __attribute__((ext_vector_type(8)));
+constexpr float kSumErr = 256.0f / 16777216.0f;           // the factor of |x_0 w_0|; the others relative to it
+constexpr int kW3Max = 72, kBiasMax = 80, kW3Words = 84;  // w3f: also the largest |W3| of every row, the largest |bias|
+
+// The workgroup's copy of W3 as binary32 and what the bound needs of it.
+template <int M>
+__device__ __forceinline__ void stage_w3(const uint16_t *W3, const float *bias, float *w3f, int tid) {
+    if (tid < M * M) w3f[tid] = half_bits_to_float(W3[tid]);
+    if (tid < M) {
+        w3f[64 + tid] = bias ? bias[tid] : 0.0f;
+        float m = 0.0f;
+#pragma unroll
+        for (int k = 0; k < M; k++) m = fmaxf(m, fabsf(half_bits_to_float(W3[tid * M + k])));
+        w3f[kW3Max + tid] = m;
+    }
+    if (tid == M) {
+        float m = 0.0f;
+        if (bias) for (int k = 0; k < M; k++) m = fmaxf(m, fabsf(bias[k]));
+        w3f[kBiasMax] = m;
+    }
+}
+
+// Operand A, held by every wavefront: row i = an output, lane 16q + i holds its weights of dims 32s + 8q .. + 7 in w[s].
+// Up to four experts: rows 0..3 = the columns of W1, 4..7 = of W2, 8..15 = 0..7 again; else rows 0..7 and 8..15.
+struct RouterWeights { v4u_r w[4], e[4]; };              // e: the weights of the bound
+// The two weight matrices as they are, in LDS (2 * kD * M halves), by all threads of the workgroup; then, behind a barrier, the operand.
+template <int M>
+__device__ __forceinline__ void stage_router_weights(const uint16_t *W1, const uint16_t *W2, uint32_t *raw, int tid, int n_threads) {
+    constexpr int n = kD * M / 2;                         // words of a matrix
+    for (int i = tid; i < n; i += n_threads) {
+        raw[i] = reinterpret_cast<const uint32_t *>(W1)[i];
+        raw[n + i] = reinterpret_cast<const uint32_t *>(W2)[i];
+    }
+}
+template <int M>
+__device__ __forceinline__ void load_router_weights(const uint32_t *raw, int lane, RouterWeights &r) {
+    constexpr int H = M <= 4 ? 4 : 8;
+    const int i = lane & (2 * H - 1), q = lane >> 4, m = i & (H - 1);
+    const uint16_t *W = reinterpret_cast<const uint16_t *>(raw) + (i < H ? 0 : kD * M) + min(m, M - 1) + 8 * q * M;
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const uint32_t w0 = m < M ? (uint32_t)W[(32 * s + 2 * k) * M] : 0u, w1 = m < M ? (uint32_t)W[(32 * s + 2 * k + 1) * M] : 0u;
+            r.w[s][k] = w0 | (w1 << 16);
+            // cutting off loses up to 2^-10 of a value, or 2^-24
+            const float f0 = (float)(256 - 64 * s - 2 * k - 8 * q) * ((1.0f + 0x1p-8f) / 256.0f), f1 = f0 - (1.0f + 0x1p-8f) / 256.0f;
+            const auto e = __builtin_amdgcn_cvt_pkrtz(fmaf(fabsf(half_bits_to_float(w0)), f0, 0x1p-23f), fmaf(fabsf(half_bits_to_float(w1)), f1, 0x1p-23f));
+            r.e[s][k] = __builtin_bit_cast(uint32_t, e);
+        }
+    }
+}
+
+__device__ __forceinline__ v4f_r mfma_router(v4u_r a, v4u_r b, v4f_r c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_r, a), __builtin_bit_cast(v8h_r, b), c, 0, 0, 0);
+}
+// k-step s of a block of 16 tokens: lane 16q + x holds the 16-byte piece 4s + q of token x's row.  sum and bound: row 4q + n
+// of the outputs for token x.
+__device__ __forceinline__ void router_step(const RouterWeights &r, int s, const uint4 &x, v4f_r &sum, v4f_r &bound) {
+    const v4u_r b = {x.x, x.y, x.z, x.w};
+    sum = mfma_router(r.w[s], b, sum);
+    bound = mfma_router(r.e[s], b & 0x7fff7fffu, bound);
+}
+
+// Outputs of 64 tokens -> every lane's own token: blocks 0..3 of 16 tokens as two pairs (0, 2) and (1, 3).  Up to four experts a
+// pair is one register set already (lanes 0..31 keep the first block, the others the second), see pick_pair.
+template <int M> struct RouterSums { static constexpr int H = M <= 4 ? 4 : 8; float A[H], B[H]; };
+__device__ __forceinline__ v4f_r pick_pair(const v4f_r &lo, const v4f_r &hi, int lane) {
+    v4f_r r;
+#pragma unroll
+    for (int n = 0; n < 4; n++) r[n] = lane < 32 ? lo[n] : hi[n];
+    return r;
+}
+__device__ __forceinline__ void swap16(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ void swap32(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    a = __builtin_bit_cast(float, (uint32_t)r[0]); b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+// c[b]: block b (up to four experts: c[0] = pair (0, 2), c[1] = pair (1, 3))
+template <int M>
+__device__ __forceinline__ void gather_sums(v4f_r (&c)[M <= 4 ? 2 : 4], RouterSums<M> &o) {
+#pragma unroll
+    for (int n = 0; n < 4; n++) {
+        if constexpr (M <= 4) {
+            float a = c[0][n], b = c[1][n];
+            swap16(a, b);
+            o.A[n] = a; o.B[n] = b;
+        } else {
+            float t0 = c[0][n], t1 = c[1][n], t2 = c[2][n], t3 = c[3][n];
+            swap32(t0, t2); swap32(t1, t3);               // t0, t1: outputs 0..7, t2, t3: 8..15
+            swap16(t0, t1); swap16(t2, t3);
+            o.A[n] = t0; o.A[4 + n] = t1; o.B[n] = t2; o.B[4 + n] = t3;
+        }
+    }
+}
+
+// The token's expert from the sums and their bounds; false if they do not tell it from the expert by the sums in order.
+template <int M>
+__device__ __forceinline__ bool certain_top(const RouterSums<M> &v, const RouterSums<M> &s, const float *w3f, bool has_bias, int &top) {
+    float hid[M], err = 0.0f, any = 0.0f;
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        const float z = v.A[m] * v.B[m];
+        const float ea = kSumErr * s.A[m], eb = kSumErr * s.B[m];
+        any += ea + eb;
+        // |z - z'| of the two products, times the slope of SiLU: the slope at z and what the second derivative, at most
+        // s (1 - s) (2 + |z|), adds within 1/4; 1.1 anywhere
+        const float ez = fmaf(fabsf(v.A[m]), eb, fmaf(fabsf(v.B[m]), ea, ea * eb));
+        const float sg = __builtin_amdgcn_rcpf(1.0f + fast_exp2(fminf(-z, 80.0f) * 1.44269504f));
+        hid[m] = z * sg;
+        const float near = fmaf(ez * 1.45f * fmaf(-sg, sg, sg), 2.0f + fabsf(z), fabsf(fmaf(hid[m], 1.0f - sg, sg)));
+        const float slope = ez <= 0.25f ? near : 1.1f;
+        // exponential, division and W3's sums on either side: (|z| + 8) 2^-21 and 2^-19 of the hidden value
+        err = fmaf(fmaf(fmaf(fabsf(z), 0x1p-21f, 0x1p-18f + 0x1p-19f), fabsf(hid[m]), ez * slope), w3f[kW3Max + m], err);
+    }
+    float best = 0.0f, second = -INFINITY;
+    top = 0;
+#pragma unroll
+    for (int k = 0; k < M; k++) {
+        float acc = has_bias ? w3f[64 + k] : 0.0f;
+#pragma unroll
+        for (int j = 0; j < M; j++) acc = fmaf(hid[j], w3f[j * M + k], acc);
+        if (k == 0) best = acc;
+        else {
+            const bool more = acc > best;
+            second = fmaxf(second, more ? best : acc);
+            top = more ? k : top; best = more ? acc : best;
+        }
+    }
+    if (has_bias) err = fmaf(w3f[kBiasMax], 0x1p-19f, err);
+    // all sums zero (rows of zeros): both sides have the same logits.  NaN: not certain
+    return M == 1 || best - second > 2.1f * err || any == 0.0f;
+}
+
+// A token's expert by the sums in order, from its key row in memory (for the wavefronts certain_top could not settle).
+template <int M, typename WP>
+__device__ __forceinline__ int ordered_top(const uint16_t *row, WP W1w, WP W2w, const float *w3f, bool has_bias) {
+    float accA[M], accB[M];
+#pragma unroll
+    for (int m = 0; m < M; m++) { accA[m] = 0.0f; accB[m] = 0.0f; }
+#pragma unroll 1
+    for (int h = 0; h < 2; h++) {
+        uint4 x[8];
+#pragma unroll
+        for (int p = 0; p < 8; p++) x[p] = reinterpret_cast<const uint4 *>(row)[8 * h + p];
+        route_half_row<M>(x, 64 * h, W1w, W2w, accA, accB);
+    }
+    return route_top<M>(accA, accB, w3f, has_bias);
+}
+
 }  // namespace moqae

@@ -107,6 +107,41 @@ def test_route_strided_and_ties(mq, ref):
     assert (expert.cpu().numpy() == 0).all() and (votes.cpu().numpy()[..., 0] == N).all()
 
 
+@pytest.mark.parametrize("M,N,C", [(2, 64, 80), (3, 32, 300), (4, 128, 70), (4, 8, 700), (5, 64, 90), (8, 96, 60), (8, 256, 40)])
+@pytest.mark.parametrize("kind", ["near", "tied", "small", "large", "zero_rows"])
+def test_route_close_decisions(mq, ref, kind, M, N, C):
+    """Logits that differ by a few ulps, or not at all, in some or all tokens: decisions and votes still equal the sums in order.
+    More chunks than the two per compute unit of the kernel for few chunks, whose sums are in order anyway."""
+    B, Hkv = 2, 8
+    if C * B * Hkv <= 512:
+        C = 600 // (B * Hkv)
+    rng = np.random.default_rng(M * N + len(kind))
+    cfg, rcfg = _cfgs(mq, ref, B, Hkv, Hkv, N, 64, ([16, 2, 4, 8, 2, 4, 8, 16])[:M], 0)
+    K, _ = _rand_kv(rng, B, Hkv, C * N)
+    W1, W2 = ((rng.standard_normal((128, M)) * 0.1).astype(np.float16) for _ in range(2))
+    W3 = np.repeat((rng.standard_normal((M, 1)) * 0.3).astype(np.float16), M, 1)
+    bias = None
+    if kind == "near":                                            # columns of W3 one ulp apart
+        W3 = (W3.view(np.uint16) + rng.integers(0, 2, (M, M)).astype(np.uint16)).view(np.float16)
+    elif kind == "small":                                         # subnormal weights and keys
+        W1, W2, K = W1 * np.float16(1e-5), W2 * np.float16(1e-5), K * np.float16(1e-4)
+        W3 = (rng.standard_normal((M, M)) * 1e-4).astype(np.float16)
+        bias = (rng.standard_normal(M) * 1e-20).astype(np.float32)
+    elif kind == "large":
+        K = (K * np.float16(800)).clip(-65504, 65504); W1 = W1 * np.float16(100)
+        W3 = (rng.standard_normal((M, M)) * 100).astype(np.float16)
+    elif kind == "zero_rows":
+        K[:, :, ::3] = 0; K[:, :, 5::7] *= np.float16(1e-3)
+        bias = np.repeat(np.float32(0.1), M)
+    e_ref, v_ref = ref.route_chunks(rcfg, K, 0, C, W1, W2, W3, bias)
+    expert = torch.full((B * Hkv, C), 255, dtype=torch.uint8, device="cuda")
+    votes = torch.full((B * Hkv, C, M), -1, dtype=torch.int32, device="cuda")
+    mq.route_chunks(cfg, _dev(K), 0, C, _dev(W1), _dev(W2), _dev(W3), None if bias is None else _dev(bias), expert, votes)
+    torch.cuda.synchronize()
+    assert np.array_equal(votes.cpu().numpy(), v_ref)
+    assert np.array_equal(expert.cpu().numpy(), e_ref)
+
+
 # ----------------------------------------------------------------------------------------------
 # quantise + pack
 # ----------------------------------------------------------------------------------------------
