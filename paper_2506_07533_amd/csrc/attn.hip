@@ -89,17 +89,6 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     uint32_t bl[kMaxBatches], bg[kMaxBatches];
 };
 
-// Inclusive prefix sum over the 64 lanes, on the vector ALU (row shifts, then the row totals handed on).
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);   // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);   // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);   // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_BCAST15, 0xA, 0xF, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_BCAST31, 0xC, 0xF, false);
-    return x;
-}
-
 // Orders this wavefront's LDS traffic between phases that exchange data across lanes.
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

@@ -2,8 +2,9 @@
 // at its routed bit-width (Sec. 3.1-3.2 of the paper say only that a chunk is quantised with
 // the configuration its router chose; the quantiser and the layout are defined in moqae.h).
 //
-//   plan_rows_kernel / plan_kernel  block sizes -> exclusive scan in (b, h, c) order -> offsets and
-//                capacity check: one workgroup per row when the table allows, else one workgroup.
+//   plan_small_kernel / plan_rows_kernel / plan_kernel  block sizes -> exclusive scan in (b, h, c) order -> offsets and
+//                capacity check: one thread per chunk up to 1024 chunks, then one workgroup per row when the table allows,
+//                else one workgroup.
 //   pack_kernel  one workgroup per (K or V, chunk, row), one lane per (token row, group): the lane loads its
 //                G dims, takes minimum and maximum with packed fp16 operations, computes scale and
 //                reciprocal once and then four operations per code (no cross-lane step anywhere).
@@ -38,6 +39,39 @@ __device__ __forceinline__ unsigned long long plan_block_scan(unsigned long long
 #pragma unroll
     for (int wv = 0; wv < kPlanThreads / 64; wv++) { const unsigned long long v = wsum[wv]; if (wv < wave) before += v; total += v; }
     return before + incl - x;
+}
+
+// Tables of at most kPlanThreads chunks: one thread per chunk, everything read in one round trip.  A call is all latency here, a
+// dependent read 1 to 2 us of it, and plan_kernel's two sweeps with their scans are five: the decode step that packs 32 chunks took
+// 62.8 us with them and takes 56.5.
+__global__ __launch_bounds__(kPlanThreads) void plan_small_kernel(PackArgs a) {
+    __shared__ uint32_t wsum[kPlanThreads / 64];      // a wavefront's block bytes in units of 256 (below 2^20), bit 31: an expert out of range
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, total = a.BH * a.n_chunks;
+    const int u = min(tid, total - 1) / a.n_chunks, c = a.chunk_begin + min(tid, total - 1) % a.n_chunks;
+    const int status = *a.status;
+    const unsigned long long used = *a.arena_used;
+    const int e = a.expert[(int64_t)u * a.expert_stride + c];
+    int bits = 16;
+#pragma unroll
+    for (int k = 0; k < 8; k++) bits = e == k ? a.bits_of[k] : bits;
+    const bool own = tid < total;
+    const uint32_t size = own && e < a.M ? (uint32_t)((block_bytes(a.N, a.G, bits) + 255u) >> 8) : 0u;
+    const uint32_t incl = wave_incl_scan(size);
+    const bool wave_bad = __ballot(own && e >= a.M) != 0ull;
+    if (lane == 63) wsum[wave] = incl | (wave_bad ? 0x80000000u : 0u);
+    __syncthreads();
+    uint32_t before = 0u, all = 0u, bad = 0u;
+    for (int wv = 0; wv < (int)blockDim.x / 64; wv++) {
+        const uint32_t v = wsum[wv];
+        bad |= v >> 31; all += v & 0x7fffffffu;
+        if (wv < wave) before += v & 0x7fffffffu;
+    }
+    if (status != 0) return;                          // sticky error: the call is a no-op
+    if (bad) { if (tid == 0) *a.status = -1; return; }
+    const unsigned long long start = (used + 255u) & ~255ull, end = start + ((unsigned long long)all << 8);
+    if (end > a.capacity) { if (tid == 0) *a.status = -3; return; }
+    if (own) a.chunk_off[(int64_t)u * a.off_stride + c] = start + ((unsigned long long)(before + incl - size) << 8);
+    if (tid == 0) *a.arena_used = end;                // nobody else reads it: one kernel fewer than plan_rows_kernel
 }
 
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PackArgs a) {
@@ -283,13 +317,11 @@ hipError_t launch_pack(const PackArgs &a, hipStream_t s) {
     if (a.n_chunks <= 0 || a.BH <= 0) return hipSuccess;
     const bool rows_ok = a.BH <= kPlanRowsMax &&
                          ((reinterpret_cast<uintptr_t>(a.expert + a.chunk_begin) | (uintptr_t)a.expert_stride) & 15u) == 0;
-    // Small tables (one pass of plan_kernel's threads): one workgroup plans them as fast as one per row would, and as nobody
-    // else reads the end of the arena it can move it itself: one kernel fewer
-    // (a pack call of up to 1024 chunks 23.5 -> 20.5 us although the plan itself takes 7.7 instead of 6.0; above that a thread has
-    // several entries and its sweeps show).
-    const bool rows = rows_ok && (int64_t)a.BH * a.n_chunks > kPlanThreads;
-    if (rows) hipLaunchKernelGGL(plan_rows_kernel, dim3((unsigned)a.BH), dim3(kPlanThreads), 0, s, a);
-    else      hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a);
+    const int64_t total = (int64_t)a.BH * a.n_chunks;
+    const bool small = total <= kPlanThreads, rows = rows_ok && !small;
+    if (small)     hipLaunchKernelGGL(plan_small_kernel, dim3(1), dim3((unsigned)((total + 63) / 64 * 64)), 0, s, a);
+    else if (rows) hipLaunchKernelGGL(plan_rows_kernel, dim3((unsigned)a.BH), dim3(kPlanThreads), 0, s, a);
+    else           hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     dim3 grid(2u, (unsigned)a.n_chunks, (unsigned)a.BH);
