@@ -65,7 +65,7 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     uint32_t wpos[REP == 1 ? 3 : 1][8][64];
     alignas(16) float vf[REP < 4 ? NWV : 1][512];                  // raw fp16 units: the value sums of the four row groups on their way to the lanes that own the dims
     uint4 kx[REP == 1 ? NWV : 1][4 * 72];                // per wavefront: the K codes of a unit on their way to the lanes that use them
-    alignas(16) float pcq[REP == 1 ? NWV : 1][4][kD];    // keys quantised per channel: q * scale of up to four token groups of a unit
+    alignas(16) uint32_t pcq[REP == 1 ? NWV : 1][4][kD]; // keys quantised per channel: q * scale of up to four token groups of a unit, two fp16 numbers each
     int iq[kD];
     int iqs16[8];
     float iqpart[3][8][2];
@@ -902,69 +902,149 @@ __device__ __forceinline__ void iq_scores(const Unit &u, const KRegs<G> &k, int 
     wave_sync();
 }
 
+// Sums (or maxima) of P = 1, 2 or 4 values per lane over the wavefront, each wave-uniform.  Four at once: every exchange across
+// half the lanes also halves the registers, 14 instructions against 40.
+template <int P, bool MAX>
+__device__ __forceinline__ void wave_fold(float (&v)[P]) {
+    if constexpr (P == 4) {
+        auto fold = [](float a, float b) { return MAX ? fmaxf(a, b) : a + b; };
+        float t[2];
+#pragma unroll
+        for (int i = 0; i < 2; i++) {                    // lanes 32.. take values 2 and 3
+            const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v[i]), __builtin_bit_cast(uint32_t, v[i + 2]), false, false);
+            t[i] = fold(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+        }
+        const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, t[0]), __builtin_bit_cast(uint32_t, t[1]), false, false);
+        float x = fold(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));   // row i of 16 lanes: value i
+        x = MAX ? group_max<16>(x) : group_sum<16>(x);
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16 * i));
+    } else {
+#pragma unroll
+        for (int i = 0; i < P; i++) v[i] = MAX ? wave_max(v[i]) : wave_sum(v[i]);
+    }
+}
+
+// The pairs of a code word for products whose sums keep 24 bits: a subnormal number enters the matrix core's sum with the smallest
+// normal exponent, so that of a code in the lowest bits of the mantissa little more than 12 bits of the product are left (sums of
+// 128: error 5.6e-6 of the result at bit 0, 6.9e-7 at bit 2, 8.6e-8 at bit 4, 2e-8 from bit 6 on; normal numbers 2e-8).  Every pair
+// is brought to the top of the mantissa: four instructions a word more than pair_reg at 2 bits, three at 4 bits, one at 8 bits.
+template <int BITS> __device__ __forceinline__ constexpr int high_pair_exp(int k) {
+    return BITS == 2 ? (k == 0 || k == 2 || k == 3 || k == 5 ? 6 : 8) : (BITS == 4 ? 6 : 2);
+}
+template <int BITS> __device__ __forceinline__ uint32_t high_pair(uint32_t w, int k) {
+    const int to = high_pair_exp<BITS>(k), from = BITS * k;
+    return (to >= from ? w << (to - from) : w >> (from - to)) & (BW<BITS>::MASK << to);
+}
+
 // Scores of a quantised unit whose keys are quantised per channel (a group = G consecutive tokens of one dim):
 //   q . k^_t = sum_d (q_d * scale_{g,d}) * code_{t,d} + sum_d q_d * zero_{g,d},   g = the token group of t,
 // so the scale folds into a copy of q per token group (built here from the unit's meta words and kept in LDS)
-// and the zero-points into one number per group.  The codes stay in the slots as loaded (lane l holds slot 64j + l
-// of KiB j = part l % SPR of a token's row); the dot products run on the vector ALU, one multiply-add per code,
-// and the SPR lanes of a token are summed by DPP.  Result as iq_scores: L.sc (log2 domain), running maximum updated.
+// and the zero-points into one number per group.  The code sums run on v_mfma_f32_16x16x32_f16, codes = the B operand (masked
+// words, see mc_scores; column = token of a 16-token tile), the copy of q = A: scaled by a power of two of its group and split
+// into two fp16 numbers, which hold the 22 bits that the product of two fp16 numbers has (down to 2^-28 of the group's largest),
+// in the rows 2i and 2i + 1: every lane gets both sums of its column and keeps those of the tile its own token lies in.
+// Result as iq_scores: L.sc (log2 domain), running maximum updated.
+// What bounds it: instruction issue and LDS.  A multiply-add per code on the vector ALU takes 64 16-byte reads of the copy of q
+// and 400 vector instructions for a 2-bit unit; this takes 4 writes and 8 half reads for the codes, 16 reads for q, and 280.
+// 40 heads of 64k tokens in groups of 32: 84.6 -> 77.5 us a call; the error against binary64 stays at 1.3e-6.
 template <int BITS, int G, int NWV>
 __device__ __forceinline__ void pc_scores(const Unit &u, const KRegs<G> &k, int lane, int wave, float scale_log2,
                                           AttnLds<G, 1, NWV> &L, WaveState<1> &st) {
-    constexpr int E = 128 / BITS, SPR = BITS, CPW = 32 / BITS;
-    constexpr int NGU = (256 / BITS) / G > 0 ? (256 / BITS) / G : 1;     // token groups a full unit spans
+    constexpr int TL = 16 / BITS, NP = (TL + 3) / 4;      // 16-token tiles of a full unit, passes of four tiles
+    constexpr int NGU = (256 / BITS) / G > 0 ? (256 / BITS) / G : 1;     // token groups a full unit spans: it starts at a group, or lies in one
+    const int x = lane & 15, q = lane >> 4;
+    // the codes of tile f: lane (x, q) takes 32 (8 bits: twice 16) dims of token 16f + x
+    uint4 kc[4];
+    uint2 kc2[TL];
+    if constexpr (BITS == 2) {
+        uint4 *buf = &L.kx[wave][0];
+#pragma unroll
+        for (int j = 0; j < 4; j++) buf[64 * j + lane] = k.c[j];
+        wave_sync();
+#pragma unroll
+        for (int f = 0; f < TL; f++) kc2[f] = reinterpret_cast<const uint2 *>(buf)[64 * f + 4 * x + q];
+        wave_sync();
+    } else {
+        iq_regroup<BITS, G, NWV>(k, lane, wave, L, kc);
+    }
     const uint32_t qq = L.qraw[lane];
     const float q0 = half_bits_to_float(qq & 0xffffu), q1 = half_bits_to_float(qq >> 16);
-    float bias[NGU];
-    // Masking a code word leaves two codes in the mantissa fields of an fp16 pair (subnormals code * 2^kp * 2^-24), whose
-    // halves a mixed-precision multiply-add takes as they are; 2^-kp rides in the copy of q (dims 2l, 2l + 1 are one pair of
-    // their word), 2^24 comes at the end.  25 vector instructions per word of 2-bit codes where extract, convert and
-    // multiply-add took 48: 85 us against 98.5 for 40 heads of 64k tokens in groups of 32
-    const float unshift = __builtin_bit_cast(float, (uint32_t)(127 - pair_exp<BITS>(lane % (CPW / 2))) << 23);
+    // dims 2l, 2l + 1 are one pair of their word: the power of two of its place rides in the copy of q
+    const float unshift = __builtin_bit_cast(float, (uint32_t)(127 - high_pair_exp<BITS>(lane % (16 / BITS))) << 23);
+    float v0[NGU], v1[NGU], big[NGU], bias[NGU], down[NGU];
 #pragma unroll
     for (int j = 0; j < NGU; j++) {
         const uint32_t m0 = k.m[j][0], m1 = k.m[j][1];
-        float2 qs;
-        qs.x = q0 * unshift * half_bits_to_float(m0 & 0xffffu); qs.y = q1 * unshift * half_bits_to_float(m1 & 0xffffu);
-        *reinterpret_cast<float2 *>(&L.pcq[wave][j][2 * lane]) = qs;
-        float bz = fmaf(q0, half_bits_to_float(m0 >> 16), q1 * half_bits_to_float(m1 >> 16));
+        v0[j] = q0 * unshift * half_bits_to_float(m0 & 0xffffu); v1[j] = q1 * unshift * half_bits_to_float(m1 & 0xffffu);
+        big[j] = fmaxf(fabsf(v0[j]), fabsf(v1[j]));
+        bias[j] = fmaf(q0, half_bits_to_float(m0 >> 16), q1 * half_bits_to_float(m1 >> 16));
+    }
+    wave_fold<NGU, true>(big);
+    wave_fold<NGU, false>(bias);
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) bz += __shfl_xor(bz, o);
-        bias[j] = bz;
+    for (int j = 0; j < NGU; j++) {
+        // 2^ef <= the largest < 2^(ef+1): times 2^(14 - ef) it is below 2^15
+        const int ef = min(max((int)((__builtin_bit_cast(uint32_t, big[j]) >> 23) & 255u) - 127, -100), 100);
+        const float up = __builtin_bit_cast(float, (uint32_t)(127 + 14 - ef) << 23);
+        down[j] = __builtin_bit_cast(float, (uint32_t)(127 + 24 - 14 + ef) << 23);       // the codes carry 2^-24
+        const float a0 = v0[j] * up, a1 = v1[j] * up;
+        const uint32_t h0 = float_to_half_bits(a0), h1 = float_to_half_bits(a1);
+        const uint32_t l0 = float_to_half_bits((a0 - half_bits_to_float(h0)) * 2048.0f), l1 = float_to_half_bits((a1 - half_bits_to_float(h1)) * 2048.0f);
+        L.pcq[wave][j][lane] = h0 | (h1 << 16);
+        L.pcq[wave][j][64 + (lane ^ 4)] = l0 | (l1 << 16);   // 16-byte pieces swapped in pairs: a read of A touches every bank once
     }
     wave_sync();
-    const int part = lane % SPR;
-    const int goff = (int)(u.kc >> (4 + u.lgb)) % G;      // tokens of the unit's first token group that lie before the unit
-    float s4[4], lmax = -INFINITY;
+    float own0[NP], own1[NP];
+    v4u A[4];
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int tk = (64 * j + lane) / SPR;             // token of the slot, counted inside the unit
-        const int gj = NGU > 1 ? (goff + tk) / G : 0;
-        const float *qp = &L.pcq[wave][gj][E * part];
-        float dots[2] = {0.0f, 0.0f};                     // two chains
+    for (int f = 0; f < TL; f++) {
+        if (NGU > 1 ? f % (G / 16) == 0 : f == 0) {       // the next token group
+            const uint32_t *base = &L.pcq[wave][NGU > 1 ? f / (G / 16) : 0][(lane & 1) * 64];
 #pragma unroll
-        for (int wd = 0; wd < 4; wd++) {
-            const uint32_t w = word_of(k.c[j], wd);
-#pragma unroll
-            for (int e4 = 0; e4 < CPW / 4; e4++) {
-                const float4 qv = *reinterpret_cast<const float4 *>(qp + wd * CPW + 4 * e4);
-                const half2_t p0 = as_half2(pair_reg<BITS>(w, 2 * e4)), p1 = as_half2(pair_reg<BITS>(w, 2 * e4 + 1));
-                dots[0] = fmaf((float)p0.x, qv.x, dots[0]); dots[1] = fmaf((float)p0.y, qv.y, dots[1]);
-                dots[0] = fmaf((float)p1.x, qv.z, dots[0]); dots[1] = fmaf((float)p1.y, qv.w, dots[1]);
+            for (int mi = 0; mi < 4; mi++) {
+                const int piece = BITS == 8 ? 8 * (mi >> 1) + 2 * q + (mi & 1) : 4 * q + mi;
+                A[mi] = *reinterpret_cast<const v4u *>(base + ((piece ^ (lane & 1)) * 4));
             }
         }
-        const float dot = group_sum<SPR>(dots[0] + dots[1]);
-        float bz = bias[0];
+        v4f c = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int g = 1; g < NGU; g++) bz = (gj == g) ? bias[g] : bz;
-        s4[j] = (j < u.nsub) ? fmaf(dot, kTwo24, bz) * scale_log2 : -INFINITY;      // KiB past a short unit: ignored
-        lmax = fmaxf(lmax, s4[j]);
+        for (int mi = 0; mi < 4; mi++) {
+            v4u b;
+            if constexpr (BITS == 2) {
+                const uint32_t w = (mi >> 1) ? kc2[f].y : kc2[f].x;
+#pragma unroll
+                for (int pr = 0; pr < 4; pr++) b[pr] = high_pair<2>(w, 4 * (mi & 1) + pr);
+            } else if constexpr (BITS == 4) {
+                const uint32_t w = word_of(kc[f], mi);
+#pragma unroll
+                for (int pr = 0; pr < 4; pr++) b[pr] = high_pair<4>(w, pr);
+            } else {
+                const uint4 &w = kc[2 * f + (mi >> 1)];
+                const uint32_t w0 = (mi & 1) ? w.z : w.x, w1 = (mi & 1) ? w.w : w.y;
+                b[0] = high_pair<8>(w0, 0); b[1] = high_pair<8>(w0, 1); b[2] = high_pair<8>(w1, 0); b[3] = high_pair<8>(w1, 1);
+            }
+            c = mfma16(A[mi], b, c);
+        }
+        own0[f / 4] = f % 4 == 0 || q == f % 4 ? c[0] : own0[f / 4];
+        own1[f / 4] = f % 4 == 0 || q == f % 4 ? c[1] : own1[f / 4];
+    }
+    float s4[NP], lmax = -INFINITY;
+    const int n_tok = u.nsub * (64 / BITS);
+#pragma unroll
+    for (int s = 0; s < NP; s++) {
+        const int t = 64 * s + lane;
+        float bz = bias[0], dn = down[0];
+#pragma unroll
+        for (int g = 1; g < NGU; g++) { bz = t >= g * G ? bias[g] : bz; dn = t >= g * G ? down[g] : dn; }
+        const float dot = fmaf(own1[s], 1.0f / 2048.0f, own0[s]);
+        s4[s] = t < n_tok && t < 16 * TL ? fmaf(dot, dn, bz) * scale_log2 : -INFINITY;       // past a short unit: ignored
+        lmax = fmaxf(lmax, s4[s]);
     }
     rescale<G, 1>(st, 0, wave_max(lmax), lane);
-    if (part == 0) {
 #pragma unroll
-        for (int j = 0; j < 4; j++) L.sc[wave][0][(64 * j + lane) / SPR] = s4[j];
-    }
+    for (int s = 0; s < NP; s++)
+        if (TL >= 4 || lane < 16 * TL) L.sc[wave][0][64 * s + lane] = s4[s];
     wave_sync();
 }
 

@@ -53,3 +53,21 @@ def test_long_rows(mq, ref, H, N, G, C, tail, mix):
     expert = rng.choice(4, size=(H, C), p=mix).astype(np.uint8)
     err = T._attn_case(mq, ref, 1, H, H, N, G, C, tail, (2, 4, 8, 16), N + C, expert=expert)
     assert err <= 2.5e-6, err
+
+
+@pytest.mark.parametrize("H,N,G,C,tail,mix", [
+    (2, 128, 32, 300, 77, (0.6, 0.3, 0.05, 0.05)),
+    (2, 256, 64, 130, 3, (0.6, 0.3, 0.05, 0.05)),
+    (2, 64, 32, 500, 0, (1, 0, 0, 0)),                # units that end early
+    (2, 192, 64, 180, 0, (0, 1, 0, 0)),
+    (2, 64, 64, 520, 50, (0, 0, 1, 0)),
+    (2, 32, 32, 1000, 9, (0.6, 0.3, 0.05, 0.05)),     # units of several chunks
+])
+def test_long_rows_per_channel(mq, ref, H, N, G, C, tail, mix):
+    """Keys quantised per channel.  q * scale of a token group is held to 2^-22 (two fp16 numbers), its products with the codes are
+    summed with 24 bits: a few 1e-7 of a score's absolute sum, as binary32 multiply-adds would err; the rest as above.  One fp16
+    number for q * scale, or codes in the lowest bits of their mantissas, give 5e-5 and more."""
+    rng = np.random.default_rng(C + G)
+    expert = rng.choice(4, size=(H, C), p=mix).astype(np.uint8)
+    err = T._attn_case(mq, ref, 1, H, H, N, G, C, tail, (2, 4, 8, 16), N + C, expert=expert, kpc=1)
+    assert err <= 5e-6, err
