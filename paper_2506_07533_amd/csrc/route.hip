@@ -4,12 +4,14 @@
 // route_kernel: persistent wavefronts over windows of 64 tokens: a part of a chunk, or (chunks of 8, 16 and 32 tokens) 64/N
 // consecutive chunks of a row, whose votes are their lanes' bits of the ballots.  The decision is defined by sequential
 // binary32 sums over the dims; it is taken from the same sums on the matrix cores where these tell it with certainty
-// (certain_top), and from the sums in order, for the whole window, where they do not.  The rows come in whole lines, half a window
+// (certain_top), and from the sums in order, for the tokens they leave open, where they do not.  The rows come in whole lines, half a window
 // ahead, and reach the lanes of the matrix products through LDS.
-// What bounds it: HBM.  5.2 M rows in 128-token chunks 211 us a call (6.35 TB/s) against 241 with a lane per token and the sums
-// in order (whose 1024 multiply-adds alone took 170); 2.1 M rows in 256-token chunks 86 against 106, in 32-token chunks 91 against
-// 103.  Two workgroups of four wavefronts per compute unit: three and four (128 registers) 213 and 220 us; a whole window
-// ahead 211; rows requested in the operands' own shape, four 16-byte pieces of a row per load, 228.
+// What bounds it: HBM, and for small calls latency.  5.2 M rows in 128-token chunks 211 us a call (6.35 TB/s) against 241 with a
+// lane per token and the sums in order (whose 1024 multiply-adds alone took 170); 524 288 rows 23.5 us against 30, 131 072 rows 9.4 to
+// 11.9 against 10.0 to 12.6, 32 768 rows in 32-token chunks 6.7 against 7.5 (9.4 while open tokens sent their whole window through
+// the sums in order).  Two workgroups of four wavefronts per compute unit: three and four (128 registers) 213 and 220 us; a whole
+// window ahead 211, and 25.3 and 10.8 us for 524 288 and 131 072 rows; rows requested in the operands' own shape, four 16-byte
+// pieces of a row per load, 228.
 // The windows begin after a row's frozen chunks, whose keys are not read.
 //
 // route_split_kernel: few chunks.
@@ -62,20 +64,23 @@ __device__ __forceinline__ void half_sums(const RouterWeights &w, const uint4 *b
 }
 template <int M>
 __device__ __forceinline__ int window_top(v4f_r (&val)[M <= 4 ? 2 : 4], v4f_r (&bnd)[M <= 4 ? 2 : 4], const uint16_t *Kc, int64_t stride_s, int n_tok,
-                                          int lane, const RouteArgs &a, const float *w3f) {
+                                          int lane, const RouteArgs &a, const uint32_t *raw, const float *w3f) {
     RouterSums<M> v, s;
     gather_sums<M>(val, v); gather_sums<M>(bnd, s);
+    RouterValues<M> o;
     int top;
-    const bool sure = certain_top<M>(v, s, w3f, a.bias != nullptr, top);
-    if (__ballot(!sure && lane < n_tok) != 0ull)
-        top = ordered_top<M>(Kc + (int64_t)min(lane, n_tok - 1) * stride_s, reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W1)),
-                             reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W2)), w3f, a.bias != nullptr);
+    const bool sure = certain_top<M>(v, s, w3f, a.bias != nullptr, o, top);
+    settle_in_order<M, 16>(__ballot(!sure && lane < n_tok), [&](int t, int p) { return reinterpret_cast<const uint4 *>(Kc + (int64_t)t * stride_s)[p]; },
+                       n_tok, raw, a.W1, a.W2, w3f, a.bias != nullptr, lane, top);
     return top;
 }
 
 // Persistent wavefronts over windows of up to 64 tokens: 64/N consecutive chunks of a row (SHORT), or a part of a chunk, whose
 // wavefront takes all its parts one after the other.
-template <int M, bool SHORT>
+// DIRECT: up to two experts and a window per wavefront: sums in order, a lane per token, from the rows as they lie.  Their 512
+// multiply-adds are done before the operands of the matrix products would be (131 072 rows in 32-token chunks 7.5 us against
+// 8.6); with four experts it is the other way round (10.0 against 9.4).
+template <int M, bool SHORT, bool DIRECT>
 __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(RouteArgs a) {
     __shared__ float w3f[kW3Words];
     __shared__ uint32_t raw[kD * M];
@@ -100,12 +105,12 @@ __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(
              + ((int64_t)(c_begin + st * cpw) * N + 64 * sh) * a.stride_s;
     };
     HalfRows hr;
-    if (u < a.BH) request_half(window(u, t, 0), a.stride_s, tokens_of(t, 0), 0, lane, hr);
-    stage_router_weights<M>(a.W1, a.W2, raw, tid, kRouteWaves * 64);
+    if (!DIRECT && u < a.BH) request_half(window(u, t, 0), a.stride_s, tokens_of(t, 0), 0, lane, hr);
+    if constexpr (!DIRECT) stage_router_weights<M>(a.W1, a.W2, raw, tid, kRouteWaves * 64);
     stage_w3<M>(a.W3, a.bias, w3f, tid);
     __syncthreads();
     RouterWeights w;
-    load_router_weights<M>(raw, lane, w);
+    if constexpr (!DIRECT) load_router_weights<M>(raw, lane, w);
     int cnt[M];
 #pragma unroll 1
     while (u < a.BH) {
@@ -114,18 +119,24 @@ __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(
             h = 0; t += step_t; u += step_u;
             if (t >= per_row) { t -= per_row; u++; }
         }
-        v4f_r val[M <= 4 ? 2 : 4], bnd[M <= 4 ? 2 : 4];
-        stage_half(hr, lane, buf);
-        request_half(window(cu, ct, ch), a.stride_s, n_tok, 1, lane, hr);
-        wave_lds_sync();
-        half_sums<M>(w, buf, 0, lane, val, bnd);
-        wave_lds_sync();
-        stage_half(hr, lane, buf);
-        if (u < a.BH) request_half(window(u, t, h), a.stride_s, tokens_of(t, h), 0, lane, hr);
-        wave_lds_sync();
-        half_sums<M>(w, buf, 1, lane, val, bnd);
-        wave_lds_sync();
-        const int top = window_top<M>(val, bnd, window(cu, ct, ch), a.stride_s, n_tok, lane, a, w3f);
+        int top;
+        if constexpr (DIRECT) {
+            const uint4 *row = reinterpret_cast<const uint4 *>(window(cu, ct, ch) + (int64_t)min(lane, n_tok - 1) * a.stride_s);
+            top = ordered_top<M>([&](int p) { return row[p]; }, a.W1, a.W2, w3f, a.bias != nullptr);
+        } else {
+            v4f_r val[M <= 4 ? 2 : 4], bnd[M <= 4 ? 2 : 4];
+            stage_half(hr, lane, buf);
+            request_half(window(cu, ct, ch), a.stride_s, n_tok, 1, lane, hr);
+            wave_lds_sync();
+            half_sums<M>(w, buf, 0, lane, val, bnd);
+            wave_lds_sync();
+            stage_half(hr, lane, buf);
+            if (u < a.BH) request_half(window(u, t, h), a.stride_s, tokens_of(t, h), 0, lane, hr);
+            wave_lds_sync();
+            half_sums<M>(w, buf, 1, lane, val, bnd);
+            wave_lds_sync();
+            top = window_top<M>(val, bnd, window(cu, ct, ch), a.stride_s, n_tok, lane, a, raw, w3f);
+        }
         if (ch == 0) {
 #pragma unroll
             for (int k = 0; k < M; k++) cnt[k] = 0;
@@ -212,8 +223,16 @@ static hipError_t launch_m(const RouteArgs &a, int n_cu, hipStream_t s) {
         if (n_wg < n_cu) n_wg = items < n_cu ? items : n_cu;
         if (n_wg < 1) n_wg = std::min(a.BH, n_cu);   // frozen chunks only: a row per wavefront
         if (n_wg > (long long)kRouteWgPerCu * n_cu) n_wg = (long long)kRouteWgPerCu * n_cu;
-        if (a.N < 64) hipLaunchKernelGGL((route_kernel<M, true>), dim3((unsigned)n_wg), dim3(kRouteWaves * 64), 0, s, a);
-        else          hipLaunchKernelGGL((route_kernel<M, false>), dim3((unsigned)n_wg), dim3(kRouteWaves * 64), 0, s, a);
+        const dim3 grid((unsigned)n_wg), block(kRouteWaves * 64);
+        if constexpr (M <= 2) {
+            if (items * ((a.N + 63) / 64) <= (long long)kRouteWgPerCu * kRouteWaves * n_cu) {
+                if (a.N < 64) hipLaunchKernelGGL((route_kernel<M, true, true>), grid, block, 0, s, a);
+                else          hipLaunchKernelGGL((route_kernel<M, false, true>), grid, block, 0, s, a);
+                return hipGetLastError();
+            }
+        }
+        if (a.N < 64) hipLaunchKernelGGL((route_kernel<M, true, false>), grid, block, 0, s, a);
+        else          hipLaunchKernelGGL((route_kernel<M, false, false>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }

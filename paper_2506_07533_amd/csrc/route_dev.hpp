@@ -165,7 +165,7 @@ __device__ __forceinline__ void route_tokens(const uint16_t *Kc, int n_tok, int6
 // cancelling ones and wide ranges among them, its error was never above a tenth of that).  So the two
 // differ by at most sum_d ((128 - d) + 32 (4 - d / 32)) 2^-24 |x_d w_d|, which comes from a second product, |x| times the weights
 // scaled so (rounded up), and is carried through SiLU and W3.  A token whose two best logits are closer than that (ties, else about one in a
-// thousand) sends its wavefront through the sums in order.  The result is the same, bit for bit, always.
+// thousand) is settled by the sums in order.  The result is the same, bit for bit, always.
 typedef float v4f_r __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_r __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h_r __attribute__((ext_vector_type(8)));
@@ -267,47 +267,59 @@ __device__ __forceinline__ void gather_sums(v4f_r (&c)[M <= 4 ? 2 : 4], RouterSu
     }
 }
 
-// The token's expert from the sums and their bounds; false if they do not tell it from the expert by the sums in order.
+// What the sums of a token lead to: SiLU of their products and its sigmoid, the logits.
+template <int M> struct RouterValues { float z[M], sg[M], hid[M], logit[M]; };
 template <int M>
-__device__ __forceinline__ bool certain_top(const RouterSums<M> &v, const RouterSums<M> &s, const float *w3f, bool has_bias, int &top) {
-    float hid[M], err = 0.0f, any = 0.0f;
+__device__ __forceinline__ void router_values(const RouterSums<M> &v, const float *w3f, bool has_bias, RouterValues<M> &o) {
 #pragma unroll
     for (int m = 0; m < M; m++) {
-        const float z = v.A[m] * v.B[m];
+        o.z[m] = v.A[m] * v.B[m];
+        o.sg[m] = __builtin_amdgcn_rcpf(1.0f + fast_exp2(fminf(-o.z[m], 80.0f) * 1.44269504f));
+        o.hid[m] = o.z[m] * o.sg[m];
+    }
+#pragma unroll
+    for (int k = 0; k < M; k++) {
+        o.logit[k] = has_bias ? w3f[64 + k] : 0.0f;
+#pragma unroll
+        for (int j = 0; j < M; j++) o.logit[k] = fmaf(o.hid[j], w3f[j * M + k], o.logit[k]);
+    }
+}
+
+// The token's expert from the sums and their bounds; false if they do not tell it from the expert by the sums in order.
+template <int M>
+__device__ __forceinline__ bool certain_top(const RouterSums<M> &v, const RouterSums<M> &s, const float *w3f, bool has_bias,
+                                            RouterValues<M> &o, int &top) {
+    float err = 0.0f, any = 0.0f;
+    router_values<M>(v, w3f, has_bias, o);
+#pragma unroll
+    for (int m = 0; m < M; m++) {
         const float ea = kSumErr * s.A[m], eb = kSumErr * s.B[m];
         any += ea + eb;
         // |z - z'| of the two products, times the slope of SiLU: the slope at z and what the second derivative, at most
         // s (1 - s) (2 + |z|), adds within 1/4; 1.1 anywhere
         const float ez = fmaf(fabsf(v.A[m]), eb, fmaf(fabsf(v.B[m]), ea, ea * eb));
-        const float sg = __builtin_amdgcn_rcpf(1.0f + fast_exp2(fminf(-z, 80.0f) * 1.44269504f));
-        hid[m] = z * sg;
-        const float near = fmaf(ez * 1.45f * fmaf(-sg, sg, sg), 2.0f + fabsf(z), fabsf(fmaf(hid[m], 1.0f - sg, sg)));
+        const float sg = o.sg[m];
+        const float near = fmaf(ez * 1.45f * fmaf(-sg, sg, sg), 2.0f + fabsf(o.z[m]), fabsf(fmaf(o.hid[m], 1.0f - sg, sg)));
         const float slope = ez <= 0.25f ? near : 1.1f;
         // exponential, division and W3's sums on either side: (|z| + 8) 2^-21 and 2^-19 of the hidden value
-        err = fmaf(fmaf(fmaf(fabsf(z), 0x1p-21f, 0x1p-18f + 0x1p-19f), fabsf(hid[m]), ez * slope), w3f[kW3Max + m], err);
+        err = fmaf(fmaf(fmaf(fabsf(o.z[m]), 0x1p-21f, 0x1p-18f + 0x1p-19f), fabsf(o.hid[m]), ez * slope), w3f[kW3Max + m], err);
     }
-    float best = 0.0f, second = -INFINITY;
+    float best = o.logit[0], second = -INFINITY;
     top = 0;
 #pragma unroll
-    for (int k = 0; k < M; k++) {
-        float acc = has_bias ? w3f[64 + k] : 0.0f;
-#pragma unroll
-        for (int j = 0; j < M; j++) acc = fmaf(hid[j], w3f[j * M + k], acc);
-        if (k == 0) best = acc;
-        else {
-            const bool more = acc > best;
-            second = fmaxf(second, more ? best : acc);
-            top = more ? k : top; best = more ? acc : best;
-        }
+    for (int k = 1; k < M; k++) {
+        const bool more = o.logit[k] > best;
+        second = fmaxf(second, more ? best : o.logit[k]);
+        top = more ? k : top; best = more ? o.logit[k] : best;
     }
     if (has_bias) err = fmaf(w3f[kBiasMax], 0x1p-19f, err);
     // all sums zero (rows of zeros): both sides have the same logits.  NaN: not certain
     return M == 1 || best - second > 2.1f * err || any == 0.0f;
 }
 
-// A token's expert by the sums in order, from its key row in memory (for the wavefronts certain_top could not settle).
-template <int M, typename WP>
-__device__ __forceinline__ int ordered_top(const uint16_t *row, WP W1w, WP W2w, const float *w3f, bool has_bias) {
+// A token per lane by the sums in order; piece(p): the 16-byte piece p of the lane's row.
+template <int M, typename F>
+__device__ __forceinline__ int ordered_top(F piece, const uint16_t *W1, const uint16_t *W2, const float *w3f, bool has_bias) {
     float accA[M], accB[M];
 #pragma unroll
     for (int m = 0; m < M; m++) { accA[m] = 0.0f; accB[m] = 0.0f; }
@@ -315,10 +327,61 @@ __device__ __forceinline__ int ordered_top(const uint16_t *row, WP W1w, WP W2w, 
     for (int h = 0; h < 2; h++) {
         uint4 x[8];
 #pragma unroll
-        for (int p = 0; p < 8; p++) x[p] = reinterpret_cast<const uint4 *>(row)[8 * h + p];
-        route_half_row<M>(x, 64 * h, W1w, W2w, accA, accB);
+        for (int p = 0; p < 8; p++) x[p] = piece(8 * h + p);
+        route_half_row<M>(x, 64 * h, reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(W1)),
+                          reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(W2)), accA, accB);
     }
     return route_top<M>(accA, accB, w3f, has_bias);
+}
+
+// The tokens of `open` (one bit per token of a window of 64, those certain_top could not settle) by the sums in order; `top`:
+// the lane's own token's expert.  A lane adds up ONE of a token's 2 M sums, so that eight tokens (more than four experts: four)
+// are settled at once in 128 dependent multiply-adds: with a token per lane all 64 wait for 1024, 5 us on an idle chip.
+// piece(t, p): the 16-byte piece p of token t's row, AHEAD of them requested at once; raw: the weights in LDS (stage_router_weights).
+// Windows with many of them (a router whose experts tie) take a token per lane all the same.
+template <int M, int AHEAD, typename F>
+__device__ __forceinline__ void settle_in_order(unsigned long long open, F piece, int n_tok, const uint32_t *raw, const uint16_t *W1,
+                                                const uint16_t *W2, const float *w3f, bool has_bias, int lane, int &top) {
+    if (open == 0ull) return;
+    if (__popcll(open) > 24) {
+        top = ordered_top<M>([&](int p) { return piece(min(lane, n_tok - 1), p); }, W1, W2, w3f, has_bias);
+        return;
+    }
+    constexpr int H = M <= 4 ? 4 : 8, TPL = 2 * H, NT = 64 / TPL;
+    const int k = lane % TPL, slot = lane / TPL;
+    const uint16_t *w = reinterpret_cast<const uint16_t *>(raw) + (k < H ? 0 : kD * M) + min(k & (H - 1), M - 1);
+    while (open != 0ull) {                               // the same for all lanes
+        int tok = 0, src = -1;                            // the token this lane works on; the lane that will hold its own token's expert
+#pragma unroll
+        for (int s = 0; s < NT; s++) {
+            if (open != 0ull) {
+                const int t = __ffsll((long long)open) - 1;
+                open &= open - 1ull;
+                tok = slot >= s ? t : tok;                // slots without a token repeat the last one
+                src = lane == t ? s * TPL : src;
+            }
+        }
+        float acc = 0.0f;
+#pragma unroll 1
+        for (int p0 = 0; p0 < 16; p0 += AHEAD) {
+            uint4 x[AHEAD];
+#pragma unroll
+            for (int p = 0; p < AHEAD; p++) x[p] = piece(tok, p0 + p);
+#pragma unroll
+            for (int p = 0; p < AHEAD; p++) {
+                const uint32_t xw[4] = {x[p].x, x[p].y, x[p].z, x[p].w};
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    acc = fmaf(half_bits_to_float((xw[e >> 1] >> (16 * (e & 1))) & 0xffffu), half_bits_to_float(w[(8 * (p0 + p) + e) * M]), acc);
+                if (p & 1) __builtin_amdgcn_sched_barrier(0);    // keeps the weights of later pieces out of the registers
+            }
+        }
+        float A[M], B[M];
+#pragma unroll
+        for (int m = 0; m < M; m++) { A[m] = __shfl(acc, slot * TPL + m); B[m] = __shfl(acc, slot * TPL + H + m); }
+        const int found = __shfl(route_top<M>(A, B, w3f, has_bias), max(src, 0));
+        top = src >= 0 ? found : top;
+    }
 }
 
 }  // namespace moqae

@@ -142,6 +142,34 @@ def test_route_close_decisions(mq, ref, kind, M, N, C):
     assert np.array_equal(expert.cpu().numpy(), e_ref)
 
 
+def _twin_router(rng, M, share, K):
+    """Experts 0 and 1 alike but for dim 127 and ahead of the others; that dim is zero in `share` of the tokens, which tie."""
+    W1, W2 = ((rng.standard_normal((128, M)) * 0.1).astype(np.float16) for _ in range(2))
+    W1[:127, 1] = W1[:127, 0]; W2[:127, 1] = W2[:127, 0]
+    W3 = (rng.standard_normal((M, M)) * 0.02).astype(np.float16)
+    W3[:, :2] = 0; W3[0, 0] = W3[1, 1] = 2
+    bias = np.zeros(M, np.float32); bias[:2] = 4
+    K[..., 127][rng.random(K.shape[:3]) < share] = 0
+    return W1, W2, W3, bias
+
+
+@pytest.mark.parametrize("M,N,C", [(2, 64, 80), (4, 128, 70), (4, 8, 700), (5, 64, 90), (8, 32, 200)])
+@pytest.mark.parametrize("share", [0.02, 0.2, 0.6])
+def test_route_some_tokens_tie(mq, ref, share, M, N, C):
+    """None to most tokens of a window of 64 tie: settled four or eight at a time, in one pass or several, or a token per lane."""
+    B, Hkv = 2, 8
+    rng = np.random.default_rng(M * N + int(100 * share))
+    cfg, rcfg = _cfgs(mq, ref, B, Hkv, Hkv, N, 64, ([16, 2, 4, 8, 2, 4, 8, 16])[:M], 0)
+    K, _ = _rand_kv(rng, B, Hkv, C * N)
+    W1, W2, W3, bias = _twin_router(rng, M, share, K)
+    e_ref, v_ref = ref.route_chunks(rcfg, K, 0, C, W1, W2, W3, bias)
+    expert = torch.full((B * Hkv, C), 255, dtype=torch.uint8, device="cuda")
+    votes = torch.full((B * Hkv, C, M), -1, dtype=torch.int32, device="cuda")
+    mq.route_chunks(cfg, _dev(K), 0, C, _dev(W1), _dev(W2), _dev(W3), _dev(bias), expert, votes)
+    torch.cuda.synchronize()
+    assert np.array_equal(votes.cpu().numpy(), v_ref) and np.array_equal(expert.cpu().numpy(), e_ref)
+
+
 # ----------------------------------------------------------------------------------------------
 # quantise + pack
 # ----------------------------------------------------------------------------------------------
