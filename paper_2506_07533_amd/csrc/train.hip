@@ -2,15 +2,18 @@
 // the router weights, over cached key rows, in one pass.
 //
 //   L = (1/T) sum_i p^i_j * (lambda * L_nll * pen_model_j + (1 - lambda) * pen_mem_j),  j = the token's top-1 expert,
-//   p^i = softmax of the token's logits.  The top-1 index comes from the same binary32 arithmetic as routing
-//   (route_kernel), so it is the routing decision bit for bit; everything after it is plain binary32.
+//   p^i = softmax of the token's logits.  The top-1 index is the routing decision (route_kernel) bit for bit; everything
+//   after it is plain binary32.
 //
 // One wavefront per tile of 64 tokens, eight wavefronts per workgroup, one workgroup per compute unit; a wavefront keeps
 // its gradient accumulators over all its tiles.
 //   rows      requested in whole rows, a tile ahead, and staged in LDS (pieces XOR-swizzled: reads by row and by piece both
 //             touch every bank), from where the forward pass takes a row per lane and the weight gradient a piece per lane.
-//   forward   one lane per token, route_half_row / the operations of route_top in their order, then the token's loss and
-//             its gradient down to d(loss)/d(xW1), d(loss)/d(xW2) (2M values per token, handed over through LDS).
+//   forward   up to five experts: xW1, xW2 and the bound on their distance from the sums in order on the matrix cores (see
+//             certain_top), a lane per token afterwards; the tokens whose top-1 index they leave open take it from the sums in
+//             order.  More experts: one lane per token, route_half_row (the operands and the eight tiles of results would not
+//             fit the registers beside the rest: 7 experts 189 us against 134).  Then the token's loss and its gradient down to
+//             d(loss)/d(xW1), d(loss)/d(xW2) (2M values per token, handed over through LDS).
 //   dW1, dW2  = x^T [128 x 64 tokens] times those values [64 tokens x 2M] on v_mfma_f32_16x16x32_f16: x is fp16 as it is; a
 //             value is scaled by a power of two of its own column (expert and matrix) and tile and split into two fp16 numbers,
 //             the second holding what the first leaves: 22 bits and more of every value that is not 2^28 times smaller than
@@ -26,10 +29,10 @@
 //             address and workgroup.  Device-wide atomic steps on one address run at about nine per microsecond here: one
 //             wavefront at a time, each with its own atomic adds (4096 per address), took 0.8 ms of the 0.89 ms that the
 //             gradient over 1.05 M rows needed.
-// 1.05 M rows: 4 experts 80 us against 888 (router_train_8k of perf/: 77 against 892), 8 experts 184 against 1742, 2 experts 58
-// against 264; 64 rows 18 against 20.  The rows alone are 38 us at the read ceiling of the chip; what is left is the forward
-// pass (1024 multiply-adds in their order).  With 7 and 8 experts the 256 registers that eight wavefronts leave are not
-// enough: 116 and 164 bytes of scratch a lane, and more than twice the time of 4 experts.
+// 1.05 M rows: 2 / 4 / 5 / 8 experts 53 / 59 / 68 / 184 us (56 / 76 / 94 / 183 with the forward pass in order for all), 0.26 M rows,
+// 4 experts: 30.5 (35.6), 64 rows: 12.8 (15.8).  The rows alone are 38 us at the read ceiling of the chip; what is left are the
+// 110 KiB of LDS traffic of a tile and the arithmetic per token, at two wavefronts per SIMD.  Error against binary64 as before or
+// below (1e-7 to 4e-7 of an array).  With 7 and 8 experts the 256 registers that eight wavefronts leave are not enough.
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
 #include "pack_dev.hpp"
@@ -83,16 +86,16 @@ __device__ __forceinline__ uint32_t column_max(uint32_t (&v)[P], int lane) {
 template <int M>
 __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArgs a) {
     constexpr int NS = M * M + M + 2;                 // sums that every lane keeps: dW3, bias, the two losses
-    __shared__ float w3f[72];
+    __shared__ float w3f[kW3Words];
     __shared__ float sums[kTrainWaves][NS];
     __shared__ uint4 stage[kTrainWaves][64 * 16];     // key rows: piece p of row r at 16r + (p ^ (r % 16)); the fold's dW at the end
     constexpr int NB = M <= 4 ? 1 : 2;                // B operands: columns 0..7 first halves, 8..15 second ones, or one each
+    constexpr bool kMatrix = M <= 5;                  // the forward pass on the matrix cores
+    __shared__ v4u_r wop[kMatrix ? 2 : 1][4][64];     // its operand A and that of its bound (registers are short)
+    __shared__ uint32_t raw[kMatrix ? kD * M : 1];    // the weights for the tokens that it leaves open
     __shared__ __attribute__((aligned(16))) uint16_t dabs[kTrainWaves][2 * kTrainH];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // wave-uniform, kept scalar
-    if (tid < M * M) w3f[tid] = half_bits_to_float(a.W3[tid]);
-    if (tid < M) w3f[64 + tid] = a.bias ? a.bias[tid] : 0.0f;
-    __syncthreads();
     const const_words W1w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W1));
     const const_words W2w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W2));
     uint4 *mine = &stage[wave][0];
@@ -129,7 +132,20 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
 #pragma unroll
         for (int j = 0; j < 16; j++) v[j] = nt_load(reinterpret_cast<const uint4 *>(Kt + (int64_t)min(4 * j + r4, last) * a.stride_s) + piece);
     };
-    if (u < a.BH) request(u, tr);
+    if (kMatrix && u < a.BH) request(u, tr);          // on their way while the weights are laid out
+    if constexpr (kMatrix) stage_router_weights<M>(a.W1, a.W2, raw, tid, kTrainWaves * 64);
+    stage_w3<M>(a.W3, a.bias, w3f, tid);
+    __syncthreads();
+    if constexpr (kMatrix) {
+        if (wave == 0) {
+            RouterWeights w;
+            load_router_weights<M>(raw, lane, w);
+#pragma unroll
+            for (int s = 0; s < 4; s++) { wop[0][s][lane] = w.w[s]; wop[1][s][lane] = w.e[s]; }
+        }
+        __syncthreads();
+    }
+    if (!kMatrix && u < a.BH) request(u, tr);
     while (u < a.BH) {
         const int b = u / a.Hkv;
         const bool active = lane < a.n_tok - tr * 64;
@@ -139,43 +155,76 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
         for (int j = 0; j < 16; j++) mine[(4 * j + r4) * 16 + (piece ^ ((4 * j + r4) & 15))] = v[j];
         if (u < a.BH) request(u, tr);
         wave_lds_sync();
-        // ---- forward, the routing arithmetic: sequential binary32 sums over d (products of two fp16 values are exact)
-        float accA[M], accB[M];
+        RouterSums<M> v1;                             // xW1, xW2
+        RouterValues<M> f;
+        int top;
+        if constexpr (kMatrix) {
+            // ---- forward: block b of 16 tokens takes the pieces 4s + l/16 of its rows in k-step s
+            constexpr int NP = M <= 4 ? 2 : 4;
+            v4f_r c[4], d[4], val[NP], bnd[NP];
 #pragma unroll
-        for (int m = 0; m < M; m++) { accA[m] = 0.0f; accB[m] = 0.0f; }
+            for (int k = 0; k < 4; k++) { c[k] = v4f_r{0.0f, 0.0f, 0.0f, 0.0f}; d[k] = c[k]; }
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                const v4u_r ww = wop[0][s][lane], we = wop[kMatrix ? 1 : 0][s][lane];
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const uint4 x = mine[(16 * k + piece) * 16 + ((4 * s + r4) ^ piece)];
+                    const v4u_r xb = {x.x, x.y, x.z, x.w};
+                    c[k] = mfma_router(ww, xb, c[k]);
+                    d[k] = mfma_router(we, xb & 0x7fff7fffu, d[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < NP; k++) {
+                val[k] = M <= 4 ? pick_pair(c[k], c[(k + 2) & 3], lane) : c[k];
+                bnd[k] = M <= 4 ? pick_pair(d[k], d[(k + 2) & 3], lane) : d[k];
+            }
+            RouterSums<M> e;
+            gather_sums<M>(val, v1); gather_sums<M>(bnd, e);
+            const bool sure = certain_top<M>(v1, e, w3f, a.bias != nullptr, f, top);       // by every lane: f and top are used below
+            settle_in_order<M, 2>(__ballot(active && !sure), [&](int t, int p) { return mine[t * 16 + (p ^ (t & 15))]; }, 64, raw, a.W1, a.W2,
+                               w3f, a.bias != nullptr, lane, top);
+        } else {
+            // ---- forward, the routing arithmetic: sequential binary32 sums over d (products of two fp16 values are exact)
+            float accA[M], accB[M];
+#pragma unroll
+            for (int m = 0; m < M; m++) { accA[m] = 0.0f; accB[m] = 0.0f; }
 #pragma unroll 1
-        for (int hr = 0; hr < 2; hr++) {
-            uint4 xr[8];
+            for (int hr = 0; hr < 2; hr++) {
+                uint4 xr[8];
 #pragma unroll
-            for (int p = 0; p < 8; p++) xr[p] = mine[lane * 16 + ((hr * 8 + p) ^ piece)];
-            route_half_row<M>(xr, hr * 64, W1w, W2w, accA, accB);
-        }
-        float z[M], sg[M], hid[M], lg[M];
+                for (int p = 0; p < 8; p++) xr[p] = mine[lane * 16 + ((hr * 8 + p) ^ piece)];
+                route_half_row<M>(xr, hr * 64, W1w, W2w, accA, accB);
+            }
 #pragma unroll
-        for (int m = 0; m < M; m++) {
-            z[m] = __fmul_rn(accA[m], accB[m]);
-            const float den = __fadd_rn(1.0f, exp_pinned(-z[m]));
-            hid[m] = __fdiv_rn(z[m], den);
-            sg[m] = 1.0f / den;
-        }
-        int top = 0; float ltop = 0.0f;
+            for (int m = 0; m < M; m++) {
+                v1.A[m] = accA[m]; v1.B[m] = accB[m];
+                f.z[m] = __fmul_rn(accA[m], accB[m]);
+                const float den = __fadd_rn(1.0f, exp_pinned(-f.z[m]));
+                f.hid[m] = __fdiv_rn(f.z[m], den);
+                f.sg[m] = 1.0f / den;
+            }
+            top = 0;
+            float ltop = 0.0f;
 #pragma unroll
-        for (int k = 0; k < M; k++) {
-            float acc = 0.0f;
+            for (int k = 0; k < M; k++) {
+                float acc = 0.0f;
 #pragma unroll
-            for (int j = 0; j < M; j++) acc = __fadd_rn(acc, __fmul_rn(hid[j], w3f[j * M + k]));
-            if (a.bias) acc = __fadd_rn(acc, w3f[64 + k]);
-            lg[k] = acc;
-            if (k == 0) ltop = acc;
-            else if (acc > ltop) { top = k; ltop = acc; }   // strict: the first maximum wins
+                for (int j = 0; j < M; j++) acc = __fadd_rn(acc, __fmul_rn(f.hid[j], w3f[j * M + k]));
+                if (a.bias) acc = __fadd_rn(acc, w3f[64 + k]);
+                f.logit[k] = acc;
+                if (k == 0) ltop = acc;
+                else if (acc > ltop) { top = k; ltop = acc; }   // strict: the first maximum wins
+            }
         }
         // ---- loss of the token and its gradient down to xW1, xW2
-        float mx = lg[0];
+        float mx = f.logit[0];
 #pragma unroll
-        for (int k = 1; k < M; k++) mx = fmaxf(mx, lg[k]);
+        for (int k = 1; k < M; k++) mx = fmaxf(mx, f.logit[k]);
         float p[M], den = 0.0f;
 #pragma unroll
-        for (int k = 0; k < M; k++) { p[k] = __expf(lg[k] - mx); den += p[k]; }
+        for (int k = 0; k < M; k++) { p[k] = __expf(f.logit[k] - mx); den += p[k]; }
         const float rden = 1.0f / den;
         float ptop = 0.0f, pm = 0.0f, pe = 0.0f;
 #pragma unroll
@@ -192,9 +241,9 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
         for (int m = 0; m < M; m++) {
             float dh = 0.0f;
 #pragma unroll
-            for (int k = 0; k < M; k++) { dh = fmaf(dl[k], w3f[m * M + k], dh); g3[m][k] = fmaf(hid[m], dl[k], g3[m][k]); }
-            const float dz = dh * (sg[m] * (1.0f + z[m] * (1.0f - sg[m])));
-            dx[m] = dz * accB[m]; dx[M + m] = dz * accA[m];
+            for (int k = 0; k < M; k++) { dh = fmaf(dl[k], w3f[m * M + k], dh); g3[m][k] = fmaf(f.hid[m], dl[k], g3[m][k]); }
+            const float dz = dh * (f.sg[m] * (1.0f + f.z[m] * (1.0f - f.sg[m])));
+            dx[m] = dz * v1.B[m]; dx[M + m] = dz * v1.A[m];
         }
         // ---- dW1, dW2.  A scale for every column: 2^ef <= its largest < 2^(ef+1): value * 2^(14 - ef) is below 2^15
         constexpr int P = M <= 1 ? 2 : (M <= 2 ? 4 : 8);                        // columns of a reduction, padded

@@ -116,3 +116,24 @@ def test_router_loss_grad_small_column(mq, ref, Hkv, S, M):
     mq.router_loss_grad(cfg, T._dev(K), 0, S, T._dev(W1), T._dev(W2), T._dev(W3), None, T._dev(nll), None, None, 0.3, *got)
     torch.cuda.synchronize()
     _check_columns(("dW1", "dW2"), got[1:3], want[1:3])
+
+
+@pytest.mark.parametrize("M", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("share,S", [(0.1, 1000), (0.6, 300), (1.0, 65)])
+def test_router_loss_grad_some_tokens_tie(mq, ref, M, share, S):
+    """Tokens whose two best experts tie take the first of them, as routing does: the other one's penalties differ by a factor."""
+    rng = np.random.default_rng(S + M)
+    bits = ((2, 16, 4, 8) * 2)[:M]
+    cfg, rcfg = T._cfgs(mq, ref, 1, 3, 3, 64, 64, bits, 0)
+    K, _ = T._rand_kv(rng, 1, 3, S)
+    W1, W2, W3, bias = T._twin_router(rng, M, share, K)
+    nll = np.array([2.0], np.float32)
+    pm, pe = np.array([1.0 / b for b in bits], np.float32), np.array([16.0 / b for b in bits], np.float32)
+    want = ref.router_loss_grad(rcfg, K, 0, S, W1, W2, W3, bias, nll, pm, pe, 0.3)
+    got = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((3,), (128, M), (128, M), (M, M), (M,))]
+    mq.router_loss_grad(cfg, T._dev(K), 0, S, T._dev(W1), T._dev(W2), T._dev(W3), T._dev(bias), T._dev(nll), None, None, 0.3, *got)
+    torch.cuda.synchronize()
+    l = got[0].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(l - want[0]) <= LOSS_TOL * np.abs(want[0]).max()), (l, want[0])
+    for g, r in zip(got[1:], want[1:]):
+        assert np.abs(g.cpu().numpy() - r).max() <= GRAD_TOL * np.abs(r).max()
