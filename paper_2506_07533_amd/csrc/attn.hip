@@ -63,14 +63,13 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     v4i qa[REP == 1 ? 8 : 1][64];
     v4i wa[REP == 1 ? NWV : 1][2][64];                   // per wavefront: weight digits of up to two token blocks
     uint32_t wpos[REP == 1 ? 3 : 1][8][64];
-    alignas(16) float vf[REP < 4 ? NWV : 1][512];                  // raw fp16 units: the value sums of the four row groups on their way to the lanes that own the dims
     uint4 kx[REP == 1 ? NWV : 1][4 * 72];                // per wavefront: the K codes of a unit on their way to the lanes that use them
     alignas(16) uint32_t pcq[REP == 1 ? NWV : 1][4][kD]; // keys quantised per channel: q * scale of up to four token groups of a unit, two fp16 numbers each
     int iq[kD];
     int iqs16[8];
     float iqpart[3][8][2];
     float iqscale[4];
-    float sc[NWV][REP][128];                             // scores (log2 domain) / fp16-path weights of a unit
+    alignas(16) float sc[NWV][REP][128];                             // scores (log2 domain) / fp16-path weights of a unit
     static constexpr int WLS = 136;                      // weight row stride in halfs: rows fall on different banks
     alignas(16) uint16_t wl[NWV][REP][NG][WLS];                     // fp16 softmax weight * V scale, pre-scaled per pair
     uint16_t zrow[WLS];                                  // zeros: the weight row of the unused tile rows
@@ -97,7 +96,7 @@ __device__ __forceinline__ void wave_sync() {
 
 template <int REP> struct WaveState {
     float m[REP], lsum[REP], z[REP];
-    float acc[REP][2];                                   // raw fp16 rows: dims (2l, 2l+1), in units of 2^-24
+    float acc[REP][2];                                   // raw fp16 rows: dims 8 (l % 16) + 2 (l / 16), + 1, in units of 2^-24
     float accq[REP][8];                                  // quantised V, one head per KV head: dims 16*ct + l%16, this lane's token slices only
     v4f accA[8];                                         // quantised V, grouped queries: matrix-core tile ct, rows 4*(l/16)..+3
 };
@@ -299,19 +298,97 @@ __device__ __forceinline__ void value_weights(const VRegs<G> &v, int lane, int w
     wave_sync();
 }
 
+// v[i] summed over the 16 lanes of a row, P values at once: a step in which a lane and its partner each hand over half of their
+// values takes half of the instructions of the step before, 45 for 16 values where a reduction of each takes 128.  Lane x of a
+// row is left with value x P / 16 (P < 16: several lanes hold the same one; P = 32: and the next).
+template <int BIT, int CTRL, int P, int PT>
+__device__ __forceinline__ void row_fold_step(float (&v)[PT], int lane) {
+    if constexpr (P > 1) {
+#pragma unroll
+        for (int i = 0; i < P / 2; i++) {
+            const float keep = (lane & BIT) ? v[i + P / 2] : v[i], give = (lane & BIT) ? v[i] : v[i + P / 2];
+            v[i] = keep + dpp_f<CTRL>(give);
+        }
+    } else {
+        v[0] += dpp_f<CTRL>(v[0]);
+    }
+}
+template <int P>
+__device__ __forceinline__ void row_fold(float (&v)[P], int lane) {
+    row_fold_step<8, 0x128, P>(v, lane);                             // row_ror:8
+    row_fold_step<4, DPP_HALF_MIRROR, (P + 1) / 2>(v, lane);
+    row_fold_step<2, DPP_XOR2, (P + 3) / 4>(v, lane);
+    row_fold_step<1, DPP_XOR1, (P + 7) / 8>(v, lane);
+}
+
 // ---- one unit of raw fp16 rows (16-bit chunks and the FP16 residual) -----------------------
-// 16 rows: lane l holds dims 8*(l%16)..+7 of row 4*j + l/16, for K and for V alike.  Every lane of
-// a row ends up with the row's score, so the weights need no trip through LDS: the score phase
-// leaves p[r][j] in registers for the value phase.
+// 16 rows: lane l holds dims 8*(l%16)..+7 of row 4*j + l/16, for K and for V alike.  One head: every lane of
+// a row ends up with the row's score, so the weights p1 need no trip through LDS and wait in registers for the value phase.
+// Several heads: one score per lane (see row_fold), the weights wait in LDS.  Registers decide here (four heads: 85 spilled before,
+// 39 now; with the same scores but all weights read back at once 90, reloads in the unit loop and 131 us): four sequences of 128k
+// tokens, 8 KV heads x 4 queries 121.5 -> 113.5 us a call, four new tokens on 32 heads x 32k 52.1 -> 48.0.
 // Several queries per sequence (nq > 1; head r belongs to query r / rep_in): query t does not see the residual rows of
 // the queries after it, the last nq - 1 - t valid rows.
 template <int G, int REP, int NWV, typename KR>
-__device__ __forceinline__ void fp16_scores(const Unit &u, const KR &k, int lane, float scale_log2, int nq, int rep_in,
+__device__ __forceinline__ void fp16_scores(const Unit &u, const KR &k, int lane, int wave, float scale_log2, int nq, int rep_in,
                                             AttnLds<G, REP, NWV> &L, WaveState<REP> &st, float (&p4)[REP][4]) {
     const int part = lane & 15, tok_l = lane >> 4;
+    if constexpr (REP > 1) {
+        // one score per lane (8 heads: two): value 4r + j is head r, row 4j + l / 16
+        constexpr int P = 4 * REP, PK = P / 16 > 0 ? P / 16 : 1, DUP = P < 16 ? 16 / P : 1;
+        float v[P];
+#pragma unroll
+        for (int r = 0; r < REP; r++) {
+            const uint4 qv = *reinterpret_cast<const uint4 *>(&L.qtab[r][part * 4]);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                float ps = dot2(k.c[j].x, qv.x, 0.0f);
+                ps = dot2(k.c[j].y, qv.y, ps);
+                ps = dot2(k.c[j].z, qv.z, ps);
+                v[4 * r + j] = dot2(k.c[j].w, qv.w, ps);
+            }
+        }
+        row_fold<P>(v, lane);
+        const int idx = part * P / 16, head = idx >> 2;              // PK consecutive values lie in one head
+        int nvalid = u.nvalid;
+        if (nq > 1) {
+#pragma unroll
+            for (int r = 0; r < REP; r++) nvalid = head == r ? min(u.nvalid, u.tail_rows - (nq - 1 - r / rep_in)) : nvalid;
+        }
+        float lmax = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < PK; i++) {
+            v[i] = 4 * ((idx & 3) + i) + tok_l < nvalid ? v[i] * scale_log2 : -INFINITY;
+            lmax = fmaxf(lmax, v[i]);
+        }
+        lmax = group_max<16 / REP>(lmax);                            // over the lanes of a head in a row, then the rows
+        {
+            const auto x = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lmax), __builtin_bit_cast(uint32_t, lmax), false, false);
+            lmax = fmaxf(__builtin_bit_cast(float, (uint32_t)x[0]), __builtin_bit_cast(float, (uint32_t)x[1]));
+            const auto y = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, lmax), __builtin_bit_cast(uint32_t, lmax), false, false);
+            lmax = fmaxf(__builtin_bit_cast(float, (uint32_t)y[0]), __builtin_bit_cast(float, (uint32_t)y[1]));
+        }
+        float m = 0.0f;
+#pragma unroll
+        for (int r = 0; r < REP; r++) {
+            rescale<G, REP>(st, r, __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lmax), r * (16 / REP))), lane);
+            m = head == r ? st.m[r] : m;
+        }
+        float *dst = &L.sc[wave][0][tok_l * P + idx], sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < PK; i++) {
+            const float p = v[i] == -INFINITY ? 0.0f : fast_exp2(v[i] - m);         // masked rows
+            dst[i] = p;
+            sum += p;
+        }
+        if (DUP > 1 && (part & (DUP - 1)) != 0) sum = 0.0f;
+#pragma unroll
+        for (int r = 0; r < REP; r++) st.lsum[r] += head == r ? sum : 0.0f;
+        wave_sync();
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < REP; r++) {
-        const int nvalid = REP == 1 ? u.nvalid : min(u.nvalid, u.tail_rows - (nq - 1 - r / rep_in));   // an fp16 unit spans 16 rows
         const uint4 qv = *reinterpret_cast<const uint4 *>(&L.qtab[r][part * 4]);
         float s4[4], lmax = -INFINITY;
 #pragma unroll
@@ -321,7 +398,7 @@ __device__ __forceinline__ void fp16_scores(const Unit &u, const KR &k, int lane
             ps = dot2(k.c[j].z, qv.z, ps);
             ps = dot2(k.c[j].w, qv.w, ps);
             ps = group_sum<16>(ps);
-            s4[j] = (4 * j + tok_l < nvalid) ? ps * scale_log2 : -INFINITY;
+            s4[j] = (4 * j + tok_l < u.nvalid) ? ps * scale_log2 : -INFINITY;
             lmax = fmaxf(lmax, s4[j]);
         }
         rescale<G, REP>(st, r, wave_max(lmax), lane);
@@ -333,26 +410,26 @@ __device__ __forceinline__ void fp16_scores(const Unit &u, const KR &k, int lane
     }
 }
 template <int G, int REP, int NWV>
-__device__ __forceinline__ void fp16_values(const Unit &u, const VRegs<G> &v, int lane, int wave,
-                                            AttnLds<G, REP, NWV> &L, WaveState<REP> &st, const float (&p4)[REP][4]) {
+__device__ __forceinline__ void fp16_values(const Unit &u, const VRegs<G> &v, int lane, int wave, AttnLds<G, REP, NWV> &L, WaveState<REP> &st, const float (&p1)[REP][4]) {
     const int tok_l = lane >> 4;
     const int nvalid = u.nvalid;
-    // staging buffer of the wavefront, 2 KiB: [row group l/16][half of the lane's 8 dims][column block l%16][4];
-    // with four or more heads it lies over the weight rows, which only quantised units use
-    float *stage;
-    if constexpr (REP >= 4) stage = reinterpret_cast<float *>(&L.wl[wave][0][0][0]);
-    else                    stage = &L.vf[wave][0];
-    static_assert(REP < 4 || sizeof(L.wl[0]) >= 2048, "staging buffer");
 #pragma unroll
     for (int r = 0; r < REP; r++) {
-        float acc8[8];
+        float acc8[8], p4[4];
+        if constexpr (REP > 1) {
+            const float4 p = *reinterpret_cast<const float4 *>(&L.sc[wave][0][tok_l * (4 * REP) + 4 * r]);
+            p4[0] = p.x; p4[1] = p.y; p4[2] = p.z; p4[3] = p.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) p4[j] = p1[0][j];
+        }
 #pragma unroll
         for (int e = 0; e < 8; e++) acc8[e] = 0.0f;
         // the packed halves feed the multiply-add directly (mixed-precision FMA), nothing is unpacked
         if (nvalid == 16) {
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const float p24 = p4[r][j] * kTwoM24;                 // accumulators carry a factor 2^-24
+                const float p24 = p4[j] * kTwoM24;                 // accumulators carry a factor 2^-24
                 const uint32_t w[4] = {v.c[j].x, v.c[j].y, v.c[j].z, v.c[j].w};
 #pragma unroll
                 for (int e = 0; e < 8; e++) {
@@ -363,7 +440,7 @@ __device__ __forceinline__ void fp16_values(const Unit &u, const VRegs<G> &v, in
         } else {                                                      // the last rows of the residual
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const float p24 = p4[r][j] * kTwoM24;
+                const float p24 = p4[j] * kTwoM24;
                 const bool ok = 4 * j + tok_l < nvalid;               // rows past nvalid may hold NaN / Inf
                 const uint32_t w[4] = {ok ? v.c[j].x : 0u, ok ? v.c[j].y : 0u, ok ? v.c[j].z : 0u, ok ? v.c[j].w : 0u};
 #pragma unroll
@@ -373,26 +450,21 @@ __device__ __forceinline__ void fp16_values(const Unit &u, const VRegs<G> &v, in
                 }
             }
         }
-        // fold the four row groups through LDS and hand every dim to the lane that owns it (2l, 2l+1)
-        float4 t0, t1;
-        t0.x = acc8[0]; t0.y = acc8[1]; t0.z = acc8[2]; t0.w = acc8[3];
-        t1.x = acc8[4]; t1.y = acc8[5]; t1.z = acc8[6]; t1.w = acc8[7];
-        float *mine_w = stage + (lane >> 4) * 128 + (lane & 15) * 4;
-        *reinterpret_cast<float4 *>(mine_w) = t0;
-        *reinterpret_cast<float4 *>(mine_w + 64) = t1;
-        wave_sync();
-        // dims 2l, 2l+1: column block l/4, element 2*(l%4) of its 8: half (l%4)/2, word 2*(l%2)
-        const float *mine_r = stage + ((lane & 3) >> 1) * 64 + (lane >> 2) * 4 + (lane & 1) * 2;
-        float2 s = *reinterpret_cast<const float2 *>(mine_r);
+        // sum over the four row groups (lanes l, l ^ 16, l ^ 32, l ^ 48), every exchange halving the dims a lane carries: lane l
+        // ends up with dims 8 (l % 16) + 2 (l / 16), + 1.  (Through LDS: six accesses and two waits per head.)
+        float t[4];
 #pragma unroll
-        for (int rg = 1; rg < 4; rg++) {
-            const float2 t = *reinterpret_cast<const float2 *>(mine_r + rg * 128);
-            s.x += t.x; s.y += t.y;
+        for (int e = 0; e < 4; e++) {
+            const auto x = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, acc8[e]), __builtin_bit_cast(uint32_t, acc8[e + 4]), false, false);
+            t[e] = __builtin_bit_cast(float, (uint32_t)x[0]) + __builtin_bit_cast(float, (uint32_t)x[1]);
         }
-        st.acc[r][0] += s.x;
-        st.acc[r][1] += s.y;
-        wave_sync();
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+            const auto x = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, t[e]), __builtin_bit_cast(uint32_t, t[e + 2]), false, false);
+            st.acc[r][e] += __builtin_bit_cast(float, (uint32_t)x[0]) + __builtin_bit_cast(float, (uint32_t)x[1]);
+        }
     }
+    if constexpr (REP > 1) wave_sync();                   // the weights are consumed
 }
 
 // ---- matrix-core path for grouped queries (REP > 1), quantised units -------------------------
@@ -1751,7 +1823,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     if (lgb == 1)      pc_scores<2, G, NWV>(cur, kr, lane, wave, a.scale_log2, L, st);
                     else if (lgb == 2) pc_scores<4, G, NWV>(cur, kr, lane, wave, a.scale_log2, L, st);
                     else if (lgb == 3) pc_scores<8, G, NWV>(cur, kr, lane, wave, a.scale_log2, L, st);
-                    else                fp16_scores<G, REP, NWV>(cur, kr, lane, a.scale_log2, a.nq, a.rep_in, L, st, p4);
+                    else                fp16_scores<G, REP, NWV>(cur, kr, lane, wave, a.scale_log2, a.nq, a.rep_in, L, st, p4);
                     load_keys(pf);                        // half a unit ahead
                     if (lgb == 1)      iq_values<2, G, NWV>(vc, lane, wave, iq_weights<2, G, NWV>(vc, lane, wave, L, st), L, st);
                     else if (lgb == 2) iq_values<4, G, NWV>(vc, lane, wave, iq_weights<4, G, NWV>(vc, lane, wave, L, st), L, st);
@@ -1761,7 +1833,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     if (lgb == 1)      iq_scores<2, G, NWV, SMALL>(cur, kr, lane, wave, L, st);
                     else if (lgb == 2) iq_scores<4, G, NWV, SMALL>(cur, kr, lane, wave, L, st);
                     else if (lgb == 3) iq_scores<8, G, NWV, SMALL>(cur, kr, lane, wave, L, st);
-                    else                fp16_scores<G, REP, NWV>(cur, kr, lane, a.scale_log2, a.nq, a.rep_in, L, st, p4);
+                    else                fp16_scores<G, REP, NWV>(cur, kr, lane, wave, a.scale_log2, a.nq, a.rep_in, L, st, p4);
                     load_keys(pf);                        // half a unit ahead
                     if (lgb == 1)      iq_values<2, G, NWV>(vc, lane, wave, iq_weights<2, G, NWV>(vc, lane, wave, L, st), L, st);
                     else if (lgb == 2) iq_values<4, G, NWV>(vc, lane, wave, iq_weights<4, G, NWV>(vc, lane, wave, L, st), L, st);
@@ -1771,7 +1843,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     if (lgb == 1)      mc_scores<2, G, REP, NWV>(cur, kr, ak, qp, lane, wave, scale24, L, st);
                     else if (lgb == 2) mc_scores<4, G, REP, NWV>(cur, kr, ak, qp, lane, wave, scale24, L, st);
                     else if (lgb == 3) mc_scores<8, G, REP, NWV>(cur, kr, ak, qp, lane, wave, scale24, L, st);
-                    else                fp16_scores<G, REP, NWV>(cur, kr, lane, a.scale_log2, a.nq, a.rep_in, L, st, p4);
+                    else                fp16_scores<G, REP, NWV>(cur, kr, lane, wave, a.scale_log2, a.nq, a.rep_in, L, st, p4);
                     load_keys(pf);                        // half a unit ahead
                     if (lgb == 1)      value_weights<2, G, REP, NWV>(vc, lane, wave, L, st);
                     else if (lgb == 2) value_weights<4, G, REP, NWV>(vc, lane, wave, L, st);
@@ -1811,6 +1883,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             }
         }
         wave_sync();
+        const int d2 = 8 * (lane & 15) + 2 * (lane >> 4);        // the lane's dims of st.acc
 #pragma unroll
         for (int r = 0; r < REP; r++) {
             float *dst = &L.comb[wave][r][0];
@@ -1819,10 +1892,10 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             strided_wave_sum<NG>(st.z[r], zg);
             float z = zg[0];
 #pragma unroll
-            for (int g = 1; g < NG; g++) z = (2 * lane) / G == g ? zg[g] : z;
-            float2 o = *reinterpret_cast<const float2 *>(&dst[2 * lane]);
+            for (int g = 1; g < NG; g++) z = d2 / G == g ? zg[g] : z;
+            float2 o = *reinterpret_cast<const float2 *>(&dst[d2]);
             o.x += fmaf(st.acc[r][0], kTwo24, z); o.y += fmaf(st.acc[r][1], kTwo24, z);
-            *reinterpret_cast<float2 *>(&dst[2 * lane]) = o;
+            *reinterpret_cast<float2 *>(&dst[d2]) = o;
             if (lane == 0) { dst[kD] = st.m[r]; dst[kD + 1] = lt; }
         }
         __syncthreads();
