@@ -174,34 +174,63 @@ __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(
     }
 }
 
-// Few chunks of more than 64 tokens (a decode step that flushes a chunk per head): one wavefront per 64 tokens of a chunk,
-// the votes added up in LDS.  A wavefront that takes a chunk's passes one after the other has nobody to hide its latency.
-// One chunk of 128 tokens for each of 32 heads: 6.9 us against 10.2; calls on 64 chunks of 256 tokens: 11.5 us against 18.4.
-// From half a wavefront per SIMD on, the other chunks' wavefronts hide it.  (The sums in order: the operands of the matrix
-// products would come through LDS first, 9.0 us instead of 8.5 for 128 chunks of 256 tokens.)
+// Few chunks of more than 64 tokens (a decode step that flushes a chunk per head): one wavefront per 64 tokens of a chunk, its
+// whole window requested at once, the votes added up in LDS.  A wavefront that takes a chunk's windows one after the other has
+// nobody to hide its latency.  From half a wavefront per SIMD on, the other chunks' wavefronts hide it.  Up to two experts: sums in
+// order, see DIRECT.
+// 64 to 256 chunks of 128 tokens 4.6 to 4.9 us (a token per lane, sums in order: 7.1 to 7.4), 32 to 128 chunks of 256 tokens 5.4 to
+// 6.9 (7.5), 512 of them 10.2 (11.1).
 template <int M>
-__global__ __launch_bounds__(256) void route_split_kernel(RouteArgs a) {
-    __shared__ float w3f[72];                        // W3 as binary32, then the optional bias
+__global__ __launch_bounds__(kRouteWaves * 64) void route_split_kernel(RouteArgs a) {
+    constexpr bool kMatrix = M > 2;
+    __shared__ float w3f[kW3Words];
+    __shared__ uint32_t raw[kMatrix ? kD * M : 1];
+    __shared__ uint4 rows[kMatrix ? kRouteWaves : 1][kHalfPieces];
     __shared__ int votes_s[8];
     const int c = a.chunk_begin + (int)blockIdx.x;
     const int u = (int)blockIdx.y;
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // wave-uniform, kept scalar
     const int64_t eidx = (int64_t)u * a.expert_stride + c;
     if (c < a.freeze_chunks) {                       // routing freezing: never routed, FP16 expert
         if (tid == 0) a.expert[eidx] = (uint8_t)a.e16;
         if (a.votes && tid < M) a.votes[eidx * M + tid] = 0;
         return;
     }
-    if (tid < M * M) w3f[tid] = half_bits_to_float(a.W3[tid]);
-    if (a.bias && tid < M) w3f[64 + tid] = a.bias[tid];
+    const int n_tok = min(64, a.N - wave * 64);
+    const uint16_t *Kc = a.K + (int64_t)(u / a.Hkv) * a.stride_b + (int64_t)(u % a.Hkv) * a.stride_h + ((int64_t)c * a.N + wave * 64) * a.stride_s;
+    HalfRows hr[2];
+    if constexpr (kMatrix) {
+#pragma unroll
+        for (int k = 0; k < 2; k++) request_half(Kc, a.stride_s, n_tok, k, lane, hr[k]);
+        stage_router_weights<M>(a.W1, a.W2, raw, tid, (int)blockDim.x);
+    }
+    stage_w3<M>(a.W3, a.bias, w3f, tid);
     if (tid < 8) votes_s[tid] = 0;
     __syncthreads();
-    const uint16_t *Kc = a.K + (int64_t)(u / a.Hkv) * a.stride_b + (int64_t)(u % a.Hkv) * a.stride_h + ((int64_t)c * a.N + wave * 64) * a.stride_s;
-    int cnt[M];
-    route_tokens<M>(Kc, min(64, a.N - wave * 64), a.stride_s, reinterpret_cast<const uint32_t *>(a.W1),
-                    reinterpret_cast<const uint32_t *>(a.W2), w3f, a.bias != nullptr, lane, cnt);
+    int top;
+    if constexpr (kMatrix) {
+        RouterWeights w;
+        load_router_weights<M>(raw, lane, w);
+        v4f_r val[M <= 4 ? 2 : 4], bnd[M <= 4 ? 2 : 4];
+        uint4 *buf = &rows[wave][0];
 #pragma unroll
-    for (int k = 0; k < M; k++) if (lane == k) atomicAdd(&votes_s[k], cnt[k]);
+        for (int k = 0; k < 2; k++) {
+            stage_half(hr[k], lane, buf);
+            wave_lds_sync();
+            half_sums<M>(w, buf, k, lane, val, bnd);
+            wave_lds_sync();
+        }
+        top = window_top<M>(val, bnd, Kc, a.stride_s, n_tok, lane, a, raw, w3f);
+    } else {
+        const uint4 *row = reinterpret_cast<const uint4 *>(Kc + (int64_t)min(lane, n_tok - 1) * a.stride_s);
+        top = ordered_top<M>([&](int p) { return row[p]; }, a.W1, a.W2, w3f, a.bias != nullptr);
+    }
+#pragma unroll
+    for (int k = 0; k < M; k++) {
+        const int cnt = __popcll(__ballot(lane < n_tok && top == k));
+        if (lane == k) atomicAdd(&votes_s[k], cnt);
+    }
     __syncthreads();
     if (tid == 0) {
         int best = 0;
