@@ -371,8 +371,8 @@ def bench_layer(args, w):
         torch.cuda.synchronize()
         t_t = np.array([a.elapsed_time(b) for a, b in tev])
         rows = BH * C * w.chunk
-        # what the step cannot do without: every key row once.  The forward pass is vector arithmetic, dW1 and dW2 are matrix
-        # products: operations per second of the two together have no one peak
+        # what the step cannot do without: every key row once.  The sums over the dims and dW1, dW2 are matrix products, the rest
+        # vector arithmetic: operations per second of the two together have no one peak
         rgb = rows * 2 * w.head_dim / (t_t.mean() * 1e-3) / 1e9
         res["router_train"] = {"bound": "hbm", "achieved": round(rgb, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(rgb / HBM_PEAK_GBPS, 4),
                                "rows": rows, "bytes_per_row": 2 * w.head_dim, "avg_ms": round(float(t_t.mean()), 4),
