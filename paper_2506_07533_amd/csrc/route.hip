@@ -176,8 +176,8 @@ __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(
 
 // Few chunks of more than 64 tokens (a decode step that flushes a chunk per head): one wavefront per 64 tokens of a chunk, its
 // whole window requested at once, the votes added up in LDS.  A wavefront that takes a chunk's windows one after the other has
-// nobody to hide its latency.  From half a wavefront per SIMD on, the other chunks' wavefronts hide it.  Up to two experts: sums in
-// order, see DIRECT.
+// nobody to hide its latency.  From three to four workgroups per compute unit on, the other chunks' wavefronts hide it.  Up to two
+// experts: sums in order, see DIRECT.
 // 64 to 256 chunks of 128 tokens 4.6 to 4.9 us (a token per lane, sums in order: 7.1 to 7.4), 32 to 128 chunks of 256 tokens 5.4 to
 // 6.9 (7.5), 512 of them 10.2 (11.1).
 template <int M>
@@ -242,7 +242,10 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_split_kernel(RouteArgs
 
 template <int M>
 static hipError_t launch_m(const RouteArgs &a, int n_cu, hipStream_t s) {
-    if (a.N > 64 && (long long)a.n_chunks * a.BH <= 2LL * n_cu) {   // fewer wavefronts than half of the SIMDs
+    // as long as the chunks' workgroups are at most one round and mostly wait for their rows: 528 / 768 / 1024 chunks of 128 tokens
+    // 7.3 / 8.8 / 10.5 us against 8.0 / 9.7 / 12.0 with route_kernel, of 256 tokens 11.1 / 12.4 / 16.6 against 13.2 / 12.9 / 15.3
+    // (two experts, 1024 chunks: 12.7 against 14.3)
+    if (a.N > 64 && (long long)a.n_chunks * a.BH <= (a.N <= 128 || M <= 2 ? 4LL : 3LL) * n_cu) {
         hipLaunchKernelGGL(route_split_kernel<M>, dim3((unsigned)a.n_chunks, (unsigned)a.BH), dim3((unsigned)((a.N + 63) / 64 * 64)), 0, s, a);
     } else {
         const int cpw = a.N < 64 ? 64 / a.N : 1, n_frozen = std::min(std::max(a.freeze_chunks - a.chunk_begin, 0), a.n_chunks);

@@ -153,7 +153,7 @@ def _twin_router(rng, M, share, K):
     return W1, W2, W3, bias
 
 
-@pytest.mark.parametrize("M,N,C", [(2, 64, 80), (2, 64, 160), (4, 128, 70), (4, 8, 700), (5, 64, 90), (8, 32, 200),
+@pytest.mark.parametrize("M,N,C", [(2, 64, 80), (2, 64, 160), (4, 128, 70), (4, 8, 700), (5, 64, 90), (8, 32, 200), (8, 256, 64),
                                    (2, 128, 5), (3, 192, 5), (4, 96, 9), (5, 256, 3), (8, 128, 32)])    # few chunks: a wavefront per 64 tokens
 @pytest.mark.parametrize("share", [0.02, 0.2, 0.6])
 def test_route_some_tokens_tie(mq, ref, share, M, N, C):
