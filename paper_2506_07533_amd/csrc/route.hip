@@ -63,13 +63,13 @@ __device__ __forceinline__ void half_sums(const RouterWeights &w, const uint4 *b
     else { val[pair] = c[0]; val[pair + 2] = c[1]; bnd[pair] = d[0]; bnd[pair + 2] = d[1]; }
 }
 template <int M>
-__device__ __forceinline__ int window_top(v4f_r (&val)[M <= 4 ? 2 : 4], v4f_r (&bnd)[M <= 4 ? 2 : 4], const uint16_t *Kc, int64_t stride_s, int n_tok,
+__device__ __forceinline__ int window_top(v4f_r (&val)[M <= 4 ? 2 : 4], v4f_r (&bnd)[M <= 4 ? 2 : 4], const RouterSums<M> &floor, const uint16_t *Kc, int64_t stride_s, int n_tok,
                                           int lane, const RouteArgs &a, const uint32_t *raw, const float *w3f) {
     RouterSums<M> v, s;
     gather_sums<M>(val, v); gather_sums<M>(bnd, s);
     RouterValues<M> o;
     int top;
-    const bool sure = certain_top<M>(v, s, w3f, a.bias != nullptr, o, top);
+    const bool sure = certain_top<M>(v, s, floor, w3f, a.bias != nullptr, o, top);
     settle_in_order<M, 16>(__ballot(!sure && lane < n_tok), [&](int t, int p) { return reinterpret_cast<const uint4 *>(Kc + (int64_t)t * stride_s)[p]; },
                        n_tok, raw, a.W1, a.W2, w3f, a.bias != nullptr, lane, top);
     return top;
@@ -110,7 +110,8 @@ __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(
     stage_w3<M>(a.W3, a.bias, w3f, tid);
     __syncthreads();
     RouterWeights w;
-    if constexpr (!DIRECT) load_router_weights<M>(raw, lane, w);
+    RouterSums<M> floor;
+    if constexpr (!DIRECT) { load_router_weights<M>(raw, lane, w); floor = bound_floor<M>(w.e); }
     int cnt[M];
 #pragma unroll 1
     while (u < a.BH) {
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(
             wave_lds_sync();
             half_sums<M>(w, buf, 1, lane, val, bnd);
             wave_lds_sync();
-            top = window_top<M>(val, bnd, window(cu, ct, ch), a.stride_s, n_tok, lane, a, raw, w3f);
+            top = window_top<M>(val, bnd, floor, window(cu, ct, ch), a.stride_s, n_tok, lane, a, raw, w3f);
         }
         if (ch == 0) {
 #pragma unroll
@@ -212,6 +213,7 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_split_kernel(RouteArgs
     if constexpr (kMatrix) {
         RouterWeights w;
         load_router_weights<M>(raw, lane, w);
+        const RouterSums<M> floor = bound_floor<M>(w.e);
         v4f_r val[M <= 4 ? 2 : 4], bnd[M <= 4 ? 2 : 4];
         uint4 *buf = &rows[wave][0];
 #pragma unroll
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_split_kernel(RouteArgs
             half_sums<M>(w, buf, k, lane, val, bnd);
             wave_lds_sync();
         }
-        top = window_top<M>(val, bnd, Kc, a.stride_s, n_tok, lane, a, raw, w3f);
+        top = window_top<M>(val, bnd, floor, Kc, a.stride_s, n_tok, lane, a, raw, w3f);
     } else {
         const uint4 *row = reinterpret_cast<const uint4 *>(Kc + (int64_t)min(lane, n_tok - 1) * a.stride_s);
         top = ordered_top<M>([&](int p) { return row[p]; }, a.W1, a.W2, w3f, a.bias != nullptr);

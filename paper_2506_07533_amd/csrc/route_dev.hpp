@@ -161,11 +161,14 @@ __device__ __forceinline__ void route_tokens(const uint16_t *Kc, int n_tok, int6
 // experts, which bound the kernels that route.  The same sums on v_mfma_f32_16x16x32_f16 (products exact, binary32 sums in an
 // order of their own) differ from them by rounding only, so that nearly every token's arg-max can be told from them with
 // certainty.  Every addition errs by at most its rounding times the absolute sum so far: in order, dim d is in 128 - d additions of
-// relative error 2^-24; in the matrix core, in at most 32 per step of 32 dims, from its own step on (over 800 000 sums of eight kinds,
-// cancelling ones and wide ranges among them, its error was never above a tenth of that).  So the two
-// differ by at most sum_d ((128 - d) + 32 (4 - d / 32)) 2^-24 |x_d w_d|, which comes from a second product, |x| times the weights
-// scaled so (rounded up), and is carried through SiLU and W3.  A token whose two best logits are closer than that (ties, else about one in a
-// thousand) is settled by the sums in order.  The result is the same, bit for bit, always.
+// relative error 2^-24; in the matrix core, in at most 32 per step of 32 dims, from its own step on.  There a subnormal number
+// counts with the smallest normal exponent (a zero not at all): the 32 products of a step are cut off at 2^-24 of the largest
+// power of two among them, that of a key of 2^-24 times 8 being 2^-14 * 8 (measured: at most 23 of the 32 allowed, normal numbers
+// 4 times 2^-24 of the absolute sum).  So the two differ by at most
+//   sum_d ((128 - d) + 32 (4 - d / 32)) 2^-24 max(|x_d|, 2^-14) max(|w_d|, 2^-14),
+// and a maximum is at most the sum: it comes from a second product, |x| times the weights scaled so, plus 2^-14 and rounded up, and
+// from 2^-14 times the sum of those weights (bound_floor), and is carried through SiLU and W3.  A token whose two best logits are closer
+// than that (ties, else about one in a thousand) is settled by the sums in order.  The result is the same, bit for bit, always.
 typedef float v4f_r __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_r __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h_r __attribute__((ext_vector_type(8)));
@@ -213,9 +216,9 @@ __device__ __forceinline__ void load_router_weights(const uint32_t *raw, int lan
         for (int k = 0; k < 4; k++) {
             const uint32_t w0 = m < M ? (uint32_t)W[(32 * s + 2 * k) * M] : 0u, w1 = m < M ? (uint32_t)W[(32 * s + 2 * k + 1) * M] : 0u;
             r.w[s][k] = w0 | (w1 << 16);
-            // cutting off loses up to 2^-10 of a value, or 2^-24
+            // at least 2^-14 each; cutting off loses up to 2^-10 of a value
             const float f0 = (float)(256 - 64 * s - 2 * k - 8 * q) * ((1.0f + 0x1p-8f) / 256.0f), f1 = f0 - (1.0f + 0x1p-8f) / 256.0f;
-            const auto e = __builtin_amdgcn_cvt_pkrtz(fmaf(fabsf(half_bits_to_float(w0)), f0, 0x1p-23f), fmaf(fabsf(half_bits_to_float(w1)), f1, 0x1p-23f));
+            const auto e = __builtin_amdgcn_cvt_pkrtz(fmaf(fabsf(half_bits_to_float(w0)), f0, 0x1.01p-14f), fmaf(fabsf(half_bits_to_float(w1)), f1, 0x1.01p-14f));
             r.e[s][k] = __builtin_bit_cast(uint32_t, e);
         }
     }
@@ -267,6 +270,20 @@ __device__ __forceinline__ void gather_sums(v4f_r (&c)[M <= 4 ? 2 : 4], RouterSu
     }
 }
 
+// The part of the bound that does not depend on the keys, the same in every lane: 2^-14 times the sums of an output's bound weights.
+template <int M>
+__device__ __forceinline__ RouterSums<M> bound_floor(const v4u_r (&e)[4]) {
+    const v4f_r zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    const v4u_r least = {0x04000400u, 0x04000400u, 0x04000400u, 0x04000400u};
+    const v4f_r c = mfma_router(e[1], least, mfma_router(e[0], least, zero)) + mfma_router(e[3], least, mfma_router(e[2], least, zero));
+    v4f_r all[M <= 4 ? 2 : 4];
+#pragma unroll
+    for (int k = 0; k < (M <= 4 ? 2 : 4); k++) all[k] = c;
+    RouterSums<M> o;
+    gather_sums<M>(all, o);
+    return o;
+}
+
 // What the sums of a token lead to: SiLU of their products and its sigmoid, the logits.
 template <int M> struct RouterValues { float z[M], sg[M], hid[M], logit[M]; };
 template <int M>
@@ -285,16 +302,15 @@ __device__ __forceinline__ void router_values(const RouterSums<M> &v, const floa
     }
 }
 
-// The token's expert from the sums and their bounds; false if they do not tell it from the expert by the sums in order.
+// The token's expert from the sums and their bounds (s + floor); false if they do not tell it from the expert by the sums in order.
 template <int M>
-__device__ __forceinline__ bool certain_top(const RouterSums<M> &v, const RouterSums<M> &s, const float *w3f, bool has_bias,
+__device__ __forceinline__ bool certain_top(const RouterSums<M> &v, const RouterSums<M> &s, const RouterSums<M> &floor, const float *w3f, bool has_bias,
                                             RouterValues<M> &o, int &top) {
-    float err = 0.0f, any = 0.0f;
+    float err = 0.0f;
     router_values<M>(v, w3f, has_bias, o);
 #pragma unroll
     for (int m = 0; m < M; m++) {
-        const float ea = kSumErr * s.A[m], eb = kSumErr * s.B[m];
-        any += ea + eb;
+        const float ea = kSumErr * (s.A[m] + floor.A[m]), eb = kSumErr * (s.B[m] + floor.B[m]);
         // |z - z'| of the two products, times the slope of SiLU: the slope at z and what the second derivative, at most
         // s (1 - s) (2 + |z|), adds within 1/4; 1.1 anywhere
         const float ez = fmaf(fabsf(v.A[m]), eb, fmaf(fabsf(v.B[m]), ea, ea * eb));
@@ -313,8 +329,8 @@ __device__ __forceinline__ bool certain_top(const RouterSums<M> &v, const Router
         top = more ? k : top; best = more ? o.logit[k] : best;
     }
     if (has_bias) err = fmaf(w3f[kBiasMax], 0x1p-19f, err);
-    // all sums zero (rows of zeros): both sides have the same logits.  NaN: not certain
-    return M == 1 || best - second > 2.1f * err || any == 0.0f;
+    // rows of zeros (the largest product of any other row stays in s): the same logits on both sides.  NaN: not certain
+    return M == 1 || best - second > 2.1f * err || s.A[0] == 0.0f;
 }
 
 // A token per lane by the sums in order; piece(p): the 16-byte piece p of the lane's row.

@@ -92,6 +92,7 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
     constexpr int NB = M <= 4 ? 1 : 2;                // B operands: columns 0..7 first halves, 8..15 second ones, or one each
     constexpr bool kMatrix = M <= 5;                  // the forward pass on the matrix cores
     __shared__ v4u_r wop[kMatrix ? 2 : 1][4][64];     // its operand A and that of its bound (registers are short)
+    __shared__ RouterSums<M> floor;
     __shared__ uint32_t raw[kMatrix ? kD * M : 1];    // the weights for the tokens that it leaves open
     __shared__ __attribute__((aligned(16))) uint16_t dabs[kTrainWaves][2 * kTrainH];
     const int tid = (int)threadIdx.x, lane = tid & 63;
@@ -142,6 +143,8 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
             load_router_weights<M>(raw, lane, w);
 #pragma unroll
             for (int s = 0; s < 4; s++) { wop[0][s][lane] = w.w[s]; wop[1][s][lane] = w.e[s]; }
+            const RouterSums<M> f = bound_floor<M>(w.e);
+            if (lane == 0) floor = f;
         }
         __syncthreads();
     }
@@ -182,7 +185,7 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
             }
             RouterSums<M> e;
             gather_sums<M>(val, v1); gather_sums<M>(bnd, e);
-            const bool sure = certain_top<M>(v1, e, w3f, a.bias != nullptr, f, top);       // by every lane: f and top are used below
+            const bool sure = certain_top<M>(v1, e, floor, w3f, a.bias != nullptr, f, top);       // by every lane: f and top are used below
             settle_in_order<M, 2>(__ballot(active && !sure), [&](int t, int p) { return mine[t * 16 + (p ^ (t & 15))]; }, 64, raw, a.W1, a.W2,
                                w3f, a.bias != nullptr, lane, top);
         } else {

@@ -171,6 +171,42 @@ def test_route_some_tokens_tie(mq, ref, share, M, N, C):
     assert np.array_equal(votes.cpu().numpy(), v_ref) and np.array_equal(expert.cpu().numpy(), e_ref)
 
 
+def _subnormal_twins(rng, kind, B, Hkv, S, M):
+    """Experts 0 and 1 with the same sums from the same products in other places: the second half of a row repeats the first, and
+    expert 1's weights are expert 0's with some dims d and d + 64 exchanged.  One product is far larger than its operands' subnormal
+    partners in the others, so that little of those is left where a subnormal operand counts with the smallest normal exponent."""
+    ints = lambda *shape: rng.integers(1, 4, shape) * rng.choice([-1.0, 1.0], shape) * 2.0 ** -24
+    if kind == "keys":                                            # one weight of 8 among weights of 0.01
+        x, w = ints(B, Hkv, S, 64), rng.standard_normal(128) * 0.01
+        x[..., 63] = np.sign(x[..., 63]) * 2.0 ** -24; w[63] = 8
+    else:                                                         # weights: one key of 8 among keys of 0.01
+        x, w = rng.standard_normal((B, Hkv, S, 64)) * 0.01, ints(128)
+        x[..., 63] = 8; w[63] = 2.0 ** -24; w[127] = 0
+    x, w = x.astype(np.float16), w.astype(np.float16)
+    W1 = np.zeros((128, M), np.float16)
+    W1[:, 0] = W1[:, 1] = w
+    for d in np.flatnonzero(rng.random(64) < 0.5):
+        W1[[d, 64 + d], 1] = W1[[64 + d, d], 1]
+    W3 = np.zeros((M, M), np.float16); W3[0, 0] = W3[1, 1] = 1
+    return np.concatenate([x, x], -1), W1, W1.copy(), W3
+
+
+@pytest.mark.parametrize("M,N,C", [(2, 64, 160), (4, 32, 300), (4, 128, 5), (5, 64, 90), (8, 128, 70)])
+@pytest.mark.parametrize("kind", ["keys", "weights"])
+def test_route_subnormal_operands(mq, ref, kind, M, N, C):
+    """Sums of subnormal keys or weights, which the matrix core cuts short: two experts tie but for the order of their sums."""
+    B, Hkv = 2, 8
+    rng = np.random.default_rng(M * N)
+    cfg, rcfg = _cfgs(mq, ref, B, Hkv, Hkv, N, 64, ([16, 2, 4, 8, 2, 4, 8, 16])[:M], 0)
+    K, W1, W2, W3 = _subnormal_twins(rng, kind, B, Hkv, C * N, M)
+    e_ref, v_ref = ref.route_chunks(rcfg, K, 0, C, W1, W2, W3, None)
+    expert = torch.full((B * Hkv, C), 255, dtype=torch.uint8, device="cuda")
+    votes = torch.full((B * Hkv, C, M), -1, dtype=torch.int32, device="cuda")
+    mq.route_chunks(cfg, _dev(K), 0, C, _dev(W1), _dev(W2), _dev(W3), None, expert, votes)
+    torch.cuda.synchronize()
+    assert np.array_equal(votes.cpu().numpy(), v_ref) and np.array_equal(expert.cpu().numpy(), e_ref)
+
+
 # ----------------------------------------------------------------------------------------------
 # quantise + pack
 # ----------------------------------------------------------------------------------------------

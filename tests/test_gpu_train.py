@@ -137,3 +137,22 @@ def test_router_loss_grad_some_tokens_tie(mq, ref, M, share, S):
     assert np.all(np.abs(l - want[0]) <= LOSS_TOL * np.abs(want[0]).max()), (l, want[0])
     for g, r in zip(got[1:], want[1:]):
         assert np.abs(g.cpu().numpy() - r).max() <= GRAD_TOL * np.abs(r).max()
+
+
+@pytest.mark.parametrize("M", [2, 4, 5, 8])
+@pytest.mark.parametrize("kind", ["keys", "weights"])
+def test_router_loss_grad_subnormal_operands(mq, ref, kind, M):
+    """Two experts that tie but for the order of their sums, of subnormal keys or weights: the top-1 index, and with it the
+    penalties (2 and 16 bits), is the one of the sums in order."""
+    rng = np.random.default_rng(M)
+    bits = ((2, 16, 4, 8) * 2)[:M]
+    cfg, rcfg = T._cfgs(mq, ref, 1, 2, 2, 64, 64, bits, 0)
+    K, W1, W2, W3 = T._subnormal_twins(rng, kind, 1, 2, 500, M)
+    nll = np.array([2.0], np.float32)
+    pm, pe = np.array([1.0 / b for b in bits], np.float32), np.array([16.0 / b for b in bits], np.float32)
+    want = ref.router_loss_grad(rcfg, K, 0, 500, W1, W2, W3, None, nll, pm, pe, 0.3)
+    got = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((3,), (128, M), (128, M), (M, M), (M,))]
+    mq.router_loss_grad(cfg, T._dev(K), 0, 500, T._dev(W1), T._dev(W2), T._dev(W3), None, T._dev(nll), None, None, 0.3, *got)
+    torch.cuda.synchronize()
+    l = got[0].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(l - want[0]) <= LOSS_TOL * np.abs(want[0]).max()), (l, want[0])
