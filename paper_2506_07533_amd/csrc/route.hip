@@ -77,7 +77,7 @@ __device__ __forceinline__ int window_top(v4f_r (&val)[M <= 4 ? 2 : 4], v4f_r (&
 
 // Persistent wavefronts over windows of up to 64 tokens: 64/N consecutive chunks of a row (SHORT), or a part of a chunk, whose
 // wavefront takes all its parts one after the other.
-// DIRECT: up to two experts and a window per wavefront: sums in order, a lane per token, from the rows as they lie.  Their 512
+// DIRECT: one expert (whose sums decide nothing), or two and a window per wavefront: sums in order, a lane per token, from the rows as they lie.  Their 512
 // multiply-adds are done before the operands of the matrix products would be (131 072 rows in 32-token chunks 7.5 us against
 // 8.6); with four experts it is the other way round (10.0 against 9.4).
 template <int M, bool SHORT, bool DIRECT>
@@ -258,15 +258,17 @@ static hipError_t launch_m(const RouteArgs &a, int n_cu, hipStream_t s) {
         if (n_wg < 1) n_wg = std::min(a.BH, n_cu);   // frozen chunks only: a row per wavefront
         if (n_wg > (long long)kRouteWgPerCu * n_cu) n_wg = (long long)kRouteWgPerCu * n_cu;
         const dim3 grid((unsigned)n_wg), block(kRouteWaves * 64);
-        if constexpr (M <= 2) {
-            if (items * ((a.N + 63) / 64) <= (long long)kRouteWgPerCu * kRouteWaves * n_cu) {
+        if constexpr (M <= 2) {                      // one expert: every token's, no key is read (5.2 M rows in 128-token chunks 194 -> 8.6 us)
+            if (M == 1 || items * ((a.N + 63) / 64) <= (long long)kRouteWgPerCu * kRouteWaves * n_cu) {
                 if (a.N < 64) hipLaunchKernelGGL((route_kernel<M, true, true>), grid, block, 0, s, a);
                 else          hipLaunchKernelGGL((route_kernel<M, false, true>), grid, block, 0, s, a);
                 return hipGetLastError();
             }
         }
-        if (a.N < 64) hipLaunchKernelGGL((route_kernel<M, true, false>), grid, block, 0, s, a);
-        else          hipLaunchKernelGGL((route_kernel<M, false, false>), grid, block, 0, s, a);
+        if constexpr (M > 1) {
+            if (a.N < 64) hipLaunchKernelGGL((route_kernel<M, true, false>), grid, block, 0, s, a);
+            else          hipLaunchKernelGGL((route_kernel<M, false, false>), grid, block, 0, s, a);
+        }
     }
     return hipGetLastError();
 }

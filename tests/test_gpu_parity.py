@@ -171,6 +171,29 @@ def test_route_some_tokens_tie(mq, ref, share, M, N, C):
     assert np.array_equal(votes.cpu().numpy(), v_ref) and np.array_equal(expert.cpu().numpy(), e_ref)
 
 
+@pytest.mark.parametrize("N", [32, 128])
+def test_route_one_expert_reads_no_keys(mq, N):
+    """One expert: the decision needs no sums, so a large call takes a fraction of what one with four experts does (a tenth; half allowed)."""
+    B, Hkv, C = 1, 16, 1 << 16
+    C //= N
+    K = torch.zeros((B, Hkv, C * N, 128), dtype=torch.float16, device="cuda")
+    expert = torch.full((Hkv, C), 255, dtype=torch.uint8, device="cuda")
+    us = {}
+    for M in (1, 4):
+        cfg = mq.Cfg(B, Hkv, Hkv, 128, N, 32, (16, 2, 4, 8)[:M], 0, 0)
+        votes = torch.full((Hkv, C, M), -1, dtype=torch.int32, device="cuda")
+        W = [torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((128, M), (128, M), (M, M))]
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                mq.route_chunks(cfg, K, 0, C, *W, None, expert, votes)
+            b.record(); torch.cuda.synchronize()
+            us[M] = min(us.get(M, math.inf), a.elapsed_time(b) * 50)
+        assert bool((expert == 0).all()) and bool((votes[..., 0] == N).all())
+    assert us[1] < us[4] / 2, us
+
+
 def _subnormal_twins(rng, kind, B, Hkv, S, M):
     """Experts 0 and 1 with the same sums from the same products in other places: the second half of a row repeats the first, and
     expert 1's weights are expert 0's with some dims d and d + 64 exchanged.  One product is far larger than its operands' subnormal
