@@ -175,12 +175,15 @@ typedef _Float16 v8h_r __attribute__((ext_vector_type(8)));
 constexpr float kSumErr = 256.0f / 16777216.0f;           // the factor of |x_0 w_0|; the others relative to it
 constexpr int kW3Max = 72, kBiasMax = 80, kW3Words = 84;  // w3f: also the largest |W3| of every row, the largest |bias|
 
-// The workgroup's copy of W3 as binary32 and what the bound needs of it.
-template <int M>
+// The workgroup's copy of W3 as binary32 and (BOUND) what the bound needs of it.
+template <int M, bool BOUND = true>
 __device__ __forceinline__ void stage_w3(const uint16_t *W3, const float *bias, float *w3f, int tid) {
     if (tid < M * M) w3f[tid] = half_bits_to_float(W3[tid]);
     if (tid < M) {
         w3f[64 + tid] = bias ? bias[tid] : 0.0f;
+    }
+    if constexpr (!BOUND) return;
+    if (tid < M) {
         float m = 0.0f;
 #pragma unroll
         for (int k = 0; k < M; k++) m = fmaxf(m, fabsf(half_bits_to_float(W3[tid * M + k])));
