@@ -97,6 +97,10 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
     __shared__ __attribute__((aligned(16))) uint16_t dabs[kTrainWaves][2 * kTrainH];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // wave-uniform, kept scalar
+    if constexpr (!kMatrix) {                         // first of all: behind the accumulators' set-up eight experts take 236 bytes of scratch instead of 164
+        stage_w3<M, false>(a.W3, a.bias, w3f, tid);
+        __syncthreads();
+    }
     const const_words W1w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W1));
     const const_words W2w = reinterpret_cast<const_words>(reinterpret_cast<uintptr_t>(a.W2));
     uint4 *mine = &stage[wave][0];
@@ -133,11 +137,11 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
 #pragma unroll
         for (int j = 0; j < 16; j++) v[j] = nt_load(reinterpret_cast<const uint4 *>(Kt + (int64_t)min(4 * j + r4, last) * a.stride_s) + piece);
     };
-    if (kMatrix && u < a.BH) request(u, tr);          // on their way while the weights are laid out
-    if constexpr (kMatrix) stage_router_weights<M>(a.W1, a.W2, raw, tid, kTrainWaves * 64);
-    stage_w3<M>(a.W3, a.bias, w3f, tid);
-    __syncthreads();
+    if (u < a.BH) request(u, tr);                     // on their way while the weights are laid out
     if constexpr (kMatrix) {
+        stage_router_weights<M>(a.W1, a.W2, raw, tid, kTrainWaves * 64);
+        stage_w3<M>(a.W3, a.bias, w3f, tid);
+        __syncthreads();
         if (wave == 0) {
             RouterWeights w;
             load_router_weights<M>(raw, lane, w);
@@ -148,7 +152,6 @@ __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArg
         }
         __syncthreads();
     }
-    if (!kMatrix && u < a.BH) request(u, tr);
     while (u < a.BH) {
         const int b = u / a.Hkv;
         const bool active = lane < a.n_tok - tr * 64;
