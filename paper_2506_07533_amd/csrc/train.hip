@@ -9,9 +9,9 @@
 // its gradient accumulators over all its tiles.
 //   rows      requested in whole rows, a tile ahead, and staged in LDS (pieces XOR-swizzled: reads by row and by piece both
 //             touch every bank), from where the forward pass takes a row per lane and the weight gradient a piece per lane.
-//   forward   up to five experts: xW1, xW2 and the bound on their distance from the sums in order on the matrix cores (see
+//   forward   up to five experts (one and two: in large calls): xW1, xW2 and the bound on their distance from the sums in order on the matrix cores (see
 //             certain_top), a lane per token afterwards; the tokens whose top-1 index they leave open take it from the sums in
-//             order.  More experts: one lane per token, route_half_row (the operands and the eight tiles of results would not
+//             order.  Else one lane per token, route_half_row (more than five experts: the operands and the eight tiles of results would not
 //             fit the registers beside the rest: 7 experts 189 us against 134).  Then the token's loss and its gradient down to
 //             d(loss)/d(xW1), d(loss)/d(xW2) (2M values per token, handed over through LDS).
 //   dW1, dW2  = x^T [128 x 64 tokens] times those values [64 tokens x 2M] on v_mfma_f32_16x16x32_f16: x is fp16 as it is; a
@@ -29,10 +29,12 @@
 //             address and workgroup.  Device-wide atomic steps on one address run at about nine per microsecond here: one
 //             wavefront at a time, each with its own atomic adds (4096 per address), took 0.8 ms of the 0.89 ms that the
 //             gradient over 1.05 M rows needed.
-// 1.05 M rows: 2 / 4 / 5 / 8 experts 53 / 59 / 68 / 184 us (56 / 76 / 94 / 183 with the forward pass in order for all), 0.26 M rows,
-// 4 experts: 30.5 (35.6), 64 rows: 12.8 (15.8).  The rows alone are 38 us at the read ceiling of the chip; what is left are the
-// 110 KiB of LDS traffic of a tile and the arithmetic per token, at two wavefronts per SIMD.  Error against binary64 as before or
-// below (1e-7 to 4e-7 of an array).  With 7 and 8 experts the 256 registers that eight wavefronts leave are not enough.
+// 1.05 M rows: 2 / 4 / 5 / 8 experts 53 / 60 / 75 / 180 us (54 / 77 / 95 / 182 with the forward pass in order for all), 0.26 M rows,
+// 4 experts: 29.0 (34.3), 64 rows: 12.6 (14.7); 8k to 32k rows, three experts: 15.7 to 17.1 (15.1 to 16.9), five: 18.7 to 21.1 (19.8
+// to 21.0), where the few open tokens of one tile hold up the call.  The rows alone are 38 us at the read ceiling of the chip; what is
+// left are the 110 KiB of LDS traffic of a tile and the arithmetic per token, at two wavefronts per SIMD.  Error against binary64 5e-8
+// to 7e-7 of an array either way (it changes from run to run with the order of the atomic adds).  With 7 and 8 experts the 256
+// registers that eight wavefronts leave are not enough: 116 and 164 bytes of scratch a lane; with 5 experts 36.
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
 #include "pack_dev.hpp"
@@ -83,14 +85,14 @@ __device__ __forceinline__ uint32_t column_max(uint32_t (&v)[P], int lane) {
     return max(v[0], dpp_u<DPP_XOR1>(v[0]));
 }
 
-template <int M>
+// kMatrix: the forward pass on the matrix cores
+template <int M, bool kMatrix>
 __global__ __launch_bounds__(kTrainWaves * 64) void router_train_kernel(TrainArgs a) {
     constexpr int NS = M * M + M + 2;                 // sums that every lane keeps: dW3, bias, the two losses
     __shared__ float w3f[kW3Words];
     __shared__ float sums[kTrainWaves][NS];
     __shared__ uint4 stage[kTrainWaves][64 * 16];     // key rows: piece p of row r at 16r + (p ^ (r % 16)); the fold's dW at the end
     constexpr int NB = M <= 4 ? 1 : 2;                // B operands: columns 0..7 first halves, 8..15 second ones, or one each
-    constexpr bool kMatrix = M <= 5;                  // the forward pass on the matrix cores
     __shared__ v4u_r wop[kMatrix ? 2 : 1][4][64];     // its operand A and that of its bound (registers are short)
     __shared__ RouterSums<M> floor;
     __shared__ uint32_t raw[kMatrix ? kD * M : 1];    // the weights for the tokens that it leaves open
@@ -378,8 +380,15 @@ __global__ void train_zero_kernel(TrainArgs a) {
 }
 
 template <int M>
-static hipError_t launch_t(const TrainArgs &a, unsigned n_wg, hipStream_t s) {
-    hipLaunchKernelGGL(router_train_kernel<M>, dim3(n_wg), dim3(kTrainWaves * 64), 0, s, a);
+static hipError_t launch_t(const TrainArgs &a, unsigned n_wg, bool many, hipStream_t s) {
+    // one and two experts: 128 or 256 multiply-adds a row are done before the weights are laid out and the open tokens settled,
+    // which two tiles per wavefront pay for (two experts, 16384 / 131072 / 262144 / 1.05 M rows: 13.0 / 20.3 / 26.5 / 53.8 us in
+    // order, 14.2 / 21.7 / 26.6 / 53.0)
+    const dim3 grid(n_wg), block(kTrainWaves * 64);
+    if constexpr (M <= 2) {
+        if (many) hipLaunchKernelGGL((router_train_kernel<M, true>), grid, block, 0, s, a);
+        else      hipLaunchKernelGGL((router_train_kernel<M, false>), grid, block, 0, s, a);
+    } else hipLaunchKernelGGL((router_train_kernel<M, (M <= 5)>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -390,15 +399,16 @@ hipError_t launch_router_train(const TrainArgs &a, int n_cu, hipStream_t s) {
     const long long n_tiles = (long long)a.BH * ((a.n_tok + 63) / 64);
     long long n_wg = (n_tiles + kTrainWaves - 1) / kTrainWaves;
     if (n_wg > n_cu) n_wg = n_cu;                      // every wavefront keeps its accumulators over many tiles
+    const bool many = n_tiles >= 2LL * kTrainWaves * n_cu;
     switch (a.M) {
-        case 1: return launch_t<1>(a, (unsigned)n_wg, s);
-        case 2: return launch_t<2>(a, (unsigned)n_wg, s);
-        case 3: return launch_t<3>(a, (unsigned)n_wg, s);
-        case 4: return launch_t<4>(a, (unsigned)n_wg, s);
-        case 5: return launch_t<5>(a, (unsigned)n_wg, s);
-        case 6: return launch_t<6>(a, (unsigned)n_wg, s);
-        case 7: return launch_t<7>(a, (unsigned)n_wg, s);
-        case 8: return launch_t<8>(a, (unsigned)n_wg, s);
+        case 1: return launch_t<1>(a, (unsigned)n_wg, many, s);
+        case 2: return launch_t<2>(a, (unsigned)n_wg, many, s);
+        case 3: return launch_t<3>(a, (unsigned)n_wg, many, s);
+        case 4: return launch_t<4>(a, (unsigned)n_wg, many, s);
+        case 5: return launch_t<5>(a, (unsigned)n_wg, many, s);
+        case 6: return launch_t<6>(a, (unsigned)n_wg, many, s);
+        case 7: return launch_t<7>(a, (unsigned)n_wg, many, s);
+        case 8: return launch_t<8>(a, (unsigned)n_wg, many, s);
     }
     return hipErrorInvalidValue;
 }

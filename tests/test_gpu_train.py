@@ -156,3 +156,31 @@ def test_router_loss_grad_subnormal_operands(mq, ref, kind, M):
     torch.cuda.synchronize()
     l = got[0].cpu().numpy().astype(np.float64)
     assert np.all(np.abs(l - want[0]) <= LOSS_TOL * np.abs(want[0]).max()), (l, want[0])
+
+
+@pytest.mark.parametrize("M,S,kind", [(1, 4096, "ties"), (2, 4096, "ties"), (2, 4096, "subnormal"), (2, 4033, "ties"), (2, 4032, "ties")])
+def test_router_loss_grad_many_tiles(mq, ref, M, S, kind):
+    """One and two experts from two tiles per wavefront on (64 rows of 64 tiles on 256 compute units; 63 tiles are too few): the
+    forward pass on the matrix cores, which the smaller calls of these do not take."""
+    rng = np.random.default_rng(S + M)
+    bits = (2, 16)[:M]
+    cfg, rcfg = T._cfgs(mq, ref, 1, 64, 64, 64, 64, bits, 0)
+    bias = None
+    if kind == "subnormal":
+        K, W1, W2, W3 = T._subnormal_twins(rng, "keys", 1, 64, S, M)
+    else:
+        K, _ = T._rand_kv(rng, 1, 64, S)
+        W1, W2, W3, bias = T._twin_router(rng, 2, 0.05, K)
+        W1, W2, W3, bias = W1[:, :M].copy(), W2[:, :M].copy(), W3[:M, :M].copy(), bias[:M].copy()
+    nll = np.array([2.0], np.float32)
+    pm, pe = np.array([1.0 / b for b in bits], np.float32), np.array([16.0 / b for b in bits], np.float32)
+    want = ref.router_loss_grad(rcfg, K, 0, S, W1, W2, W3, bias, nll, pm, pe, 0.3)
+    got = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((3,), (128, M), (128, M), (M, M), (M,))]
+    mq.router_loss_grad(cfg, T._dev(K), 0, S, T._dev(W1), T._dev(W2), T._dev(W3), None if bias is None else T._dev(bias), T._dev(nll),
+                        None, None, 0.3, *got)
+    torch.cuda.synchronize()
+    l = got[0].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(l - want[0]) <= LOSS_TOL * np.abs(want[0]).max()), (l, want[0])
+    if kind != "subnormal":                                       # (whose gradients are of the order of 1e-20)
+        for g, r in zip(got[1:], want[1:]):
+            assert np.abs(g.cpu().numpy() - r).max() <= GRAD_TOL * max(np.abs(r).max(), 1e-6)
