@@ -1395,9 +1395,16 @@ __device__ __forceinline__ bool weigh_rows(const AttnArgs &a, int tid, int lane,
 
 // RAGGED: the sequences of the batch have their own numbers of chunks and residual rows (a.seq_chunks,
 // a.seq_tail, device arrays indexed by sequence); a.n_chunks is then the bound that sizes the segments.
+// MODE: how the rows are split, a kernel each.  In one kernel every call held the registers of all three (four heads: 39 spilled;
+// on intervals 30, on fixed rows, which need no loop over rows, 2) and looked at its rows later: intervals, 2 x 32 ragged rows of up
+// to 1152 tokens 24.4 -> 23.7 us, 40 heads of 128k tokens 114.7 -> 113.8, four sequences of 128k tokens on 8 heads x 4 queries 113.5 ->
+// 111.6; fixed rows, 8 heads x 2k tokens 14.7 -> 12.8.
 // SMALL: chunks of 8, 16 or 32 tokens, see Gather (one query head per KV head) and load_v (grouped queries).  KPC: keys quantised per channel (REP == 1 only), see pc_scores.
-template <int G, int REP, int NWV, bool RAGGED, bool SMALL, bool KPC>
+constexpr int kIntervals = 0, kRows = 1, kRowsWeighed = 2;
+template <int G, int REP, int NWV, bool RAGGED, int MODE, bool SMALL, bool KPC>
 __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
+    constexpr bool ROWS = MODE != kIntervals, WEIGH = MODE == kRowsWeighed;
+    static_assert(!RAGGED || !ROWS, "rows of different lengths: intervals");
     static_assert(!KPC || REP == 1, "per-channel keys: one query head per KV head");
     __shared__ AttnLds<G, REP, NWV> L;
     constexpr int NG = kD / G;
@@ -1414,8 +1421,8 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
     const int seg_chunks = attn_segment_chunks(N);
     const int n_seg = max(1, (a.n_chunks + seg_chunks - 1) / seg_chunks);
     // ---- the workgroup's interval of the unit axis, or its part of a row (a.row_wgs workgroups per row, see AttnArgs)
-    const int RW = a.row_wgs;
-    bool fixed = RW > 0;
+    const int RW = ROWS ? a.row_wgs : 1;
+    bool fixed = ROWS;
     uint32_t q_first = 0u;                               // a row's queries and the chunk descriptors of its first segment, as loaded
     uint8_t e_first[2] = {0, 0};
     uint64_t o_first[2] = {0ull, 0ull};
@@ -1436,8 +1443,8 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             if (k < KPT && c < min(C, seg_chunks)) { e_first[k] = erow[c]; o_first[k] = orow[c]; }
         }
     };
-    const bool weigh = !RAGGED && a.weigh != 0 && !a.weigh_ws;          // the costs are added up here, see weigh_rows
-    const bool by_counter = RW == 0 || a.weigh_ws;       // the workgroups of a row draw its tickets from a counter
+    const bool weigh = WEIGH && !a.weigh_ws;             // the costs are added up here, see weigh_rows
+    const bool by_counter = !ROWS || (WEIGH && a.weigh_ws);         // the workgroups of a row draw its tickets from a counter
     uint4 piece[kWeighPieces];
     if (weigh) {
         load_decisions<NT>(a, tid, piece);
@@ -1464,7 +1471,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
         static_assert(kMaxWeightedRows <= 2 * NT, "two rows per thread");
         const uint32_t incl = wave_incl_scan(v0 + v1);
         if (lane == 63) L.wscan[wave] = incl;
-        if (tid == 0) L.uneven = 0u;
+        if (ROWS && tid == 0) L.uneven = 0u;
         __syncthreads();
         uint32_t excl = incl - (v0 + v1), total = 0u;
 #pragma unroll
@@ -1505,7 +1512,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
         const uint32_t P = fixed ? (uint32_t)RW : (uint32_t)(axis.owner(ue - 1u) - wg_first + 1);
         const uint32_t ov = min(hi, ue) - max(lo, ub);
         const bool whole = (lo >= ub && hi <= ue) || (ub >= lo && ue <= hi);   // the interval inside the row, or the row inside it
-        if ((!RW || a.weigh) && w == wg_first && tid == 0) row_wgs[u] = fixed && RW == 1 ? kRowDone : P;
+        if ((!ROWS || WEIGH) && w == wg_first && tid == 0) row_wgs[u] = fixed && RW == 1 ? kRowDone : P;
 
         // ---- (a) row set-up.  One round trip to memory for everything the first units need: the raw
         //      queries, the chunk descriptors of the first segment and the first batch of tickets.  The
@@ -1661,7 +1668,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             }
             __syncthreads();
 
-            if (seg == 0) { e_first[0] = e_first[1] = 0; o_first[0] = o_first[1] = 0ull; }   // not carried through the unit loop
+            if (ROWS && seg == 0) { e_first[0] = e_first[1] = 0; o_first[0] = o_first[1] = 0ull; }   // not carried through the unit loop
 
             // One wavefront at a time asks the row's counter for the next batch.
             auto fetch = [&]() {
@@ -2015,18 +2022,18 @@ __global__ __launch_bounds__(kD *kMergeGroups) void attn_merge_kernel(const floa
 template <int REP> constexpr int waves_per_wg() { return 8; }
 
 // The split kernel of a call: the instantiation for its batch shape (uniform / ragged) and chunk size.
-template <int G, int REP, bool KPC>
+template <int G, int REP, bool SMALL, bool KPC>
 static void launch_split(const AttnArgs &a, dim3 grid, dim3 block, hipStream_t s) {
     constexpr int NWV = waves_per_wg<REP>();
-    if (a.N < 64) {
-        if constexpr (!(KPC && G == 64)) {               // groups of 64 tokens do not fit a shorter chunk (checked by the caller)
-            if (a.seq_chunks) hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, true, KPC>), grid, block, 0, s, a);
-            else              hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, true, KPC>), grid, block, 0, s, a);
-        }
-    } else {
-        if (a.seq_chunks) hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, false, KPC>), grid, block, 0, s, a);
-        else              hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, false, KPC>), grid, block, 0, s, a);
-    }
+    if (a.seq_chunks)         hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, kIntervals, SMALL, KPC>), grid, block, 0, s, a);
+    else if (a.row_wgs == 0)  hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kIntervals, SMALL, KPC>), grid, block, 0, s, a);
+    else if (a.weigh == 0)    hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kRows, SMALL, KPC>), grid, block, 0, s, a);
+    else                      hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kRowsWeighed, SMALL, KPC>), grid, block, 0, s, a);
+}
+template <int G, int REP, bool KPC>
+static void launch_split(const AttnArgs &a, dim3 grid, dim3 block, hipStream_t s) {
+    if (a.N >= 64) launch_split<G, REP, false, KPC>(a, grid, block, s);
+    else if constexpr (!(KPC && G == 64)) launch_split<G, REP, true, KPC>(a, grid, block, s);   // groups of 64 tokens do not fit a shorter chunk (checked by the caller)
 }
 
 template <int G, int REP>
