@@ -123,7 +123,9 @@ int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false
 //   different times, but the worst of them (all at 16 bits) has eight units per wavefront.  Up to three rounds of workgroups of
 //   one row each (600 tokens: 640 rows 49.5 -> 42.4 us, 1600 rows 89 -> 94).
 //   part <= 640, tables of at most 16 KiB: the same, if no row costs much more than the mean.  Every workgroup adds up all costs
-//   while its row's descriptors are on their way (1 us); else intervals, whose parts of a row are static too.
+//   while its row's descriptors are on their way (1 us); else intervals, whose parts of a row are static too.  Up to 540 only where
+//   more than one compute unit in 64 would get nothing to do (240 workgroups on 24 or 40 rows: part = 520 37.4 us and 38.3 on
+//   intervals, part = 560 40.5 and 39.5, part = 625 42.4 and 41.4).
 //   part <= 1400: by the costs in the workspace; a row's workgroups share its tickets through its counter.  Above that the
 //   ends of uneven rows cost what the second set-ups do (128k tokens x 32 rows 122.5 and 122.8 us).
 // "Much more": a second set-up is worth about 10 us, in which a wavefront does 220 tokens (50 where sixteen (query head, group)
@@ -131,7 +133,7 @@ int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false
 // a quarter (16 rows of 84k tokens under four queries, groups of 32, P = 16: 188 us on intervals, 197 on fixed rows 6 % apart).
 // 8 heads x 2k tokens 23.0 -> 16.6 us a step (on the GPU), 16 x 500 19.8 -> 13.6, 120 x 200 21.6 -> 13.5, 40 x 389 under four queries each
 // 32.1 -> 23.5, 32 x 32k under four queries 58 -> 50, 256 x 8k in 32-token chunks 69 -> 58.
-constexpr int kSplitEven = 128, kSplitWeighed = 640, kSplitPlanned = 1400, kSplitSetup = 220, kSplitRounds = 3;
+constexpr int kSplitEven = 128, kSplitWeighed = 640, kSplitIdle = 540, kSplitPlanned = 1400, kSplitSetup = 220, kSplitRounds = 3;
 bool rows_split(const moqae_cfg *c, AttnArgs &a) {
     const int64_t rows = a.BH, tokens = ((int64_t)a.n_chunks + 1) * c->chunk, cus = cu_count();
     a.row_wgs = a.weigh = a.weigh_ws = 0;
@@ -144,8 +146,9 @@ bool rows_split(const moqae_cfg *c, AttnArgs &a) {
     } else {
         if (part > kSplitPlanned || n > cus || !room) return false;
         const int64_t setup = a.rep * (kD / a.G) >= 16 ? kSplitSetup / 4 : kSplitSetup;
-        if (part > kSplitWeighed || !attn_weigh(a, (int)(100 + 100 * setup / part))) {
-            if (64 * n < 63 * cus) return false;
+        const bool idle = 64 * n < 63 * cus;
+        if (part > (idle ? kSplitIdle : kSplitWeighed) || !attn_weigh(a, (int)(100 + 100 * setup / part))) {
+            if (idle) return false;
             a.weigh = (int)(100 + 25 * setup * (P + 3) / (P * part)); a.weigh_ws = 1;
         }
     }
