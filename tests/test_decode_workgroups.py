@@ -107,8 +107,14 @@ def test_ragged_call_needs_its_own_workspace_only(ref, H, N, C):
     (4, 16, 16, 64, 64, 70, False),      # table rows that begin anywhere
     (4, 16, 16, 64, 64, 70, True),       # one row costs several times the others: intervals
     (2, 64, 32, 64, 64, 65, True),
-    (8, 32, 32, 32, 64, 70, False),      # costs in the workspace, tickets by counters
+    (8, 32, 32, 32, 64, 70, False),      # costs in the workspace, one workgroup per row
     (8, 32, 32, 32, 64, 70, True),
+    (8, 16, 16, 32, 64, 150, False),     # costs in the workspace, two workgroups per row share its tickets by the counter
+    (8, 16, 16, 32, 64, 150, True),      # ... one row costs several times the others: intervals by the same costs
+    (4, 64, 32, 64, 64, 150, False),     # the same for grouped queries
+    (4, 64, 32, 64, 64, 150, True),
+    (1, 8, 8, 16, 64, 70, False),        # short chunks: every P-th unit for each of a row's workgroups
+    (1, 1, 1, 8, 64, 1100, False),       # ... in two segments
     (2, 8, 2, 8, 64, 1100, False),       # two segments of a row
 ])
 def test_fixed_workgroups_per_row(ref, B, Hq, Hkv, N, G, C, heavy):
@@ -129,7 +135,7 @@ def test_fixed_workgroups_per_row(ref, B, Hq, Hkv, N, G, C, heavy):
     ed, scale = P._dev(expert), 128 ** -0.5
     ws = torch.full((mq.decode_workspace_bytes(cfg, C),), 0xFF, dtype=torch.uint8, device="cuda")
     mq.decode_plan(cfg, ed, C, ws)
-    for rows, planned in ((1, True), (N - 1, True), (0, True), (N // 2, False)):
+    for rows, planned in ((1, True), (N - 1, True), (0, True), (N // 2, False)):   # a planned call leaves the counters as it found them
         q = rng.standard_normal((B, Hq, 128), dtype=np.float32).astype(np.float16)
         Kt = np.full((B, Hkv, N, 128), np.nan, np.float16); Vt = Kt.copy()
         Kt[:, :, :rows] = K[:, :, C * N:C * N + rows]; Vt[:, :, :rows] = V[:, :, C * N:C * N + rows]

@@ -107,14 +107,18 @@ def test_route_strided_and_ties(mq, ref):
     assert (expert.cpu().numpy() == 0).all() and (votes.cpu().numpy()[..., 0] == N).all()
 
 
-@pytest.mark.parametrize("M,N,C", [(2, 64, 80), (3, 32, 300), (4, 128, 70), (4, 8, 700), (5, 64, 90), (8, 96, 60), (8, 256, 40)])
+def _persistent_chunks(M, N, chunks):
+    """More long chunks than the kernel for few of them takes (a wavefront per 64 tokens): the persistent one."""
+    return N <= 64 or chunks > (4 if N <= 128 or M <= 2 else 3) * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("M,N,C", [(2, 64, 80), (3, 32, 300), (4, 128, 70), (4, 160, 50), (4, 8, 700), (5, 64, 90), (8, 96, 66), (8, 256, 50),
+                                   (4, 96, 9), (8, 256, 5)])            # the last two: few chunks
 @pytest.mark.parametrize("kind", ["near", "tied", "small", "large", "zero_rows"])
 def test_route_close_decisions(mq, ref, kind, M, N, C):
-    """Logits that differ by a few ulps, or not at all, in some or all tokens: decisions and votes still equal the sums in order.
-    More chunks than the two per compute unit of the kernel for few chunks, whose sums are in order anyway."""
+    """Logits that differ by a few ulps, or not at all, in some or all tokens: decisions and votes still equal the sums in order."""
     B, Hkv = 2, 8
-    if C * B * Hkv <= 512:
-        C = 600 // (B * Hkv)
+    assert _persistent_chunks(M, N, C * B * Hkv) == (N <= 64 or C >= 50)
     rng = np.random.default_rng(M * N + len(kind))
     cfg, rcfg = _cfgs(mq, ref, B, Hkv, Hkv, N, 64, ([16, 2, 4, 8, 2, 4, 8, 16])[:M], 0)
     K, _ = _rand_kv(rng, B, Hkv, C * N)
@@ -140,6 +144,35 @@ def test_route_close_decisions(mq, ref, kind, M, N, C):
     torch.cuda.synchronize()
     assert np.array_equal(votes.cpu().numpy(), v_ref)
     assert np.array_equal(expert.cpu().numpy(), e_ref)
+
+
+@pytest.mark.parametrize("M,N,C", [(1, 64, 20), (2, 64, 160), (4, 32, 300), (4, 128, 9), (5, 64, 90), (8, 96, 66)])
+@pytest.mark.parametrize("kind", ["keys", "weights", "w3", "bias"])
+def test_route_infinities_and_nan(mq, ref, kind, M, N, C):
+    """A NaN logit is never the larger one, on either path; infinities and NaN in keys and weights reach the logits."""
+    B, Hkv = 2, 8
+    rng = np.random.default_rng(M * N + len(kind))
+    cfg, rcfg = _cfgs(mq, ref, B, Hkv, Hkv, N, 64, ([16, 2, 4, 8, 2, 4, 8, 16])[:M], 0)
+    K, _ = _rand_kv(rng, B, Hkv, C * N)
+    W = [(rng.standard_normal(s) * 0.2).astype(np.float16) for s in ((128, M), (128, M), (M, M))]
+    bias = (rng.standard_normal(M) * 0.05).astype(np.float32)
+    for value in (np.nan, np.inf, -np.inf):
+        k, w, b = K.copy(), [x.copy() for x in W], bias.copy()
+        if kind == "keys":
+            k.reshape(-1)[rng.integers(0, k.size, k.size // 400)] = value
+        elif kind == "weights":
+            w[1][77, M - 1] = value
+        elif kind == "w3":
+            w[2][0, M // 2] = value
+        else:
+            b[M // 2] = value
+        with np.errstate(all="ignore"):
+            e_ref, v_ref = ref.route_chunks(rcfg, k, 0, C, *w, b)
+        expert = torch.full((B * Hkv, C), 255, dtype=torch.uint8, device="cuda")
+        votes = torch.full((B * Hkv, C, M), -1, dtype=torch.int32, device="cuda")
+        mq.route_chunks(cfg, _dev(k), 0, C, *[_dev(x) for x in w], _dev(b), expert, votes)
+        torch.cuda.synchronize()
+        assert np.array_equal(votes.cpu().numpy(), v_ref) and np.array_equal(expert.cpu().numpy(), e_ref), value
 
 
 def _twin_router(rng, M, share, K):
@@ -447,14 +480,17 @@ def test_attention_single_bit_width(mq, ref, bits, N, G, rep):
 
 
 @pytest.mark.parametrize("heavy,B,Hkv,rep,N,C,T", [
-    (3, 1, 8, 1, 128, 160, 40),      # one row of 16-bit chunks among 2-bit rows: that row takes most workgroups
+    (3, 1, 8, 1, 128, 160, 40),      # one row of 16-bit chunks among 2-bit rows: the rows have the same number of workgroups all the same
     (0, 2, 4, 1, 64, 300, 0),
     (-1, 1, 8, 1, 128, 160, 0),      # the reverse: one 2-bit row among 16-bit rows
     (5, 1, 8, 4, 256, 60, 100),      # grouped queries
-    (2, 1, 40, 1, 128, 48, 7),       # more rows than some workgroup counts divide evenly
+    (2, 1, 40, 1, 128, 48, 7),       # the workgroups add up the rows' costs and find them too uneven: intervals
+    (3, 75, 4, 1, 128, 8, 7),        # more rows than compute units, on intervals: the heavy row takes most workgroups
+    (-1, 75, 4, 2, 128, 8, 0),
+    (5, 1, 40, 1, 16, 410, 3),       # intervals, short chunks: 240 workgroups would leave compute units idle
 ])
 def test_attention_rows_of_unequal_cost(mq, ref, heavy, B, Hkv, rep, N, C, T):
-    # the workgroups split the rows by their cost (bytes to read): rows whose mixes differ as much as they can
+    """Rows whose mixes of bit-widths differ as much as they can, on even shares and on intervals of equal cost."""
     bits = (2, 4, 8, 16)
     BH = B * Hkv
     expert = np.zeros((BH, C), np.uint8)                          # 2 bits everywhere ...

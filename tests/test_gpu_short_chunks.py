@@ -111,10 +111,11 @@ def test_units_of_several_chunks_on_a_plan(mq, ref, B, Hkv, N, G, C, mix, kpc):
 
 @pytest.mark.parametrize("Hkv,N,C,M,freeze", [
     (2, 128, 3, 4, 1), (1, 96, 5, 3, 0), (3, 224, 2, 8, 0), (2, 256, 1, 2, 0),   # a wavefront per 64 tokens of a chunk
-    (65, 96, 8, 4, 1), (40, 160, 13, 5, 0),                                     # 520 chunks: a wavefront per chunk
+    (130, 96, 8, 4, 1), (64, 160, 13, 5, 0), (100, 224, 8, 8, 0),               # more than four (three) per compute unit: a wavefront per chunk
     (40, 128, 60, 1, 0), (40, 128, 60, 2, 55),                                  # one expert; two, and few chunks that are not frozen
 ])
 def test_route_few_and_many_long_chunks(mq, ref, Hkv, N, C, M, freeze):
+    assert T._persistent_chunks(M, N, Hkv * C) == (Hkv >= 40)
     rng = np.random.default_rng(N + C)
     cfg, rcfg = T._cfgs(mq, ref, 1, Hkv, Hkv, N, 32, (16, 2, 4, 8, 2, 4, 8, 16)[:M], freeze)
     K, _ = T._rand_kv(rng, 1, Hkv, C * N)
