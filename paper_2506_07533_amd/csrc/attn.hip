@@ -1395,15 +1395,19 @@ __device__ __forceinline__ bool weigh_rows(const AttnArgs &a, int tid, int lane,
 
 // RAGGED: the sequences of the batch have their own numbers of chunks and residual rows (a.seq_chunks,
 // a.seq_tail, device arrays indexed by sequence); a.n_chunks is then the bound that sizes the segments.
-// MODE: how the rows are split, a kernel each.  In one kernel every call held the registers of all three (four heads: 39 spilled;
-// on intervals 30, on fixed rows, which need no loop over rows, 2) and looked at its rows later: intervals, 2 x 32 ragged rows of up
-// to 1152 tokens 24.4 -> 23.7 us, 40 heads of 128k tokens 114.7 -> 113.8, four sequences of 128k tokens on 8 heads x 4 queries 113.5 ->
-// 111.6; fixed rows, 8 heads x 2k tokens 14.7 -> 12.8.
+// MODE: how the rows are split, a kernel each: intervals; fixed rows; fixed rows if the costs allow it, added up here or (Planned) in the
+// workspace.  In one kernel every call held the registers of all of them (four heads: 39 spilled; intervals alone 30, fixed rows
+// alone, which need no loop over rows, 2) and looked at its rows later: intervals, 2 x 32 ragged rows of up to 1152 tokens 24.4 ->
+// 23.7 us, 40 heads of 128k tokens 114.7 -> 113.8, four sequences of 128k tokens on 8 heads x 4 queries 113.5 -> 111.6; fixed rows,
+// 8 heads x 2k tokens 14.7 -> 12.8; weighed ones, 256 rows of 8k tokens in 32-token chunks 56.7 -> 56.3.  Grouped queries weigh in one
+// kernel, and test a.weigh there although it is never 0: with a kernel for each way, or without the test, four heads spill 55
+// registers and not 39 (four new tokens on 32 heads x 32k 48.1 us against 48.9).
 // SMALL: chunks of 8, 16 or 32 tokens, see Gather (one query head per KV head) and load_v (grouped queries).  KPC: keys quantised per channel (REP == 1 only), see pc_scores.
-constexpr int kIntervals = 0, kRows = 1, kRowsWeighed = 2;
+constexpr int kIntervals = 0, kRows = 1, kRowsWeighed = 2, kRowsPlanned = 3;
 template <int G, int REP, int NWV, bool RAGGED, int MODE, bool SMALL, bool KPC>
 __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
     constexpr bool ROWS = MODE != kIntervals, WEIGH = MODE == kRowsWeighed;
+    static_assert(REP == 1 || MODE != kRowsPlanned, "grouped queries: kRowsWeighed, told apart by a.weigh_ws");
     static_assert(!RAGGED || !ROWS, "rows of different lengths: intervals");
     static_assert(!KPC || REP == 1, "per-channel keys: one query head per KV head");
     __shared__ AttnLds<G, REP, NWV> L;
@@ -1443,8 +1447,8 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             if (k < KPT && c < min(C, seg_chunks)) { e_first[k] = erow[c]; o_first[k] = orow[c]; }
         }
     };
-    const bool weigh = WEIGH && !a.weigh_ws;             // the costs are added up here, see weigh_rows
-    const bool by_counter = !ROWS || (WEIGH && a.weigh_ws);         // the workgroups of a row draw its tickets from a counter
+    const bool weigh = WEIGH && (REP == 1 || (a.weigh != 0 && !a.weigh_ws));    // the costs are added up here, see weigh_rows
+    const bool by_counter = MODE == kIntervals || MODE == kRowsPlanned || (REP > 1 && WEIGH && a.weigh_ws);   // the workgroups of a row draw its tickets from a counter
     uint4 piece[kWeighPieces];
     if (weigh) {
         load_decisions<NT>(a, tid, piece);
@@ -1512,7 +1516,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
         const uint32_t P = fixed ? (uint32_t)RW : (uint32_t)(axis.owner(ue - 1u) - wg_first + 1);
         const uint32_t ov = min(hi, ue) - max(lo, ub);
         const bool whole = (lo >= ub && hi <= ue) || (ub >= lo && ue <= hi);   // the interval inside the row, or the row inside it
-        if ((!ROWS || WEIGH) && w == wg_first && tid == 0) row_wgs[u] = fixed && RW == 1 ? kRowDone : P;
+        if (MODE != kRows && (REP == 1 || !ROWS || a.weigh) && w == wg_first && tid == 0) row_wgs[u] = fixed && RW == 1 ? kRowDone : P;
 
         // ---- (a) row set-up.  One round trip to memory for everything the first units need: the raw
         //      queries, the chunk descriptors of the first segment and the first batch of tickets.  The
@@ -2033,7 +2037,12 @@ static void launch_split(const AttnArgs &a, dim3 grid, dim3 block, hipStream_t s
     if (a.seq_chunks)         hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, true, kIntervals, SMALL, KPC>), grid, block, 0, s, a);
     else if (a.row_wgs == 0)  hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kIntervals, SMALL, KPC>), grid, block, 0, s, a);
     else if (a.weigh == 0)    hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kRows, SMALL, KPC>), grid, block, 0, s, a);
-    else                      hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kRowsWeighed, SMALL, KPC>), grid, block, 0, s, a);
+    else {
+        if constexpr (REP == 1) {
+            if (a.weigh_ws) { hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kRowsPlanned, SMALL, KPC>), grid, block, 0, s, a); return; }
+        }
+        hipLaunchKernelGGL((attn_split_kernel<G, REP, NWV, false, kRowsWeighed, SMALL, KPC>), grid, block, 0, s, a);
+    }
 }
 template <int G, int REP, bool KPC>
 static void launch_split(const AttnArgs &a, dim3 grid, dim3 block, hipStream_t s) {
