@@ -121,7 +121,7 @@ int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false
 //   part <= 128: every workgroup takes an even share of its row's tickets: no costs, no counters, no kernel that prepares them,
 //   and with one workgroup per row, which then writes the output itself, no merge.  Rows whose mixes of bit-widths differ end at
 //   different times, but the worst of them (all at 16 bits) has eight units per wavefront.  Up to three rounds of workgroups of
-//   one row each (600 tokens: 640 rows 49.5 -> 42.4 us, 1600 rows 89 -> 94).
+//   one row each (600 tokens: 640 rows 47.4 -> 35.5 us; 1600 rows stay on intervals: 89 -> 94 when both were one kernel).
 //   part <= 640, tables of at most 16 KiB: the same, if no row costs much more than the mean.  Every workgroup adds up all costs
 //   while its row's descriptors are on their way (1 us); else intervals, whose parts of a row are static too.  Up to 540 only where
 //   more than one compute unit in 64 would get nothing to do (240 workgroups on 24 or 40 rows: part = 520 37.4 us and 38.3 on
@@ -130,9 +130,11 @@ int choose_wgs(const moqae_cfg *c, int n_chunks, int n_tail, bool ragged = false
 //   ends of uneven rows cost what the second set-ups do (128k tokens x 32 rows 122.5 and 122.8 us).
 // "Much more": a second set-up is worth about 10 us, in which a wavefront does 220 tokens (50 where sixteen (query head, group)
 // pairs fill the tile); where a counter evens out what a row's workgroups do, that is shared by the row's P workgroups, down to
-// a quarter (16 rows of 84k tokens under four queries, groups of 32, P = 16: 188 us on intervals, 197 on fixed rows 6 % apart).
-// 8 heads x 2k tokens 23.0 -> 16.6 us a step (on the GPU), 16 x 500 19.8 -> 13.6, 120 x 200 21.6 -> 13.5, 40 x 389 under four queries each
-// 32.1 -> 23.5, 32 x 32k under four queries 58 -> 50, 256 x 8k in 32-token chunks 69 -> 58.
+// a quarter (16 rows of 84k tokens under four queries, groups of 32, P = 16: 188 us on intervals, 197 on fixed rows 6 % apart, in one
+// kernel; 154 on intervals now).
+// Calls against intervals: 8 heads x 2k tokens 20.7 -> 13.0 us, 16 x 500 19.3 -> 11.6, 120 x 200 20.8 -> 11.7, 40 x 389 under four queries
+// each 33.8 -> 13.4, 32 x 32k under four queries 59 -> 48, 256 x 8k in 32-token chunks 68 -> 56; rows of 2-bit chunks but for one, every
+// eighth or half of them at 16 bits, part <= 128: 16.1 to 36.9 -> 14.7 to 34.2 over nine shapes.
 constexpr int kSplitEven = 128, kSplitWeighed = 640, kSplitIdle = 540, kSplitPlanned = 1400, kSplitSetup = 220, kSplitRounds = 3;
 bool rows_split(const moqae_cfg *c, AttnArgs &a) {
     const int64_t rows = a.BH, tokens = ((int64_t)a.n_chunks + 1) * c->chunk, cus = cu_count();

@@ -325,7 +325,7 @@ __device__ __forceinline__ void row_fold(float (&v)[P], int lane) {
 // 16 rows: lane l holds dims 8*(l%16)..+7 of row 4*j + l/16, for K and for V alike.  One head: every lane of
 // a row ends up with the row's score, so the weights p1 need no trip through LDS and wait in registers for the value phase.
 // Several heads: one score per lane (see row_fold), the weights wait in LDS.  Registers decide here (four heads: 85 spilled before,
-// 39 now; with the same scores but all weights read back at once 90, reloads in the unit loop and 131 us): four sequences of 128k
+// 39 with it; with the same scores but all weights read back at once 90, reloads in the unit loop and 131 us): four sequences of 128k
 // tokens, 8 KV heads x 4 queries 121.5 -> 113.5 us a call, four new tokens on 32 heads x 32k 52.1 -> 48.0.
 // Several queries per sequence (nq > 1; head r belongs to query r / rep_in): query t does not see the residual rows of
 // the queries after it, the last nq - 1 - t valid rows.

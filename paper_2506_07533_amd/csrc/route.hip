@@ -7,8 +7,8 @@
 // (certain_top), and from the sums in order, for the tokens they leave open, where they do not.  The rows come in whole lines, half a window
 // ahead, and reach the lanes of the matrix products through LDS.
 // What bounds it: HBM, and for small calls latency.  5.2 M rows in 128-token chunks 211 us a call (6.35 TB/s) against 241 with a
-// lane per token and the sums in order (whose 1024 multiply-adds alone took 170); 524 288 rows 23.5 us against 30, 131 072 rows 9.4 to
-// 11.9 against 10.0 to 12.6, 32 768 rows in 32-token chunks 6.7 against 7.5 (9.4 while open tokens sent their whole window through
+// lane per token and the sums in order (whose 1024 multiply-adds alone took 170); 524 288 rows 24.3 us against 29.6, 131 072 rows 9.3 to
+// 10.3 against 10.2 to 12.5, 32 768 rows in 32-token chunks 6.6 against 7.2 (9.4 while open tokens sent their whole window through
 // the sums in order).  Two workgroups of four wavefronts per compute unit: three and four (128 registers) 213 and 220 us; a whole
 // window ahead 211, and 25.3 and 10.8 us for 524 288 and 131 072 rows; rows requested in the operands' own shape, four 16-byte
 // pieces of a row per load, 228.
@@ -181,8 +181,8 @@ __global__ __launch_bounds__(kRouteWaves * 64, kRouteWgPerCu) void route_kernel(
 // whole window requested at once, the votes added up in LDS.  A wavefront that takes a chunk's windows one after the other has
 // nobody to hide its latency.  From three to four workgroups per compute unit on, the other chunks' wavefronts hide it.  Up to two
 // experts: sums in order, see DIRECT.
-// 64 to 256 chunks of 128 tokens 4.6 to 4.9 us (a token per lane, sums in order: 7.1 to 7.4), 32 to 128 chunks of 256 tokens 5.4 to
-// 6.9 (7.5), 512 of them 10.2 (11.1).
+// 64 to 256 chunks of 128 tokens 4.7 to 4.9 us (a token per lane, sums in order: 7.1 to 7.2), 32 to 128 chunks of 256 tokens 5.4 to
+// 7.0 (7.5 to 7.7), 512 of them 10.4 (10.8).
 template <int M>
 __global__ __launch_bounds__(kRouteWaves * 64) void route_split_kernel(RouteArgs a) {
     constexpr bool kMatrix = M > 2;
