@@ -179,8 +179,12 @@ _cfgs: dict = {}                                          # by value: a Cfg may 
 
 def _cref(cfg: Cfg):
     """Reference to the C structure of the configuration's present values."""
-    key = (cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.chunk, cfg.group, tuple(cfg.expert_bits), cfg.freeze_chunks,
-           cfg.k_per_channel)
+    b, q, h, d, n, g, f, k = (cfg.batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.chunk, cfg.group, cfg.freeze_chunks,
+                              cfg.k_per_channel)
+    bits = tuple(cfg.expert_bits)
+    if type(b + q + h + d + n + g + f + k + sum(bits)) is not int:   # 8.0 == 8 would find the structure of 8: accepted or refused by ctypes
+        return C.byref(cfg.c())
+    key = (b, q, h, d, n, g, f, k, bits)
     ref = _cfgs.get(key)
     if ref is None:
         if len(_cfgs) >= 256:

@@ -30,6 +30,22 @@ def test_every_declared_symbol_is_exported(mq):
     assert "arena" in mq.strerror(mq.E_ARENA) and mq.strerror(0) == "ok"
 
 
+def test_configuration_types(mq):
+    """What the C structure refuses stays refused after an equal configuration was used, what it takes is taken."""
+    import numpy as np
+    want = mq.decode_workspace_bytes(mq.Cfg(2, 8, 8), 4)
+    for bad in (mq.Cfg(2.0, 8, 8), mq.Cfg(2, 8, 8, chunk=128.0), mq.Cfg(2, 8, 8, expert_bits=(2, 4, 8, 16.0)), mq.Cfg(np.float64(2), 8, 8),
+                mq.Cfg("2", 8, 8)):
+        with pytest.raises(TypeError):
+            mq.decode_workspace_bytes(bad, 4)
+    for good in (mq.Cfg(np.int64(2), 8, 8), mq.Cfg(np.array(2), 8, 8), mq.Cfg(2, 8, 8, expert_bits=np.array([2, 4, 8, 16])),
+                 mq.Cfg(2, 8, 8, expert_bits=[2, 4, 8, 16])):
+        assert mq.decode_workspace_bytes(good, 4) == want
+    cfg = mq.Cfg(2, 8, 8)
+    cfg.batch = 3                                          # changed between calls
+    assert mq.decode_workspace_bytes(cfg, 4) == mq.decode_workspace_bytes(mq.Cfg(3, 8, 8), 4) != want
+
+
 def test_block_sizes_closed_form(mq):
     cfg = mq.Cfg(1, 40, 40, 128, 128, 64, (2, 4, 8, 16), 1)
     assert [mq.chunk_block_bytes(cfg, b) for b in (2, 4, 8, 16)] == [10240, 18432, 34816, 65536]
