@@ -140,7 +140,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // Tokens the V code area of a chunk has room for: N, but at least one slice of the V layout (max(32/b, 8) tokens):
 // 8 tokens at 2 bits take a slice of 16 whose upper half holds zero codes.
 __host__ __device__ inline int v_token_room(int N, int b) {
-    const int TQ = 32 / b > 8 ? 32 / b : 8;
+    const int TQ = b == 2 ? 16 : 8;
     return N < TQ ? TQ : N;
 }
 // Bytes of one chunk block (K and V) at bit-width b.

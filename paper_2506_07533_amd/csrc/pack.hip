@@ -5,12 +5,16 @@
 //   plan_small_kernel / plan_rows_kernel / plan_kernel  block sizes -> exclusive scan in (b, h, c) order -> offsets and
 //                capacity check: one thread per chunk up to 1024 chunks, then one workgroup per row when the table allows,
 //                else one workgroup.
-//   pack_kernel  one workgroup per (K or V, chunk, row), one lane per (token row, group): the lane loads its
-//                G dims, takes minimum and maximum with packed fp16 operations, computes scale and
-//                reciprocal once and then four operations per code (no cross-lane step anywhere).
-//                K words are assembled in registers (row-major layout); V codes go through LDS as
-//                bytes and are gathered token-wise into the dimension-major tile layout.
-//                HBM-bound: reads 2*N*D*2 bytes, writes the block.
+//   pack_kernel  two wavefronts per (K or V, 64 tokens, row), 32 rows each; chunks of 32 tokens and less: one (pack_wave_kernel).
+//                The rows go from memory to LDS in whole lines, past the registers; then one lane per line of 64 dims takes
+//                minimum and maximum with packed fp16 operations, computes scale and reciprocal once per group and then four
+//                operations per code (no cross-lane step anywhere).  K words are assembled in registers (row-major layout);
+//                V codes go through LDS as bytes and are gathered token-wise into the dimension-major tile layout.  Every
+//                store of codes covers whole lines.
+//                HBM-bound: reads 2*N*D*2 bytes, writes the block.  40 heads of 128k tokens (2.68 GB read, 0.68 GB written)
+//                573 us, 5.87 TB/s, where a kernel that only moves such bytes reaches 5.8 to 6.1 with streaming loads and 5.4
+//                to 5.8 with ordinary ones; a lane that loads its own line into registers, eight ordinary loads of 16 bytes: 605 to
+//                613, and, where 8-bit codes leave in pieces of lines, 1016 against 731 for 8 bits alone.
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
 #include "pack_dev.hpp"
@@ -245,56 +249,305 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rows_kernel(PackArgs a) {
     }
 }
 
-template <int G, bool KPC>
-__global__ __launch_bounds__(kPackThreads) void pack_kernel(PackArgs a) {
-    extern __shared__ uint8_t vcodes[];               // [N][kVRow] code bytes (V only); odd dword stride: rows fall on different banks
-    if (*a.status != 0) return;
+// ---- the pack kernels: 32 rows of K or V to a wavefront ----
+// A row is two lines of 128 bytes, a lane owns a line: 64 dims, one group of 64 or two of 32.  A wavefront's lines go straight
+// to its region of LDS (16 bytes per lane and load, no register holds them on their way), eight whole lines per load
+// instruction: piece p of line l in slot 8 l + (p ^ l % 8), so that a lane that reads its line piece by piece shares no bank
+// with the seven lanes beside it.
+constexpr int kLine = 128, kRegionRows = 32, kRegion = kRegionRows * 2 * kLine;
+__device__ __forceinline__ void lines_request(const uint16_t *rows, int64_t stride_s, int n_rows, bool stream, uint8_t *region, int lane) {
+    typedef const __attribute__((address_space(1))) uint32_t *global_p;
+    typedef __attribute__((address_space(3))) uint32_t *lds_p;
+    const uint16_t *p = rows + (int64_t)(lane >> 4) * stride_s + ((lane >> 3) & 1) * 64 + ((lane & 7) ^ (lane >> 3)) * 8;
+    if (stream) {
+#pragma unroll
+        for (int j = 0; j < kRegionRows / 4; j++)         // four rows a load; the last argument 2: streaming
+            if (4 * j < n_rows) __builtin_amdgcn_global_load_lds((global_p)(p + (int64_t)(4 * j) * stride_s), (lds_p)(region + j * 1024), 16, 0, 2);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kRegionRows / 4; j++)
+            if (4 * j < n_rows) __builtin_amdgcn_global_load_lds((global_p)(p + (int64_t)(4 * j) * stride_s), (lds_p)(region + j * 1024), 16, 0, 0);
+    }
+}
+__device__ __forceinline__ void lines_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void line_read(const uint8_t *region, int lane, int n_lines, uint32_t (&w)[32]) {
+    const uint4 *buf = reinterpret_cast<const uint4 *>(region) + min(lane, n_lines - 1) * 8;
+#pragma unroll
+    for (int p = 0; p < 8; p++) { const uint4 t = buf[p ^ (lane & 7)]; w[4 * p] = t.x; w[4 * p + 1] = t.y; w[4 * p + 2] = t.z; w[4 * p + 3] = t.w; }
+}
 
-    const int isV = (int)blockIdx.x;                  // K and V of a chunk side by side in launch order: the lighter K
-    const int c = a.chunk_begin + (int)blockIdx.y;    // workgroups and the V workgroups (LDS phase) share the CUs at all times
-    const int u = (int)blockIdx.z;
-    const int tid = (int)threadIdx.x;
+// A lane's line at BITS bits: meta words to meta_w, V codes to the staging rows in the region (over the lines, which are in
+// registers by now), K codes to kw.
+template <int G, int BITS, bool isV>
+__device__ __forceinline__ void pack_line(const uint32_t (&w)[32], int lane, uint32_t *meta_w, uint8_t *region, uint32_t (&kw)[2 * BITS]) {
+    constexpr int NI = 64 / G;                            // groups of a line
+    uint32_t mw[NI];
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+        pack_item_regs<G, BITS, true, true>(&w[i * (G / 2)], isV, &mw[i], &kw[i * (2 * BITS / NI)],
+                                            reinterpret_cast<uint32_t *>(region + (lane >> 1) * kVRow + (lane & 1) * 64 + i * G));
+    if constexpr (NI == 1) nt_store(meta_w, mw[0]);
+    else                   nt_store(reinterpret_cast<uint2 *>(meta_w), uint2{mw[0], mw[NI - 1]});
+}
+// The K codes of the wavefront's lines, consecutive bytes at dst: a lane's own 16, 32 or 64 of them go through LDS, from where they
+// leave 1 KiB per store.  Stored by their lanes in 16-byte pieces 64 bytes apart, 8-bit K codes took an all-8-bit call of 5.2 M rows
+// from 750 to 1016 us.  Piece q of lane l in slot PPL l + (q ^ l / (8 / PPL) % PPL): both ways every bank once.
+template <int BITS>
+__device__ __forceinline__ int k_slot(int l, int q) {
+    constexpr int PPL = BITS / 2;
+    return l * PPL + (q ^ ((l / (8 / PPL)) & (PPL - 1)));
+}
+template <int BITS>
+__device__ __forceinline__ void k_stage(const uint32_t (&kw)[2 * BITS], int lane, uint8_t *region) {
+#pragma unroll
+    for (int q = 0; q < BITS / 2; q++) reinterpret_cast<uint4 *>(region)[k_slot<BITS>(lane, q)] = uint4{kw[4 * q], kw[4 * q + 1], kw[4 * q + 2], kw[4 * q + 3]};
+}
+template <int G, int BITS>
+__device__ __forceinline__ void pack_k_lines(const uint32_t (&w)[32], int lane, uint32_t *codes_w, uint32_t *meta_w, uint8_t *region) {
+    uint32_t kw[2 * BITS];
+    pack_line<G, BITS, false>(w, lane, meta_w + lane * (64 / G), region, kw);
+    uint4 *dst = reinterpret_cast<uint4 *>(codes_w) + lane;
+    if constexpr (BITS == 2) nt_store(dst, uint4{kw[0], kw[1], kw[2], kw[3]});
+    else {
+        k_stage<BITS>(kw, lane, region);
+        wave_lds_sync();
+        constexpr int PPL = BITS / 2;
+#pragma unroll
+        for (int k = 0; k < PPL; k++) nt_store(dst + 64 * k, reinterpret_cast<const uint4 *>(region)[k_slot<BITS>((64 * k + lane) / PPL, lane & (PPL - 1))]);
+    }
+}
+template <int G, int BITS>
+__device__ __forceinline__ void pack_v_lines(const uint32_t (&w)[32], int lane, uint32_t *meta_w, uint8_t *region) {
+    uint32_t unused[2 * BITS];
+    pack_line<G, BITS, true>(w, lane, meta_w + lane * (64 / G), region, unused);
+}
+
+// Keys quantised per channel: the wavefront's 32 rows, a group of 32 tokens or half of one of 64 (whose other half is the other
+// wavefront's); codes_w and meta_w: those of the part's first row and group.  The lines come through LDS as the others do and the
+// codes leave in whole lines: 40 heads of 64k tokens, groups of 64, routed and packed 381 us; a wavefront per group, its rows' words
+// loaded into 64 registers and every code word stored by its lane, 420.
+template <int G, int BITS>
+__device__ __forceinline__ void pack_k_columns(int lane, int wave, uint8_t *region, uint8_t *lds, uint32_t *codes_w, uint32_t *meta_w) {
+    uint32_t w[kRegionRows], mnp, mxp, metaw[2];
+    float nmn[2], inv[2];
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(region);
+#pragma unroll
+    for (int r = 0; r < kRegionRows; r++) {               // word l of row r: piece l % 32 / 4 of line 2r + l / 32
+        const int line = 2 * r + (lane >> 5);
+        w[r] = words[(line * 8 + (((lane >> 2) & 7) ^ (line & 7))) * 4 + (lane & 3)];
+    }
+    column_range<kRegionRows>(w, mnp, mxp);
+    if constexpr (G == 64) {
+        __syncthreads();                                  // the lines are in registers
+        uint2 *range = reinterpret_cast<uint2 *>(lds + kRegion / 2);     // behind the codes
+        range[wave * 64 + lane] = uint2{mnp, mxp};
+        __syncthreads();
+        const uint2 other = range[(wave ^ 1) * 64 + lane];
+        mnp = pk_min_f16(mnp, other.x); mxp = pk_max_f16(mxp, other.y);
+    }
+    column_scale<BITS>(mnp, mxp, nmn, inv, metaw);
+    if (G == 32 || wave == 0) nt_store(reinterpret_cast<uint2 *>(meta_w + (G == 32 ? wave * kD : 0) + 2 * lane), uint2{metaw[0], metaw[1]});
+    if constexpr (G == 32) wave_lds_sync();
+    column_codes<BITS, kRegionRows, true>(w, nmn, inv, reinterpret_cast<uint32_t *>(region), lane);
+    wave_lds_sync();
+    uint4 *dst = reinterpret_cast<uint4 *>(codes_w + wave * kRegionRows * (kD * BITS / 32)) + lane;
+#pragma unroll
+    for (int k = 0; k < BITS / 2; k++) nt_store(dst + 64 * k, reinterpret_cast<const uint4 *>(region)[64 * k + lane]);
+}
+
+// Rows [r0, r0 + 32 n_waves) of K or V of a chunk -> its block, by n_waves wavefronts (1: a chunk of 32 tokens; 2) whose regions
+// follow one another in `lds`; `wave` is this one's index.
+template <int G, bool KPC>
+__device__ __forceinline__ void pack_part(const PackArgs &a, int isV, int c, int u, int r0, int n_waves, int wave, int lane, uint8_t *lds) {
+    constexpr int NG = kD / G;
     const int N = a.N;
-    const int bits = a.bits_of[a.expert[(int64_t)u * a.expert_stride + c]];
+    uint8_t *region = lds + wave * kRegion;
+    const uint16_t *src = (isV ? a.V : a.K) + (int64_t)(u / a.Hkv) * a.stride_b + (int64_t)(u % a.Hkv) * a.stride_h + ((int64_t)c * N + r0) * a.stride_s;
+    // on their way before anything else is looked at
+    lines_request(src + (int64_t)(wave * kRegionRows) * a.stride_s, a.stride_s, kRegionRows, a.stream, region, lane);
+    const int status = *a.status;
+    const int bits = a.bits_of[a.expert[(int64_t)u * a.expert_stride + c] & 7];   // an expert out of range has set the status
     uint8_t *blk = a.arena + a.chunk_off[(int64_t)u * a.off_stride + c];
-    const int b = u / a.Hkv, h = u % a.Hkv;
-    const uint16_t *src = (isV ? a.V : a.K) + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h
-                        + (int64_t)c * N * a.stride_s;
+    lines_wait();                                         // also where the call is a no-op: LDS is not given back under a load
+    if (status != 0) return;
+    wave_lds_sync();
 
-    pack_side<G, KPC>(src, a.stride_s, N, bits, isV, blk, vcodes, tid, kPackThreads);
+    const int row0 = r0 + wave * kRegionRows;
+    if (bits == 16) {                                     // FP16 expert: rows copied verbatim
+        uint4 *dst = reinterpret_cast<uint4 *>(blk + (isV ? (size_t)N * kD * 2 : 0)) + row0 * 16 + lane;
+        const uint4 *buf = reinterpret_cast<const uint4 *>(region) + (lane ^ (lane >> 3));
+#pragma unroll
+        for (int j = 0; j < kRegionRows / 4; j++) nt_store(dst + 64 * j, buf[64 * j]);
+        return;
+    }
+    uint8_t *area = blk + (isV ? (size_t)N * kD * bits / 8 + (size_t)N * NG * 4 : 0);
+    uint32_t *codes_w = reinterpret_cast<uint32_t *>(area) + (size_t)r0 * (kD * bits / 32);
+    uint32_t *meta_w = reinterpret_cast<uint32_t *>(area + (size_t)N * kD * bits / 8) + r0 * NG;
+    if (KPC && !isV) {                                    // keys per channel: 32 rows of a group to a wavefront
+        if (bits == 2)      pack_k_columns<G, 2>(lane, wave, region, lds, codes_w, meta_w);
+        else if (bits == 4) pack_k_columns<G, 4>(lane, wave, region, lds, codes_w, meta_w);
+        else                pack_k_columns<G, 8>(lane, wave, region, lds, codes_w, meta_w);
+        return;
+    }
+    uint32_t w[32];
+    line_read(region, lane, 64, w);
+    wave_lds_sync();
+    meta_w += wave * kRegionRows * NG;
+    if (!isV) {
+        codes_w += wave * kRegionRows * (kD * bits / 32);
+        if (bits == 2)      pack_k_lines<G, 2>(w, lane, codes_w, meta_w, region);
+        else if (bits == 4) pack_k_lines<G, 4>(w, lane, codes_w, meta_w, region);
+        else                pack_k_lines<G, 8>(w, lane, codes_w, meta_w, region);
+        return;
+    }
+    if (bits == 2)      pack_v_lines<G, 2>(w, lane, meta_w, region);
+    else if (bits == 4) pack_v_lines<G, 4>(w, lane, meta_w, region);
+    else                pack_v_lines<G, 8>(w, lane, meta_w, region);
+    if (n_waves > 1) __syncthreads(); else wave_lds_sync();
+    const int rows = n_waves * kRegionRows;               // whole token blocks of the V layout
+    v_gather(rows, bits, rows, codes_w, lds, wave * 64 + lane, n_waves * 64, kRegion);
 }
 
-// Short chunks: one wavefront per (K or V, chunk, row), four of them in a workgroup.  A 32-token chunk has 64 or 128 (token
-// row, group) items per side, a fraction of pack_kernel's 256 threads.  2.1 M rows, groups of 64 (32) tokens, against
-// pack_kernel: 8 tokens 467 (384) us against 846 (767), 16 tokens 259 (249) against 455 (410), 32 tokens 251 (259) against
-// 280 (266).  At 64 tokens pack_kernel is the better one (245 against 253), except for keys per channel in groups of 64:
-// there K is ONE token group, a wavefront's work whatever the workgroup (255 against 302).
-static bool pack_by_wavefront(const PackArgs &a) { return a.N < 64 || (a.N == 64 && a.kpc && a.G == 64); }
-template <int G, bool KPC>
-__global__ __launch_bounds__(kPackThreads) void pack_wave_kernel(PackArgs a) {
-    extern __shared__ uint8_t vcodes[];               // [4][N][kVRow] code bytes (V only)
-    if (*a.status != 0) return;
-    const int lane = (int)threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int side = (int)blockIdx.x * (kPackThreads / 64) + wave;       // K and V of a chunk side by side
-    if (side >= 2 * a.n_chunks) return;
-    const int isV = side & 1, c = a.chunk_begin + (side >> 1), u = (int)blockIdx.y, N = a.N;
-    const int bits = a.bits_of[a.expert[(int64_t)u * a.expert_stride + c]];
-    uint8_t *blk = a.arena + a.chunk_off[(int64_t)u * a.off_stride + c];
-    const int b = u / a.Hkv, h = u % a.Hkv;
-    const uint16_t *src = (isV ? a.V : a.K) + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h
-                        + (int64_t)c * N * a.stride_s;
-    pack_side<G, KPC, true>(src, a.stride_s, N, bits, isV, blk, vcodes + wave * N * kVRow, lane, 64);
+// 32 / N chunks of 8 or 16 tokens, one after the other in memory: K or V of the chunks [c, c + n) by one wavefront, every lane at its
+// chunk's bit-width.  (A wavefront per chunk leaves half or three quarters of its lanes without a line.)  The codes of all widths are
+// made in one pass, as bytes.  1.3 M rows of the usual mix, routed and packed: 8 tokens 247 us (346 with a wavefront per chunk), 16
+// tokens 208 (222).
+template <int G>
+__device__ __forceinline__ void pack_chunks(const PackArgs &a, int isV, int c, int n, int u, int lane, uint8_t *region) {
+    constexpr int NG = kD / G;
+    const int N = a.N, lines = 2 * N, n_lines = n * lines;
+    const uint16_t *src = (isV ? a.V : a.K) + (int64_t)(u / a.Hkv) * a.stride_b + (int64_t)(u % a.Hkv) * a.stride_h + (int64_t)c * N * a.stride_s;
+    lines_request(src, a.stride_s, n * N, a.stream, region, lane);
+    const int mine = min(lane / lines, n - 1);            // the lane's chunk
+    const int status = *a.status;
+    const int e = a.expert[(int64_t)u * a.expert_stride + c + mine];
+    const unsigned long long off = a.chunk_off[(int64_t)u * a.off_stride + c + mine];
+    int bits = 16;
+#pragma unroll
+    for (int k = 0; k < 8; k++) bits = e == k ? a.bits_of[k] : bits;
+    if (lane >= n_lines) bits = 0;
+    lines_wait();
+    if (status != 0) return;
+    wave_lds_sync();
+    auto area_of = [&](uint8_t *blk, int b) { return blk + (isV ? (size_t)N * kD * b / 8 + (size_t)N * NG * 4 : 0); };
+    auto uniform = [&](int j, int &b, uint8_t *&blk) {    // of chunk j, on the scalar unit
+        b = __builtin_amdgcn_readlane(bits, j * lines);
+        blk = a.arena + (((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(off >> 32), j * lines) << 32)
+                         | (uint32_t)__builtin_amdgcn_readlane((int)off, j * lines));
+    };
+    for (int j = 0; j < n; j++) {                         // FP16 expert: rows copied verbatim
+        int b; uint8_t *blk;
+        uniform(j, b, blk);
+        if (b != 16) continue;
+        uint4 *dst = reinterpret_cast<uint4 *>(blk + (isV ? (size_t)N * kD * 2 : 0)) + lane;
+        const uint4 *buf = reinterpret_cast<const uint4 *>(region) + j * lines * 8 + (lane ^ (lane >> 3));
+        for (int i = 0; i < N / 4; i++) nt_store(dst + 64 * i, buf[64 * i]);
+    }
+    uint32_t w[32];
+    line_read(region, lane, n_lines, w);
+    wave_lds_sync();
+    // the codes as bytes, whatever the width
+    constexpr int NI = 64 / G;                            // groups of a line
+    uint32_t bytes[16], mw[NI];
+    const float qmax = (float)((1 << (bits & 15)) - 1);
+#pragma unroll
+    for (int i = 0; i < NI; i++) {
+        float nmn, inv;
+        mw[i] = group_scale<G>(&w[i * (G / 2)], qmax, nmn, inv);
+#pragma unroll
+        for (int k = 0; k < G / 4; k++) bytes[i * (G / 4) + k] = four_codes(&w[i * (G / 2)], 4 * k, nmn, inv);
+    }
+    uint8_t *own = area_of(a.arena + off, bits);
+    const int line = lane - mine * lines;                 // in its chunk
+    if (bits != 0 && bits != 16) {
+        uint32_t *meta_w = reinterpret_cast<uint32_t *>(own + (size_t)(isV ? v_token_room(N, bits) : N) * kD * bits / 8) + line * NI;
+        if constexpr (NI == 1) nt_store(meta_w, mw[0]);
+        else                   nt_store(reinterpret_cast<uint2 *>(meta_w), uint2{mw[0], mw[NI - 1]});
+    }
+    if (isV) {
+        if (lane < n_lines) {
+            uint32_t *row = reinterpret_cast<uint32_t *>(region + (lane >> 1) * kVRow + (lane & 1) * 64);
+#pragma unroll
+            for (int k = 0; k < 16; k++) row[k] = bytes[k];
+        }
+    } else {
+        // a code word from the bytes: the codes 2k and 2k + 1 share the shift bits * k
+        auto pair = [&](int k) { return __builtin_amdgcn_perm(0u, bytes[k >> 1], (k & 1) ? 0x0c030c02u : 0x0c010c00u); };
+        if (bits == 2) {
+            uint32_t kw[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                kw[i] = pair(8 * i);
+#pragma unroll
+                for (int k = 1; k < 8; k++) kw[i] |= pair(8 * i + k) << (2 * k);
+            }
+            nt_store(reinterpret_cast<uint4 *>(own) + line, uint4{kw[0], kw[1], kw[2], kw[3]});
+        } else if (bits == 4) {                           // lanes of different widths stage their codes in places that do not meet: 4 bits
+            uint32_t kw[8];                               // the first 2 KiB, 8 bits the upper half
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                kw[i] = pair(4 * i);
+#pragma unroll
+                for (int k = 1; k < 4; k++) kw[i] |= pair(4 * i + k) << (4 * k);
+            }
+            k_stage<4>(kw, lane, region);
+        } else if (bits == 8) {
+            uint32_t kw[16];
+#pragma unroll
+            for (int i = 0; i < 16; i++) kw[i] = pair(2 * i) | (pair(2 * i + 1) << 8);
+            k_stage<8>(kw, lane, region + kRegion / 2);
+        }
+    }
+    wave_lds_sync();
+    for (int j = 0; j < n; j++) {
+        int b; uint8_t *blk;
+        uniform(j, b, blk);
+        if (b == 16 || (!isV && b == 2)) continue;
+        uint8_t *area = area_of(blk, b);
+        if (isV) v_gather(N, b, v_token_room(N, b), reinterpret_cast<uint32_t *>(area), region + j * N * kVRow, lane, 64);
+        else {
+            uint4 *dst = reinterpret_cast<uint4 *>(area) + lane;
+            if (b == 4) { if (lane < lines * 2) nt_store(dst, reinterpret_cast<const uint4 *>(region)[k_slot<4>(j * lines + lane / 2, lane & 1)]); }
+            else for (int k = 0; k * 64 < lines * 4; k++)
+                nt_store(dst + 64 * k, reinterpret_cast<const uint4 *>(region + kRegion / 2)[k_slot<8>(j * lines + (64 * k + lane) / 4, lane & 3)]);
+        }
+    }
 }
 
-// The new end of the arena = the end of the last block in (b, h, c) order.  A kernel of its own, after
-// plan_rows_kernel: its workgroups read the counter at different times, so none of them may move
-// it, and the few registers this takes would cost the pack kernel occupancy.
-__global__ void arena_end_kernel(PackArgs a) {
+// The new end of the arena = the end of the last block in (b, h, c) order.  plan_rows_kernel cannot move the counter, its
+// workgroups read it at different times; nobody reads it here.
+__device__ __forceinline__ void move_arena_end(const PackArgs &a) {
     if (*a.status != 0) return;
     const int64_t lu = a.BH - 1, lc = a.chunk_begin + a.n_chunks - 1;
     const unsigned long long sz = (block_bytes(a.N, a.G, a.bits_of[a.expert[lu * a.expert_stride + lc]]) + 255u) & ~255ull;
     *a.arena_used = a.chunk_off[lu * a.off_stride + lc] + sz;
+}
+
+// Chunks of 64 tokens and more: a workgroup of two wavefronts per (K or V, 64 tokens, chunk, row).
+constexpr int kPartRows = 2 * kRegionRows;
+template <int G, bool KPC>
+__global__ __launch_bounds__(kPartRows * 2) void pack_kernel(PackArgs a) {
+    __shared__ uint4 lds[2 * kRegion / 16];
+    const int isV = (int)blockIdx.x & 1;              // K and V of a chunk side by side in launch order
+    const int c = a.chunk_begin + (int)blockIdx.y, u = (int)blockIdx.z, tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x + blockIdx.y + blockIdx.z == 0 && tid == 0) move_arena_end(a);
+    pack_part<G, KPC>(a, isV, c, u, ((int)blockIdx.x >> 1) * kPartRows, 2, wave, tid & 63, reinterpret_cast<uint8_t *>(lds));
+}
+
+// Short chunks: a wavefront per (K or V, 32 tokens, row), four of them in a workgroup.  SEVERAL: chunks of 8 and 16 tokens.
+template <int G, bool KPC, bool SEVERAL>
+__global__ __launch_bounds__(kPackThreads) void pack_wave_kernel(PackArgs a) {
+    __shared__ uint4 lds[kPackThreads / 64][kRegion / 16];
+    const int lane = (int)threadIdx.x & 63, u = (int)blockIdx.y;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int side = (int)blockIdx.x * (kPackThreads / 64) + wave, isV = side & 1;       // K and V side by side
+    const int per = SEVERAL ? kRegionRows / a.N : 1, c0 = (side >> 1) * per;
+    if (blockIdx.x + blockIdx.y == 0 && threadIdx.x == 0) move_arena_end(a);
+    if (c0 >= a.n_chunks) return;
+    uint8_t *region = reinterpret_cast<uint8_t *>(&lds[wave][0]);
+    if constexpr (!SEVERAL) pack_part<G, KPC>(a, isV, a.chunk_begin + c0, u, 0, 1, 0, lane, region);
+    else                    pack_chunks<G>(a, isV, a.chunk_begin + c0, min(per, a.n_chunks - c0), u, lane, region);
 }
 
 // The new token's K and V rows (fp16 [B*Hkv, D]) into row n_tail of the FP16 residual buffers ([B*Hkv, N, D]): one
@@ -313,8 +566,12 @@ hipError_t launch_append_tail(const void *k_new, const void *v_new, void *K_tail
     return hipGetLastError();
 }
 
-hipError_t launch_pack(const PackArgs &a, hipStream_t s) {
+hipError_t launch_pack(PackArgs a, hipStream_t s) {
     if (a.n_chunks <= 0 || a.BH <= 0) return hipSuccess;
+    // Streaming loads from 384 MiB of K and V on: 503 MB (40 heads x 24k tokens, 128-token chunks) routed and packed 157 us against 163,
+    // 1342 MB 391 against 406.  Below, ordinary loads keep what the last-level cache (256 MiB) holds of K from the routing, and
+    // of both from whoever wrote them: 336 MB 105 us against 113, 252 MB 80 against 86.
+    a.stream = (int64_t)a.BH * a.n_chunks * a.N * (2 * kD * 2) > (384ll << 20);
     const bool rows_ok = a.BH <= kPlanRowsMax &&
                          ((reinterpret_cast<uintptr_t>(a.expert + a.chunk_begin) | (uintptr_t)a.expert_stride) & 15u) == 0;
     const int64_t total = (int64_t)a.BH * a.n_chunks;
@@ -324,28 +581,27 @@ hipError_t launch_pack(const PackArgs &a, hipStream_t s) {
     else           hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    dim3 grid(2u, (unsigned)a.n_chunks, (unsigned)a.BH);
-    const size_t lds = (size_t)a.N * kVRow;
-    if (pack_by_wavefront(a)) {
-        constexpr int kSides = kPackThreads / 64;
-        const dim3 wgrid((unsigned)((2 * a.n_chunks + kSides - 1) / kSides), (unsigned)a.BH);
-        if (a.kpc) {
-            if (a.G == 32) hipLaunchKernelGGL((pack_wave_kernel<32, true>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
-            else           hipLaunchKernelGGL((pack_wave_kernel<64, true>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
+    if (a.N < 64) {
+        const int per = kRegionRows / a.N, sides = 2 * ((a.n_chunks + per - 1) / per), waves = kPackThreads / 64;
+        const dim3 grid((unsigned)((sides + waves - 1) / waves), (unsigned)a.BH), block(kPackThreads);
+        if (a.kpc)            hipLaunchKernelGGL((pack_wave_kernel<32, true, false>), grid, block, 0, s, a);   // groups of 64 tokens do not fit
+        else if (a.G == 32) {
+            if (per > 1)      hipLaunchKernelGGL((pack_wave_kernel<32, false, true>), grid, block, 0, s, a);
+            else              hipLaunchKernelGGL((pack_wave_kernel<32, false, false>), grid, block, 0, s, a);
         } else {
-            if (a.G == 32) hipLaunchKernelGGL((pack_wave_kernel<32, false>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
-            else           hipLaunchKernelGGL((pack_wave_kernel<64, false>), wgrid, dim3(kPackThreads), kSides * lds, s, a);
+            if (per > 1)      hipLaunchKernelGGL((pack_wave_kernel<64, false, true>), grid, block, 0, s, a);
+            else              hipLaunchKernelGGL((pack_wave_kernel<64, false, false>), grid, block, 0, s, a);
         }
-    } else if (a.kpc) {
-        if (a.G == 32) hipLaunchKernelGGL((pack_kernel<32, true>), grid, dim3(kPackThreads), lds, s, a);
-        else           hipLaunchKernelGGL((pack_kernel<64, true>), grid, dim3(kPackThreads), lds, s, a);
-    } else {
-        if (a.G == 32) hipLaunchKernelGGL((pack_kernel<32, false>), grid, dim3(kPackThreads), lds, s, a);
-        else           hipLaunchKernelGGL((pack_kernel<64, false>), grid, dim3(kPackThreads), lds, s, a);
+        return hipGetLastError();
     }
-    e = hipGetLastError();
-    if (e != hipSuccess || !rows) return e;
-    hipLaunchKernelGGL(arena_end_kernel, dim3(1), dim3(1), 0, s, a);
+    const dim3 grid((unsigned)(2 * a.N / kPartRows), (unsigned)a.n_chunks, (unsigned)a.BH), block(kPartRows * 2);
+    if (a.kpc) {
+        if (a.G == 32) hipLaunchKernelGGL((pack_kernel<32, true>), grid, block, 0, s, a);
+        else           hipLaunchKernelGGL((pack_kernel<64, true>), grid, block, 0, s, a);
+    } else {
+        if (a.G == 32) hipLaunchKernelGGL((pack_kernel<32, false>), grid, block, 0, s, a);
+        else           hipLaunchKernelGGL((pack_kernel<64, false>), grid, block, 0, s, a);
+    }
     return hipGetLastError();
 }
 

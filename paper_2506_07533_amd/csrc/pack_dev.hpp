@@ -57,18 +57,11 @@ __device__ __forceinline__ float add_hi_f16(uint32_t w, float c) {
 constexpr float kMagic = 12582912.0f;
 constexpr uint32_t kMagicBits = 0x4B400000u;
 
-// One (token row, group) item of a quantised chunk: G consecutive dims, all in one lane.  No lane ever
-// needs another lane's data: minimum and maximum come from packed fp16 operations on the words as
-// loaded, scale and reciprocal are computed once per group, and a code costs four operations: x - min
-// (with the conversion folded in), * 1/scale, + magic (the rounding), shift-and-add into its word.  The
-// words are sums of bits(t + magic) << shift, i.e. of the codes plus a constant that is taken off at
-// the end; no code is ever masked.  No clamp is needed: the scale is rounded up, so that
-// (x - min) * (1/scale) <= qmax * (1 + 2e-7) and rounds to at most qmax, and x >= min.
-// STAGED: meta_dst is a register of the caller and k_dst a staging row in LDS (plain stores), see pack_row.
-template <int G, int BITS, bool STAGED = false>
-__device__ __forceinline__ void pack_item_regs(const uint32_t *w, bool isV, uint32_t *__restrict__ meta_dst,
-                                               uint32_t *__restrict__ k_dst, uint32_t *__restrict__ v_lds) {
-    constexpr int NW = G / 2;                        // input words (fp16 pairs) of the item, w[0..NW)
+// Scale and zero-point of a group of G dims, all in one lane: w its fp16 pairs as loaded.  Minimum and maximum come from packed fp16
+// operations; returns the meta word, minus the minimum and 1 / scale.
+template <int G>
+__device__ __forceinline__ uint32_t group_scale(const uint32_t *w, float qmax, float &nmn, float &inv) {
+    constexpr int NW = G / 2;                        // input words (fp16 pairs), w[0..NW)
     static_assert(NW >= 16, "G >= 32");
     uint32_t mn4[4], mx4[4];                          // four independent chains, folded at the end
 #pragma unroll
@@ -81,28 +74,45 @@ __device__ __forceinline__ void pack_item_regs(const uint32_t *w, bool isV, uint
     float mx = fmaxf(half_bits_to_float(mxp & 0xffffu), half_bits_to_float(mxp >> 16));
     if (mn == 0.0f) mn = 0.0f;                        // -0 is stored as +0
     if (mx == 0.0f) mx = 0.0f;
-    constexpr float qmax = (float)((1 << BITS) - 1);
     const float R = __fsub_rn(mx, mn);
     const float s32 = __fdiv_rn(R, qmax);
     uint32_t s16 = float_to_half_bits(s32);
     if (half_bits_to_float(s16) < s32) s16 += 1;      // the scale is rounded up
     if (s16 == 0) s16 = 0x3C00u;                      // constant group: scale 1
-    const float inv = __fdiv_rn(1.0f, half_bits_to_float(s16));
-    if constexpr (STAGED) *meta_dst = s16 | (float_to_half_bits(mn) << 16);
-    else                  nt_store(meta_dst, s16 | (float_to_half_bits(mn) << 16));
-    const float nmn = -mn;
-    auto ubits = [&](int d) -> uint32_t {             // kMagicBits + code of dim d of the item
-        const float diff = (d & 1) ? add_hi_f16(w[d >> 1], nmn) : add_lo_f16(w[d >> 1], nmn);
-        return __builtin_bit_cast(uint32_t, __fadd_rn(__fmul_rn(diff, inv), kMagic));
-    };
+    inv = __fdiv_rn(1.0f, half_bits_to_float(s16));
+    nmn = -mn;
+    return s16 | (float_to_half_bits(mn) << 16);
+}
+// kMagicBits + code of dim d of the group
+__device__ __forceinline__ uint32_t magic_code(const uint32_t *w, int d, float nmn, float inv) {
+    const float diff = (d & 1) ? add_hi_f16(w[d >> 1], nmn) : add_lo_f16(w[d >> 1], nmn);
+    return __builtin_bit_cast(uint32_t, __fadd_rn(__fmul_rn(diff, inv), kMagic));
+}
+// Four codes as the bytes of a word
+__device__ __forceinline__ uint32_t four_codes(const uint32_t *w, int d, float nmn, float inv) {
+    uint32_t acc = magic_code(w, d, nmn, inv);
+    acc += magic_code(w, d + 1, nmn, inv) << 8; acc += magic_code(w, d + 2, nmn, inv) << 16; acc += magic_code(w, d + 3, nmn, inv) << 24;
+    return acc - kMagicBits * 0x01010101u;
+}
+
+// One (token row, group) item of a quantised chunk: G consecutive dims, all in one lane.  No lane ever
+// needs another lane's data: minimum and maximum come from packed fp16 operations on the words as
+// loaded, scale and reciprocal are computed once per group, and a code costs four operations: x - min
+// (with the conversion folded in), * 1/scale, + magic (the rounding), shift-and-add into its word.  The
+// words are sums of bits(t + magic) << shift, i.e. of the codes plus a constant that is taken off at
+// the end; no code is ever masked.  No clamp is needed: the scale is rounded up, so that
+// (x - min) * (1/scale) <= qmax * (1 + 2e-7) and rounds to at most qmax, and x >= min.
+// STAGED: meta_dst is a register of the caller and k_dst a staging row in LDS (plain stores), see pack_row, or (REGS) registers too.
+template <int G, int BITS, bool STAGED = false, bool REGS = false>
+__device__ __forceinline__ void pack_item_regs(const uint32_t *w, bool isV, uint32_t *__restrict__ meta_dst,
+                                               uint32_t *__restrict__ k_dst, uint32_t *__restrict__ v_lds) {
+    float nmn, inv;
+    const uint32_t meta = group_scale<G>(w, (float)((1 << BITS) - 1), nmn, inv);
+    if constexpr (STAGED) *meta_dst = meta;
+    else                  nt_store(meta_dst, meta);
     if (isV) {                                        // one code per byte into the staging rows
-        constexpr uint32_t KC = kMagicBits * 0x01010101u;
 #pragma unroll
-        for (int k = 0; k < G / 4; k++) {
-            uint32_t acc = ubits(4 * k);
-            acc += ubits(4 * k + 1) << 8; acc += ubits(4 * k + 2) << 16; acc += ubits(4 * k + 3) << 24;
-            v_lds[k] = acc - KC;
-        }
+        for (int k = 0; k < G / 4; k++) v_lds[k] = four_codes(w, 4 * k, nmn, inv);
     } else {                                          // the words of the token-major K layout
         constexpr int CPW = 32 / BITS, WPL = G / CPW;
         uint32_t ksum = 0;
@@ -112,12 +122,15 @@ __device__ __forceinline__ void pack_item_regs(const uint32_t *w, bool isV, uint
         uint32_t out[WPL];
 #pragma unroll
         for (int k = 0; k < WPL; k++) {
-            uint32_t acc = ubits(k * CPW);
+            uint32_t acc = magic_code(w, k * CPW, nmn, inv);
 #pragma unroll
-            for (int e = 1; e < CPW; e++) acc += ubits(k * CPW + e) << code_shift(e, BITS);
+            for (int e = 1; e < CPW; e++) acc += magic_code(w, k * CPW + e, nmn, inv) << code_shift(e, BITS);
             out[k] = acc - KC;
         }
-        if constexpr (WPL >= 4) {
+        if constexpr (REGS) {
+#pragma unroll
+            for (int k = 0; k < WPL; k++) k_dst[k] = out[k];
+        } else if constexpr (WPL >= 4) {
 #pragma unroll
             for (int k = 0; k < WPL; k += 4) {
                 const uint4 o = uint4{out[k], out[k + 1], out[k + 2], out[k + 3]};
@@ -146,29 +159,23 @@ __device__ __forceinline__ void pack_item(const uint4 *__restrict__ p, bool isV,
     pack_item_regs<G, BITS>(w, isV, meta_dst, k_dst, v_lds);
 }
 
-// Keys quantised per channel: a group is G consecutive tokens of one dim.  One wavefront per token group, lane l owns
-// dims 2l, 2l+1 (one 32-bit column of fp16 pairs): it reads the G rows' words (a row is one coalesced 256-byte piece per
-// wavefront), takes the packed minimum / maximum over the tokens, computes scale and reciprocal of both dims as
-// pack_item does (the same binary32 operations, so the same bits), then per token its two codes, which the n/2
-// lanes of a code word OR together (DPP) before one of them stores the word at its token-major place.
-template <int G, int BITS>
-__device__ __forceinline__ void pack_k_channel_group(const uint16_t *src, int64_t stride_s, int tg, uint32_t *codes_w,
-                                                     uint32_t *meta_w, int lane) {
-    const uint32_t *col = reinterpret_cast<const uint32_t *>(src + (int64_t)tg * G * stride_s) + lane;
-    const int64_t rw = stride_s / 2;                  // row stride in words
-    uint32_t w[G];
-#pragma unroll
-    for (int i = 0; i < G; i++) w[i] = col[i * rw];
+// Keys quantised per channel: a group is G consecutive tokens of one dim.  A wavefront holds rows of a group, lane l dims 2l, 2l+1
+// (one 32-bit column of fp16 pairs).
+// Packed minimum and maximum of NR rows' words.
+template <int NR>
+__device__ __forceinline__ void column_range(const uint32_t (&w)[NR], uint32_t &mnp, uint32_t &mxp) {
     uint32_t mn4[4], mx4[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) { mn4[k] = pk_min_f16(w[k], w[k + 4]); mx4[k] = pk_max_f16(w[k], w[k + 4]); }
 #pragma unroll
-    for (int k = 8; k < G; k++) { mn4[k & 3] = pk_min_f16(mn4[k & 3], w[k]); mx4[k & 3] = pk_max_f16(mx4[k & 3], w[k]); }
-    const uint32_t mnp = pk_min_f16(pk_min_f16(mn4[0], mn4[1]), pk_min_f16(mn4[2], mn4[3]));
-    const uint32_t mxp = pk_max_f16(pk_max_f16(mx4[0], mx4[1]), pk_max_f16(mx4[2], mx4[3]));
+    for (int k = 8; k < NR; k++) { mn4[k & 3] = pk_min_f16(mn4[k & 3], w[k]); mx4[k & 3] = pk_max_f16(mx4[k & 3], w[k]); }
+    mnp = pk_min_f16(pk_min_f16(mn4[0], mn4[1]), pk_min_f16(mn4[2], mn4[3]));
+    mxp = pk_max_f16(pk_max_f16(mx4[0], mx4[1]), pk_max_f16(mx4[2], mx4[3]));
+}
+// Scale and zero-point of the lane's two dims (the binary32 operations of group_scale, so the same bits)
+template <int BITS>
+__device__ __forceinline__ void column_scale(uint32_t mnp, uint32_t mxp, float (&nmn)[2], float (&inv)[2], uint32_t (&metaw)[2]) {
     constexpr float qmax = (float)((1 << BITS) - 1);
-    float nmn[2], inv[2];
-    uint32_t metaw[2];
 #pragma unroll
     for (int e = 0; e < 2; e++) {
         float mn = half_bits_to_float((mnp >> (16 * e)) & 0xffffu), mx = half_bits_to_float((mxp >> (16 * e)) & 0xffffu);
@@ -182,20 +189,39 @@ __device__ __forceinline__ void pack_k_channel_group(const uint16_t *src, int64_
         nmn[e] = -mn;
         metaw[e] = s16 | (float_to_half_bits(mn) << 16);
     }
-    nt_store(reinterpret_cast<uint2 *>(meta_w + (size_t)tg * kD + 2 * lane), uint2{metaw[0], metaw[1]});
+}
+// The codes of NR rows, row 0 at codes_w: the n/2 lanes of a code word OR their pairs together (DPP) before one of them stores the
+// word at its token-major place.  STAGED: codes_w lies in LDS.
+template <int BITS, int NR, bool STAGED = false>
+__device__ __forceinline__ void column_codes(const uint32_t (&w)[NR], const float (&nmn)[2], const float (&inv)[2], uint32_t *codes_w, int lane) {
     constexpr int CPW = 32 / BITS, LPW = CPW / 2;     // codes per word, lanes per word
     const int pi = lane % LPW;                        // this lane's pair inside its word
-    uint32_t *dst = codes_w + (size_t)tg * G * (kD / CPW) + lane / LPW;
+    uint32_t *dst = codes_w + lane / LPW;
 #pragma unroll
-    for (int i = 0; i < G; i++) {
+    for (int i = 0; i < NR; i++) {
         const uint32_t c0 = __builtin_bit_cast(uint32_t, __fadd_rn(__fmul_rn(add_lo_f16(w[i], nmn[0]), inv[0]), kMagic)) - kMagicBits;
         const uint32_t c1 = __builtin_bit_cast(uint32_t, __fadd_rn(__fmul_rn(add_hi_f16(w[i], nmn[1]), inv[1]), kMagic)) - kMagicBits;
         uint32_t x = (c0 << (BITS * pi)) | (c1 << (16 + BITS * pi));
         x |= dpp_u<DPP_XOR1>(x);
         if constexpr (LPW >= 4) x |= dpp_u<DPP_XOR2>(x);
         if constexpr (LPW >= 8) x |= dpp_u<DPP_HALF_MIRROR>(x);
-        if (pi == 0) nt_store(dst + (size_t)i * (kD / CPW), x);
+        if (pi == 0) { if constexpr (STAGED) dst[i * (kD / CPW)] = x; else nt_store(dst + (size_t)i * (kD / CPW), x); }
     }
+}
+// Token group tg of the rows at src, all by one wavefront: it reads the G rows' words (a row is one coalesced 256-byte piece).
+template <int G, int BITS>
+__device__ __forceinline__ void pack_k_channel_group(const uint16_t *src, int64_t stride_s, int tg, uint32_t *codes_w,
+                                                     uint32_t *meta_w, int lane) {
+    const uint32_t *col = reinterpret_cast<const uint32_t *>(src + (int64_t)tg * G * stride_s) + lane;
+    const int64_t rw = stride_s / 2;                  // row stride in words
+    uint32_t w[G], mnp, mxp, metaw[2];
+    float nmn[2], inv[2];
+#pragma unroll
+    for (int i = 0; i < G; i++) w[i] = col[i * rw];
+    column_range<G>(w, mnp, mxp);
+    column_scale<BITS>(mnp, mxp, nmn, inv, metaw);
+    nt_store(reinterpret_cast<uint2 *>(meta_w + (size_t)tg * kD + 2 * lane), uint2{metaw[0], metaw[1]});
+    column_codes<BITS, G>(w, nmn, inv, codes_w + (size_t)tg * G * (kD * BITS / 32), lane);
 }
 
 // The V codes of a chunk from the staging rows (vcodes: one code per byte, kVRow bytes per token row) into the
@@ -204,9 +230,9 @@ __device__ __forceinline__ void pack_k_channel_group(const uint16_t *src, int64_
 // (TW = 32/bits per word, WD = TQ/TW words) of CPK = 4/WD dimensions that lie 16 apart; a token block is
 // TB = min(4*TQ, room) tokens = QD slices (QD = 4, i.e. 1-KiB tiles, for N >= 64; a shorter chunk is one block of
 // 1, 2 or 4 slices; 8 tokens at 2 bits fill half a slice); slot 16*qd + j of tile cg of a block: dims
-// 16*(cg*CPK + n/WD) + j, token slice qd.
+// 16*(cg*CPK + n/WD) + j, token slice qd.  Staging rows 32k .. 32k + 31 begin at vcodes + k * region.
 template <int BITS>
-__device__ __forceinline__ void v_gather_bits(int N, int room, uint32_t *codes_w, const uint8_t *vcodes, int tid, int NT) {
+__device__ __forceinline__ void v_gather_bits(int N, int room, uint32_t *codes_w, const uint8_t *vcodes, int tid, int NT, int region) {
     constexpr int TW = 32 / BITS, TQ = TW > 8 ? TW : 8, WD = TQ / TW, CPK = 4 / WD, NCG = kD / (16 * CPK);
     const int TB = min(4 * TQ, room), QD = TB / TQ;
     const int n_groups = room * kD * BITS / 128;      // a thread builds the words of four adjacent dims at a time
@@ -215,7 +241,7 @@ __device__ __forceinline__ void v_gather_bits(int N, int room, uint32_t *codes_w
         const int cg = tile % NCG, block = tile / NCG;
         const int d0 = 16 * (cg * CPK + n / WD) + 4 * jq, t0 = block * TB + qd * TQ + (n % WD) * TW;
         uint32_t wk[4] = {0u, 0u, 0u, 0u};
-        const uint8_t *src = vcodes + t0 * kVRow + d0;                  // the codes of dims d0..d0+3 of token t0 + e: word e*kVRow
+        const uint8_t *src = vcodes + (t0 >> 5) * region + (t0 & 31) * kVRow + d0;   // the codes of dims d0..d0+3 of token t0 + e: word e*kVRow
         if (t0 + TW <= N) {
             // tokens 2k (low half-word) and 2k+1 (high) of a word share the shift BITS*k: one byte permute puts the two
             // codes of a dim in place, one shift-or adds the pair to the dim's word
@@ -250,10 +276,10 @@ __device__ __forceinline__ void v_gather_bits(int N, int room, uint32_t *codes_w
         nt_store(reinterpret_cast<uint4 *>(codes_w + (tile * 16 * QD + 16 * qd + 4 * jq + n) * 4), uint4{wk[0], wk[1], wk[2], wk[3]});
     }
 }
-__device__ __forceinline__ void v_gather(int N, int bits, int room, uint32_t *codes_w, const uint8_t *vcodes, int tid, int NT) {
-    if (bits == 2)      v_gather_bits<2>(N, room, codes_w, vcodes, tid, NT);
-    else if (bits == 4) v_gather_bits<4>(N, room, codes_w, vcodes, tid, NT);
-    else                v_gather_bits<8>(N, room, codes_w, vcodes, tid, NT);
+__device__ __forceinline__ void v_gather(int N, int bits, int room, uint32_t *codes_w, const uint8_t *vcodes, int tid, int NT, int region = 32 * kVRow) {
+    if (bits == 2)      v_gather_bits<2>(N, room, codes_w, vcodes, tid, NT, region);
+    else if (bits == 4) v_gather_bits<4>(N, room, codes_w, vcodes, tid, NT, region);
+    else                v_gather_bits<8>(N, room, codes_w, vcodes, tid, NT, region);
 }
 
 // Token rows of a chunk from memory into the registers of the threads that own them (thread 64*wave + lane: row

@@ -56,6 +56,40 @@ def test_pack_wavefront_per_side(mq, ref, B, Hkv, N, G, C, kpc):
     assert np.array_equal(arena.cpu().numpy(), arena_ref)
 
 
+@pytest.mark.parametrize("B,Hkv,N,G,C,kpc,bits", [
+    (1, 2, 8, 64, 1, 0, (2, 4, 8, 16)), (1, 3, 8, 32, 6, 0, (2, 4, 8, 16)), (2, 2, 8, 64, 11, 0, (8,)),      # groups of four chunks, the last in part
+    (1, 2, 16, 32, 1, 0, (2, 4, 8, 16)), (1, 3, 16, 64, 5, 0, (2, 4, 8, 16)), (1, 2, 16, 64, 4, 0, (4,)),    # pairs
+    (1, 2, 32, 32, 3, 0, (8,)), (1, 2, 32, 32, 5, 1, (2, 4, 8, 16)),
+    (1, 2, 64, 64, 3, 1, (2, 4, 8, 16)), (1, 2, 64, 32, 3, 1, (8,)), (2, 1, 128, 64, 5, 1, (2, 4, 8, 16)),   # a group of 64 by two wavefronts
+    (1, 2, 192, 64, 3, 0, (8,)), (1, 3, 192, 32, 4, 1, (2, 4, 8, 16)), (1, 2, 256, 32, 4, 0, (2, 4, 8, 16)), # three and four parts of a chunk
+])
+def test_pack_rows_by_lines(mq, ref, B, Hkv, N, G, C, kpc, bits):
+    """K and V as views of a [B, S, 3, H, D] tensor (rows far apart), the chunks after the first two, an arena that ends where
+    the last block does and bytes behind it that stay: byte for byte the oracle's."""
+    rng = np.random.default_rng(N * 1000 + G + C + kpc)
+    M, BH, C0 = len(bits), B * Hkv, 2
+    cfg, rcfg = T._cfgs(mq, ref, B, Hkv, Hkv, N, G, bits, 0, kpc)
+    K, V = T._rand_kv(rng, B, Hkv, (C0 + C) * N)
+    qkv = torch.zeros(B, (C0 + C) * N, 3, Hkv, 128, dtype=torch.float16, device="cuda")
+    qkv[:, :, 1], qkv[:, :, 2] = T._dev(K).transpose(1, 2), T._dev(V).transpose(1, 2)
+    Kd, Vd = qkv[:, :, 1].transpose(1, 2), qkv[:, :, 2].transpose(1, 2)
+    expert = rng.integers(0, M, (BH, C0 + C)).astype(np.uint8)
+    need = sum((ref.chunk_block_bytes(rcfg, bits[e]) + 255) // 256 * 256 for e in expert[:, C0:].ravel())
+    guard = 4096
+    arena_ref = np.zeros(need, np.uint8); used_ref = np.zeros(1, np.uint64); off_ref = np.zeros((BH, C0 + C), np.uint64)
+    assert ref.quantize_pack(rcfg, K, V, C0, C0 + C, expert, arena_ref, used_ref, off_ref) == 0
+    arena = torch.full((need + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    arena[:need] = 0
+    used = torch.zeros(1, dtype=torch.int64, device="cuda"); status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    off = torch.zeros((BH, C0 + C), dtype=torch.int64, device="cuda")
+    mq.quantize_pack(cfg, Kd, Vd, C0, C0 + C, T._dev(expert), arena[:need], used, off, status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and int(used.item()) == int(used_ref[0])
+    assert np.array_equal(off.cpu().numpy().astype(np.uint64), off_ref)
+    got = arena.cpu().numpy()
+    assert np.array_equal(got[:need], arena_ref) and (got[need:] == 0xA5).all()
+
+
 @pytest.mark.parametrize("B,Hkv,N,G,C,tail,mix", [
     (1, 2, 32, 64, 9, 31, (1, 0, 0, 0)),        # 2 bits: four chunks a unit, the last unit holds one
     (2, 1, 32, 32, 7, 5, (0, 1, 0, 0)),         # 4 bits: two a unit
