@@ -22,7 +22,9 @@ struct PackArgs {
     int chunk_begin, n_chunks, BH, N, G, Hkv, M;
     int kpc;                    // keys quantised per channel (groups of G tokens of one dim)
     int bits_of[8];
-    bool stream;                // streaming loads of K and V (made by launch_pack)
+    // made by launch_pack:
+    uint32_t size_lo[2], size_hi[2];   // low and high byte of every expert's block size in units of 256 bytes (below 2^16)
+    bool stream;                // streaming loads of K and V
 };
 hipError_t launch_pack(PackArgs a, hipStream_t s);
 hipError_t launch_append_tail(const void *k_new, const void *v_new, void *K_tail, void *V_tail, int BH, int N, int n_tail,

@@ -90,6 +90,37 @@ def test_pack_rows_by_lines(mq, ref, B, Hkv, N, G, C, kpc, bits):
     assert np.array_equal(got[:need], arena_ref) and (got[need:] == 0xA5).all()
 
 
+@pytest.mark.parametrize("BH,C,c0", [(1, 2049, 0), (3, 1040, 16), (130, 33, 0), (300, 47, 32), (1024, 3, 0), (5, 1023, 0)])
+def test_pack_plan_per_row(mq, ref, BH, C, c0):
+    """Offsets, the arena's end and the verdict on an expert out of range, wherever it stands: more than a pass of 1024 chunks in a row,
+    pieces of 16 decisions that are whole or end early, more than one batch of pieces per thread."""
+    rng = np.random.default_rng(BH * 7 + C)
+    N, bits = 8, (2, 4, 8, 16, 16, 2)
+    cfg, rcfg = T._cfgs(mq, ref, 1, BH, BH, N, 64, bits, 0)
+    cols = (c0 + C + 15) // 16 * 16
+    size = np.array([(ref.chunk_block_bytes(rcfg, b) + 255) // 256 * 256 for b in bits])
+    K = torch.zeros(1, BH, (c0 + C) * N, 128, dtype=torch.float16, device="cuda")
+    expert = rng.integers(0, len(bits), (BH, cols)).astype(np.uint8)
+    expert[:, :c0] = 200; expert[:, c0 + C:] = 200                           # not the call's
+    sizes = size[expert[:, c0:c0 + C]]
+    need = int(sizes.sum())
+    want = 512 + (np.cumsum(sizes.ravel()) - sizes.ravel()).reshape(BH, C)
+    arena = torch.zeros(512 + need, dtype=torch.uint8, device="cuda")
+    off = torch.full((BH, cols), -7, dtype=torch.int64, device="cuda")
+    used = torch.full((1,), 300, dtype=torch.int64, device="cuda"); status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    mq.quantize_pack(cfg, K, K, c0, c0 + C, T._dev(expert), arena, used, off, status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and int(used.item()) == 512 + need
+    o = off.cpu().numpy()
+    assert np.array_equal(o[:, c0:c0 + C], want) and (o[:, :c0] == -7).all() and (o[:, c0 + C:] == -7).all()
+    for u, c, e in [(0, c0, 6), (BH - 1, c0 + C - 1, 255), (BH // 2, c0 + C // 2, 129), (BH - 1, c0 + C - 1, 7)]:
+        bad = expert.copy(); bad[u, c] = e
+        used.fill_(300); off.fill_(-7); status.zero_()
+        mq.quantize_pack(cfg, K, K, c0, c0 + C, T._dev(bad), arena, used, off, status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == mq.E_INVAL and int(used.item()) == 300 and (off == -7).all().item()
+
+
 @pytest.mark.parametrize("B,Hkv,N,G,C,tail,mix", [
     (1, 2, 32, 64, 9, 31, (1, 0, 0, 0)),        # 2 bits: four chunks a unit, the last unit holds one
     (2, 1, 32, 32, 7, 5, (0, 1, 0, 0)),         # 4 bits: two a unit
