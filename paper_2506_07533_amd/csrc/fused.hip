@@ -96,8 +96,8 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
         if (e >= M) {
             atomicCAS(a.status, 0, -1);
         } else {
-            // tails do not move during this call; a head that ran past its tail (the ring was empty when several
-            // workgroups tried) is pulled back by the next call's first kernel
+            // tails do not move during this call; a head that runs past its tail (the ring was empty when several workgroups
+            // tried) is taken back by those who moved it: it is never below the tail on the way, so that nobody else gets a page
             uint32_t *heads = a.state + 16 + e * 2 * kPoolShards, *tails = heads + kPoolShards;
             const uint32_t s0 = (uint32_t)(u * 131 + c * 7);
             bool got = false;
@@ -109,6 +109,8 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
                     const uint32_t page = a.state[a.ring_start[e] + sh * a.ring_cap[e] + hv % a.ring_cap[e]];
                     off = a.pool_base[e] + (unsigned long long)page * a.page_bytes[e];
                     got = true;
+                } else {
+                    atomicSub(&heads[sh], 1u);
                 }
             }
             if (!got) atomicCAS(a.status, 0, -3);
@@ -148,21 +150,8 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
     }
 }
 
-// Before every call: the status word is latched for the call's workgroups, and heads that ran past their tails on
-// empty rings in an earlier call come back to them.
-__global__ void paged_begin_kernel(PagedArgs a) {
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);   // 8 * kPoolShards threads
-    if (i == 0) a.state[0] = (uint32_t)*a.status;
-    const int j = i / kPoolShards, sh = i % kPoolShards;
-    uint32_t *heads = a.state + 16 + j * 2 * kPoolShards;
-    if (j < a.M && (int32_t)(heads[kPoolShards + sh] - heads[sh]) < 0) heads[sh] = heads[kPoolShards + sh];
-}
-__global__ void pool_clamp_kernel(PagedArgs a) {
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x), j = i / kPoolShards, sh = i % kPoolShards;
-    uint32_t *heads = a.state + 16 + j * 2 * kPoolShards;
-    if (j < a.M && (int32_t)(heads[kPoolShards + sh] - heads[sh]) < 0) heads[sh] = heads[kPoolShards + sh];
-}
-
+// Before every call: the status word is latched for the call's workgroups.
+__global__ void paged_begin_kernel(PagedArgs a) { a.state[0] = (uint32_t)*a.status; }
 // Every page free: page p in ring p % kPoolShards at position p / kPoolShards.
 __global__ void pool_init_kernel(PagedArgs a) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -177,7 +166,8 @@ __global__ void pool_init_kernel(PagedArgs a) {
         if (i < a.n_pages[j]) a.state[a.ring_start[j] + (i % kPoolShards) * a.ring_cap[j] + i / kPoolShards] = i;
 }
 
-// One thread per (row, chunk) of the range: its page goes back to the ring it came from.
+// One thread per (row, chunk) of the range: its page goes back to the ring it came from.  No head is past its tail between calls
+// (a kernel that saw to that before this one took 2 us of every release).
 __global__ void pool_release_kernel(PagedArgs a, int row_begin, int n_rows) {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (i >= n_rows * a.n_chunks) return;
@@ -231,7 +221,7 @@ static hipError_t launch_rp(const PagedArgs &a, dim3 grid, size_t lds, hipStream
 
 hipError_t launch_route_pack_paged(const PagedArgs &a, hipStream_t s) {
     if (a.n_chunks <= 0 || a.BH <= 0) return hipSuccess;
-    hipLaunchKernelGGL(paged_begin_kernel, dim3(8 * kPoolShards / 256), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(paged_begin_kernel, dim3(1), dim3(1), 0, s, a);
     hipError_t e0 = hipGetLastError();
     if (e0 != hipSuccess) return e0;
     dim3 grid((unsigned)a.n_chunks, (unsigned)a.BH);
@@ -263,7 +253,6 @@ hipError_t launch_pool_init(const PagedArgs &a, hipStream_t s) {
 hipError_t launch_pool_release(const PagedArgs &a, int row_begin, int n_rows, hipStream_t s) {
     const long long n = (long long)n_rows * a.n_chunks;
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pool_clamp_kernel, dim3(8 * kPoolShards / 256), dim3(256), 0, s, a);   // heads left past their tails by a call that found rings empty
     hipLaunchKernelGGL(pool_release_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a, row_begin, n_rows);
     return hipGetLastError();
 }

@@ -366,8 +366,8 @@ __device__ __forceinline__ void k_flush(int N, int bits, uint8_t *blk, const uin
 // K (isV = 0) or V (isV = 1) of one chunk -> its block `blk` at bit-width `bits`, by one workgroup of NT threads
 // (a multiple of 64).  src: the chunk's first row (row stride stride_s elements); vcodes: N * kVRow bytes of LDS (V only).
 // KPC: the keys' groups run along tokens (pack_k_channel_group); a template flag so that its G registers per lane stay out
-// of the ordinary kernels.  WAVE: one wavefront does it alone (NT = 64, vcodes its own).
-template <int G, bool KPC, bool WAVE = false>
+// of the ordinary kernels.
+template <int G, bool KPC>
 __device__ __forceinline__ void pack_side(const uint16_t *src, int64_t stride_s, int N, int bits, int isV, uint8_t *blk,
                                           uint8_t *vcodes, int tid, int NT = kPackThreads) {
     if (bits == 16) {                                 // FP16 expert: rows copied verbatim
@@ -404,7 +404,7 @@ __device__ __forceinline__ void pack_side(const uint16_t *src, int64_t stride_s,
     }
     if (!isV) return;
 
-    if constexpr (WAVE) wave_lds_sync(); else __syncthreads();
+    __syncthreads();
     v_gather(N, bits, room, codes_w, vcodes, tid, NT);
 }
 
