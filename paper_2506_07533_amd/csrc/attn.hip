@@ -80,8 +80,8 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     unsigned long long desc[kDescCap];                   // chunk descriptors of the current pass: offset | log2 bits (Gather: offsets, ordered by bit-width)
     // ticket queue of the workgroup: local tickets [0, limit) are granted; batch i maps local
     // tickets from bl[i] on to the row's tickets from bg[i] on
-    uint16_t ustart[kDescCap];                           // first unit of every chunk of the segment (not with Gather, whose units
-    uint16_t inv[kUnitCap];                              // follow from the counts), and unit -> chunk of the segment
+    uint16_t ustart[REP > 1 ? kDescCap : 0];             // grouped queries: first unit of every chunk of the segment
+    uint16_t inv[kUnitCap];                              // unit -> chunk of the segment, one head per KV head | unit of the chunk << 10 (not with Gather, whose units follow from the counts)
     uint32_t wscan[NWV], wscan2[NWV];
     uint32_t U[kMaxWeightedRowsLds + 1], r0, uneven;            // prefix sums of the rows' units
     uint32_t next, limit, done, fetching, g_seen, nb;
@@ -1638,13 +1638,24 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             } else {
 #pragma unroll
                 for (int wv = 0; wv < NWV; wv++) { if (wv < wave) pos += L.wscan[wv]; n_chunk_units += L.wscan[wv]; }
+                if constexpr (REP == 1) n_chunk_units = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_chunk_units);
             }
             const uint32_t T = n_chunk_units + (uint32_t)(seg == n_seg - 1 ? (n_tail + 15) / 16 : 0);
             unsigned int *counter = a.counters + ((size_t)u * n_seg + seg) * kCounterStride;
             // no cap for a workgroup whose whole interval lies in this row, or that covers the whole row
             const uint32_t quota = whole || fixed || !by_counter ? 0xffffffffu : (uint32_t)((float)T * ((float)ov / (float)ru)) + 2u;   // never below T * ov / ru
-            if (P == 1u || !by_counter) {                       // nobody shares the row, or everybody's part of it is fixed: no counter in memory needed
-                if (tid == 0) {
+            // static: nobody shares the row, or everybody's part of it is fixed; no counter in memory needed, and every wavefront
+            // knows the tickets
+            const bool fixed_part = REP == 1 && (P == 1u || !by_counter);
+            // the latest batch of tickets that this wavefront has looked up: local tickets below c_hi are tickets c_off + t of the row;
+            // no more have to be asked for as long as t + NWV < c_lim.  With the grant, the batch and a chunk's first unit looked up
+            // in LDS at every draw, one behind the other, and a draw that the compiler waited for (see issue_draw), the next unit was
+            // known after 1300 clocks and more, of the 6000 that a unit takes: now 600 where the parts are fixed.  (Grouped queries look everything
+            // up: their kernel holds no register more; with these it is 1 to 2 % slower, with four heads in groups of 32 9 %.)  256 rows of 8k tokens in 32-token chunks
+            // 56.5 -> 54.4 us a call, 32 heads x 32k tokens 1 us; caches larger than the last-level cache wait for memory either way.
+            uint32_t c_hi = 0u, c_off = 0u, c_lim = 0u;
+            if (P == 1u || !by_counter) {
+                if (REP == 1 || tid == 0) {
                     uint32_t g0 = 0u, g1 = T;
                     if (GATH && fixed) {                 // ordered by bit-width, whose units differ by up to half in time: every P-th
                         g0 = (uint32_t)(w - wg_first); g1 = g0 + (T + P - 1u - g0) / P;
@@ -1655,7 +1666,8 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                         if (lo > ub) g0 = (uint32_t)((float)T * ((float)(lo - ub) / (float)ru));
                         if (hi < ue) g1 = (uint32_t)((float)T * ((float)(hi - ub) / (float)ru));
                     }
-                    L.bl[0] = 0u; L.bg[0] = g0; L.nb = 1u; L.limit = g1 - g0; L.g_seen = T; L.done = 1u;
+                    if constexpr (REP == 1) { c_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)g0); c_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(g1 - g0)); }
+                    else { L.bl[0] = 0u; L.bg[0] = g0; L.nb = 1u; L.limit = g1 - g0; L.g_seen = T; L.done = 1u; }
                 }
             } else if (seg == 0 && tid == 0) {           // the batch asked for during the row set-up
                 const uint32_t granted = g_first < T ? min(b_first, T - g_first) : 0u;
@@ -1667,8 +1679,9 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             for (int k = 0; k < (GATH ? 0 : 2); k++) {
                 const int c = cs + tid * KPT + k;
                 if (k < KPT && c < ce) {
-                    L.ustart[c - cs] = (uint16_t)pos;
-                    for (uint32_t i = 0; i < ucnt[k]; i++) L.inv[pos + i] = (uint16_t)(c - cs);
+                    static_assert(kDescCap == 1024, "a chunk in ten bits, its units (at most 16) in six");
+                    if constexpr (REP > 1) L.ustart[c - cs] = (uint16_t)pos;
+                    for (uint32_t i = 0; i < ucnt[k]; i++) L.inv[pos + i] = (uint16_t)((uint32_t)(c - cs) | (REP == 1 ? i << 10 : 0u));
                     pos += ucnt[k];
                 }
             }
@@ -1720,11 +1733,51 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             // against shares of consecutive ones, some of them all raw rows; longer chunks lie in their order, mixed)
             const uint32_t stride = GATH && ROWS && fixed && !by_counter ? P : 1u;
             int bcur = 0;                                // batch of this wavefront's latest ticket
-            auto issue_draw = [&]() { if (lane == 0) pend = atomicAdd(&L.next, 1u); };
+            // One head per KV head: the address comes from a vector register, as an atomic addition at a uniform address is combined over the
+            // wavefront by the compiler, which then waits for its result on the spot.
+            uint32_t *next = &L.next;
+            if constexpr (REP == 1) { uint32_t vzero = 0u; asm volatile("" : "+v"(vzero)); next += vzero; }
+            auto issue_draw = [&]() { if (lane == 0) pend = atomicAdd(REP == 1 ? next : &L.next, 1u); };
+            constexpr uint32_t kNoTicket = 0xffffffffu;
+            auto ticket = [&](auto t) -> uint32_t {      // one head per KV head: the row's ticket for local ticket t; waits until it is granted, or nothing is left
+              if constexpr (REP > 1) return kNoTicket;
+              else {
+                if (fixed_part) {
+                    if (t >= c_hi) return kNoTicket;
+                } else if (t >= c_hi || t + (uint32_t)NWV >= c_lim) {
+                    uint32_t limit;
+                    for (;;) {                           // wait until local ticket t is granted, or nothing is left
+                        limit = (uint32_t)__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.limit, __ATOMIC_RELAXED));
+                        if (t < limit) break;
+                        if (__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.done, __ATOMIC_RELAXED))) {
+                            limit = (uint32_t)__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.limit, __ATOMIC_RELAXED));
+                            if (t < limit) break;        // done is written after the last limit
+                            return kNoTicket;
+                        }
+                        if (!try_fetch()) __builtin_amdgcn_s_sleep(2);
+                    }
+                    c_lim = limit;
+                    if (t + (uint32_t)NWV >= limit) {
+                        if (__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.done, __ATOMIC_RELAXED))) c_lim = 0xffffffffu;   // there will be no more
+                        else try_fetch();                // top up ahead of need; whoever gets the lock does it
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                    // the batch of ticket t ends where the next one begins, or at the limit read above (a batch is granted before the limit says so)
+                    for (;;) {
+                        const bool later = bcur + 1 < __builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.nb, __ATOMIC_RELAXED));
+                        c_hi = later ? (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bl[bcur + 1]) : limit;
+                        if (t < c_hi) break;
+                        bcur++;
+                    }
+                    c_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)(L.bg[bcur] - L.bl[bcur]));
+                }
+                return c_off + t * stride;
+              }
+            };
             auto next_unit = [&](Unit &un) -> bool {     // the pending draw becomes the next unit
                 const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)pend);
-                uint32_t limit;
-                for (;;) {                               // wait until local ticket t is granted, or nothing is left
+                uint32_t limit;                          // grouped queries (with this code in the else branch of a choice their kernel in groups of 32 spills 141 registers and not 129: 338 -> 355 us)
+                for (; REP > 1;) {                       // wait until local ticket t is granted, or nothing is left
                     limit = (uint32_t)__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.limit, __ATOMIC_RELAXED));
                     if (t < limit) break;
                     if (__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.done, __ATOMIC_RELAXED))) {
@@ -1734,12 +1787,13 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     }
                     if (!try_fetch()) __builtin_amdgcn_s_sleep(2);
                 }
-                if (t + (uint32_t)NWV >= limit && !__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.done, __ATOMIC_RELAXED)))
+                if (REP > 1 && t + (uint32_t)NWV >= limit && !__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.done, __ATOMIC_RELAXED)))
                     try_fetch();                         // top up ahead of need; whoever gets the lock does it
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                while (bcur + 1 < __builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.nb, __ATOMIC_RELAXED)) &&
+                if (REP > 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                while (REP > 1 && bcur + 1 < __builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.nb, __ATOMIC_RELAXED)) &&
                        t >= (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bl[bcur + 1])) bcur++;
-                const uint32_t tk = (uint32_t)__builtin_amdgcn_readfirstlane((int)(L.bg[bcur] + (t - L.bl[bcur]) * stride));
+                const uint32_t tk = REP == 1 ? ticket(t) : (uint32_t)__builtin_amdgcn_readfirstlane((int)(L.bg[bcur] + (t - L.bl[bcur]) * stride));
+                if (REP == 1 && tk == kNoTicket) return false;
                 issue_draw();
                 Unit n;                                  // assigned as a whole: stores of single fields through the reference, merged across
                                                          // the branches, would keep the unit in memory
@@ -1768,11 +1822,11 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     }
                     n.nsub = max((n.nvalid + (1 << (6 - lgb)) - 1) >> (6 - lgb), 1);
                 } else if (!GATH && tk < n_chunk_units) {
-                    const int cl = __builtin_amdgcn_readfirstlane((int)L.inv[tk]);
+                    const int cu = __builtin_amdgcn_readfirstlane((int)L.inv[tk]), cl = REP == 1 ? cu & (kDescCap - 1) : cu;
                     const unsigned long long dsc = L.desc[cl];
                     const uint32_t dlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)dsc);
                     const uint32_t dhi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(dsc >> 32));
-                    const int sidx = (int)tk - __builtin_amdgcn_readfirstlane((int)L.ustart[cl]);
+                    const int sidx = REP == 1 ? cu >> 10 : (int)tk - __builtin_amdgcn_readfirstlane((int)L.ustart[REP == 1 ? 0 : cl]);
                     const int lgb = (int)(dlo & 7u);
                     const uint8_t *blk = a.arena + (((unsigned long long)dhi << 32) | (dlo & ~0xffu));
                     const int t0 = sidx << (8 - lgb);
