@@ -307,7 +307,7 @@ def bench_layer(args, w):
     res["pct_of_hbm_peak"] = round(100 * res["decode_call"]["frac"], 2)
     if not args.decode_only:
         res["roofline_route"] = dict(roof(route_bytes, t_route), kernel="route_kernel")
-        res["roofline_pack"] = dict(roof(pack_bytes, t_pack), kernel="plan_rows_kernel + pack_kernel + arena_end_kernel (+ attn_prep_kernel: the decode plan)")
+        res["roofline_pack"] = dict(roof(pack_bytes, t_pack), kernel="plan_rows_kernel + pack_kernel (+ attn_prep_kernel: the decode plan)")
         res["route_pack_chunks_per_s"] = round(n_units / ((t_route.mean() + t_pack.mean()) * 1e-3), 1)
         res["route_chunks_per_s"] = round(n_units / (t_route.mean() * 1e-3), 1)
         res["pack_chunks_per_s"] = round(n_units / (t_pack.mean() * 1e-3), 1)
