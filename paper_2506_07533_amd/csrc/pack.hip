@@ -459,6 +459,7 @@ __device__ __forceinline__ void pack_chunks(const PackArgs &a, int isV, int c, i
         const uint4 *buf = reinterpret_cast<const uint4 *>(region) + j * lines * 8 + (lane ^ (lane >> 3));
         for (int i = 0; i < N / 4; i++) nt_store(dst + 64 * i, buf[64 * i]);
     }
+    if (__ballot(bits != 0 && bits != 16) == 0ull) return;   // raw chunks alone (32 rows of one chunk 7.4 -> 6.4 us a call)
     uint32_t w[32];
     line_read(region, lane, n_lines, w);
     wave_lds_sync();

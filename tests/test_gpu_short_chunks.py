@@ -59,6 +59,7 @@ def test_pack_wavefront_per_side(mq, ref, B, Hkv, N, G, C, kpc):
 @pytest.mark.parametrize("B,Hkv,N,G,C,kpc,bits", [
     (1, 2, 8, 64, 1, 0, (2, 4, 8, 16)), (1, 3, 8, 32, 6, 0, (2, 4, 8, 16)), (2, 2, 8, 64, 11, 0, (8,)),      # groups of four chunks, the last in part
     (1, 2, 16, 32, 1, 0, (2, 4, 8, 16)), (1, 3, 16, 64, 5, 0, (2, 4, 8, 16)), (1, 2, 16, 64, 4, 0, (4,)),    # pairs
+    (1, 3, 8, 64, 13, 0, (16,)), (1, 2, 16, 32, 3, 0, (16,)), (1, 3, 8, 32, 61, 0, (16, 16, 16, 2)),         # groups of raw chunks alone
     (1, 2, 32, 32, 3, 0, (8,)), (1, 2, 32, 32, 5, 1, (2, 4, 8, 16)),
     (1, 2, 64, 64, 3, 1, (2, 4, 8, 16)), (1, 2, 64, 32, 3, 1, (8,)), (2, 1, 128, 64, 5, 1, (2, 4, 8, 16)),   # a group of 64 by two wavefronts
     (1, 2, 192, 64, 3, 0, (8,)), (1, 3, 192, 32, 4, 1, (2, 4, 8, 16)), (1, 2, 256, 32, 4, 0, (2, 4, 8, 16)), # three and four parts of a chunk
