@@ -1706,7 +1706,9 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                         uint32_t granted = 0;
                         if (g0 < T) {
                             granted = min(want, T - g0);
-                            L.bl[nb] = limit; L.bg[nb] = g0; L.nb = nb + 1;
+                            L.bl[nb] = limit; L.bg[nb] = g0;
+                            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // whoever sees the new nb may look at its batch before the limit grants it
+                            __atomic_store_n(&L.nb, nb + 1, __ATOMIC_RELAXED);
                             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                             __atomic_store_n(&L.limit, limit + granted, __ATOMIC_RELAXED);
                         }
@@ -1723,7 +1725,10 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                 uint32_t won = 0;
                 if (lane == 0) won = atomicCAS(&L.fetching, 0u, 1u) == 0u ? 1u : 0u;
                 won = (uint32_t)__builtin_amdgcn_readfirstlane((int)won);
-                if (won) fetch();
+                if (won) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");                 // what the last holder wrote
+                    fetch();
+                }
                 return won != 0;
             };
 
@@ -1765,6 +1770,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                     // the batch of ticket t ends where the next one begins, or at the limit read above (a batch is granted before the limit says so)
                     for (;;) {
                         const bool later = bcur + 1 < __builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.nb, __ATOMIC_RELAXED));
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");             // nb before its batch
                         c_hi = later ? (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bl[bcur + 1]) : limit;
                         if (t < c_hi) break;
                         bcur++;
@@ -1790,8 +1796,11 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
                 if (REP > 1 && t + (uint32_t)NWV >= limit && !__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.done, __ATOMIC_RELAXED)))
                     try_fetch();                         // top up ahead of need; whoever gets the lock does it
                 if (REP > 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                while (REP > 1 && bcur + 1 < __builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.nb, __ATOMIC_RELAXED)) &&
-                       t >= (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bl[bcur + 1])) bcur++;
+                while (REP > 1 && bcur + 1 < __builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.nb, __ATOMIC_RELAXED))) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");                 // nb before its batch
+                    if (t < (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bl[bcur + 1])) break;
+                    bcur++;
+                }
                 const uint32_t tk = REP == 1 ? ticket(t) : (uint32_t)__builtin_amdgcn_readfirstlane((int)(L.bg[bcur] + (t - L.bl[bcur]) * stride));
                 if (REP == 1 && tk == kNoTicket) return false;
                 issue_draw();
