@@ -166,8 +166,8 @@ __global__ void pool_init_kernel(PagedArgs a) {
         if (i < a.n_pages[j]) a.state[a.ring_start[j] + (i % kPoolShards) * a.ring_cap[j] + i / kPoolShards] = i;
 }
 
-// One thread per (row, chunk) of the range: its page goes back to the ring it came from.  No head is past its tail between calls
-// (a kernel that saw to that before this one took 2 us of every release).
+// One thread per (row, chunk) of the range: its page goes back to the ring it came from, behind the tail, which no head has passed
+// between calls (route_pack_kernel).
 __global__ void pool_release_kernel(PagedArgs a, int row_begin, int n_rows) {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (i >= n_rows * a.n_chunks) return;
@@ -187,7 +187,7 @@ __global__ void pool_free_pages_kernel(PagedArgs a, uint32_t *counts) {
     const int j = (int)blockIdx.x, lane = (int)threadIdx.x;        // one wavefront per pool
     const uint32_t *heads = a.state + 16 + j * 2 * kPoolShards;
     int n = 0;
-    if (j < a.M) for (int sh = lane; sh < kPoolShards; sh += 64) n += max((int32_t)(heads[kPoolShards + sh] - heads[sh]), 0);
+    if (j < a.M) for (int sh = lane; sh < kPoolShards; sh += 64) n += (int32_t)(heads[kPoolShards + sh] - heads[sh]);   // no head is past its tail
     for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
     if (lane == 0) counts[j] = (uint32_t)n;
 }

@@ -150,3 +150,43 @@ def test_release_reuse_shared_decisions_and_exhaustion(mq, ref):
                 assert mq.pool_base(cfg, pages, j) <= int(got[u, c]) < mq.pool_base(cfg, pages, j) + pages[j] * mq.pool_page_bytes(cfg, j)
                 blk = ref.pack_chunk(rcfg, BITS[j], K2[b, h, c * N:(c + 1) * N], V2[b, h, c * N:(c + 1) * N])
                 assert np.array_equal(arena_h[int(got[u, c]):int(got[u, c]) + blk.size], blk)
+
+
+def test_contended_rings_end_empty_and_not_beyond(mq, ref):
+    """Thousands of chunks ask one pool for 300 pages, most rings holding a single one: workgroups that saw a page and came too
+    late take their step back.  Every page is handed out once, heads meet tails, and the pages given back serve exactly as many chunks again."""
+    rng = np.random.default_rng(31)
+    B, Hkv, N, G, C, n, shards = 1, 60, 8, 64, 64, 300, 256
+    cfg, rcfg = T._cfgs(mq, ref, B, Hkv, Hkv, N, G, (2, 4), 0)
+    pages = (0, n)
+    K, V = T._rand_kv(rng, B, Hkv, C * N)
+    Kd, Vd = T._dev(K), T._dev(V)
+    arena = torch.zeros(mq.pool_arena_bytes(cfg, pages), dtype=torch.uint8, device="cuda")
+    state = torch.zeros(mq.pool_state_bytes(cfg, pages) // 4, dtype=torch.int32, device="cuda")
+    mq.pool_init(cfg, pages, state)
+    expert = torch.ones((Hkv, C), dtype=torch.uint8, device="cuda")
+    off = torch.zeros((Hkv, C), dtype=torch.int64, device="cuda"); status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    all_pages = [mq.pool_base(cfg, pages, 1) + p * mq.pool_page_bytes(cfg, 1) for p in range(n)]
+
+    def heads_and_tails():
+        rings = state.cpu().numpy()[16:16 + 8 * 2 * shards].reshape(8, 2, shards)
+        return rings[:, 0], rings[:, 1]
+
+    for turn in range(1, 4):
+        mq.route_pack_paged(cfg, pages, Kd, Vd, 0, C, None, expert, None, arena, state, off, status)
+        torch.cuda.synchronize()
+        got = off.cpu().numpy().ravel()
+        assert int(status.item()) == mq.E_ARENA and sorted(got[got != -1].tolist()) == all_pages
+        heads, tails = heads_and_tails()
+        assert np.array_equal(heads, tails) and mq.pool_free_pages(cfg, pages, state) == [0, 0]
+        mq.pool_release(cfg, pages, expert, off, 0, Hkv, 0, C, state)
+        status.zero_()
+        assert (off == -1).all().item() and mq.pool_free_pages(cfg, pages, state) == list(pages)
+        heads, tails = heads_and_tails()
+        assert (tails - heads)[1].tolist() == [n // shards + (sh < n % shards) for sh in range(shards)]
+        mq.route_pack_paged(cfg, pages, Kd, Vd, 0, n // Hkv, None, expert, None, arena, state, off, status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0 and mq.pool_free_pages(cfg, pages, state) == [0, 0]
+        _check_pages(mq, ref, cfg, rcfg, pages, K, V, expert.cpu().numpy(), off.cpu().numpy().astype(np.uint64), arena.cpu().numpy(), 0, n // Hkv)
+        mq.pool_release(cfg, pages, expert, off, 0, Hkv, 0, n // Hkv, state)
+    assert mq.pool_free_pages(cfg, pages, state) == list(pages)
