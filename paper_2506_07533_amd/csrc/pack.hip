@@ -168,9 +168,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PackArgs a) {
 // into the high bytes of their sizes and dot products add them up, and one barrier hands all sums over.  (Sizes looked up one by
 // one and added to a sum per row in LDS, then scanned: 65536 chunks of 256 rows 15.4 us against 8.4, 40960 of 40 rows 11.5 against 5.8.)
 constexpr int kPlanRowsMax = 1024;
+// The pieces lie evenly over the wavefronts, so that a wavefront's 32-bit sum holds its share of the largest table (65535 chunks a row,
+// as the entry point has it) of the largest blocks (256 raw tokens: 512 units).
+static_assert((unsigned long long)kPlanRowsMax * 65535 * 512 / (kPlanThreads / 64) + 64 * 16 * 512 < (1ull << 32), "sums of the wavefronts");
 __global__ __launch_bounds__(kPlanThreads) void plan_rows_kernel(PackArgs a) {
     constexpr int kWaves = kPlanThreads / 64, kBatch = 4;
-    __shared__ uint32_t wall[kWaves], wbefore[kWaves], wown[2][kWaves];   // sums of the wavefronts, in units of 256 bytes (below 2^32, see kPlanRowsMax)
+    __shared__ uint32_t wall[kWaves], wbefore[kWaves], wown[2][kWaves];   // sums of the wavefronts, in units of 256 bytes
     __shared__ int wbad[kWaves], status_in;
     const int tid = (int)threadIdx.x, lane = tid & 63, u_own = (int)blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);            // wave-uniform, kept scalar

@@ -121,16 +121,23 @@ def test_refused_call_reads_no_rows(mq, N):
     assert fastest(mq.E_ARENA) < 0.4 * fastest(0)
 
 
-@pytest.mark.parametrize("BH,C,c0", [(1, 2049, 0), (3, 1040, 16), (130, 33, 0), (300, 47, 32), (1024, 3, 0), (5, 1023, 0)])
-def test_pack_plan_per_row(mq, ref, BH, C, c0):
+SMALL, LARGE = (8, (2, 4, 8, 16, 16, 2)), (256, (2, 16, 8, 4, 16, 8))       # blocks of up to 16 and 512 units of 256 bytes
+
+
+@pytest.mark.parametrize("BH,C,c0,blocks", [
+    (1, 2049, 0, SMALL), (3, 1040, 16, SMALL), (130, 33, 0, SMALL), (300, 47, 32, SMALL), (1024, 3, 0, SMALL), (5, 1023, 0, SMALL),
+    (1024, 67, 0, SMALL), (300, 231, 16, SMALL), (1000, 48, 0, SMALL),       # 5120, 4500 and 3000 pieces: a second batch, the second to fourth piece of the first
+    (130, 33, 0, LARGE), (7, 147, 16, LARGE),                                # sizes of two bytes
+])
+def test_pack_plan_per_row(mq, ref, BH, C, c0, blocks):
     """Offsets, the arena's end and the verdict on an expert out of range, wherever it stands: more than a pass of 1024 chunks in a row,
-    pieces of 16 decisions that are whole or end early, more than one batch of pieces per thread."""
+    pieces of 16 decisions that are whole or end early, more than a batch of four pieces for each of the 1024 threads."""
     rng = np.random.default_rng(BH * 7 + C)
-    N, bits = 8, (2, 4, 8, 16, 16, 2)
+    N, bits = blocks
     cfg, rcfg = T._cfgs(mq, ref, 1, BH, BH, N, 64, bits, 0)
     cols = (c0 + C + 15) // 16 * 16
     size = np.array([(ref.chunk_block_bytes(rcfg, b) + 255) // 256 * 256 for b in bits])
-    K = torch.zeros(1, BH, (c0 + C) * N, 128, dtype=torch.float16, device="cuda")
+    K = torch.zeros(1, 1, (c0 + C) * N, 128, dtype=torch.float16, device="cuda").expand(1, BH, -1, -1)
     expert = rng.integers(0, len(bits), (BH, cols)).astype(np.uint8)
     expert[:, :c0] = 200; expert[:, c0 + C:] = 200                           # not the call's
     sizes = size[expert[:, c0:c0 + C]]
@@ -144,7 +151,7 @@ def test_pack_plan_per_row(mq, ref, BH, C, c0):
     assert int(status.item()) == 0 and int(used.item()) == 512 + need
     o = off.cpu().numpy()
     assert np.array_equal(o[:, c0:c0 + C], want) and (o[:, :c0] == -7).all() and (o[:, c0 + C:] == -7).all()
-    for u, c, e in [(0, c0, 6), (BH - 1, c0 + C - 1, 255), (BH // 2, c0 + C // 2, 129), (BH - 1, c0 + C - 1, 7)]:
+    for u, c, e in [(0, c0, 6), (BH - 1, c0 + C - 1, 255), (BH // 2, c0 + C // 2, 129), (BH - 1, c0 + C - 1, 7), (BH - 1, c0, 6)]:
         bad = expert.copy(); bad[u, c] = e
         used.fill_(300); off.fill_(-7); status.zero_()
         mq.quantize_pack(cfg, K, K, c0, c0 + C, T._dev(bad), arena, used, off, status)
