@@ -91,6 +91,34 @@ def test_pack_rows_by_lines(mq, ref, B, Hkv, N, G, C, kpc, bits):
     assert np.array_equal(got[:need], arena_ref) and (got[need:] == 0xA5).all()
 
 
+@pytest.mark.parametrize("N,G,kpc", [(8, 64, 0), (8, 32, 0), (16, 32, 0), (32, 32, 0), (32, 32, 1), (64, 64, 1), (64, 32, 1), (128, 32, 0)])
+def test_pack_streaming_loads(mq, ref, N, G, kpc):
+    """Calls on more than 384 MiB of K and V: the keys and values of 1000 heads are views of one head's."""
+    BH, C, bits = 1000, 896 // N, (2, 4, 8, 16)
+    assert BH * C * N * 512 > 384 << 20
+    rng = np.random.default_rng(N + G + kpc)
+    cfg, rcfg = T._cfgs(mq, ref, 1, BH, BH, N, G, bits, 0, kpc)
+    K, V = T._rand_kv(rng, 1, 1, C * N)
+    expert = rng.choice(4, (BH, C), p=(0.6, 0.3, 0.05, 0.05)).astype(np.uint8)
+    sizes = np.array([(ref.chunk_block_bytes(rcfg, b) + 255) // 256 * 256 for b in bits])[expert].ravel()
+    want = (np.cumsum(sizes) - sizes).reshape(BH, C)
+    arena = torch.zeros(int(sizes.sum()), dtype=torch.uint8, device="cuda")
+    used = torch.zeros(1, dtype=torch.int64, device="cuda"); status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    off = torch.zeros((BH, C), dtype=torch.int64, device="cuda")
+    mq.quantize_pack(cfg, T._dev(K).expand(1, BH, -1, -1), T._dev(V).expand(1, BH, -1, -1), 0, C, T._dev(expert), arena, used, off, status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and int(used.item()) == arena.numel() and np.array_equal(off.cpu().numpy(), want)
+    got, blocks = arena.cpu().numpy(), {}
+    rows = np.concatenate([[0, BH - 1], rng.choice(BH, min(BH, 4000 // C), replace=False)])
+    for u in rows:
+        for c in range(C):
+            b = bits[expert[u, c]]
+            if (b, c) not in blocks:
+                blocks[b, c] = ref.pack_chunk(rcfg, b, K[0, 0, c * N:(c + 1) * N], V[0, 0, c * N:(c + 1) * N])
+            blk = blocks[b, c]
+            assert np.array_equal(got[want[u, c]:want[u, c] + blk.size], blk), (u, c, b)
+
+
 @pytest.mark.parametrize("N", [8, 64])
 def test_refused_call_reads_no_rows(mq, N):
     """A call on a status that is set is a no-op in time too: on 537 MB of K and V about 20 us, a sixth of an accepted call, and
