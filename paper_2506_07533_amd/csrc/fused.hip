@@ -28,6 +28,78 @@
 
 namespace moqae {
 
+// Token group tg of the rows at src, all by one wavefront: it reads the G rows' words (a row is one coalesced 256-byte piece).
+template <int G, int BITS>
+__device__ __forceinline__ void pack_k_channel_group(const uint16_t *src, int64_t stride_s, int tg, uint32_t *codes_w,
+                                                     uint32_t *meta_w, int lane) {
+    const uint32_t *col = reinterpret_cast<const uint32_t *>(src + (int64_t)tg * G * stride_s) + lane;
+    const int64_t rw = stride_s / 2;                  // row stride in words
+    uint32_t w[G], mnp, mxp, metaw[2];
+    float nmn[2], inv[2];
+#pragma unroll
+    for (int i = 0; i < G; i++) w[i] = col[i * rw];
+    column_range<G>(w, mnp, mxp);
+    column_scale<BITS>(mnp, mxp, nmn, inv, metaw);
+    nt_store(reinterpret_cast<uint2 *>(meta_w + (size_t)tg * kD + 2 * lane), uint2{metaw[0], metaw[1]});
+    column_codes<BITS, G>(w, nmn, inv, codes_w + (size_t)tg * G * (kD * BITS / 32), lane);
+}
+
+// One group of G dims of a value row, from memory: its meta word to meta_dst, its codes, one per byte, to the staging row at v_lds.
+template <int G, int BITS>
+__device__ __forceinline__ void pack_v_item(const uint4 *__restrict__ p, uint32_t *__restrict__ meta_dst, uint32_t *__restrict__ v_lds) {
+    uint32_t w[G / 2];
+#pragma unroll
+    for (int j = 0; j < G / 8; j++) {                // the whole item is requested at once: its 128-byte line arrives once
+        // (ordinary loads: the lane's eight loads share the line through the cache; streaming loads here fetch it eight times)
+        const uint4 t = p[j];
+        w[4 * j] = t.x; w[4 * j + 1] = t.y; w[4 * j + 2] = t.z; w[4 * j + 3] = t.w;
+    }
+    uint32_t meta;
+    pack_item<G, BITS>(w, true, &meta, nullptr, v_lds);
+    nt_store(meta_dst, meta);
+}
+
+// Keys per channel: K (isV = 0) or V (isV = 1) of one chunk -> its block `blk` at bit-width `bits`, by one workgroup of NT threads
+// (a multiple of 64).  src: the chunk's first row (row stride stride_s elements); vcodes: N * kVRow bytes of LDS (V only).
+template <int G>
+__device__ __forceinline__ void pack_side(const uint16_t *src, int64_t stride_s, int N, int bits, int isV, uint8_t *blk,
+                                          uint8_t *vcodes, int tid, int NT) {
+    if (bits == 16) {                                 // FP16 expert: rows copied verbatim
+        const int lane16 = tid & 15, rsub = tid >> 4;
+        uint4 *dst = reinterpret_cast<uint4 *>(blk + (isV ? (size_t)N * kD * 2 : 0));
+        for (int row = rsub; row < N; row += NT / 16)
+            nt_store(&dst[row * 16 + lane16], nt_load(reinterpret_cast<const uint4 *>(src + (int64_t)row * stride_s + lane16 * 8)));
+        return;
+    }
+
+    constexpr int NG = kD / G;                        // groups per row
+    const int room = isV ? v_token_room(N, bits) : N;  // tokens the code area has room for (V: at least one slice)
+    const size_t k_code_bytes = (size_t)N * kD * bits / 8, meta_bytes = (size_t)N * NG * 4;
+    uint8_t *area = blk + (isV ? k_code_bytes + meta_bytes : 0);
+    uint32_t *codes_w = reinterpret_cast<uint32_t *>(area);
+    uint32_t *meta_w = reinterpret_cast<uint32_t *>(area + (size_t)room * kD * bits / 8);
+
+    if (!isV) {                                      // one wavefront per group of G tokens
+        for (int tg = tid >> 6; tg < N / G; tg += NT >> 6) {
+            if (bits == 2)      pack_k_channel_group<G, 2>(src, stride_s, tg, codes_w, meta_w, tid & 63);
+            else if (bits == 4) pack_k_channel_group<G, 4>(src, stride_s, tg, codes_w, meta_w, tid & 63);
+            else                pack_k_channel_group<G, 8>(src, stride_s, tg, codes_w, meta_w, tid & 63);
+        }
+        return;
+    }
+    // item = (token row, group): consecutive lanes take consecutive 2G-byte pieces of the chunk
+    for (int item = tid; item < N * NG; item += NT) {
+        const int row = item / NG, g = item % NG;
+        const uint4 *p = reinterpret_cast<const uint4 *>(src + (int64_t)row * stride_s + g * G);
+        uint32_t *vl = reinterpret_cast<uint32_t *>(vcodes + row * kVRow + g * G);
+        if (bits == 2)      pack_v_item<G, 2>(p, &meta_w[item], vl);
+        else if (bits == 4) pack_v_item<G, 4>(p, &meta_w[item], vl);
+        else                pack_v_item<G, 8>(p, &meta_w[item], vl);
+    }
+    __syncthreads();
+    v_gather(N, bits, room, codes_w, vcodes, tid, NT);
+}
+
 template <int M, int G, bool KPC>
 __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
     extern __shared__ uint4 dyn_lds[];                // keys per channel: the chunk's key rows as the router read them (N * kStageRow
@@ -141,12 +213,12 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
         v_gather(N, bits, room, reinterpret_cast<uint32_t *>(blk + (size_t)N * kD * bits / 8 + (size_t)N * (kD / G) * 4), vcodes, tid, NT);
     } else {
         if (routed) {                                 // the keys are in LDS: K comes from memory once
-            pack_side<G, KPC>(reinterpret_cast<const uint16_t *>(dyn_lds), kStageRow * 8, N, bits, 0, blk, vcodes, tid, NT);
+            pack_side<G>(reinterpret_cast<const uint16_t *>(dyn_lds), kStageRow * 8, N, bits, 0, blk, vcodes, tid, NT);
             __syncthreads();                          // the key rows are consumed: the V staging rows take their place
         } else {
-            pack_side<G, KPC>(a.K + base, a.stride_s, N, bits, 0, blk, vcodes, tid, NT);
+            pack_side<G>(a.K + base, a.stride_s, N, bits, 0, blk, vcodes, tid, NT);
         }
-        pack_side<G, KPC>(a.V + base, a.stride_s, N, bits, 1, blk, vcodes, tid, NT);
+        pack_side<G>(a.V + base, a.stride_s, N, bits, 1, blk, vcodes, tid, NT);
     }
 }
 

@@ -303,8 +303,8 @@ __device__ __forceinline__ void pack_line(const uint32_t (&w)[32], int lane, uin
     uint32_t mw[NI];
 #pragma unroll
     for (int i = 0; i < NI; i++)
-        pack_item_regs<G, BITS, true, true>(&w[i * (G / 2)], isV, &mw[i], &kw[i * (2 * BITS / NI)],
-                                            reinterpret_cast<uint32_t *>(region + (lane >> 1) * kVRow + (lane & 1) * 64 + i * G));
+        pack_item<G, BITS, true>(&w[i * (G / 2)], isV, &mw[i], &kw[i * (2 * BITS / NI)],
+                                 reinterpret_cast<uint32_t *>(region + (lane >> 1) * kVRow + (lane & 1) * 64 + i * G));
     if constexpr (NI == 1) nt_store(meta_w, mw[0]);
     else                   nt_store(reinterpret_cast<uint2 *>(meta_w), uint2{mw[0], mw[NI - 1]});
 }

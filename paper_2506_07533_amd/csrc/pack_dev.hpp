@@ -102,14 +102,12 @@ __device__ __forceinline__ uint32_t four_codes(const uint32_t *w, int d, float n
 // words are sums of bits(t + magic) << shift, i.e. of the codes plus a constant that is taken off at
 // the end; no code is ever masked.  No clamp is needed: the scale is rounded up, so that
 // (x - min) * (1/scale) <= qmax * (1 + 2e-7) and rounds to at most qmax, and x >= min.
-// STAGED: meta_dst is a register of the caller and k_dst a staging row in LDS (plain stores), see pack_row, or (REGS) registers too.
-template <int G, int BITS, bool STAGED = false, bool REGS = false>
-__device__ __forceinline__ void pack_item_regs(const uint32_t *w, bool isV, uint32_t *__restrict__ meta_dst,
-                                               uint32_t *__restrict__ k_dst, uint32_t *__restrict__ v_lds) {
+// meta: a register; k_dst: a staging row in LDS (see pack_row) or, with REGS, registers.
+template <int G, int BITS, bool REGS = false>
+__device__ __forceinline__ void pack_item(const uint32_t *w, bool isV, uint32_t *__restrict__ meta, uint32_t *__restrict__ k_dst,
+                                          uint32_t *__restrict__ v_lds) {
     float nmn, inv;
-    const uint32_t meta = group_scale<G>(w, (float)((1 << BITS) - 1), nmn, inv);
-    if constexpr (STAGED) *meta_dst = meta;
-    else                  nt_store(meta_dst, meta);
+    *meta = group_scale<G>(w, (float)((1 << BITS) - 1), nmn, inv);
     if (isV) {                                        // one code per byte into the staging rows
 #pragma unroll
         for (int k = 0; k < G / 4; k++) v_lds[k] = four_codes(w, 4 * k, nmn, inv);
@@ -132,31 +130,12 @@ __device__ __forceinline__ void pack_item_regs(const uint32_t *w, bool isV, uint
             for (int k = 0; k < WPL; k++) k_dst[k] = out[k];
         } else if constexpr (WPL >= 4) {
 #pragma unroll
-            for (int k = 0; k < WPL; k += 4) {
-                const uint4 o = uint4{out[k], out[k + 1], out[k + 2], out[k + 3]};
-                if constexpr (STAGED) *reinterpret_cast<uint4 *>(k_dst + k) = o;
-                else                  nt_store(reinterpret_cast<uint4 *>(k_dst + k), o);
-            }
+            for (int k = 0; k < WPL; k += 4) *reinterpret_cast<uint4 *>(k_dst + k) = uint4{out[k], out[k + 1], out[k + 2], out[k + 3]};
         } else {
             static_assert(WPL == 2, "G = 32 at 2 bits");
-            if constexpr (STAGED) *reinterpret_cast<uint2 *>(k_dst) = uint2{out[0], out[1]};
-            else                  nt_store(reinterpret_cast<uint2 *>(k_dst), uint2{out[0], out[1]});
+            *reinterpret_cast<uint2 *>(k_dst) = uint2{out[0], out[1]};
         }
     }
-}
-
-// The same from memory: p = the item's G fp16 values.
-template <int G, int BITS>
-__device__ __forceinline__ void pack_item(const uint4 *__restrict__ p, bool isV, uint32_t *__restrict__ meta_dst,
-                                          uint32_t *__restrict__ k_dst, uint32_t *__restrict__ v_lds) {
-    uint32_t w[G / 2];
-#pragma unroll
-    for (int j = 0; j < G / 8; j++) {                // the whole item is requested at once: its 128-byte line arrives once
-        // (ordinary loads: the lane's eight loads share the line through the cache; streaming loads here fetch it eight times)
-        const uint4 t = p[j];
-        w[4 * j] = t.x; w[4 * j + 1] = t.y; w[4 * j + 2] = t.z; w[4 * j + 3] = t.w;
-    }
-    pack_item_regs<G, BITS>(w, isV, meta_dst, k_dst, v_lds);
 }
 
 // Keys quantised per channel: a group is G consecutive tokens of one dim.  A wavefront holds rows of a group, lane l dims 2l, 2l+1
@@ -208,22 +187,6 @@ __device__ __forceinline__ void column_codes(const uint32_t (&w)[NR], const floa
         if (pi == 0) { if constexpr (STAGED) dst[i * (kD / CPW)] = x; else nt_store(dst + (size_t)i * (kD / CPW), x); }
     }
 }
-// Token group tg of the rows at src, all by one wavefront: it reads the G rows' words (a row is one coalesced 256-byte piece).
-template <int G, int BITS>
-__device__ __forceinline__ void pack_k_channel_group(const uint16_t *src, int64_t stride_s, int tg, uint32_t *codes_w,
-                                                     uint32_t *meta_w, int lane) {
-    const uint32_t *col = reinterpret_cast<const uint32_t *>(src + (int64_t)tg * G * stride_s) + lane;
-    const int64_t rw = stride_s / 2;                  // row stride in words
-    uint32_t w[G], mnp, mxp, metaw[2];
-    float nmn[2], inv[2];
-#pragma unroll
-    for (int i = 0; i < G; i++) w[i] = col[i * rw];
-    column_range<G>(w, mnp, mxp);
-    column_scale<BITS>(mnp, mxp, nmn, inv, metaw);
-    nt_store(reinterpret_cast<uint2 *>(meta_w + (size_t)tg * kD + 2 * lane), uint2{metaw[0], metaw[1]});
-    column_codes<BITS, G>(w, nmn, inv, codes_w + (size_t)tg * G * (kD * BITS / 32), lane);
-}
-
 // The V codes of a chunk from the staging rows (vcodes: one code per byte, kVRow bytes per token row) into the
 // dimension-major tile layout at codes_w, by NT threads; room = v_token_room(N, bits).
 // V: dimension-major tiles of 16*QD slots x 4 words.  A slot holds TQ = max(TW, 8) consecutive tokens
@@ -320,7 +283,7 @@ __device__ __forceinline__ void rows_transpose(const uint4 (&v)[16], uint8_t *tb
 }
 
 // One token row (sixteen 16-byte pieces, in registers) of a chunk's K (isV = 0) or V (isV = 1) -> the chunk's block at
-// bit-width `bits`: its NG items as pack_side would pack them, by the thread that owns the row.  Consecutive lanes own
+// bit-width `bits`: its NG items (pack_item), by the thread that owns the row.  Consecutive lanes own
 // consecutive rows, so what a lane would store itself are pieces of lines: the row's meta words leave as one
 // store per lane (a contiguous run over the wavefront), the K codes go to staging rows in LDS (`stage`, kKStageRow(bits)
 // bytes per row) from where k_flush writes them out in whole lines, the V codes to the staging rows of v_gather.
@@ -345,9 +308,9 @@ __device__ __forceinline__ void pack_row(const uint4 (&x)[16], int row, int N, i
     for (int g = 0; g < NG; g++) {
         uint32_t *vl = reinterpret_cast<uint32_t *>(stage + row * kVRow + g * G);
         uint32_t *kl = reinterpret_cast<uint32_t *>(stage + row * k_stage_row(bits) + g * (G * bits / 8));
-        if (bits == 2)      pack_item_regs<G, 2, true>(&w[g * NW], isV, &mw[g], kl, vl);
-        else if (bits == 4) pack_item_regs<G, 4, true>(&w[g * NW], isV, &mw[g], kl, vl);
-        else                pack_item_regs<G, 8, true>(&w[g * NW], isV, &mw[g], kl, vl);
+        if (bits == 2)      pack_item<G, 2>(&w[g * NW], isV, &mw[g], kl, vl);
+        else if (bits == 4) pack_item<G, 4>(&w[g * NW], isV, &mw[g], kl, vl);
+        else                pack_item<G, 8>(&w[g * NW], isV, &mw[g], kl, vl);
     }
     if constexpr (NG == 2) nt_store(reinterpret_cast<uint2 *>(meta_w + row * NG), uint2{mw[0], mw[1]});
     else                   nt_store(reinterpret_cast<uint4 *>(meta_w + row * NG), uint4{mw[0], mw[1], mw[2], mw[3]});
@@ -361,51 +324,6 @@ __device__ __forceinline__ void k_flush(int N, int bits, uint8_t *blk, const uin
         const int row = p / ppr, col = p % ppr;
         nt_store(&dst[p], *reinterpret_cast<const uint4 *>(stage + row * srow + col * 16));
     }
-}
-
-// K (isV = 0) or V (isV = 1) of one chunk -> its block `blk` at bit-width `bits`, by one workgroup of NT threads
-// (a multiple of 64).  src: the chunk's first row (row stride stride_s elements); vcodes: N * kVRow bytes of LDS (V only).
-// KPC: the keys' groups run along tokens (pack_k_channel_group); a template flag so that its G registers per lane stay out
-// of the ordinary kernels.
-template <int G, bool KPC>
-__device__ __forceinline__ void pack_side(const uint16_t *src, int64_t stride_s, int N, int bits, int isV, uint8_t *blk,
-                                          uint8_t *vcodes, int tid, int NT = kPackThreads) {
-    if (bits == 16) {                                 // FP16 expert: rows copied verbatim
-        const int lane16 = tid & 15, rsub = tid >> 4;
-        uint4 *dst = reinterpret_cast<uint4 *>(blk + (isV ? (size_t)N * kD * 2 : 0));
-        for (int row = rsub; row < N; row += NT / 16)
-            nt_store(&dst[row * 16 + lane16], nt_load(reinterpret_cast<const uint4 *>(src + (int64_t)row * stride_s + lane16 * 8)));
-        return;
-    }
-
-    constexpr int NG = kD / G;                        // groups per row
-    const int room = isV ? v_token_room(N, bits) : N;  // tokens the code area has room for (V: at least one slice)
-    const size_t k_code_bytes = (size_t)N * kD * bits / 8, meta_bytes = (size_t)N * NG * 4;
-    uint8_t *area = blk + (isV ? k_code_bytes + meta_bytes : 0);
-    uint32_t *codes_w = reinterpret_cast<uint32_t *>(area);
-    uint32_t *meta_w = reinterpret_cast<uint32_t *>(area + (size_t)room * kD * bits / 8);
-
-    if (KPC && !isV) {                               // keys quantised per channel: one wavefront per group of G tokens
-        for (int tg = tid >> 6; tg < N / G; tg += NT >> 6) {
-            if (bits == 2)      pack_k_channel_group<G, 2>(src, stride_s, tg, codes_w, meta_w, tid & 63);
-            else if (bits == 4) pack_k_channel_group<G, 4>(src, stride_s, tg, codes_w, meta_w, tid & 63);
-            else                pack_k_channel_group<G, 8>(src, stride_s, tg, codes_w, meta_w, tid & 63);
-        }
-        return;
-    }
-    // item = (token row, group): consecutive lanes take consecutive 2G-byte pieces of the chunk
-    for (int item = tid; item < N * NG; item += NT) {
-        const int row = item / NG, g = item % NG;
-        const uint4 *p = reinterpret_cast<const uint4 *>(src + (int64_t)row * stride_s + g * G);
-        uint32_t *vl = reinterpret_cast<uint32_t *>(vcodes + row * kVRow + g * G);
-        if (bits == 2)      pack_item<G, 2>(p, isV, &meta_w[item], codes_w + item * (G / 16), vl);
-        else if (bits == 4) pack_item<G, 4>(p, isV, &meta_w[item], codes_w + item * (G / 8), vl);
-        else                pack_item<G, 8>(p, isV, &meta_w[item], codes_w + item * (G / 4), vl);
-    }
-    if (!isV) return;
-
-    __syncthreads();
-    v_gather(N, bits, room, codes_w, vcodes, tid, NT);
 }
 
 }  // namespace moqae
