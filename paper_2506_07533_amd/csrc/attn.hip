@@ -81,7 +81,8 @@ template <int G, int REP, int NWV> struct alignas(16) AttnLds {
     // ticket queue of the workgroup: local tickets [0, limit) are granted; batch i maps local
     // tickets from bl[i] on to the row's tickets from bg[i] on
     uint16_t ustart[REP > 1 ? kDescCap : 0];             // grouped queries: first unit of every chunk of the segment
-    uint16_t inv[kUnitCap];                              // unit -> chunk of the segment, one head per KV head | unit of the chunk << 10 (not with Gather, whose units follow from the counts)
+    uint16_t inv[kUnitCap];                              // unit -> chunk of the segment, with one head per KV head | unit of the
+                                                         // chunk << 10 (not with Gather, whose units follow from the counts)
     uint32_t wscan[NWV], wscan2[NWV];
     uint32_t U[kMaxWeightedRowsLds + 1], r0, uneven;            // prefix sums of the rows' units
     uint32_t next, limit, done, fetching, g_seen, nb;
@@ -1648,11 +1649,10 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             // knows the tickets
             const bool fixed_part = REP == 1 && (P == 1u || !by_counter);
             // the latest batch of tickets that this wavefront has looked up: local tickets below c_hi are tickets c_off + t of the row;
-            // no more have to be asked for as long as t + NWV < c_lim.  With the grant, the batch and a chunk's first unit looked up
-            // in LDS at every draw, one behind the other, and a draw that the compiler waited for (see issue_draw), the next unit was
-            // known after 1300 clocks and more, of the 6000 that a unit takes: now 600 where the parts are fixed.  (Grouped queries look everything
-            // up: their kernel holds no register more; with these it is 1 to 2 % slower, with four heads in groups of 32 9 %.)  256 rows of 8k tokens in 32-token chunks
-            // 56.5 -> 54.4 us a call, 32 heads x 32k tokens 1 us; caches larger than the last-level cache wait for memory either way.
+            // no more have to be asked for as long as t + NWV < c_lim.  Looked up in LDS at every draw, the grant, the batch and a chunk's
+            // first unit are reads that wait for one another before the next unit is known (256 rows of 8k tokens in 32-token chunks
+            // 56.3 us a call against 54.1, 13B-shaped 128k caches no different: they wait for memory).  Grouped queries look everything
+            // up, their kernels hold no register more: kept as here it is 1 to 2 % slower, with four heads in groups of 32 9 %.
             uint32_t c_hi = 0u, c_off = 0u, c_lim = 0u;
             if (P == 1u || !by_counter) {
                 if (REP == 1 || tid == 0) {
@@ -1744,7 +1744,8 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             if constexpr (REP == 1) { uint32_t vzero = 0u; asm volatile("" : "+v"(vzero)); next += vzero; }
             auto issue_draw = [&]() { if (lane == 0) pend = atomicAdd(REP == 1 ? next : &L.next, 1u); };
             constexpr uint32_t kNoTicket = 0xffffffffu;
-            auto ticket = [&](auto t) -> uint32_t {      // one head per KV head: the row's ticket for local ticket t; waits until it is granted, or nothing is left
+            // one head per KV head: the row's ticket for local ticket t; waits until it is granted, or nothing is left
+            auto ticket = [&](auto t) -> uint32_t {
               if constexpr (REP > 1) return kNoTicket;
               else {
                 if (fixed_part) {
@@ -1782,7 +1783,9 @@ __global__ __launch_bounds__(NWV * 64) void attn_split_kernel(AttnArgs a) {
             };
             auto next_unit = [&](Unit &un) -> bool {     // the pending draw becomes the next unit
                 const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)pend);
-                uint32_t limit;                          // grouped queries (with this code in the else branch of a choice their kernel in groups of 32 spills 141 registers and not 129: 338 -> 355 us)
+                // grouped queries; one function for this wait and that of ticket() spills 141 registers and not 129 with four heads in
+                // groups of 32 (32 rows of 64k tokens 206 -> 218 us)
+                uint32_t limit;
                 for (; REP > 1;) {                       // wait until local ticket t is granted, or nothing is left
                     limit = (uint32_t)__builtin_amdgcn_readfirstlane((int)__atomic_load_n(&L.limit, __ATOMIC_RELAXED));
                     if (t < limit) break;
