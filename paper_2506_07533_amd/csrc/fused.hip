@@ -108,10 +108,6 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
     __shared__ int votes_s[8];
     __shared__ unsigned long long page_off;
     __shared__ int expert_s, status_in;
-    __shared__ uint8_t past[kPoolShards];             // rings whose heads this workgroup moved past their tails
-    static_assert(kPoolShards <= 256, "a ring in a byte");
-    int n_past = 0;                                   // thread 0
-    uint32_t *past_heads = nullptr;
 
     const int c = a.chunk_begin + (int)blockIdx.x, u = (int)blockIdx.y;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, NT = (int)blockDim.x;
@@ -173,7 +169,7 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
             atomicCAS(a.status, 0, -1);
         } else {
             // tails do not move during this call; a head that runs past its tail (the ring was empty when several workgroups
-            // tried) is taken back by those who moved it, below: it is never below the tail on the way, so that nobody else gets a page
+            // tried) is taken back by those who moved it: it is never below the tail on the way, so that nobody else gets a page
             uint32_t *heads = a.state + 16 + e * 2 * kPoolShards, *tails = heads + kPoolShards;
             const uint32_t s0 = (uint32_t)(u * 131 + c * 7);
             bool got = false;
@@ -186,7 +182,7 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
                     off = a.pool_base[e] + (unsigned long long)page * a.page_bytes[e];
                     got = true;
                 } else {
-                    past[n_past++] = (uint8_t)sh; past_heads = heads;
+                    atomicSub(&heads[sh], 1u);
                 }
             }
             if (!got) atomicCAS(a.status, 0, -3);
@@ -196,9 +192,6 @@ __global__ __launch_bounds__(kPackThreads) void route_pack_kernel(PagedArgs a) {
     }
     if (a.votes && a.W1 != nullptr && tid < M) a.votes[eidx * M + tid] = routed ? votes_s[tid] : 0;
     __syncthreads();
-    // Not during the search, whose next load would wait for it: 256 chunks on pools with eight pages to spare 105 us a call, 91 so.  (Steps
-    // that are taken only if the head has not moved, compare and swap, meet too often: 32768 chunks of 32 tokens 416 us against 316.)
-    for (int i = 0; i < n_past; i++) atomicSub(&past_heads[past[i]], 1u);
     if (page_off == ~0ull) return;
     // ---- (3) quantise and pack K, then V, into the page
     const int bits = a.bits_of[expert_s];
