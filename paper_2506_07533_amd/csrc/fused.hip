@@ -11,7 +11,7 @@
 //                      own through LDS: rows_request, rows_transpose), routes it (route_row, the operations of
 //                      route_kernel in the same order), the votes are added up in LDS, one thread takes a page of the
 //                      routed expert's pool, then every thread quantises the row it still holds in registers and
-//                      after it its value row (pack_row, the arithmetic of pack_kernel).  A thread's codes are pieces
+//                      after it its value row (pack_row; pack_item, as in pack_kernel).  A thread's codes are pieces
 //                      of lines, so the K codes and the V codes both go through staging rows in LDS and leave in
 //                      whole lines (k_flush, v_gather).  No key row is kept in LDS: 18 KiB per 128-token workgroup,
 //                      eight workgroups per compute unit.
@@ -20,7 +20,7 @@
 //   pool_*_kernel      the free rings.  Device-wide atomic steps on ONE address run at about nine per microsecond on
 //                      this eight-die chip (40 960 chunks on four pool counters took 3.5 ms, 0.8 ms without them), so
 //                      every pool's free pages are spread over kPoolShards rings: a chunk starts at a ring chosen by
-//                      its indices and walks on while rings are empty; a page goes back to the ring it came from.
+//                      its indices and walks on, in a stride of its own, while rings are empty; a page goes back to the ring it came from.
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
 #include "pack_dev.hpp"

@@ -11,10 +11,10 @@
 //                operations per code (no cross-lane step anywhere).  K words are assembled in registers (row-major layout);
 //                V codes go through LDS as bytes and are gathered token-wise into the dimension-major tile layout.  Every
 //                store of codes covers whole lines.
-//                HBM-bound: reads 2*N*D*2 bytes, writes the block.  40 heads of 128k tokens (2.68 GB read, 0.68 GB written)
-//                573 us, 5.87 TB/s, where a kernel that only moves such bytes reaches 5.8 to 6.1 with streaming loads and 5.4
-//                to 5.8 with ordinary ones; a lane that loads its own line into registers, eight ordinary loads of 16 bytes: 605 to
-//                613, and, where 8-bit codes leave in pieces of lines, 1016 against 731 for 8 bits alone.
+//                HBM-bound: reads 2*N*D*2 bytes, writes the block.  40 heads of 128k tokens (2.68 GB read, 0.69 GB written)
+//                544 us, 6.2 TB/s, what a kernel that only moves such bytes reaches with streaming loads and stores (5.7 with
+//                ordinary ones); a lane that loads its own line into registers, eight ordinary loads of 16 bytes: 588 to 595, and, where
+//                8-bit codes leave in pieces of lines, 1024 against 693 for 8 bits alone.
 #include "moqae_dev.hpp"
 #include "moqae_kernels.hpp"
 #include "pack_dev.hpp"
@@ -309,8 +309,8 @@ __device__ __forceinline__ void pack_line(const uint32_t (&w)[32], int lane, uin
     else                   nt_store(reinterpret_cast<uint2 *>(meta_w), uint2{mw[0], mw[NI - 1]});
 }
 // The K codes of the wavefront's lines, consecutive bytes at dst: a lane's own 16, 32 or 64 of them go through LDS, from where they
-// leave 1 KiB per store.  Stored by their lanes in 16-byte pieces 64 bytes apart, 8-bit K codes took an all-8-bit call of 5.2 M rows
-// from 750 to 1016 us.  Piece q of lane l in slot PPL l + (q ^ l / (8 / PPL) % PPL): both ways every bank once.
+// leave 1 KiB per store.  (Stored by their lanes in 16-byte pieces 64 bytes apart, 8-bit K codes took an all-8-bit call of 5.2 M rows
+// to 1024 us, 693 so.)  Piece q of lane l in slot PPL l + (q ^ l / (8 / PPL) % PPL): both ways every bank once.
 template <int BITS>
 __device__ __forceinline__ int k_slot(int l, int q) {
     constexpr int PPL = BITS / 2;
@@ -343,8 +343,8 @@ __device__ __forceinline__ void pack_v_lines(const uint32_t (&w)[32], int lane, 
 
 // Keys quantised per channel: the wavefront's 32 rows, a group of 32 tokens or half of one of 64 (whose other half is the other
 // wavefront's); codes_w and meta_w: those of the part's first row and group.  The lines come through LDS as the others do and the
-// codes leave in whole lines: 40 heads of 64k tokens, groups of 64, routed and packed 381 us; a wavefront per group, its rows' words
-// loaded into 64 registers and every code word stored by its lane, 420.
+// codes leave in whole lines: 40 heads of 64k tokens, groups of 64, routed and packed 382 us; a wavefront per group, its rows' words
+// loaded into 64 registers and every code word stored by its lane, 416.
 template <int G, int BITS>
 __device__ __forceinline__ void pack_k_columns(int lane, int wave, uint8_t *region, uint8_t *lds, uint32_t *codes_w, uint32_t *meta_w) {
     uint32_t w[kRegionRows], mnp, mxp, metaw[2];
@@ -429,8 +429,8 @@ __device__ __forceinline__ void pack_part(const PackArgs &a, int isV, int c, int
 
 // 32 / N chunks of 8 or 16 tokens, one after the other in memory: K or V of the chunks [c, c + n) by one wavefront, every lane at its
 // chunk's bit-width.  (A wavefront per chunk leaves half or three quarters of its lanes without a line.)  The codes of all widths are
-// made in one pass, as bytes.  1.3 M rows of the usual mix, routed and packed: 8 tokens 247 us (346 with a wavefront per chunk), 16
-// tokens 208 (222).
+// made in one pass, as bytes.  1.3 M rows of the usual mix, routed and packed: 8 tokens 227 us (343 with a wavefront per chunk), 16
+// tokens 194 (217).  One chunk of 16 tokens a row, whose lanes then have 64 dims each and not 32, is slower: 32 rows 8.2 us (7.4).
 template <int G>
 __device__ __forceinline__ void pack_chunks(const PackArgs &a, int isV, int c, int n, int u, int lane, uint8_t *region) {
     constexpr int NG = kD / G;
@@ -593,9 +593,10 @@ hipError_t launch_pack(PackArgs a, hipStream_t s) {
         const uint32_t size = (uint32_t)((block_bytes(a.N, a.G, a.bits_of[e]) + 255u) >> 8);
         a.size_lo[e >> 2] |= (size & 255u) << (8 * (e & 3)); a.size_hi[e >> 2] |= (size >> 8) << (8 * (e & 3));
     }
-    // Streaming loads from 384 MiB of K and V on: 503 MB (40 heads x 24k tokens, 128-token chunks) routed and packed 157 us against 163,
-    // 1342 MB 391 against 406.  Below, ordinary loads keep what the last-level cache (256 MiB) holds of K from the routing, and
-    // of both from whoever wrote them: 336 MB 105 us against 113, 252 MB 80 against 86.
+    // Streaming loads from 384 MiB of K and V on: 419 MB (40 heads x 20k tokens, 128-token chunks) routed and packed 124 us against 130, 503 MB 145
+    // against 156, 1342 MB 364 against 394.  Below, ordinary loads keep what the last-level cache (256 MiB) holds of K from the routing,
+    // and of both from whoever wrote them: 336 MB 98 us against 101, 252 MB 76 against 79.  (Given decisions and keys that nobody has
+    // just read: 336 MB 78 against 72, 252 MB 53 against 56.)
     a.stream = (int64_t)a.BH * a.n_chunks * a.N * (2 * kD * 2) > (384ll << 20);
     const bool rows_ok = a.BH <= kPlanRowsMax &&
                          ((reinterpret_cast<uintptr_t>(a.expert + a.chunk_begin) | (uintptr_t)a.expert_stride) & 15u) == 0;
