@@ -1,5 +1,5 @@
-"""Chunks shorter than a window of 64 tokens share wavefronts in the routing kernel, take a wavefront per side in the packing
-kernel and share units in the decode kernel: windows that end inside a row, frozen chunks inside a window, calls that begin
+"""Chunks shorter than a window of 64 tokens share wavefronts in the routing kernel, take a wavefront per side and 32 tokens in the
+packing kernel and share units in the decode kernel: windows that end inside a row, frozen chunks inside a window, calls that begin
 inside one, odd numbers of chunk sides (bit-exact against the CPU oracle); units with fewer chunks than they hold."""
 import numpy as np
 import pytest
